@@ -69,6 +69,10 @@ extern "C" {
 #define LOONG_COMPUTE_DELTA  4    /* bwd: fill `delta` from o and d_o before the step */
 #define LOONG_BWD_ONLY_DKV   8    /* bwd: compute dk/dv only (dq may be NULL and is not touched) */
 #define LOONG_BWD_ONLY_DQ    16   /* bwd: compute this step's share of dq only (dk, dv may be NULL) */
+#define LOONG_OVERWRITE_DQ   32   /* bwd: dq is written (rows that see no key get 0) instead of added to: the first step */
+#define LOONG_WORKSPACE_CLEAN 64  /* bwd: the first LOONG_WORKSPACE_HEAD bytes of `workspace` are zero on entry, as every call
+                                     leaves them: the caller cleared them once, the call need not */
+#define LOONG_WORKSPACE_HEAD 65536
 /* Tuning/testing knob of the 16-bit kernels that own query rows (forward, dQ): bits 8..10 of
  * `flags` hold 1, 2 or 4 to force that many key splits per workgroup (waves that share the
  * same rows and divide every staged key tile); 0 = chosen from the shape and the device. */
@@ -141,7 +145,7 @@ LOONG_API int loong_lse_merge(int64_t rows, int32_t head_dim, float* out, float*
  * With LOONG_COMPUTE_DELTA, `o` (stored output, same type/strides as q) must be given and
  * delta is written first; otherwise `o` may be NULL.
  * Outputs: dq [B,Hq,q_len,d] fp32 (o_stride) is ADDED to (zero it before the first
- * step); every row is updated by one thread group in a fixed order, so dq is
+ * step, or let the first step write it: LOONG_OVERWRITE_DQ); every row is updated by one thread group in a fixed order, so dq is
  * bit-reproducible.  dk, dv fp32 contiguous [B,Hkv,kv_len,d] are overwritten, or added to
  * with LOONG_ACCUM_DKV (a plain read-modify-write: two calls that add into the same dk, dv
  * must be ordered).  dk, dv are bit-reproducible too: when a step has too few key tiles to
@@ -150,10 +154,10 @@ LOONG_API int loong_lse_merge(int64_t rows, int32_t head_dim, float* out, float*
  * counters live in `workspace`, device memory of the caller's, 16-byte aligned, at least
  * loong_workspace_bytes(desc) bytes (that may be 0: then `workspace` may be NULL).  It
  * may hold anything on entry (the call clears what it counts in with a kernel of its own on
- * `stream`) and holds nothing of value afterwards; calls that share one workspace must be
+ * `stream`; with LOONG_WORKSPACE_CLEAN it need not) and holds nothing of value afterwards; calls that share one workspace must be
  * ordered on one stream.  A missing or too small workspace is LOONG_E_NULL / LOONG_E_SHAPE
  * and nothing is enqueued.  The bf16/fp16 kernels only; the fp32 kernels need none.
- * The two halves run as two kernels on `stream`; LOONG_BWD_ONLY_DKV / LOONG_BWD_ONLY_DQ
+ * The two halves run as one launch on `stream`; LOONG_BWD_ONLY_DKV / LOONG_BWD_ONLY_DQ
  * run one of them (both flags together: LOONG_E_UNSUPPORTED).
  */
 LOONG_API int loong_attn_step_bwd(const loong_step_desc* desc, const void* q, const void* k, const void* v,

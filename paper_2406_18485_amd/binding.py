@@ -16,6 +16,8 @@ OK, E_NULL, E_SHAPE, E_UNSUPPORTED, E_ALIGN, E_DTYPE, E_HIP = 0, -1, -2, -3, -4,
 BF16, FP32, FP16 = 0, 1, 2
 SKIP, FULL, DIAG = 0, 1, 2
 FUSE_MERGE, ACCUM_DKV, COMPUTE_DELTA, BWD_ONLY_DKV, BWD_ONLY_DQ = 1, 2, 4, 8, 16
+OVERWRITE_DQ, WORKSPACE_CLEAN = 32, 64
+WORKSPACE_HEAD = 65536   # bytes of a workspace that WORKSPACE_CLEAN speaks of
 KEY_SPLITS_SHIFT = 8
 
 

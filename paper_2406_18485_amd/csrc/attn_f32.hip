@@ -134,11 +134,12 @@ __global__ __launch_bounds__(64) void bwd_dq_f32_kernel(F32Params p) {
   __syncthreads();
   const int64_t srow = (b * p.Hq + h) * (int64_t)p.q_len + i;
   const float lse_i = p.lse_in[srow], dl = p.delta[srow];
-  if (lse_i == -INFINITY) return;
+  const bool overwrite = p.flags & LOONG_OVERWRITE_DQ;
+  if (lse_i == -INFINITY && !overwrite) return;
   const int qa = (p.g.nq == 2 && i >= p.g.q[1].start) ? 1 : 0;
   const int qoff = i - p.g.q[qa].start;
   float acc0 = 0.f, acc1 = 0.f;
-  for (int kb = 0; kb < p.g.nk; ++kb) {
+  for (int kb = 0; kb < p.g.nk && lse_i != -INFINITY; ++kb) {
     const int kmax = visible_keys(p.g, qa, kb, qoff);
     const float* kbase = p.k + b * p.ks[0] + hk * p.ks[1] + (int64_t)p.g.k[kb].start * p.ks[2];
     const float* vbase = p.v + b * p.ks[0] + hk * p.ks[1] + (int64_t)p.g.k[kb].start * p.ks[2];
@@ -160,8 +161,8 @@ __global__ __launch_bounds__(64) void bwd_dq_f32_kernel(F32Params p) {
     }
   }
   float* dqrow = p.dq + b * p.os[0] + h * p.os[1] + (int64_t)i * p.os[2];
-  if (lane < p.d) dqrow[lane] += acc0;
-  if (lane + 64 < p.d) dqrow[lane + 64] += acc1;
+  if (lane < p.d) dqrow[lane] = (overwrite ? 0.f : dqrow[lane]) + acc0;
+  if (lane + 64 < p.d) dqrow[lane + 64] = (overwrite ? 0.f : dqrow[lane + 64]) + acc1;
 }
 
 // ---- backward, dK/dV of the visiting chunk: one wave per key row ---------------------------
@@ -262,7 +263,7 @@ int launch_bwd_f32(const loong_step_desc& d, const StepGeom& g, const void* q, c
   p.lse_in = lse; p.delta = delta; p.dq = dq; p.dk = dk; p.dv = dv;
   hipStream_t st = static_cast<hipStream_t>(stream);
   const bool do_dq = !(d.flags & LOONG_BWD_ONLY_DKV), do_dkv = !(d.flags & LOONG_BWD_ONLY_DQ);
-  if (do_dq && qrows > 0 && krows > 0) {
+  if (do_dq && qrows > 0 && (krows > 0 || (d.flags & LOONG_OVERWRITE_DQ))) {
     bwd_dq_f32_kernel<<<dim3((unsigned)qrows), dim3(64), 0, st>>>(p);
     if (int rc = check_launch("loong_attn_step_bwd (fp32 dq)")) return rc;
   }

@@ -16,6 +16,7 @@
 // Every row belongs to one wave (after the key splits are summed through LDS), so dQ is
 // updated with plain loads and stores in a fixed order: the result is reproducible and no
 // atomic traffic goes to L2.
+#pragma once
 #include <hip/hip_runtime.h>
 
 #include "device_utils.h"
@@ -37,6 +38,7 @@ struct DqParams {
   int q_len;
   StepGeom g;
   float scale, c;  // softmax scale; scale * log2(e)
+  int overwrite;   // 1: dq is written, not added to
   int ntile[2];    // q tiles per q segment
   int tiles_total;
   int hgroups;     // Hq / GS
@@ -65,16 +67,15 @@ struct DqCfg {
 };
 
 template <class E, int D, int KS>
-__global__ __launch_bounds__(kRowWaves * 64) void dq_kernel(const DqParams p) {
+__device__ __forceinline__ void dq_body(const DqParams& p, uint32_t block, unsigned char* smem) {
   using C = DqCfg<D, KS>;
   constexpr int NRB = C::NRB, NJB = C::NJB, BNS = C::BNS, TK = C::TK, NBUF = C::NBUF, PD = C::PD, KI = C::KI;
   constexpr int NDB = D / 32, NKS = D / 16, ROWB = C::ROWB, CH = C::CH;
-  __shared__ __attribute__((aligned(1024))) unsigned char smem[C::SMEM_BYTES];
 
   // ---- which (batch, head group, q tile): within a head group the tiles with the most
   // visible keys come first
   int bh, rank;
-  if (!decode_work(p.map, blockIdx.x, bh, rank)) return;
+  if (!decode_work(p.map, block, bh, rank)) return;
   const int tt = p.tiles_total - 1 - rank;
   const int b = bh / p.hgroups, hg = bh - b * p.hgroups;
   const int qa = tt >= p.ntile[0] ? 1 : 0;
@@ -105,7 +106,17 @@ __global__ __launch_bounds__(kRowWaves * 64) void dq_kernel(const DqParams p) {
   const int kend1 = cls1 == LOONG_SKIP ? 0 : cls1 == LOONG_FULL ? klen1 : min(klen1, last_off_wg + 1);
   const int ntk0 = (kend0 + TK - 1) / TK, ntk1 = (kend1 + TK - 1) / TK;
   const int total_t = ntk0 + ntk1;
-  if (total_t == 0) return;  // nothing visible: no share of dQ in this step
+  float* const dq_row = p.dq + b * p.os[0] + h * p.os[1] + (int64_t)my_row * p.os[2];
+  if (total_t == 0) {  // nothing visible: no share of dQ in this step
+    if (p.overwrite && ksp == 0 && row_ok) {
+#pragma unroll
+      for (int db = 0; db < NDB; ++db)
+#pragma unroll
+        for (int vq = 0; vq < 4; ++vq)
+          *reinterpret_cast<float4*>(dq_row + db * 32 + 8 * vq + 4 * hh) = make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+    return;
+  }
 
   // ---- Q and dO fragments (B operands): row my_row, columns 16 ks + 8 hh .. +7; the row's
   // LSE in log2 units, negated, and its delta.  A row with LSE = -inf sees no key at all.
@@ -291,10 +302,13 @@ __global__ __launch_bounds__(kRowWaves * 64) void dq_kernel(const DqParams p) {
 
   // ---- sum the key splits: splits 1.. park their dQ^T in LDS, split 0 adds them in order.
   // Split 0 requests its rows of dQ first: the round trip to memory runs while the others park.
-  float* const dq_row = p.dq + b * p.os[0] + h * p.os[1] + (int64_t)my_row * p.os[2];
   float4 old[NDB][4];
+#pragma unroll
+  for (int db = 0; db < NDB; ++db)
+#pragma unroll
+    for (int vq = 0; vq < 4; ++vq) old[db][vq] = make_float4(0.f, 0.f, 0.f, 0.f);
   if (KS > 1) {
-    if (ksp == 0 && row_ok) {
+    if (ksp == 0 && row_ok && !p.overwrite) {
 #pragma unroll
       for (int db = 0; db < NDB; ++db)
 #pragma unroll
@@ -333,7 +347,8 @@ __global__ __launch_bounds__(kRowWaves * 64) void dq_kernel(const DqParams p) {
 #pragma unroll
       for (int vq = 0; vq < 4; ++vq) {
         float4* dst = reinterpret_cast<float4*>(dq_row + db * 32 + 8 * vq + 4 * hh);
-        float4 x = KS > 1 ? old[db][vq] : *dst;
+        float4 x = old[db][vq];
+        if (KS == 1 && !p.overwrite) x = *dst;
         x.x = fmaf(acc[db][4 * vq + 0], p.scale, x.x); x.y = fmaf(acc[db][4 * vq + 1], p.scale, x.y);
         x.z = fmaf(acc[db][4 * vq + 2], p.scale, x.z); x.w = fmaf(acc[db][4 * vq + 3], p.scale, x.w);
         *dst = x;
@@ -341,48 +356,5 @@ __global__ __launch_bounds__(kRowWaves * 64) void dq_kernel(const DqParams p) {
   }
 }
 
-template <class E, int D, int KS>
-int launch_cfg(DqParams& p, hipStream_t st) {
-  const RowTiling rt = make_row_tiling(p.g, p.G, p.Hq, p.B, kRowWaves / KS, /*list_blind=*/false);
-  p.GS = rt.GS; p.ntile[0] = rt.ntile[0]; p.ntile[1] = rt.ntile[1];
-  p.tiles_total = rt.tiles_total; p.hgroups = rt.hgroups;
-  if (rt.total_wg == 0) return LOONG_OK;
-  if (rt.total_wg > 0x3ffffff0) return fail(LOONG_E_UNSUPPORTED, "backward (dQ) grid too large");
-  p.map = make_work_map((int64_t)p.B * rt.hgroups, rt.tiles_total);
-  dq_kernel<E, D, KS><<<dim3(p.map.grid), dim3(kRowWaves * 64), 0, st>>>(p);
-  return check_launch("loong_attn_step_bwd (bf16, dQ)");
-}
-
-template <class E>
-int pick_cfg(DqParams& p, int head_dim, int ks, hipStream_t st) {
-  if (head_dim == 128) {
-    if (ks == 1) return launch_cfg<E, 128, 1>(p, st);
-    if (ks == 2) return launch_cfg<E, 128, 2>(p, st);
-    return launch_cfg<E, 128, 4>(p, st);
-  }
-  if (ks == 1) return launch_cfg<E, 64, 1>(p, st);
-  if (ks == 2) return launch_cfg<E, 64, 2>(p, st);
-  return launch_cfg<E, 64, 4>(p, st);
-}
-
 }  // namespace
-
-int launch_bwd_dq_bf16(const loong_step_desc& d, const StepGeom& g, const void* q, const void* k,
-                       const void* v, const void* d_o, const float* lse, const float* delta, float* dq,
-                       void* stream) {
-  if (d.kv_len == 0 || d.q_len == 0) return LOONG_OK;
-  DqParams p{};
-  p.q = (const uint16_t*)q; p.k = (const uint16_t*)k; p.v = (const uint16_t*)v; p.d_o = (const uint16_t*)d_o;
-  p.lse = lse; p.delta = delta; p.dq = dq;
-  p.B = d.batch; p.Hq = d.n_q_heads; p.Hkv = d.n_kv_heads; p.G = d.n_q_heads / d.n_kv_heads;
-  for (int i = 0; i < 3; ++i) { p.qs[i] = d.q_stride[i]; p.ks[i] = d.kv_stride[i]; p.os[i] = d.o_stride[i]; }
-  p.q_len = d.q_len; p.g = g; p.scale = d.softmax_scale; p.c = d.softmax_scale * kLog2e;
-  hipStream_t st = static_cast<hipStream_t>(stream);
-  DeviceFacts dev;
-  if (int rc = device_facts(&dev)) return rc;
-  const int ks = pick_key_splits(g, p.G, p.Hq, p.B, forced_key_splits(d.flags), dev.cus);
-  if (d.dtype == LOONG_FP16) return pick_cfg<Fp16>(p, d.head_dim, ks, st);
-  return pick_cfg<Bf16>(p, d.head_dim, ks, st);
-}
-
 }  // namespace loong

@@ -15,6 +15,7 @@ namespace {
 // counters + 64 MiB of partial sums: enough for every step of the 32K..1M-token benchmark shapes
 // (at most 512 (key tile, split) slots of 128 KiB)
 constexpr int64_t kScratchBytes = LOONG_STATIC_SCRATCH_BYTES;
+static_assert(loong::kWsHeadBytes == LOONG_WORKSPACE_HEAD, "header and layout disagree");
 static_assert(kScratchBytes == loong::kWsHeadBytes + ((int64_t)64 << 20), "header and layout disagree");
 
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];

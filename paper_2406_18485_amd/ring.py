@@ -71,7 +71,8 @@ class RingReplay:
         self.block_lse = None
         # caller-owned scratch of the backward steps: the largest any micro-step asks for
         need = max(B.workspace_bytes(_desc(s, step, 0)) for step in self.plan)
-        self.workspace = torch.empty(max(need, 16), dtype=torch.uint8, device=self.dev)
+        # (zero once: every call leaves its counters zero, so none has to clear them)
+        self.workspace = torch.zeros(max(need, 16), dtype=torch.uint8, device=self.dev)
 
     # ---- forward: cp x (Attention [+ Update]) then the cast to the stored activation type
     def forward(self, q, k_by_src, v_by_src, fuse_merge=True, stream=None):
@@ -96,12 +97,10 @@ class RingReplay:
     # ---- backward from the stored O and LSE: delta once, then cp step kernels
     def backward(self, q, k_by_src, v_by_src, d_o, stream=None):
         s = self.shape
-        self.dq.zero_()
-        first = True
-        for step in self.plan:
+        for t, step in enumerate(self.plan):
             src = step["src_rank"]
-            flags = B.COMPUTE_DELTA if first else 0
-            first = False
+            # the first step also forms delta and writes dq, the later ones add to it
+            flags = B.WORKSPACE_CLEAN | (0 if t else B.COMPUTE_DELTA | B.OVERWRITE_DQ)
             B.attn_step_bwd(_desc(s, step, flags), q, k_by_src[src], v_by_src[src], self.o, d_o, self.lse,
                             self.delta, self.dq, self.dk[src], self.dv[src], self.workspace, stream=stream)
 

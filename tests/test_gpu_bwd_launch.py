@@ -1,0 +1,71 @@
+"""The backward step as one launch: what it clears, writes and leaves behind besides the gradients that
+the parity tests compare (dq written instead of added to, keys nobody sees, the workspace's counters)."""
+import math
+
+import pytest
+import torch
+
+import paper_2406_18485_amd as P
+from gpu_harness import DEV, workspace_for
+
+pytestmark = pytest.mark.gpu
+
+TORCH = {P.BF16: torch.bfloat16, P.FP16: torch.float16, P.FP32: torch.float32}
+
+
+def _step(dtype, hq, hkv, d, c, q_chunk, kv_chunk, seed):
+    g = torch.Generator(device="cpu").manual_seed(seed)
+    mk = lambda h: (torch.randn(1, h, 2 * c, d, generator=g) * 0.5).to(TORCH[dtype]).to(DEV)
+    t = dict(q=mk(hq), k=mk(hkv), v=mk(hkv), d_o=mk(hq))
+    t["lse"] = (torch.rand(1, hq, 2 * c, generator=g) + math.log(2 * c)).to(DEV)
+    t["lse"][0, 0, 0] = -math.inf   # a row that takes no part
+    t["delta"] = torch.randn(1, hq, 2 * c, generator=g).to(DEV) * 0.1
+    desc = lambda flags: P.make_desc(batch=1, n_q_heads=hq, n_kv_heads=hkv, head_dim=d, q_len=2 * c, kv_len=2 * c, dtype=dtype,
+                                     softmax_scale=1 / math.sqrt(d), causal=True, chunk_len=c, q_chunk=q_chunk,
+                                     kv_chunk=kv_chunk, flags=flags)
+    return t, desc
+
+
+def _run(t, desc, dq, workspace):
+    dk, dv = torch.full(t["k"].shape, 7.0, device=DEV), torch.full(t["k"].shape, 7.0, device=DEV)
+    P.attn_step_bwd(desc, t["q"], t["k"], t["v"], None, t["d_o"], t["lse"], t["delta"], dq, dk, dv, workspace)
+    torch.cuda.synchronize()
+    return dq, dk, dv
+
+
+STEPS = [((1, 6), (1, 6)), ((1, 6), (0, 7)), ((1, 6), (3, 4))]   # diagonal; late keys unseen; early rows blind
+
+
+@pytest.mark.parametrize("chunks", STEPS)
+@pytest.mark.parametrize("dtype,hq,hkv,d,c", [
+    (P.BF16, 4, 1, 128, 200), (P.BF16, 2, 2, 64, 33), (P.FP16, 3, 1, 128, 129), (P.BF16, 8, 8, 128, 1024), (P.FP32, 2, 1, 64, 65)])
+def test_overwritten_dq_and_cleared_gradients(dtype, hq, hkv, d, c, chunks):
+    t, desc = _step(dtype, hq, hkv, d, c, *chunks, seed=c)
+    ws = workspace_for(desc(0))
+    ws.fill_(0xA5)   # anything may be in it
+    want = _run(t, desc(0), torch.zeros(t["q"].shape, device=DEV), ws)
+    got = _run(t, desc(P.OVERWRITE_DQ), torch.full(t["q"].shape, 3.0, device=DEV), ws)
+    for a, b in zip(got, want):
+        assert torch.equal(a, b)
+    assert float(got[0][0, 0, 0].abs().max()) == 0.0
+    if chunks[1] == (0, 7):
+        assert float(got[1][:, :, c:].abs().max()) == 0.0 and float(got[2][:, :, c:].abs().max()) == 0.0
+    if chunks[1] == (3, 4):
+        assert float(got[0][:, :, :c].abs().max()) == 0.0
+
+
+@pytest.mark.parametrize("hq,hkv,d,c,chunks,shared", [
+    (4, 1, 128, 200, STEPS[1], True), (4, 1, 64, 777, STEPS[0], True), (8, 8, 128, 1024, STEPS[1], True), (8, 8, 128, 2048, STEPS[2], False)])
+def test_counters_stay_zero_between_calls(hq, hkv, d, c, chunks, shared):
+    t, desc = _step(P.BF16, hq, hkv, d, c, *chunks, seed=d + c)
+    need = P.workspace_bytes(desc(0))
+    assert (need > 0) == shared
+    head = P.WORKSPACE_HEAD
+    ws = torch.zeros(max(need, 16), dtype=torch.uint8, device=DEV)
+    junk = torch.full_like(ws, 0xFF)
+    want = _run(t, desc(0), torch.zeros(t["q"].shape, device=DEV), junk)
+    for _ in range(3):
+        got = _run(t, desc(P.WORKSPACE_CLEAN), torch.zeros(t["q"].shape, device=DEV), ws)
+        assert int(ws[:head].count_nonzero()) == 0
+        for a, b in zip(got, want):
+            assert torch.equal(a, b)
