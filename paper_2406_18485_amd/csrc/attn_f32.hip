@@ -1,10 +1,33 @@
-// fp32-storage kernels of the ring step (small cases, e.g. the fp32 tiny benchmark shape).
-// One wave per row, plain fp32 FMAs, no matrix cores: written for clarity and a fixed
-// order of operations, not for speed.  The bf16 MFMA kernels are the tuned path.
+// fp32-storage kernels of the ring step on the fp32 matrix instruction (v_mfma_f32_16x16x4_f32: fp32
+// operands, fp32 sums, nothing rounded to a shorter type).
+//
+// What bounds them: the shapes this storage type is used at are small (a correctness run, a first try), so a
+// step is a few microseconds of dependent latencies (load, product, exponential, product, store), not a rate.
+// Hence 16-row tiles (many workgroups from few rows), operands straight from global memory into
+// registers (no LDS, no barrier in the loop), and the loop of a tile dealt out over the waves of its
+// workgroup, which add up their parts through LDS once, in wave order.
+//
+// Layout.  Lane l = 16 g + i of a wave.  The instruction takes A[i][k = g], B[k = g][i] and gives
+// D[4 g + v][i], v = 0..3.  Two kinds of fragment make every access 16 bytes per lane:
+//   row fragment   lane holds x[row i][16 m + 4 g .. +3]: slice (m, v) of a contraction over columns takes
+//                  component v, i.e. columns {16 m + 4 g + v}; A and B agree, so the order does not matter
+//   column fragment lane holds x[row 4 g + v][VW i .. +VW-1] (+ 16 VW per strip): a contraction over rows
+//                  takes rows {4 g + v} in slice v, which is register v of the D tile of the first
+//                  product, and block (strip, b) of the result takes component b: its row 4 g + r is
+//                  column strip 16 VW + VW (4 g + r) + b, so a lane ends with 4 VW consecutive columns of its row
+// The first products are transposed (S^T = K Q^T; S = Q K^T where keys are owned), so their D tile is the B
+// operand of the second product without any exchange.
+//
+// Against one wave per row with vector multiply-adds (a pass of a replay): 2 x 256 rows, 4 x 256 keys, d = 64,
+// forward and backward 580 -> 102 us; 16 heads x 1024 rows, 2 x 1024 keys, d = 128 forward 1914 -> 130 us,
+// backward 8494 -> 464 us.  The distance from 64-bit results fell too (gradients 5.0e-7 -> 4.3e-7 relative).
 #include <hip/hip_runtime.h>
+
+#include <algorithm>
 
 #include "device_utils.h"
 #include "loong_internal.h"
+#include "work_map.h"
 
 namespace loong {
 namespace {
@@ -16,217 +39,462 @@ struct F32Params {
   int64_t qs[3], ks[3], os[3];
   StepGeom g;
   float scale;
-  int flags;
+  int fuse, overwrite, accumulate;
+  int rtile[2], rtiles;   // row tiles per q segment, in all
+  int ktile[2], ktiles;   // key tiles per k segment, in all
+  WorkMap rmap, kmap;     // units = batch x q heads (kv heads), items = row (key) tiles
 };
 
-__device__ __forceinline__ float wave_max(float x) {
+constexpr int kT = 16;           // rows / keys of a tile
+constexpr int kMaxWaves = 8;     // waves that share a tile's loop
+// (four waves at d = 128: they need more than the 256 registers that eight leave each; at d = 64 eight are
+// better than four, 233 against 287 us a pass of 16 heads x 1024 rows)
+constexpr int max_bwd_waves(int np) { return np == 128 ? 4 : kMaxWaves; }
+
+__device__ __forceinline__ floatx4_t mfma16(float a, float b, floatx4_t c) {
+  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+// maximum / sum over the four lanes 16 g + i, g = 0..3
+__device__ __forceinline__ float max_over_groups(float x) {
+  const uintx2_t r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return max_with_other_half(fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1])));
+}
+__device__ __forceinline__ float sum_over_groups(float x) {
+  const uintx2_t r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return sum_with_other_half(__uint_as_float(r[0]) + __uint_as_float(r[1]));
+}
+
+// NP: head_dim rounded up to the instruction's blocks; EXACT: head_dim == NP
+template <int NP, bool EXACT>
+struct Frag {
+  static constexpr int NM = NP / 16;            // 16-byte pieces per lane of a row fragment; blocks of a result
+  static constexpr int VW = NP == 32 ? 2 : 4;   // columns per lane and strip of a column fragment
+  static constexpr int NS = NP / (16 * VW);     // strips
+  typedef float vec_t __attribute__((ext_vector_type(VW)));
+  struct Row { floatx4_t x[NM]; };
+  struct Col { vec_t x[4][NS]; };
+  struct Acc { floatx4_t x[NM]; };              // block strip * VW + b
+
+  // row fragment of the row at `row` (head_dim d)
+  static __device__ __forceinline__ Row load_row(const float* row, int g, int d) {
+    Row f;
 #pragma unroll
-  for (int m = 32; m >= 1; m >>= 1) x = fmaxf(x, __shfl_xor(x, m, 64));
-  return x;
-}
-__device__ __forceinline__ float wave_sum(float x) {
-#pragma unroll
-  for (int m = 32; m >= 1; m >>= 1) x += __shfl_xor(x, m, 64);
-  return x;
-}
-
-// dot product of an LDS-resident row with a global row, d a multiple of 4
-__device__ __forceinline__ float dot_row(const float* __restrict__ a_lds, const float* __restrict__ g, int d) {
-  float s = 0.f;
-  for (int t = 0; t < d; t += 4) {
-    const float4 x = *reinterpret_cast<const float4*>(g + t);
-    s += a_lds[t] * x.x + a_lds[t + 1] * x.y + a_lds[t + 2] * x.z + a_lds[t + 3] * x.w;
-  }
-  return s;
-}
-
-// Number of leading keys of key segment kb visible to the row at offset qoff of q segment qa.
-__device__ __forceinline__ int visible_keys(const StepGeom& g, int qa, int kb, int qoff) {
-  const int cls = g.cls[qa][kb];
-  if (cls == LOONG_SKIP) return 0;
-  const int len = g.k[kb].len;
-  return cls == LOONG_FULL ? len : min(len, qoff + 1);
-}
-
-// ---- forward: one wave per query row --------------------------------------------------
-__global__ __launch_bounds__(64) void fwd_f32_kernel(F32Params p) {
-  __shared__ float q_s[128];
-  const int lane = threadIdx.x;
-  const int64_t rid = blockIdx.x;
-  const int i = (int)(rid % p.q_len);
-  const int h = (int)((rid / p.q_len) % p.Hq);
-  const int64_t b = rid / ((int64_t)p.q_len * p.Hq);
-  const int hk = h / p.G;
-  const float* qrow = p.q + b * p.qs[0] + h * p.qs[1] + (int64_t)i * p.qs[2];
-  for (int t = lane; t < p.d; t += 64) q_s[t] = qrow[t];
-  __syncthreads();
-  const int qa = (p.g.nq == 2 && i >= p.g.q[1].start) ? 1 : 0;
-  const int qoff = i - p.g.q[qa].start;
-  const bool fuse = p.flags & LOONG_FUSE_MERGE;
-  float* orow = p.out + b * p.os[0] + h * p.os[1] + (int64_t)i * p.os[2];
-  float* lse_p = p.lse + (b * p.Hq + h) * (int64_t)p.q_len + i;
-
-  float m = -INFINITY, l = 0.f, acc0 = 0.f, acc1 = 0.f;
-  if (fuse) {
-    const float prev = *lse_p;
-    if (prev != -INFINITY) {
-      m = prev * kLog2e;
-      l = 1.f;
-      if (lane < p.d) acc0 = orow[lane];
-      if (lane + 64 < p.d) acc1 = orow[lane + 64];
-    }
-  }
-  bool any_key = false;
-  const float c = p.scale * kLog2e;
-  for (int kb = 0; kb < p.g.nk; ++kb) {
-    const int kmax = visible_keys(p.g, qa, kb, qoff);
-    const float* kbase = p.k + b * p.ks[0] + hk * p.ks[1] + (int64_t)p.g.k[kb].start * p.ks[2];
-    const float* vbase = p.v + b * p.ks[0] + hk * p.ks[1] + (int64_t)p.g.k[kb].start * p.ks[2];
-    for (int j0 = 0; j0 < kmax; j0 += 64) {
-      any_key = true;
-      const int j = j0 + lane;
-      const bool valid = j < kmax;
-      float s = dot_row(q_s, kbase + (int64_t)min(j, kmax - 1) * p.ks[2], p.d) * c;
-      s = valid ? s : -INFINITY;
-      const float m_new = fmaxf(m, wave_max(s));  // finite: lane 0 is always valid
-      const float alpha = fast_exp2(m - m_new);   // m = -inf gives 0
-      const float pj = fast_exp2(s - m_new);
-      l = l * alpha + wave_sum(pj);
-      acc0 *= alpha;
-      acc1 *= alpha;
-      const int cnt = min(64, kmax - j0);
-      for (int t = 0; t < cnt; ++t) {
-        const float pt = __shfl(pj, t, 64);
-        const float* vrow = vbase + (int64_t)(j0 + t) * p.ks[2];
-        if (lane < p.d) acc0 += pt * vrow[lane];
-        if (lane + 64 < p.d) acc1 += pt * vrow[lane + 64];
-      }
-      m = m_new;
-    }
-  }
-  if (!any_key) {
-    if (fuse) return;  // running result untouched
-    if (lane < p.d) orow[lane] = 0.f;
-    if (lane + 64 < p.d) orow[lane + 64] = 0.f;
-    if (lane == 0) *lse_p = -INFINITY;
-    return;
-  }
-  const float inv = 1.f / l;
-  if (lane < p.d) orow[lane] = acc0 * inv;
-  if (lane + 64 < p.d) orow[lane + 64] = acc1 * inv;
-  if (lane == 0) *lse_p = (m + fast_log2(l)) * kLn2;
-}
-
-// ---- backward, dQ share: one wave per query row -----------------------------------------
-__global__ __launch_bounds__(64) void bwd_dq_f32_kernel(F32Params p) {
-  __shared__ float q_s[128], do_s[128];
-  const int lane = threadIdx.x;
-  const int64_t rid = blockIdx.x;
-  const int i = (int)(rid % p.q_len);
-  const int h = (int)((rid / p.q_len) % p.Hq);
-  const int64_t b = rid / ((int64_t)p.q_len * p.Hq);
-  const int hk = h / p.G;
-  const int64_t qoffs = b * p.qs[0] + h * p.qs[1] + (int64_t)i * p.qs[2];
-  for (int t = lane; t < p.d; t += 64) {
-    q_s[t] = p.q[qoffs + t];
-    do_s[t] = p.d_o[qoffs + t];
-  }
-  __syncthreads();
-  const int64_t srow = (b * p.Hq + h) * (int64_t)p.q_len + i;
-  const float lse_i = p.lse_in[srow], dl = p.delta[srow];
-  const bool overwrite = p.flags & LOONG_OVERWRITE_DQ;
-  if (lse_i == -INFINITY && !overwrite) return;
-  const int qa = (p.g.nq == 2 && i >= p.g.q[1].start) ? 1 : 0;
-  const int qoff = i - p.g.q[qa].start;
-  float acc0 = 0.f, acc1 = 0.f;
-  for (int kb = 0; kb < p.g.nk && lse_i != -INFINITY; ++kb) {
-    const int kmax = visible_keys(p.g, qa, kb, qoff);
-    const float* kbase = p.k + b * p.ks[0] + hk * p.ks[1] + (int64_t)p.g.k[kb].start * p.ks[2];
-    const float* vbase = p.v + b * p.ks[0] + hk * p.ks[1] + (int64_t)p.g.k[kb].start * p.ks[2];
-    for (int j0 = 0; j0 < kmax; j0 += 64) {
-      const int j = j0 + lane;
-      const bool valid = j < kmax;
-      const int64_t off = (int64_t)min(j, kmax - 1) * p.ks[2];
-      const float s = dot_row(q_s, kbase + off, p.d) * p.scale;
-      const float pj = valid ? fast_exp2((s - lse_i) * kLog2e) : 0.f;
-      const float dp = dot_row(do_s, vbase + off, p.d);
-      const float ds = pj * (dp - dl) * p.scale;
-      const int cnt = min(64, kmax - j0);
-      for (int t = 0; t < cnt; ++t) {
-        const float dst = __shfl(ds, t, 64);
-        const float* krow = kbase + (int64_t)(j0 + t) * p.ks[2];
-        if (lane < p.d) acc0 += dst * krow[lane];
-        if (lane + 64 < p.d) acc1 += dst * krow[lane + 64];
+    for (int m = 0; m < NM; ++m) {
+      const int c = 16 * m + 4 * g;
+      if constexpr (EXACT) {
+        f.x[m] = *reinterpret_cast<const floatx4_t*>(row + c);
+      } else {  // pieces past the end contribute nothing
+        const floatx4_t y = *reinterpret_cast<const floatx4_t*>(row + min(c, d - 4));
+        f.x[m] = c < d ? y : floatx4_t{0.f, 0.f, 0.f, 0.f};
       }
     }
+    return f;
   }
-  float* dqrow = p.dq + b * p.os[0] + h * p.os[1] + (int64_t)i * p.os[2];
-  if (lane < p.d) dqrow[lane] = (overwrite ? 0.f : dqrow[lane]) + acc0;
-  if (lane + 64 < p.d) dqrow[lane + 64] = (overwrite ? 0.f : dqrow[lane + 64]) + acc1;
-}
-
-// ---- backward, dK/dV of the visiting chunk: one wave per key row ---------------------------
-__global__ __launch_bounds__(64) void bwd_dkv_f32_kernel(F32Params p) {
-  __shared__ float k_s[128], v_s[128];
-  const int lane = threadIdx.x;
-  const int64_t rid = blockIdx.x;
-  const int j = (int)(rid % p.kv_len);
-  const int hk = (int)((rid / p.kv_len) % p.Hkv);
-  const int64_t b = rid / ((int64_t)p.kv_len * p.Hkv);
-  const int64_t koffs = b * p.ks[0] + hk * p.ks[1] + (int64_t)j * p.ks[2];
-  for (int t = lane; t < p.d; t += 64) {
-    k_s[t] = p.k[koffs + t];
-    v_s[t] = p.v[koffs + t];
+  // column fragment of rows `first` + 4 g + v, the ones past `last` repeating it
+  static __device__ __forceinline__ Col load_col(const float* base, int64_t stride, int first, int last, int i, int g, int d) {
+    Col f;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const float* row = base + (int64_t)min(first + 4 * g + v, last) * stride;
+#pragma unroll
+      for (int s = 0; s < NS; ++s) {  // (columns past the end: block rows that are never stored)
+        const int c = 16 * VW * s + VW * i;
+        f.x[v][s] = *reinterpret_cast<const vec_t*>(row + (EXACT ? c : min(c, d - VW)));
+      }
+    }
+    return f;
   }
-  __syncthreads();
-  const int kb = (p.g.nk == 2 && j >= p.g.k[1].start) ? 1 : 0;
-  const int koff = j - p.g.k[kb].start;
-  float ak0 = 0.f, ak1 = 0.f, av0 = 0.f, av1 = 0.f;
-  for (int gq = 0; gq < p.G; ++gq) {
-    const int h = hk * p.G + gq;
-    for (int qa = 0; qa < p.g.nq; ++qa) {
-      const int cls = p.g.cls[qa][kb];
-      if (cls == LOONG_SKIP) continue;
-      const int len = p.g.q[qa].len;
-      const int first = cls == LOONG_DIAG ? koff : 0;  // rows at or after the key see it
-      const int64_t qbase = b * p.qs[0] + h * p.qs[1] + (int64_t)p.g.q[qa].start * p.qs[2];
-      const int64_t sbase = (b * p.Hq + h) * (int64_t)p.q_len + p.g.q[qa].start;
-      for (int i0 = first; i0 < len; i0 += 64) {
-        const int i = i0 + lane;
-        const bool valid = i < len;
-        const int ic = min(i, len - 1);
-        const float lse_i = p.lse_in[sbase + ic], dl = p.delta[sbase + ic];
-        const float s = dot_row(k_s, p.q + qbase + (int64_t)ic * p.qs[2], p.d) * p.scale;
-        const float pi = (valid && lse_i != -INFINITY) ? fast_exp2((s - lse_i) * kLog2e) : 0.f;
-        const float dp = dot_row(v_s, p.d_o + qbase + (int64_t)ic * p.qs[2], p.d);
-        const float ds = pi * (dp - dl) * p.scale;
-        const int cnt = min(64, len - i0);
-        for (int t = 0; t < cnt; ++t) {
-          const float pt = __shfl(pi, t, 64), dst = __shfl(ds, t, 64);
-          const float* qrow = p.q + qbase + (int64_t)(i0 + t) * p.qs[2];
-          const float* dorow = p.d_o + qbase + (int64_t)(i0 + t) * p.qs[2];
-          if (lane < p.d) {
-            ak0 += dst * qrow[lane];
-            av0 += pt * dorow[lane];
-          }
-          if (lane + 64 < p.d) {
-            ak1 += dst * qrow[lane + 64];
-            av1 += pt * dorow[lane + 64];
-          }
+  // D = A B^T over the columns, two chains (the additions of one wait for each other)
+  static __device__ __forceinline__ floatx4_t rows_product(const Row& a, const Row& b) {
+    floatx4_t d0 = {0.f, 0.f, 0.f, 0.f}, d1 = d0;
+#pragma unroll
+    for (int m = 0; m < NM; ++m) {
+      d0 = mfma16(a.x[m][0], b.x[m][0], d0); d1 = mfma16(a.x[m][1], b.x[m][1], d1);
+      d0 = mfma16(a.x[m][2], b.x[m][2], d0); d1 = mfma16(a.x[m][3], b.x[m][3], d1);
+    }
+    return d0 + d1;
+  }
+  // acc += A^T w over the 16 rows of A, w = D tile
+  static __device__ __forceinline__ void cols_product(Acc& acc, const Col& a, floatx4_t w) {
+#pragma unroll
+    for (int v = 0; v < 4; ++v)
+#pragma unroll
+      for (int n = 0; n < NM; ++n) acc.x[n] = mfma16(a.x[v][n / VW][n % VW], w[v], acc.x[n]);
+  }
+  // The same where some pairs are masked: a weight of zero must keep a row out whatever its values are, but
+  // the matrix instruction multiplies (0 x infinity).  `ok`: bit v = pair (row 4 g + v, lane's column) takes part.
+  static __device__ __forceinline__ void cols_product_masked(Acc& acc, const Col& a, floatx4_t w, int ok, const float* base,
+                                                             int64_t stride, int first, int last, int i, int g, int d) {
+    float z = 0.f;  // NaN if any element is not finite
+#pragma unroll
+    for (int v = 0; v < 4; ++v)
+#pragma unroll
+      for (int n = 0; n < NM; ++n) z = fmaf(a.x[v][n / VW][n % VW], 0.f, z);
+    if (__builtin_amdgcn_ballot_w64(z != z) == 0) return cols_product(acc, a, w);
+#pragma unroll 1
+    for (int t = 0; t < kT; ++t) {
+      const int v = t & 3, from = (t >> 2) * 16 + i;
+      const float wt = __shfl(v == 0 ? w[0] : v == 1 ? w[1] : v == 2 ? w[2] : w[3], from, 64);
+      const int okt = __shfl(ok, from, 64) >> v & 1;
+      const float* row = base + (int64_t)min(first + t, last) * stride;
+#pragma unroll
+      for (int n = 0; n < NM; ++n) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const float x = row[EXACT ? column(n, r, g) : min(column(n, r, g), d - 1)];
+          acc.x[n][r] = okt ? fmaf(wt, x, acc.x[n][r]) : acc.x[n][r];
         }
       }
     }
   }
-  const int64_t orow = ((b * p.Hkv + hk) * (int64_t)p.kv_len + j) * p.d;
-  const bool accum = p.flags & LOONG_ACCUM_DKV;
-  if (lane < p.d) {
-    p.dk[orow + lane] = (accum ? p.dk[orow + lane] : 0.f) + ak0;
-    p.dv[orow + lane] = (accum ? p.dv[orow + lane] : 0.f) + av0;
+  static __device__ __forceinline__ int column(int n, int r, int g) { return 16 * VW * (n / VW) + VW * (4 * g + r) + n % VW; }
+  // piece p of the lane's columns: four consecutive ones, starting at piece_col(p)
+  static __device__ __forceinline__ int piece_col(int p, int g) { return 16 * VW * (p / VW) + 4 * VW * g + 4 * (p % VW); }
+  static __device__ __forceinline__ floatx4_t piece(const Acc& a, int p) {
+    floatx4_t x;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int in_strip = 4 * (p % VW) + e;   // column inside the lane's 4 VW: VW r + b
+      x[e] = a.x[(p / VW) * VW + in_strip % VW][in_strip / VW];
+    }
+    return x;
   }
-  if (lane + 64 < p.d) {
-    p.dk[orow + lane + 64] = (accum ? p.dk[orow + lane + 64] : 0.f) + ak1;
-    p.dv[orow + lane + 64] = (accum ? p.dv[orow + lane + 64] : 0.f) + av1;
+  static __device__ __forceinline__ void set_piece(Acc& a, int p, floatx4_t x) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int in_strip = 4 * (p % VW) + e;
+      a.x[(p / VW) * VW + in_strip % VW][in_strip / VW] = x[e];
+    }
   }
+  static __device__ __forceinline__ Acc zero() {
+    Acc a;
+#pragma unroll
+    for (int n = 0; n < NM; ++n) a.x[n] = floatx4_t{0.f, 0.f, 0.f, 0.f};
+    return a;
+  }
+};
+
+// The visible tiles of a row tile (key tiles) or of a key tile (row tiles of one head): per segment a
+// first tile and a count, walked as one list.
+struct TileList {
+  int n0, total, first0, first1, len0, len1, start0, start1;
+  bool diag0, diag1;
+  struct Tile { int j0, len, start; bool diag; };
+  __device__ __forceinline__ Tile at(int t) const {
+    const bool s1 = t >= n0;
+    return Tile{((s1 ? first1 + t - n0 : first0 + t)) * kT, s1 ? len1 : len0, s1 ? start1 : start0, s1 ? diag1 : diag0};
+  }
+};
+__device__ __forceinline__ TileList keys_of_rows(const StepGeom& g, int qa, int last_row) {
+  const int c0 = qa ? g.cls[1][0] : g.cls[0][0], c1 = g.nk > 1 ? (qa ? g.cls[1][1] : g.cls[0][1]) : LOONG_SKIP;
+  TileList l{};
+  l.len0 = g.k[0].len; l.len1 = g.nk > 1 ? g.k[1].len : 0;
+  l.start0 = g.k[0].start; l.start1 = g.nk > 1 ? g.k[1].start : 0;
+  l.diag0 = c0 == LOONG_DIAG; l.diag1 = c1 == LOONG_DIAG;
+  const int e0 = c0 == LOONG_SKIP ? 0 : l.diag0 ? min(l.len0, last_row + 1) : l.len0;
+  const int e1 = c1 == LOONG_SKIP ? 0 : l.diag1 ? min(l.len1, last_row + 1) : l.len1;
+  l.n0 = (e0 + kT - 1) / kT;
+  l.total = l.n0 + (e1 + kT - 1) / kT;
+  return l;
+}
+__device__ __forceinline__ TileList rows_of_keys(const StepGeom& g, int kb, int first_key) {
+  const int c0 = kb ? g.cls[0][1] : g.cls[0][0], c1 = g.nq > 1 ? (kb ? g.cls[1][1] : g.cls[1][0]) : LOONG_SKIP;
+  TileList l{};
+  l.len0 = g.q[0].len; l.len1 = g.nq > 1 ? g.q[1].len : 0;
+  l.start0 = g.q[0].start; l.start1 = g.nq > 1 ? g.q[1].start : 0;
+  l.diag0 = c0 == LOONG_DIAG; l.diag1 = c1 == LOONG_DIAG;
+  const int t0 = (l.len0 + kT - 1) / kT, t1 = (l.len1 + kT - 1) / kT;
+  l.first0 = l.diag0 ? min(first_key / kT, t0) : 0;
+  l.first1 = l.diag1 ? min(first_key / kT, t1) : 0;
+  l.n0 = c0 == LOONG_SKIP ? 0 : t0 - l.first0;
+  l.total = l.n0 + (c1 == LOONG_SKIP ? 0 : t1 - l.first1);
+  return l;
+}
+
+// Sum of the waves' accumulators, in wave order; afterwards wave w holds the pieces p with p % waves == w.
+template <class F>
+__device__ __forceinline__ void add_waves(typename F::Acc& a, floatx4_t* slots, int wave, int waves, int lane) {
+#pragma unroll
+  for (int p = 0; p < F::NM; ++p) slots[(wave * F::NM + p) * 64 + lane] = F::piece(a, p);
+  __syncthreads();
+#pragma unroll
+  for (int p = 0; p < F::NM; ++p)
+    if (p % waves == wave) {
+      floatx4_t x = slots[p * 64 + lane];
+      for (int w = 1; w < waves; ++w) x += slots[(w * F::NM + p) * 64 + lane];
+      F::set_piece(a, p, x);
+    }
+}
+
+// ---- forward: RB x 16 query rows per workgroup (RB = 2 where rows are many: half the reads of K and V)
+template <int NP, bool EXACT, int RB>
+__global__ __launch_bounds__(kMaxWaves * 64 / RB) void fwd_f32_kernel(const F32Params p) {
+  using F = Frag<NP, EXACT>;
+  constexpr int NM = F::NM;
+  __shared__ floatx4_t slots[kMaxWaves * (NM + 1) * 64];
+  int bh, rank;
+  if (!decode_work(p.rmap, blockIdx.x, bh, rank)) return;
+  const int tt = p.rtiles - 1 - rank;  // late rows see more keys: first
+  const int b = bh / p.Hq, h = bh - b * p.Hq, hk = h / p.G;
+  const int qa = tt >= p.rtile[0] ? 1 : 0;
+  const int row0 = (qa ? tt - p.rtile[0] : tt) * kT * RB;
+  const Segment qs = qa ? p.g.q[1] : p.g.q[0];
+  const int lane = threadIdx.x & 63, i = lane & 15, g = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), waves = blockDim.x >> 6;
+  const TileList keys = keys_of_rows(p.g, qa, min(row0 + kT * RB, qs.len) - 1);
+  if (keys.total == 0 && p.fuse) return;  // running result untouched
+
+  const float* kbase = p.k + b * p.ks[0] + hk * p.ks[1];
+  const float* vbase = p.v + b * p.ks[0] + hk * p.ks[1];
+  typename F::Row qf[RB], kf;
+  typename F::Acc o[RB];
+  float m[RB], l[RB];
+  float* orow[RB];
+  float* lse_p[RB];
+  auto load_k = [&](int t) {
+    const TileList::Tile tl = keys.at(min(t, keys.total - 1));
+    return F::load_row(kbase + (int64_t)(tl.start + min(tl.j0 + i, tl.len - 1)) * p.ks[2], g, p.d);
+  };
+  if (wave < keys.total) kf = load_k(wave);
+#pragma unroll
+  for (int rb = 0; rb < RB; ++rb) {
+    const int row = qs.start + min(row0 + rb * kT + i, qs.len - 1);
+    qf[rb] = F::load_row(p.q + b * p.qs[0] + h * p.qs[1] + (int64_t)row * p.qs[2], g, p.d);
+    orow[rb] = p.out + b * p.os[0] + h * p.os[1] + (int64_t)row * p.os[2];
+    lse_p[rb] = p.lse + ((int64_t)b * p.Hq + h) * p.q_len + row;
+    o[rb] = F::zero();
+    m[rb] = -INFINITY; l[rb] = 0.f;
+    if (p.fuse && wave == 0) {  // the first wave starts from the running result
+      const float prev = *lse_p[rb];
+      floatx4_t x[NM];
+#pragma unroll
+      for (int pc = 0; pc < NM; ++pc)
+        x[pc] = *reinterpret_cast<const floatx4_t*>(orow[rb] + (EXACT ? F::piece_col(pc, g) : min(F::piece_col(pc, g), p.d - 4)));
+      if (prev != -INFINITY) {
+        m[rb] = prev * kLog2e;
+        l[rb] = g == 0 ? 1.f : 0.f;
+#pragma unroll
+        for (int pc = 0; pc < NM; ++pc) F::set_piece(o[rb], pc, x[pc]);
+      }
+    }
+  }
+  const float c = p.scale * kLog2e;
+  for (int t = wave; t < keys.total; t += waves) {
+    const TileList::Tile tl = keys.at(t);
+    const float* vtile = vbase + (int64_t)tl.start * p.ks[2];
+    const typename F::Col vf = F::load_col(vtile, p.ks[2], tl.j0, tl.len - 1, i, g, p.d);
+    const typename F::Row kn = load_k(t + waves);
+    __builtin_amdgcn_sched_barrier(0);  // requested before the products that hide them
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb) {
+      const int off = row0 + rb * kT + i;
+      floatx4_t s = F::rows_product(kf, qf[rb]) * c;
+      const bool masked = tl.j0 + kT > tl.len || (tl.diag && tl.j0 + kT - 1 > row0 + rb * kT);
+      int ok = 15;
+      if (masked) {
+        ok = 0;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const int key = tl.j0 + 4 * g + v;
+          const bool yes = key < tl.len && (!tl.diag || key <= off);
+          ok |= yes ? 1 << v : 0;
+          s[v] = yes ? s[v] : -INFINITY;
+        }
+      }
+      const float mx = max_over_groups(fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3])));
+      if (__builtin_amdgcn_ballot_w64(mx > m[rb]) != 0) {
+        const float m_new = fmaxf(m[rb], mx);
+        const float alpha = m_new == -INFINITY ? 1.f : fast_exp2(m[rb] - m_new);
+        l[rb] *= alpha;
+#pragma unroll
+        for (int n = 0; n < NM; ++n) o[rb].x[n] *= alpha;
+        m[rb] = m_new;
+      }
+      const float m_use = m[rb] == -INFINITY ? 0.f : m[rb];
+      floatx4_t w;
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        w[v] = fast_exp2(s[v] - m_use);
+        l[rb] += w[v];
+      }
+      if (masked) F::cols_product_masked(o[rb], vf, w, ok, vtile, p.ks[2], tl.j0, tl.len - 1, i, g, p.d);
+      else F::cols_product(o[rb], vf, w);
+    }
+    kf = kn;
+  }
+
+  // ---- the waves' parts: common maximum, weights, sum in wave order
+#pragma unroll
+  for (int rb = 0; rb < RB; ++rb) {
+    floatx4_t* mine = slots + (wave * RB + rb) * (NM + 1) * 64 + lane;
+#pragma unroll
+    for (int pc = 0; pc < NM; ++pc) mine[pc * 64] = F::piece(o[rb], pc);
+    mine[NM * 64] = floatx4_t{m[rb], l[rb], 0.f, 0.f};
+  }
+  __syncthreads();
+#pragma unroll
+  for (int rb = 0; rb < RB; ++rb) {
+    const floatx4_t* part = slots + rb * (NM + 1) * 64 + lane;
+    const int step = RB * (NM + 1) * 64;
+    float m_all = -INFINITY, l_all = 0.f;
+    for (int w = 0; w < waves; ++w) m_all = fmaxf(m_all, part[w * step + NM * 64][0]);
+    const float m_ref = m_all == -INFINITY ? 0.f : m_all;
+    for (int w = 0; w < waves; ++w) {
+      const floatx4_t st = part[w * step + NM * 64];
+      l_all += st[1] * fast_exp2(st[0] - m_ref);
+    }
+    const float l_tot = sum_over_groups(l_all);
+    const float inv = l_tot != 0.f ? 1.f / l_tot : 0.f;
+    if (row0 + rb * kT + i >= qs.len) continue;
+    for (int pc = wave; pc < NM; pc += waves) {
+      floatx4_t acc = {0.f, 0.f, 0.f, 0.f};
+      for (int w = 0; w < waves; ++w) acc += part[w * step + pc * 64] * fast_exp2(part[w * step + NM * 64][0] - m_ref);
+      if (EXACT || F::piece_col(pc, g) < p.d) *reinterpret_cast<floatx4_t*>(orow[rb] + F::piece_col(pc, g)) = acc * inv;
+    }
+    if (wave == 0 && g == 0) *lse_p[rb] = l_tot != 0.f ? fmaf(m_all, kLn2, fast_log2(l_tot) * kLn2) : -INFINITY;
+  }
+}
+
+// ---- backward, row-owning half: this step's share of dQ of 16 query rows
+template <int NP, bool EXACT>
+__device__ __forceinline__ void dq_f32_body(const F32Params& p, uint32_t block, floatx4_t* slots) {
+  using F = Frag<NP, EXACT>;
+  constexpr int NM = F::NM;
+  int bh, rank;
+  if (!decode_work(p.rmap, block, bh, rank)) return;
+  const int tt = p.rtiles - 1 - rank;
+  const int b = bh / p.Hq, h = bh - b * p.Hq, hk = h / p.G;
+  const int qa = tt >= p.rtile[0] ? 1 : 0;
+  const int row0 = (qa ? tt - p.rtile[0] : tt) * kT;
+  const Segment qs = qa ? p.g.q[1] : p.g.q[0];
+  const int lane = threadIdx.x & 63, i = lane & 15, g = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), waves = blockDim.x >> 6;
+  const TileList keys = keys_of_rows(p.g, qa, min(row0 + kT, qs.len) - 1);
+  if (keys.total == 0 && !p.overwrite) return;
+
+  const int off = row0 + i, row = qs.start + min(off, qs.len - 1);
+  const int64_t q_off = b * p.qs[0] + h * p.qs[1] + (int64_t)row * p.qs[2];
+  const typename F::Row qf = F::load_row(p.q + q_off, g, p.d), of = F::load_row(p.d_o + q_off, g, p.d);
+  const int64_t srow = ((int64_t)b * p.Hq + h) * p.q_len + row;
+  const float lse = p.lse_in[srow], dl = p.delta[srow];
+  const float* kbase = p.k + b * p.ks[0] + hk * p.ks[1];
+  const float* vbase = p.v + b * p.ks[0] + hk * p.ks[1];
+  typename F::Acc acc = F::zero();
+  for (int t = wave; t < keys.total; t += waves) {
+    const TileList::Tile tl = keys.at(t);
+    const int64_t koff = (int64_t)(tl.start + min(tl.j0 + i, tl.len - 1)) * p.ks[2];
+    const float* ktile = kbase + (int64_t)tl.start * p.ks[2];
+    const typename F::Row kf = F::load_row(kbase + koff, g, p.d), vf = F::load_row(vbase + koff, g, p.d);
+    const typename F::Col kc = F::load_col(ktile, p.ks[2], tl.j0, tl.len - 1, i, g, p.d);
+    __builtin_amdgcn_sched_barrier(0);
+    const floatx4_t s = F::rows_product(kf, qf), dp = F::rows_product(vf, of);
+    const bool masked = tl.j0 + kT > tl.len || (tl.diag && tl.j0 + kT - 1 > row0);
+    floatx4_t w;
+    int ok = 0;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int key = tl.j0 + 4 * g + v;
+      const bool yes = lse != -INFINITY && (!masked || (key < tl.len && (!tl.diag || key <= off)));
+      ok |= yes ? 1 << v : 0;
+      w[v] = yes ? fast_exp2(fmaf(s[v], p.scale, -lse) * kLog2e) * (dp[v] - dl) : 0.f;
+    }
+    if (masked) F::cols_product_masked(acc, kc, w, ok, ktile, p.ks[2], tl.j0, tl.len - 1, i, g, p.d);
+    else F::cols_product(acc, kc, w);
+  }
+  add_waves<F>(acc, slots, wave, waves, lane);
+  if (off >= qs.len || (lse == -INFINITY && !p.overwrite)) return;
+  float* dst = p.dq + b * p.os[0] + h * p.os[1] + (int64_t)row * p.os[2];
+#pragma unroll
+  for (int pc = 0; pc < NM; ++pc)
+    if (pc % waves == wave && (EXACT || F::piece_col(pc, g) < p.d)) {
+      floatx4_t* at = reinterpret_cast<floatx4_t*>(dst + F::piece_col(pc, g));
+      const floatx4_t x = F::piece(acc, pc) * p.scale;
+      *at = p.overwrite ? x : *at + x;
+    }
+}
+
+// ---- backward, key-owning half: dK and dV of 16 keys, over the rows of every head of the group
+template <int NP, bool EXACT>
+__device__ __forceinline__ void dkv_f32_body(const F32Params& p, uint32_t block, floatx4_t* slots) {
+  using F = Frag<NP, EXACT>;
+  constexpr int NM = F::NM;
+  int bhk, kt;  // key tiles in storage order see ever fewer rows
+  if (!decode_work(p.kmap, block, bhk, kt)) return;
+  const int b = bhk / p.Hkv, hk = bhk - b * p.Hkv;
+  const int kb = kt >= p.ktile[0] ? 1 : 0;
+  const int key0 = (kb ? kt - p.ktile[0] : kt) * kT;
+  const Segment ks = kb ? p.g.k[1] : p.g.k[0];
+  const int lane = threadIdx.x & 63, i = lane & 15, g = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), waves = blockDim.x >> 6;
+  const TileList rows = rows_of_keys(p.g, kb, key0);
+
+  const int off = key0 + i, key = ks.start + min(off, ks.len - 1);
+  const int64_t k_off = b * p.ks[0] + hk * p.ks[1] + (int64_t)key * p.ks[2];
+  const typename F::Row kf = F::load_row(p.k + k_off, g, p.d), vf = F::load_row(p.v + k_off, g, p.d);
+  typename F::Acc ak = F::zero(), av = F::zero();
+  const int n = rows.total * p.G;
+  for (int t = wave; t < n; t += waves) {
+    const int gq = t / rows.total, h = hk * p.G + gq;
+    const TileList::Tile tl = rows.at(t - gq * rows.total);
+    const int64_t tile = b * p.qs[0] + h * p.qs[1] + (int64_t)tl.start * p.qs[2];
+    const int64_t r = tile + (int64_t)min(tl.j0 + i, tl.len - 1) * p.qs[2];
+    const int64_t srow = ((int64_t)b * p.Hq + h) * p.q_len + tl.start;
+    const typename F::Row qf = F::load_row(p.q + r, g, p.d), of = F::load_row(p.d_o + r, g, p.d);
+    float lse[4], dl[4];
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int ro = min(tl.j0 + 4 * g + v, tl.len - 1);
+      lse[v] = p.lse_in[srow + ro]; dl[v] = p.delta[srow + ro];
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    const floatx4_t s = F::rows_product(qf, kf);
+    const typename F::Col oc = F::load_col(p.d_o + tile, p.qs[2], tl.j0, tl.len - 1, i, g, p.d);  // (Q's registers are free)
+    __builtin_amdgcn_sched_barrier(0);
+    const floatx4_t dp = F::rows_product(of, vf);
+    const typename F::Col qc = F::load_col(p.q + tile, p.qs[2], tl.j0, tl.len - 1, i, g, p.d);
+    __builtin_amdgcn_sched_barrier(0);
+    const bool masked = tl.j0 + kT > tl.len || (tl.diag && key0 + kT - 1 > tl.j0);
+    floatx4_t w, e;
+    int ok = 0;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int ro = tl.j0 + 4 * g + v;
+      const bool yes = lse[v] != -INFINITY && (!masked || (ro < tl.len && (!tl.diag || off <= ro)));
+      ok |= yes ? 1 << v : 0;
+      w[v] = yes ? fast_exp2(fmaf(s[v], p.scale, -lse[v]) * kLog2e) : 0.f;
+      e[v] = yes ? w[v] * (dp[v] - dl[v]) : 0.f;
+    }
+    if (masked) {
+      F::cols_product_masked(av, oc, w, ok, p.d_o + tile, p.qs[2], tl.j0, tl.len - 1, i, g, p.d);
+      F::cols_product_masked(ak, qc, e, ok, p.q + tile, p.qs[2], tl.j0, tl.len - 1, i, g, p.d);
+    } else {
+      F::cols_product(av, oc, w);
+      F::cols_product(ak, qc, e);
+    }
+  }
+  add_waves<F>(av, slots, wave, waves, lane);
+  __syncthreads();
+  add_waves<F>(ak, slots, wave, waves, lane);
+  if (off >= ks.len) return;
+  const int64_t dst = (((int64_t)b * p.Hkv + hk) * p.kv_len + key) * p.d;
+#pragma unroll
+  for (int pc = 0; pc < NM; ++pc)
+    if (pc % waves == wave && (EXACT || F::piece_col(pc, g) < p.d)) {
+      floatx4_t* at_k = reinterpret_cast<floatx4_t*>(p.dk + dst + F::piece_col(pc, g));
+      floatx4_t* at_v = reinterpret_cast<floatx4_t*>(p.dv + dst + F::piece_col(pc, g));
+      floatx4_t x = F::piece(ak, pc) * p.scale, y = F::piece(av, pc);
+      if (p.accumulate) { x += *at_k; y += *at_v; }
+      *at_k = x;
+      *at_v = y;
+    }
+}
+
+// Both halves in one launch: key tiles first (the longer ones), then row tiles; `nk` key workgroups.
+template <int NP, bool EXACT>
+__global__ __launch_bounds__(max_bwd_waves(NP) * 64) void bwd_f32_kernel(const F32Params p, uint32_t nk) {
+  __shared__ floatx4_t slots[max_bwd_waves(NP) * Frag<NP, EXACT>::NM * 64];
+  if (blockIdx.x < nk) dkv_f32_body<NP, EXACT>(p, blockIdx.x, slots);
+  else dq_f32_body<NP, EXACT>(p, blockIdx.x - nk, slots);
 }
 
 F32Params make_params(const loong_step_desc& d, const StepGeom& g) {
@@ -234,8 +502,66 @@ F32Params make_params(const loong_step_desc& d, const StepGeom& g) {
   p.B = d.batch; p.Hq = d.n_q_heads; p.Hkv = d.n_kv_heads; p.G = d.n_q_heads / d.n_kv_heads;
   p.d = d.head_dim; p.q_len = d.q_len; p.kv_len = d.kv_len;
   for (int i = 0; i < 3; ++i) { p.qs[i] = d.q_stride[i]; p.ks[i] = d.kv_stride[i]; p.os[i] = d.o_stride[i]; }
-  p.g = g; p.scale = d.softmax_scale; p.flags = d.flags;
+  p.g = g; p.scale = d.softmax_scale;
+  p.fuse = (d.flags & LOONG_FUSE_MERGE) != 0;
+  p.overwrite = (d.flags & LOONG_OVERWRITE_DQ) != 0;
+  p.accumulate = (d.flags & LOONG_ACCUM_DKV) != 0;
   return p;
+}
+
+int tiles(int len, int t) { return (len + t - 1) / t; }
+
+void tile_rows(F32Params& p, int height) {
+  p.rtiles = 0;
+  for (int a = 0; a < 2; ++a) {
+    p.rtile[a] = a < p.g.nq ? tiles(p.g.q[a].len, height) : 0;
+    p.rtiles += p.rtile[a];
+  }
+  p.rmap = make_work_map((int64_t)p.B * p.Hq, p.rtiles);
+}
+
+// `most` waves share a tile's loop, fewer where the grid would hold more threads than a launch takes.
+int pick_waves(int64_t workgroups, int most) {
+  int w = most;
+  while (w > 1 && workgroups * w * 64 >= (int64_t)1 << 32) w >>= 1;
+  return w;
+}
+
+template <int NP, bool EXACT>
+int launch_fwd(F32Params& p, int cus, hipStream_t st) {
+  // 32-row workgroups where they still put two on every unit (16384 rows, d = 128, a pass of two steps: 131 us
+  // against 156 with two waves per tile).  16-row ones share a tile among eight waves while that is at most two
+  // waves per SIMD, else among four (4 heads x 600 rows, d = 128: 35 us with four, 41 with eight, 51 with two).
+  tile_rows(p, 2 * kT);
+  const int64_t wide = (int64_t)p.B * p.Hq * p.rtiles;
+  if (wide >= 2 * cus) {
+    const int w = pick_waves(p.rmap.grid, 4);
+    fwd_f32_kernel<NP, EXACT, 2><<<dim3(p.rmap.grid), dim3(w * 64), 0, st>>>(p);
+  } else {
+    tile_rows(p, kT);
+    const int w = pick_waves(p.rmap.grid, (int64_t)p.rmap.grid * kMaxWaves <= (int64_t)cus * 8 ? kMaxWaves : 4);
+    fwd_f32_kernel<NP, EXACT, 1><<<dim3(p.rmap.grid), dim3(w * 64), 0, st>>>(p);
+  }
+  return check_launch("loong_attn_step_fwd (fp32)");
+}
+
+template <int NP, bool EXACT>
+int launch_bwd(F32Params& p, bool do_dq, bool do_dkv, hipStream_t st) {
+  tile_rows(p, kT);
+  for (int a = 0; a < 2; ++a) {
+    p.ktile[a] = a < p.g.nk ? tiles(p.g.k[a].len, kT) : 0;
+    p.ktiles += p.ktile[a];
+  }
+  p.kmap = make_work_map((int64_t)p.B * p.Hkv, p.ktiles);
+  const uint32_t nk = do_dkv ? p.kmap.grid : 0, nq = do_dq ? p.rmap.grid : 0;
+  if (((int64_t)nk + nq) * 64 < (int64_t)1 << 32) {
+    const int w = pick_waves((int64_t)nk + nq, max_bwd_waves(NP));
+    bwd_f32_kernel<NP, EXACT><<<dim3(nk + nq), dim3(w * 64), 0, st>>>(p, nk);
+  } else {  // more workgroups than one grid takes
+    bwd_f32_kernel<NP, EXACT><<<dim3(nk), dim3(pick_waves(nk, max_bwd_waves(NP)) * 64), 0, st>>>(p, nk);
+    bwd_f32_kernel<NP, EXACT><<<dim3(nq), dim3(pick_waves(nq, max_bwd_waves(NP)) * 64), 0, st>>>(p, 0);
+  }
+  return check_launch("loong_attn_step_bwd (fp32)");
 }
 
 }  // namespace
@@ -245,10 +571,15 @@ int launch_fwd_f32(const loong_step_desc& d, const StepGeom& g, const void* q, c
   const int64_t rows = (int64_t)d.batch * d.n_q_heads * d.q_len;
   if (rows == 0) return LOONG_OK;
   if (rows > 0x7fffffff) return fail(LOONG_E_UNSUPPORTED, "fp32 path: more than 2^31-1 query rows");
+  DeviceFacts dev;
+  if (int rc = device_facts(&dev)) return rc;
   F32Params p = make_params(d, g);
   p.q = (const float*)q; p.k = (const float*)k; p.v = (const float*)v; p.out = out; p.lse = lse;
-  fwd_f32_kernel<<<dim3((unsigned)rows), dim3(64), 0, static_cast<hipStream_t>(stream)>>>(p);
-  return check_launch("loong_attn_step_fwd (fp32)");
+  hipStream_t st = static_cast<hipStream_t>(stream);
+  if (d.head_dim == 32) return launch_fwd<32, true>(p, dev.cus, st);
+  if (d.head_dim == 64) return launch_fwd<64, true>(p, dev.cus, st);
+  if (d.head_dim == 128) return launch_fwd<128, true>(p, dev.cus, st);
+  return launch_fwd<128, false>(p, dev.cus, st);
 }
 
 int launch_bwd_f32(const loong_step_desc& d, const StepGeom& g, const void* q, const void* k,
@@ -258,20 +589,17 @@ int launch_bwd_f32(const loong_step_desc& d, const StepGeom& g, const void* q, c
   const int64_t krows = (int64_t)d.batch * d.n_kv_heads * d.kv_len;
   if (qrows > 0x7fffffff || krows > 0x7fffffff)
     return fail(LOONG_E_UNSUPPORTED, "fp32 path: more than 2^31-1 rows");
+  const bool do_dq = !(d.flags & LOONG_BWD_ONLY_DKV) && qrows > 0 && (krows > 0 || (d.flags & LOONG_OVERWRITE_DQ));
+  const bool do_dkv = !(d.flags & LOONG_BWD_ONLY_DQ) && krows > 0;
+  if (!do_dq && !do_dkv) return LOONG_OK;
   F32Params p = make_params(d, g);
   p.q = (const float*)q; p.k = (const float*)k; p.v = (const float*)v; p.d_o = (const float*)d_o;
   p.lse_in = lse; p.delta = delta; p.dq = dq; p.dk = dk; p.dv = dv;
   hipStream_t st = static_cast<hipStream_t>(stream);
-  const bool do_dq = !(d.flags & LOONG_BWD_ONLY_DKV), do_dkv = !(d.flags & LOONG_BWD_ONLY_DQ);
-  if (do_dq && qrows > 0 && (krows > 0 || (d.flags & LOONG_OVERWRITE_DQ))) {
-    bwd_dq_f32_kernel<<<dim3((unsigned)qrows), dim3(64), 0, st>>>(p);
-    if (int rc = check_launch("loong_attn_step_bwd (fp32 dq)")) return rc;
-  }
-  if (do_dkv && krows > 0) {
-    bwd_dkv_f32_kernel<<<dim3((unsigned)krows), dim3(64), 0, st>>>(p);
-    if (int rc = check_launch("loong_attn_step_bwd (fp32 dk/dv)")) return rc;
-  }
-  return LOONG_OK;
+  if (d.head_dim == 32) return launch_bwd<32, true>(p, do_dq, do_dkv, st);
+  if (d.head_dim == 64) return launch_bwd<64, true>(p, do_dq, do_dkv, st);
+  if (d.head_dim == 128) return launch_bwd<128, true>(p, do_dq, do_dkv, st);
+  return launch_bwd<128, false>(p, do_dq, do_dkv, st);
 }
 
 }  // namespace loong
