@@ -166,6 +166,21 @@ LOONG_API int loong_attn_step_bwd(const loong_step_desc* desc, const void* q, co
                         void* stream);
 
 /*
+ * A run of backward micro-steps whose visiting chunks are all resident, in as few launches as pay off:
+ * the result of loong_attn_step_bwd called for step 0, 1, ... n_steps - 1, within rounding (dq is
+ * summed over all steps in registers before it is added to or written).  `descs` are equal in all but
+ * kv_chunk (LOONG_E_SHAPE otherwise); k, v, dk, dv are host arrays of n_steps device pointers; the steps
+ * run in no order, so their dk and dv must be distinct memory (equal pointers: LOONG_E_SHAPE).  Flags as for one step;
+ * LOONG_COMPUTE_DELTA and LOONG_OVERWRITE_DQ apply once, to the run.  `workspace`: at least
+ * loong_workspace_bytes_steps(descs, n_steps) bytes, same contract.  The results are bit-reproducible.
+ */
+LOONG_API int loong_attn_steps_bwd(const loong_step_desc* descs, int32_t n_steps, const void* q, const void* const* k,
+                         const void* const* v, const void* o, const void* d_o, const float* lse, float* delta,
+                         float* dq, float* const* dk, float* const* dv, void* workspace, int64_t workspace_bytes,
+                         void* stream);
+LOONG_API int loong_workspace_bytes_steps(const loong_step_desc* descs, int32_t n_steps, int64_t* bytes);
+
+/*
  * loong_attn_step_bwd for callers that cannot allocate device memory or bring a workspace: code
  * under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same
  * arguments, semantics, results (bit for bit) and errors as loong_attn_step_bwd, except that

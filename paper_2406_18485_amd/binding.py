@@ -31,6 +31,7 @@ EXPORTS = (
     "loong_bwd_delta", "loong_init_running", "loong_finalize_out", "loong_validate_step",
     "loong_last_error", "loong_version", "loong_mfma_probe", "loong_cost_model", "loong_cost_search",
     "loong_permute_rows", "loong_reduce_replicas", "loong_workspace_bytes", "loong_attn_step_bwd_static",
+    "loong_attn_steps_bwd", "loong_workspace_bytes_steps",
 )
 
 
@@ -88,6 +89,9 @@ lib.loong_attn_step_fwd.argtypes = [C.POINTER(StepDesc), _vp, _vp, _vp, _vp, _vp
 lib.loong_lse_merge.argtypes = [_i64, _i32, _vp, _vp, _vp, _vp, _vp]
 lib.loong_attn_step_bwd.argtypes = [C.POINTER(StepDesc)] + [_vp] * 11 + [_i64, _vp]
 lib.loong_attn_step_bwd_static.argtypes = [C.POINTER(StepDesc)] + [_vp] * 11
+lib.loong_attn_steps_bwd.argtypes = ([C.POINTER(StepDesc), _i32, _vp, C.POINTER(_vp), C.POINTER(_vp)] + [_vp] * 5 +
+                                     [C.POINTER(_vp)] * 2 + [_vp, _i64, _vp])
+lib.loong_workspace_bytes_steps.argtypes = [C.POINTER(StepDesc), _i32, C.POINTER(C.c_int64)]
 lib.loong_bwd_delta.argtypes = [C.POINTER(StepDesc), _vp, _vp, _vp, _vp]
 lib.loong_init_running.argtypes = [_i64, _i32, _vp, _vp, _vp]
 lib.loong_finalize_out.argtypes = [_i64, _i32, _vp, _vp, _i32, _vp]
@@ -232,6 +236,21 @@ def attn_step_bwd(desc: StepDesc, q, k, v, o, d_o, lse, delta, dq, dk, dv, works
     _check(lib.loong_attn_step_bwd(C.byref(desc), _ptr(q), _ptr(k), _ptr(v), _ptr(o), _ptr(d_o), _ptr(lse),
                                    _ptr(delta), _ptr(dq), _ptr(dk), _ptr(dv), _ptr(workspace), workspace_bytes,
                                    _stream(stream)))
+
+
+def workspace_bytes_steps(descs) -> int:
+    """Bytes of workspace attn_steps_bwd needs; `descs` is a ctypes array of StepDesc."""
+    n = C.c_int64(0)
+    _check(lib.loong_workspace_bytes_steps(descs, len(descs), C.byref(n)))
+    return n.value
+
+
+def attn_steps_bwd(descs, q, k, v, o, d_o, lse, delta, dq, dk, dv, workspace, stream=None):
+    """loong_attn_steps_bwd: `descs` is a ctypes array of StepDesc; k, v, dk, dv hold one tensor (or pointer) per step."""
+    ptrs = [(_vp * len(descs))(*map(_ptr, x)) for x in (k, v, dk, dv)]
+    _check(lib.loong_attn_steps_bwd(descs, len(descs), _ptr(q), ptrs[0], ptrs[1], _ptr(o), _ptr(d_o), _ptr(lse), _ptr(delta),
+                                    _ptr(dq), ptrs[2], ptrs[3], _ptr(workspace), workspace.numel() * workspace.element_size(),
+                                    _stream(stream)))
 
 
 STATIC_SCRATCH_BYTES = (64 << 20) + 65536

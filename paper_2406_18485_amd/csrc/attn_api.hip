@@ -1,9 +1,52 @@
 // C entry points of the forward and backward micro-step: validate, then dispatch on dtype.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+#include <cmath>
+#include <cstring>
+
 #include "loong_internal.h"
+#include "step_table.h"
 
 using namespace loong;
+
+namespace {
+
+// Step `t` of a run: valid by itself and equal to the first in all but the visiting chunk's ids.
+int check_run(const loong_step_desc* descs, int t, StepGeom* g) {
+  if (!descs) return fail(LOONG_E_NULL, "descriptor is NULL");
+  if (int rc = check_step(&descs[t], g)) return rc;
+  const loong_step_desc &a = descs[0], &b = descs[t];
+  if (a.batch != b.batch || a.n_q_heads != b.n_q_heads || a.n_kv_heads != b.n_kv_heads || a.head_dim != b.head_dim ||
+      a.q_len != b.q_len || a.kv_len != b.kv_len || a.chunk_len != b.chunk_len ||
+      std::memcmp(a.q_chunk, b.q_chunk, sizeof(a.q_chunk)) || a.causal != b.causal || a.dtype != b.dtype ||
+      a.softmax_scale != b.softmax_scale || a.flags != b.flags || std::memcmp(a.q_stride, b.q_stride, sizeof(a.q_stride)) ||
+      std::memcmp(a.kv_stride, b.kv_stride, sizeof(a.kv_stride)) || std::memcmp(a.o_stride, b.o_stride, sizeof(a.o_stride)))
+    return fail(LOONG_E_SHAPE, "step %d of a run differs from the first in more than its key chunks", t);
+  return LOONG_OK;
+}
+
+// Steps of a valid run that go into one launch.  More steps hide more ramps and ragged ends, but the
+// key-owning workgroups of a long launch drift apart and no longer find each other's query tiles in L2: a
+// launch takes steps up to about 1.3 ms of work (the rate at head_dim 64 is 0.6 of that at 128), and never splits one.  Backward passes with 1 / 2 / 4 / all steps per
+// launch: 8 steps of 98 us (4 heads x 4096 rows) 781 / 676 / 525 / 472 us, 8 of 425 us (8 x 8192 rows, one kv
+// head) 3398 / 3365 / 3247 / 3313, 8 of 820 us (4 x 16384) 6541 / 6477 / 6503 / 6707, 4 of 1090 us
+// (8 x 16000 rows, head_dim 64) 4352 / 4727 / 5118 / 5066.
+int steps_per_launch(const loong_step_desc* descs, int n_steps) {
+  const loong_step_desc& d = descs[0];
+  double pairs = 0;
+  StepGeom g;
+  for (int t = 0; t < n_steps; ++t) {
+    check_step(&descs[t], &g);
+    for (int a = 0; a < g.nq; ++a) pairs += keys_of_rows(g, a) * g.q[a].len;
+  }
+  const double flops = 14. * d.head_dim * pairs * d.n_q_heads * d.batch;
+  const double per_launch = 9.4e9 * d.head_dim;
+  const int launches = (int)std::max(std::min(std::ceil(flops / per_launch), (double)n_steps), std::ceil(n_steps / (double)kMaxSteps));
+  return (n_steps + launches - 1) / launches;
+}
+
+}  // namespace
 
 extern "C" {
 
@@ -23,23 +66,42 @@ int loong_attn_step_fwd(const loong_step_desc* desc, const void* q, const void* 
 int loong_attn_step_bwd(const loong_step_desc* desc, const void* q, const void* k, const void* v,
                         const void* o, const void* d_o, const float* lse, float* delta, float* dq,
                         float* dk, float* dv, void* workspace, int64_t workspace_bytes, void* stream) {
+  return loong_attn_steps_bwd(desc, 1, q, &k, &v, o, d_o, lse, delta, dq, &dk, &dv, workspace, workspace_bytes, stream);
+}
+
+int loong_attn_steps_bwd(const loong_step_desc* descs, int32_t n_steps, const void* q, const void* const* k,
+                         const void* const* v, const void* o, const void* d_o, const float* lse, float* delta,
+                         float* dq, float* const* dk, float* const* dv, void* workspace, int64_t workspace_bytes,
+                         void* stream) {
   clear_error();
-  StepGeom g;
-  if (int rc = check_step(desc, &g)) return rc;
+  if (n_steps < 1) return fail(LOONG_E_SHAPE, "loong_attn_steps_bwd: %d steps", n_steps);
+  StepGeom g[kMaxSteps];
+  // every step is validated before anything is enqueued
+  for (int t = 0; t < n_steps; ++t)
+    if (int rc = check_run(descs, t, &g[0])) return rc;
+  const loong_step_desc* desc = descs;
   const bool only_dkv = desc->flags & LOONG_BWD_ONLY_DKV, only_dq = desc->flags & LOONG_BWD_ONLY_DQ;
   if (only_dkv && only_dq)
     return fail(LOONG_E_UNSUPPORTED, "loong_attn_step_bwd: LOONG_BWD_ONLY_DKV and LOONG_BWD_ONLY_DQ exclude each other");
   if (!q || !k || !v || !d_o || !lse || !delta || (!only_dkv && !dq) || (!only_dq && (!dk || !dv)))
     return fail(LOONG_E_NULL, "loong_attn_step_bwd: NULL tensor");
+  for (int t = 0; t < n_steps; ++t)
+    if (!k[t] || !v[t] || (!only_dq && (!dk[t] || !dv[t]))) return fail(LOONG_E_NULL, "loong_attn_step_bwd: NULL tensor");
   const bool want_delta = desc->flags & LOONG_COMPUTE_DELTA;
   if (want_delta && !o) return fail(LOONG_E_NULL, "loong_attn_step_bwd: LOONG_COMPUTE_DELTA needs o");
-  if (!aligned16(q) || !aligned16(k) || !aligned16(v) || !aligned16(d_o) || (!only_dkv && !aligned16(dq)) ||
-      (!only_dq && (!aligned16(dk) || !aligned16(dv))) || (want_delta && !aligned16(o)))
-    return fail(LOONG_E_ALIGN, "loong_attn_step_bwd: tensors must be 16-byte aligned");
+  bool aligned = aligned16(q) && aligned16(d_o) && (only_dkv || aligned16(dq)) && (!want_delta || aligned16(o));
+  for (int t = 0; t < n_steps; ++t)
+    aligned = aligned && aligned16(k[t]) && aligned16(v[t]) && (only_dq || (aligned16(dk[t]) && aligned16(dv[t])));
+  if (!aligned) return fail(LOONG_E_ALIGN, "loong_attn_step_bwd: tensors must be 16-byte aligned");
+  for (int t = 1; t < n_steps && !only_dq; ++t)  // the steps of a launch run in no order
+    for (int u = 0; u < t; ++u)
+      if (dk[t] == dk[u] || dv[t] == dv[u] || dk[t] == dv[u] || dv[t] == dk[u])
+        return fail(LOONG_E_SHAPE, "loong_attn_steps_bwd: steps %d and %d have the same dk or dv", u, t);
   if (workspace_bytes < 0) return fail(LOONG_E_SHAPE, "loong_attn_step_bwd: negative workspace size");
   if (desc->batch == 0) return LOONG_OK;
   if (desc->dtype != LOONG_FP32) {  // scratch for shared query loops: checked before anything is enqueued
-    const int64_t need = bwd_workspace_bytes_bf16(*desc, g);
+    int64_t need = 0;
+    if (int rc = loong_workspace_bytes_steps(descs, n_steps, &need)) return rc;
     if (need > 0) {
       if (!workspace)
         return fail(LOONG_E_NULL, "loong_attn_step_bwd: this step needs a workspace of %lld bytes (loong_workspace_bytes)",
@@ -52,17 +114,42 @@ int loong_attn_step_bwd(const loong_step_desc* desc, const void* q, const void* 
   }
   if (want_delta)
     if (int rc = loong_bwd_delta(desc, o, d_o, delta, stream)) return rc;
-  return desc->dtype == LOONG_FP32
-             ? launch_bwd_f32(*desc, g, q, k, v, d_o, lse, delta, dq, dk, dv, stream)
-             : launch_bwd_bf16(*desc, g, q, k, v, d_o, lse, delta, dq, dk, dv, workspace, workspace_bytes, stream);
+  const int per_launch = steps_per_launch(descs, n_steps);
+  for (int t0 = 0; t0 < n_steps; t0 += per_launch) {
+    const int n = std::min(n_steps - t0, per_launch);
+    loong_step_desc d = *desc;
+    for (int t = 0; t < n; ++t)
+      if (int rc = check_step(&descs[t0 + t], &g[t])) return rc;
+    if (t0 > 0) d.flags &= ~LOONG_OVERWRITE_DQ;
+    float *const *dk_t = only_dq ? nullptr : dk + t0, *const *dv_t = only_dq ? nullptr : dv + t0;
+    if (int rc = desc->dtype == LOONG_FP32
+                     ? launch_bwd_f32(d, g, n, q, k + t0, v + t0, d_o, lse, delta, dq, dk_t, dv_t, stream)
+                     : launch_bwd_bf16(d, g, n, q, k + t0, v + t0, d_o, lse, delta, dq, dk_t, dv_t, workspace, workspace_bytes, stream))
+      return rc;
+  }
+  return LOONG_OK;
 }
 
 int loong_workspace_bytes(const loong_step_desc* desc, int64_t* bytes) {
+  return loong_workspace_bytes_steps(desc, 1, bytes);
+}
+
+int loong_workspace_bytes_steps(const loong_step_desc* descs, int32_t n_steps, int64_t* bytes) {
   clear_error();
-  StepGeom g;
-  if (int rc = check_step(desc, &g)) return rc;
+  if (n_steps < 1) return fail(LOONG_E_SHAPE, "loong_workspace_bytes_steps: %d steps", n_steps);
+  StepGeom g[kMaxSteps];
+  for (int t = 0; t < n_steps; ++t)
+    if (int rc = check_run(descs, t, &g[0])) return rc;
   if (!bytes) return fail(LOONG_E_NULL, "loong_workspace_bytes: NULL result");
-  *bytes = desc->dtype == LOONG_FP32 ? 0 : bwd_workspace_bytes_bf16(*desc, g);
+  *bytes = 0;
+  if (descs->dtype == LOONG_FP32) return LOONG_OK;
+  const int per_launch = steps_per_launch(descs, n_steps);
+  for (int t0 = 0; t0 < n_steps; t0 += per_launch) {
+    const int n = std::min(n_steps - t0, per_launch);
+    for (int t = 0; t < n; ++t)
+      if (int rc = check_step(&descs[t0 + t], &g[t])) return rc;
+    *bytes = std::max(*bytes, bwd_workspace_bytes_bf16(descs[0], g, n));
+  }
   return LOONG_OK;
 }
 

@@ -16,6 +16,9 @@
 namespace loong {
 namespace {
 
+constexpr double kLoopShare = 0.3;  // several steps per launch: a key tile's loop over the time of a unit
+constexpr double kRowShare = 0.8;   // the same for the loop of a row-owning workgroup, which starts first
+
 __global__ __launch_bounds__(256) void zero_kernel(int64_t n4, float4* a, float4* b) {
   const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (i < n4) {
@@ -31,43 +34,81 @@ __global__ __launch_bounds__(256) void clear_counters_kernel(int n, uint32_t* cn
   if (i < n) cnt[i] = 0u;
 }
 
-// Work list of a step: key tiles per key segment (only segments some query can see), whether
-// a key segment nobody sees exists (its gradients are cleared by the zero pass), and how many
-// workgroups share the query loop of a key tile: more than one when the listed tiles are
-// fewer than the compute units (`cus`), and twice as many when a diagonal block makes the loop
-// lengths uneven.
+// Work list of a launch over `n` micro-steps that differ in the visiting chunk only: the key halves some
+// row sees and those nobody sees (their gradients are cleared), and how many workgroups share the query
+// loop of a key tile.
 struct SplitPlan {
-  int nkt[2], kt_total, nsplit;
-  bool unseen_keys;
+  int nkt, nsplit;
   int64_t busy;  // listed key tiles x kv heads x batch
+  double per_cu, longest_loop, longest_row;  // multiply-adds per head_dim: all / CUs; of a key tile's loop; of a row's keys
 };
 
-SplitPlan plan_split(const StepGeom& g, int G, int Hkv, int B, int q_len, int cus) {
+SplitPlan plan_split(const StepGeom* g, int n, int G, int Hkv, int B, int q_len, int cus, StepTable* tab) {
   constexpr int BM = kBwdBM, BN = kBwdBN;
   SplitPlan s{};
+  uint32_t entry[kMaxHalves];
+  int64_t rows[kMaxHalves];
+  int n_halves = 0, n_seen = 0, n_list[2] = {0, 0}, n_diag[2] = {0, 0};
   bool diag = false;
-  for (int kb = 0; kb < 2; ++kb) {
-    bool seen = false;
-    if (kb < g.nk)
-      for (int a = 0; a < g.nq; ++a) {
-        seen |= g.cls[a][kb] != LOONG_SKIP && g.q[a].len > 0;
-        diag |= g.cls[a][kb] == LOONG_DIAG;
+  double pairs = 0, most_keys = 0;
+  int64_t most_rows = 0;
+  for (int t = 0; t < n; ++t)
+    for (int kb = 0; kb < g[t].nk; ++kb) {
+      if (g[t].k[kb].len == 0) continue;
+      uint32_t e = (uint32_t)t | (uint32_t)kb << 8;
+      int64_t seen = 0;
+      for (int a = 0; a < g[t].nq; ++a) {
+        const int cls = g[t].cls[a][kb];
+        e |= (uint32_t)cls << (10 + 2 * a);
+        if (cls == LOONG_SKIP || g[t].q[a].len == 0) continue;
+        seen += g[t].q[a].len;
+        diag |= cls == LOONG_DIAG;
+        if (tab) tab->row_list[a][n_list[a]] = (uint32_t)t | (uint32_t)kb << 8 | (cls == LOONG_DIAG ? kDiagEntry : 0u);
+        ++n_list[a];
+        n_diag[a] += cls == LOONG_DIAG;
       }
-    s.nkt[kb] = seen ? (g.k[kb].len + BN - 1) / BN : 0;
-    s.kt_total += s.nkt[kb];
-    s.unseen_keys |= kb < g.nk && !seen && g.k[kb].len > 0;
+      // halves with longer query loops first, visit order among equals, unseen ones last
+      int at = n_halves++;
+      for (; at > 0 && rows[at - 1] < seen && (n > 1 || rows[at - 1] == 0); --at) { rows[at] = rows[at - 1]; entry[at] = entry[at - 1]; }
+      rows[at] = seen; entry[at] = e;
+      n_seen += seen > 0;
+      most_rows = std::max(most_rows, seen);
+    }
+  for (int a = 0; a < g[0].nq; ++a) {
+    double keys = 0;
+    for (int t = 0; t < n; ++t) keys += keys_of_rows(g[t], a);
+    pairs += keys * g[0].q[a].len;
+    most_keys = std::max(most_keys, keys);
   }
-  s.busy = (int64_t)s.kt_total * Hkv * B;
+  const int klen = g[0].k[0].len;
+  s.nkt = (klen + BN - 1) / BN;
+  s.busy = (int64_t)n_seen * s.nkt * Hkv * B;
+  // (the dK/dV half does 8 head_dim operations per pair, the dQ half 6)
+  s.per_cu = 14. * pairs * G * Hkv * B / cus;
+  s.longest_loop = 8. * BN * most_rows * G;
+  s.longest_row = 6. * most_keys;
+  if (tab) {
+    tab->klen = klen; tab->n_seen = n_seen; tab->n_halves = n_halves;
+    for (int i = 0; i < n_halves; ++i) tab->half[i] = entry[i];
+    for (int a = 0; a < 2; ++a) { tab->n_list[a] = n_list[a]; tab->n_diag[a] = n_diag[a]; }
+  }
   int nsplit = 1;
   const int64_t q_tiles = std::max<int64_t>((int64_t)G * ((q_len + BM - 1) / BM), 1);
-  if (s.busy > 0 && s.busy < cus) nsplit = (int)std::min<int64_t>((cus + s.busy - 1) / s.busy, 16);
-  if (diag && s.busy * nsplit <= 2 * cus) nsplit *= 2;
+  if (n == 1) {
+    // one step: more than one workgroup when the listed tiles are fewer than the compute units, and
+    // twice as many when a diagonal block makes the loop lengths uneven
+    if (s.busy > 0 && s.busy < cus) nsplit = (int)std::min<int64_t>((cus + s.busy - 1) / s.busy, 16);
+    if (diag && s.busy * nsplit <= 2 * cus) nsplit *= 2;
+  } else if (s.busy > 0) {
+    // several steps: the tiles fill the chip, the split keeps the longest loop a small part of a unit's time
+    nsplit = (int)std::min(std::max(std::ceil(s.longest_loop / (kLoopShare * s.per_cu)), 1.), 16.);
+  }
   // The last workgroup of a key tile adds up all its partial sums alone, at one CU's memory
   // rate (about 1.1 us per split), while a split shortens the loop by q_tiles x 1.9 us / n:
   // past n = sqrt(1.76 q_tiles) more splits lengthen the launch.
   nsplit = (int)std::min<int64_t>(nsplit, std::max<int64_t>(2, (int64_t)std::sqrt(1.76 * (double)q_tiles)));
   nsplit = (int)std::min<int64_t>(nsplit, q_tiles);
-  if (s.busy > kWsCounters) nsplit = 1;  // (cannot happen: loops are only shared when key tiles are few)
+  if (s.busy > kWsCounters) nsplit = 1;  // (cannot happen for one step: loops are only shared when key tiles are few)
   s.nsplit = nsplit;
   return s;
 }
@@ -77,77 +118,83 @@ size_t partial_bytes(const SplitPlan& s, int head_dim) {
   return s.nsplit > 1 ? (size_t)s.busy * s.nsplit * kBwdWaves * (head_dim / 32) * 16 * 64 * sizeof(float) : 0;
 }
 
-// ---- kernels: the two halves of a step, alone and in one launch.  In the common launch the key-owning
-// workgroups come first (they are the longer ones) and the row-owning ones fill the compute
+// ---- kernels: the two halves of a step, alone and in one launch.  In the common launch of one step the
+// key-owning workgroups come first (they are the longer ones) and the row-owning ones fill the compute
 // units as these finish: no gap and no second ramp between the halves, and where neither half has
 // a workgroup for every unit they run side by side.  A whole step, two launches (and the passes that
 // cleared counters and unseen keys) -> one: 2048 rows x 4096 keys x 8 heads 119.5 -> 116.2 us, the step
 // of the same work whose keys are half unseen 135.3 -> 116.0, 3000 x 5000 without mask 315 -> 216,
 // 400 rows x 200 keys x 4 heads 45 -> 19, 32768 x 16384 x 4 heads 3030 -> 3012.
+// With several steps in the launch the row-owning workgroups are the longer ones (their loop runs over the
+// keys of every step, dQ stays in registers throughout) and come first; the key tiles of all
+// steps fill the chip, so few query loops are shared and one ramp and one ragged end serve all steps.
+// A backward pass step by step -> as a run: 8 steps of 2048 rows x 4096 keys x 8 heads 1036 -> 850 us, 32 steps of
+// 2048 rows x 4 heads, one kv head 1522 -> 510, 4 steps of 400 rows x 4 heads 163 -> 81 (with its forward).
+// (Key-owning workgroups first in a run: 7 % slower at 8 x 2048 rows.  A split so fine that a key tile's loop
+// is 0.15 of a unit's time, not 0.3: 1 % slower there, 3 % at 8 heads x 3998 rows, head_dim 64.)
 template <class E, int D>
-__global__ __launch_bounds__(kBwdWaves * 64) void bwd_dkv_kernel(const DkvParams p) {
+__global__ __launch_bounds__(kBwdWaves * 64) void bwd_dkv_kernel(const StepTable tab, const DkvParams p) {
   __shared__ __attribute__((aligned(1024))) unsigned char smem[BwdCfg<D>::SMEM_BYTES];
-  dkv_body<E, D>(p, blockIdx.x, smem);
+  dkv_body<E, D>(tab, p, blockIdx.x, smem);
 }
 
 template <class E, int D, int KS>
-__global__ __launch_bounds__(kRowWaves * 64) void dq_kernel(const DqParams p) {
+__global__ __launch_bounds__(kRowWaves * 64) void dq_kernel(const StepTable tab, const DqParams p) {
   __shared__ __attribute__((aligned(1024))) unsigned char smem[DqCfg<D, KS>::SMEM_BYTES];
-  dq_body<E, D, KS>(p, blockIdx.x, smem);
+  dq_body<E, D, KS>(tab, p, blockIdx.x, smem);
 }
 
 template <class E, int D, int KS>
-__global__ __launch_bounds__(kBwdWaves * 64) void bwd_step_kernel(const DkvParams pk, const DqParams pq) {
+__global__ __launch_bounds__(kBwdWaves * 64) void bwd_step_kernel(const StepTable tab, const DkvParams pk, const DqParams pq) {
   constexpr int BYTES = BwdCfg<D>::SMEM_BYTES > DqCfg<D, KS>::SMEM_BYTES ? BwdCfg<D>::SMEM_BYTES : DqCfg<D, KS>::SMEM_BYTES;
   static_assert(kBwdWaves == kRowWaves, "one workgroup size for both halves");
   __shared__ __attribute__((aligned(1024))) unsigned char smem[BYTES];
-  if (blockIdx.x < pk.map.grid) dkv_body<E, D>(pk, blockIdx.x, smem);
-  else dq_body<E, D, KS>(pq, blockIdx.x - pk.map.grid, smem);
+  const bool second = blockIdx.x >= pq.first_grid;
+  const uint32_t block = blockIdx.x - (second ? pq.first_grid : 0u);
+  if (second == pq.rows_first) dkv_body<E, D>(tab, pk, block, smem);
+  else dq_body<E, D, KS>(tab, pq, block, smem);
 }
 
-// What a step enqueues: either half may be absent (flags, or nothing visible).
+// What a launch enqueues: either half may be absent (flags, or nothing visible).
 struct StepLaunch {
+  StepTable tab;
   DkvParams kv;
   DqParams q;
+  StepGeom rows;   // the q segments, and which of them see keys in any step
   bool do_kv, do_q;
 };
 
 // Key-owning half: work list, workspace and what is enqueued before it.
-int plan_dkv(DkvParams& p, int flags, int D, void* workspace, int64_t workspace_bytes, hipStream_t st, bool* launch) {
-  *launch = false;
+int plan_dkv(StepLaunch& s, const SplitPlan& plan, int n, int flags, int D, void* workspace, int64_t workspace_bytes, hipStream_t st) {
+  DkvParams& p = s.kv;
+  s.do_kv = false;
   // Only key tiles that some query can see are listed (eight equal ranges of the list, one
   // per XCD, then carry equal work).
-  const SplitPlan plan = plan_split(p.g, p.G, p.Hkv, p.B, p.q_len, planning_cus());
-  p.nkt[0] = plan.nkt[0]; p.nkt[1] = plan.nkt[1]; p.kt_total = plan.kt_total;
+  p.nkt = plan.nkt; p.kt_total = s.tab.n_seen * plan.nkt;
   p.nsplit = plan.nsplit;
   p.accumulate = (flags & LOONG_ACCUM_DKV) ? 1 : 0;
   const int64_t total = plan.busy * plan.nsplit;
   if (total > 0x3ffffff0) return fail(LOONG_E_UNSUPPORTED, "backward grid too large");
+  if (total == 0) {
+    if (p.accumulate) return LOONG_OK;
+    const int64_t n4 = (int64_t)p.B * p.Hkv * p.kv_len * D / 4;
+    for (int t = 0; t < n; ++t)
+      zero_kernel<<<dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, st>>>(n4, reinterpret_cast<float4*>(s.tab.dk[t]),
+                                                                            reinterpret_cast<float4*>(s.tab.dv[t]));
+    return check_launch("loong_attn_step_bwd (clear dk/dv)");
+  }
   p.map = make_work_map((int64_t)p.Hkv * p.B, (int64_t)p.kt_total * plan.nsplit);
   if (plan.nsplit > 1) {  // (size and alignment were checked by the entry point, against the same plan)
     if (!workspace || workspace_bytes < kWsHeadBytes + (int64_t)partial_bytes(plan, D))
       return fail(LOONG_E_SHAPE, "loong_attn_step_bwd: workspace too small");
     p.ws_cnt = static_cast<uint32_t*>(workspace);
     p.ws_part = reinterpret_cast<float*>(static_cast<unsigned char*>(workspace) + kWsHeadBytes);
-  }
-  if (total == 0) {
-    if (plan.unseen_keys && !p.accumulate) {
-      const int64_t n4 = (int64_t)p.B * p.Hkv * p.kv_len * D / 4;
-      zero_kernel<<<dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, st>>>(n4, reinterpret_cast<float4*>(p.dk),
-                                                                            reinterpret_cast<float4*>(p.dv));
-      return check_launch("loong_attn_step_bwd (clear dk/dv)");
+    if (!(flags & LOONG_WORKSPACE_CLEAN)) {
+      clear_counters_kernel<<<dim3((unsigned)((plan.busy + 255) / 256)), dim3(256), 0, st>>>((int)plan.busy, p.ws_cnt);
+      if (int rc = check_launch("loong_attn_step_bwd (clear counters)")) return rc;
     }
-    return LOONG_OK;
   }
-  if (plan.unseen_keys && !p.accumulate) {  // one of the two segments: the other one is listed
-    const Segment& z = p.g.k[plan.nkt[0] == 0 ? 0 : 1];
-    p.zero_start = z.start; p.zero_len = z.len;
-  }
-  if (plan.nsplit > 1 && !(flags & LOONG_WORKSPACE_CLEAN)) {
-    clear_counters_kernel<<<dim3((unsigned)((plan.busy + 255) / 256)), dim3(256), 0, st>>>((int)plan.busy, p.ws_cnt);
-    if (int rc = check_launch("loong_attn_step_bwd (clear counters)")) return rc;
-  }
-  *launch = true;
+  s.do_kv = true;
   return LOONG_OK;
 }
 
@@ -155,7 +202,7 @@ template <class E, int D, int KS>
 int launch_cfg(StepLaunch& s, hipStream_t st) {
   if (s.do_q) {
     DqParams& p = s.q;
-    const RowTiling rt = make_row_tiling(p.g, p.G, p.Hq, p.B, kRowWaves / KS, /*list_blind=*/p.overwrite);
+    const RowTiling rt = make_row_tiling(s.rows, p.G, p.Hq, p.B, kRowWaves / KS, /*list_blind=*/p.overwrite);
     p.GS = rt.GS; p.ntile[0] = rt.ntile[0]; p.ntile[1] = rt.ntile[1];
     p.tiles_total = rt.tiles_total; p.hgroups = rt.hgroups;
     if (rt.total_wg > 0x3ffffff0) return fail(LOONG_E_UNSUPPORTED, "backward (dQ) grid too large");
@@ -163,11 +210,12 @@ int launch_cfg(StepLaunch& s, hipStream_t st) {
     s.do_q = rt.total_wg > 0;
   }
   const dim3 block(kBwdWaves * 64);
-  if (s.do_kv && s.do_q && (int64_t)s.kv.map.grid + s.q.map.grid < 0x40000000)
-    bwd_step_kernel<E, D, KS><<<dim3(s.kv.map.grid + s.q.map.grid), block, 0, st>>>(s.kv, s.q);
-  else {
-    if (s.do_kv) bwd_dkv_kernel<E, D><<<dim3(s.kv.map.grid), block, 0, st>>>(s.kv);
-    if (s.do_q) dq_kernel<E, D, KS><<<dim3(s.q.map.grid), block, 0, st>>>(s.q);
+  if (s.do_kv && s.do_q && (int64_t)s.kv.map.grid + s.q.map.grid < 0x40000000) {
+    s.q.first_grid = s.q.rows_first ? s.q.map.grid : s.kv.map.grid;
+    bwd_step_kernel<E, D, KS><<<dim3(s.kv.map.grid + s.q.map.grid), block, 0, st>>>(s.tab, s.kv, s.q);
+  } else {
+    if (s.do_kv) bwd_dkv_kernel<E, D><<<dim3(s.kv.map.grid), block, 0, st>>>(s.tab, s.kv);
+    if (s.do_q) dq_kernel<E, D, KS><<<dim3(s.q.map.grid), block, 0, st>>>(s.tab, s.q);
   }
   return check_launch("loong_attn_step_bwd (bf16)");
 }
@@ -186,43 +234,62 @@ int pick_cfg(StepLaunch& s, int head_dim, int ks, hipStream_t st) {
 
 }  // namespace
 
-int launch_bwd_bf16(const loong_step_desc& d, const StepGeom& g, const void* q, const void* k,
-                    const void* v, const void* d_o, const float* lse, const float* delta, float* dq,
-                    float* dk, float* dv, void* workspace, int64_t workspace_bytes, void* stream) {
+int launch_bwd_bf16(const loong_step_desc& d, const StepGeom* g, int n, const void* q, const void* const* k,
+                    const void* const* v, const void* d_o, const float* lse, const float* delta, float* dq,
+                    float* const* dk, float* const* dv, void* workspace, int64_t workspace_bytes, void* stream) {
   hipStream_t st = static_cast<hipStream_t>(stream);
   DeviceFacts dev;
   if (int rc = device_facts(&dev)) return rc;
+  const int G = d.n_q_heads / d.n_kv_heads;
   StepLaunch s{};
   s.do_kv = !(d.flags & LOONG_BWD_ONLY_DQ) && d.kv_len > 0;
   s.do_q = !(d.flags & LOONG_BWD_ONLY_DKV) && d.q_len > 0 && (d.kv_len > 0 || (d.flags & LOONG_OVERWRITE_DQ));
+  for (int t = 0; t < n; ++t) {
+    s.tab.k[t] = (const uint16_t*)k[t]; s.tab.v[t] = (const uint16_t*)v[t];
+    if (s.do_kv) { s.tab.dk[t] = dk[t]; s.tab.dv[t] = dv[t]; }
+  }
+  const SplitPlan plan = plan_split(g, n, G, d.n_kv_heads, d.batch, d.q_len, planning_cus(), &s.tab);
+  s.rows = g[0];
+  for (int t = 1; t < n; ++t)  // (which segments see keys at all is what the row tiling asks)
+    for (int a = 0; a < g[t].nq; ++a)
+      if (segment_sees_keys(g[t], a)) s.rows.cls[a][0] = LOONG_FULL;
   if (s.do_kv) {
     DkvParams& p = s.kv;
-    p.q = (const uint16_t*)q; p.k = (const uint16_t*)k; p.v = (const uint16_t*)v; p.d_o = (const uint16_t*)d_o;
-    p.lse = lse; p.delta = delta; p.dk = dk; p.dv = dv;
-    p.B = d.batch; p.Hq = d.n_q_heads; p.Hkv = d.n_kv_heads; p.G = d.n_q_heads / d.n_kv_heads;
+    p.q = (const uint16_t*)q; p.d_o = (const uint16_t*)d_o;
+    p.lse = lse; p.delta = delta;
+    p.B = d.batch; p.Hq = d.n_q_heads; p.Hkv = d.n_kv_heads; p.G = G;
     p.q_len = d.q_len; p.kv_len = d.kv_len;
     for (int i = 0; i < 3; ++i) { p.qs[i] = d.q_stride[i]; p.ks[i] = d.kv_stride[i]; }
-    p.g = g; p.scale = d.softmax_scale; p.c = d.softmax_scale * kLog2e;
-    if (int rc = plan_dkv(p, d.flags, d.head_dim, workspace, workspace_bytes, st, &s.do_kv)) return rc;
+    p.nq = g[0].nq; p.qseg[0] = g[0].q[0]; p.qseg[1] = g[0].q[1];
+    p.scale = d.softmax_scale; p.c = d.softmax_scale * kLog2e;
+    if (int rc = plan_dkv(s, plan, n, d.flags, d.head_dim, workspace, workspace_bytes, st)) return rc;
   }
   if (s.do_q) {
     DqParams& p = s.q;
-    p.q = (const uint16_t*)q; p.k = (const uint16_t*)k; p.v = (const uint16_t*)v; p.d_o = (const uint16_t*)d_o;
+    p.q = (const uint16_t*)q; p.d_o = (const uint16_t*)d_o;
     p.lse = lse; p.delta = delta; p.dq = dq;
-    p.B = d.batch; p.Hq = d.n_q_heads; p.Hkv = d.n_kv_heads; p.G = d.n_q_heads / d.n_kv_heads;
+    p.B = d.batch; p.Hq = d.n_q_heads; p.Hkv = d.n_kv_heads; p.G = G;
     for (int i = 0; i < 3; ++i) { p.qs[i] = d.q_stride[i]; p.ks[i] = d.kv_stride[i]; p.os[i] = d.o_stride[i]; }
-    p.q_len = d.q_len; p.g = g; p.scale = d.softmax_scale; p.c = d.softmax_scale * kLog2e;
+    p.q_len = d.q_len; p.qseg[0] = g[0].q[0]; p.qseg[1] = g[0].q[1];
+    p.scale = d.softmax_scale; p.c = d.softmax_scale * kLog2e;
     p.overwrite = (d.flags & LOONG_OVERWRITE_DQ) ? 1 : 0;
+    p.rows_first = n > 1;
   }
   if (!s.do_kv && !s.do_q) return LOONG_OK;
-  const int ks = pick_key_splits(g, d.n_q_heads / d.n_kv_heads, d.n_q_heads, d.batch, forced_key_splits(d.flags), dev.cus);
+  int ks = forced_key_splits(d.flags);
+  if (!ks && n > 1) {
+    // several steps: the tallest row tiles whose loop still fits beside the other work of a unit
+    for (ks = 1; ks < 4 && s.do_kv && plan.longest_row * (32 * kRowWaves / ks) > kRowShare * plan.per_cu;) ks *= 2;
+    if (!s.do_kv) ks = 0;
+  }
+  if (!ks) ks = pick_key_splits(s.rows, G, d.n_q_heads, d.batch, 0, dev.cus);
   if (d.dtype == LOONG_FP16) return pick_cfg<Fp16>(s, d.head_dim, ks, st);
   return pick_cfg<Bf16>(s, d.head_dim, ks, st);
 }
 
-int64_t bwd_workspace_bytes_bf16(const loong_step_desc& d, const StepGeom& g) {
+int64_t bwd_workspace_bytes_bf16(const loong_step_desc& d, const StepGeom* g, int n) {
   if (d.kv_len == 0 || d.batch == 0 || (d.flags & LOONG_BWD_ONLY_DQ)) return 0;
-  const SplitPlan plan = plan_split(g, d.n_q_heads / d.n_kv_heads, d.n_kv_heads, d.batch, d.q_len, planning_cus());
+  const SplitPlan plan = plan_split(g, n, d.n_q_heads / d.n_kv_heads, d.n_kv_heads, d.batch, d.q_len, planning_cus(), nullptr);
   return plan.nsplit > 1 ? kWsHeadBytes + (int64_t)partial_bytes(plan, d.head_dim) : 0;
 }
 

@@ -27,14 +27,15 @@
 
 #include "device_utils.h"
 #include "loong_internal.h"
+#include "step_table.h"
 #include "work_map.h"
 
 namespace loong {
 namespace {
 
 struct F32Params {
-  const float *q, *k, *v, *d_o, *lse_in, *delta;
-  float *out, *lse, *dq, *dk, *dv;
+  const float *q, *k, *v, *d_o, *lse_in, *delta;   // (k, v: forward)
+  float *out, *lse, *dq;
   int B, Hq, Hkv, G, d, q_len, kv_len;
   int64_t qs[3], ks[3], os[3];
   StepGeom g;
@@ -44,6 +45,21 @@ struct F32Params {
   int ktile[2], ktiles;   // key tiles per k segment, in all
   WorkMap rmap, kmap;     // units = batch x q heads (kv heads), items = row (key) tiles
 };
+
+// The micro-steps of a backward launch (a pass of 4 steps, 2 heads x 256 rows, d = 64, with its forward: 81 us
+// with a launch per step, 61 with one): they share the geometry but for the block classes (two bits each:
+// q segment 0 x key segments 0, 1, then q segment 1).
+struct F32Run {
+  const float *k[kMaxSteps], *v[kMaxSteps];
+  float *dk[kMaxSteps], *dv[kMaxSteps];
+  uint32_t cls[kMaxSteps];
+  int n;
+};
+__device__ __forceinline__ StepGeom with_classes(const StepGeom& g, uint32_t c) {
+  StepGeom x = g;
+  x.cls[0][0] = c & 3; x.cls[0][1] = c >> 2 & 3; x.cls[1][0] = c >> 4 & 3; x.cls[1][1] = c >> 6 & 3;
+  return x;
+}
 
 constexpr int kT = 16;           // rows / keys of a tile
 constexpr int kMaxWaves = 8;     // waves that share a tile's loop
@@ -355,9 +371,9 @@ __global__ __launch_bounds__(kMaxWaves * 64 / RB) void fwd_f32_kernel(const F32P
   }
 }
 
-// ---- backward, row-owning half: this step's share of dQ of 16 query rows
+// ---- backward, row-owning half: the share of dQ of 16 query rows that the launch's steps have
 template <int NP, bool EXACT>
-__device__ __forceinline__ void dq_f32_body(const F32Params& p, uint32_t block, floatx4_t* slots) {
+__device__ __forceinline__ void dq_f32_body(const F32Params& p, const F32Run& run, uint32_t block, floatx4_t* slots) {
   using F = Frag<NP, EXACT>;
   constexpr int NM = F::NM;
   int bh, rank;
@@ -369,38 +385,41 @@ __device__ __forceinline__ void dq_f32_body(const F32Params& p, uint32_t block, 
   const Segment qs = qa ? p.g.q[1] : p.g.q[0];
   const int lane = threadIdx.x & 63, i = lane & 15, g = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), waves = blockDim.x >> 6;
-  const TileList keys = keys_of_rows(p.g, qa, min(row0 + kT, qs.len) - 1);
-  if (keys.total == 0 && !p.overwrite) return;
-
   const int off = row0 + i, row = qs.start + min(off, qs.len - 1);
   const int64_t q_off = b * p.qs[0] + h * p.qs[1] + (int64_t)row * p.qs[2];
   const typename F::Row qf = F::load_row(p.q + q_off, g, p.d), of = F::load_row(p.d_o + q_off, g, p.d);
   const int64_t srow = ((int64_t)b * p.Hq + h) * p.q_len + row;
   const float lse = p.lse_in[srow], dl = p.delta[srow];
-  const float* kbase = p.k + b * p.ks[0] + hk * p.ks[1];
-  const float* vbase = p.v + b * p.ks[0] + hk * p.ks[1];
   typename F::Acc acc = F::zero();
-  for (int t = wave; t < keys.total; t += waves) {
-    const TileList::Tile tl = keys.at(t);
-    const int64_t koff = (int64_t)(tl.start + min(tl.j0 + i, tl.len - 1)) * p.ks[2];
-    const float* ktile = kbase + (int64_t)tl.start * p.ks[2];
-    const typename F::Row kf = F::load_row(kbase + koff, g, p.d), vf = F::load_row(vbase + koff, g, p.d);
-    const typename F::Col kc = F::load_col(ktile, p.ks[2], tl.j0, tl.len - 1, i, g, p.d);
-    __builtin_amdgcn_sched_barrier(0);
-    const floatx4_t s = F::rows_product(kf, qf), dp = F::rows_product(vf, of);
-    const bool masked = tl.j0 + kT > tl.len || (tl.diag && tl.j0 + kT - 1 > row0);
-    floatx4_t w;
-    int ok = 0;
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int key = tl.j0 + 4 * g + v;
-      const bool yes = lse != -INFINITY && (!masked || (key < tl.len && (!tl.diag || key <= off)));
-      ok |= yes ? 1 << v : 0;
-      w[v] = yes ? fast_exp2(fmaf(s[v], p.scale, -lse) * kLog2e) * (dp[v] - dl) : 0.f;
+  bool any = false;
+  for (int step = 0; step < run.n; ++step) {
+    const TileList keys = keys_of_rows(with_classes(p.g, run.cls[step]), qa, min(row0 + kT, qs.len) - 1);
+    any |= keys.total > 0;
+    const float* kbase = run.k[step] + b * p.ks[0] + hk * p.ks[1];
+    const float* vbase = run.v[step] + b * p.ks[0] + hk * p.ks[1];
+    for (int t = wave; t < keys.total; t += waves) {
+      const TileList::Tile tl = keys.at(t);
+      const int64_t koff = (int64_t)(tl.start + min(tl.j0 + i, tl.len - 1)) * p.ks[2];
+      const float* ktile = kbase + (int64_t)tl.start * p.ks[2];
+      const typename F::Row kf = F::load_row(kbase + koff, g, p.d), vf = F::load_row(vbase + koff, g, p.d);
+      const typename F::Col kc = F::load_col(ktile, p.ks[2], tl.j0, tl.len - 1, i, g, p.d);
+      __builtin_amdgcn_sched_barrier(0);
+      const floatx4_t s = F::rows_product(kf, qf), dp = F::rows_product(vf, of);
+      const bool masked = tl.j0 + kT > tl.len || (tl.diag && tl.j0 + kT - 1 > row0);
+      floatx4_t w;
+      int ok = 0;
+  #pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int key = tl.j0 + 4 * g + v;
+        const bool yes = lse != -INFINITY && (!masked || (key < tl.len && (!tl.diag || key <= off)));
+        ok |= yes ? 1 << v : 0;
+        w[v] = yes ? fast_exp2(fmaf(s[v], p.scale, -lse) * kLog2e) * (dp[v] - dl) : 0.f;
+      }
+      if (masked) F::cols_product_masked(acc, kc, w, ok, ktile, p.ks[2], tl.j0, tl.len - 1, i, g, p.d);
+      else F::cols_product(acc, kc, w);
     }
-    if (masked) F::cols_product_masked(acc, kc, w, ok, ktile, p.ks[2], tl.j0, tl.len - 1, i, g, p.d);
-    else F::cols_product(acc, kc, w);
   }
+  if (!any && !p.overwrite) return;
   add_waves<F>(acc, slots, wave, waves, lane);
   if (off >= qs.len || (lse == -INFINITY && !p.overwrite)) return;
   float* dst = p.dq + b * p.os[0] + h * p.os[1] + (int64_t)row * p.os[2];
@@ -415,7 +434,7 @@ __device__ __forceinline__ void dq_f32_body(const F32Params& p, uint32_t block, 
 
 // ---- backward, key-owning half: dK and dV of 16 keys, over the rows of every head of the group
 template <int NP, bool EXACT>
-__device__ __forceinline__ void dkv_f32_body(const F32Params& p, uint32_t block, floatx4_t* slots) {
+__device__ __forceinline__ void dkv_f32_body(const F32Params& p, const F32Run& run, int step, uint32_t block, floatx4_t* slots) {
   using F = Frag<NP, EXACT>;
   constexpr int NM = F::NM;
   int bhk, kt;  // key tiles in storage order see ever fewer rows
@@ -426,11 +445,11 @@ __device__ __forceinline__ void dkv_f32_body(const F32Params& p, uint32_t block,
   const Segment ks = kb ? p.g.k[1] : p.g.k[0];
   const int lane = threadIdx.x & 63, i = lane & 15, g = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), waves = blockDim.x >> 6;
-  const TileList rows = rows_of_keys(p.g, kb, key0);
+  const TileList rows = rows_of_keys(with_classes(p.g, run.cls[step]), kb, key0);
 
   const int off = key0 + i, key = ks.start + min(off, ks.len - 1);
   const int64_t k_off = b * p.ks[0] + hk * p.ks[1] + (int64_t)key * p.ks[2];
-  const typename F::Row kf = F::load_row(p.k + k_off, g, p.d), vf = F::load_row(p.v + k_off, g, p.d);
+  const typename F::Row kf = F::load_row(run.k[step] + k_off, g, p.d), vf = F::load_row(run.v[step] + k_off, g, p.d);
   typename F::Acc ak = F::zero(), av = F::zero();
   const int n = rows.total * p.G;
   for (int t = wave; t < n; t += waves) {
@@ -480,8 +499,8 @@ __device__ __forceinline__ void dkv_f32_body(const F32Params& p, uint32_t block,
 #pragma unroll
   for (int pc = 0; pc < NM; ++pc)
     if (pc % waves == wave && (EXACT || F::piece_col(pc, g) < p.d)) {
-      floatx4_t* at_k = reinterpret_cast<floatx4_t*>(p.dk + dst + F::piece_col(pc, g));
-      floatx4_t* at_v = reinterpret_cast<floatx4_t*>(p.dv + dst + F::piece_col(pc, g));
+      floatx4_t* at_k = reinterpret_cast<floatx4_t*>(run.dk[step] + dst + F::piece_col(pc, g));
+      floatx4_t* at_v = reinterpret_cast<floatx4_t*>(run.dv[step] + dst + F::piece_col(pc, g));
       floatx4_t x = F::piece(ak, pc) * p.scale, y = F::piece(av, pc);
       if (p.accumulate) { x += *at_k; y += *at_v; }
       *at_k = x;
@@ -489,12 +508,21 @@ __device__ __forceinline__ void dkv_f32_body(const F32Params& p, uint32_t block,
     }
 }
 
-// Both halves in one launch: key tiles first (the longer ones), then row tiles; `nk` key workgroups.
+// Both halves of all steps in one launch, the longer workgroups first: the key-owning ones (`nk` per step) for one
+// step, the `nq` row-owning ones, which walk over every step's keys, for several.
 template <int NP, bool EXACT>
-__global__ __launch_bounds__(max_bwd_waves(NP) * 64) void bwd_f32_kernel(const F32Params p, uint32_t nk) {
+__global__ __launch_bounds__(max_bwd_waves(NP) * 64) void bwd_f32_kernel(const F32Params p, const F32Run run, uint32_t nk, uint32_t nq) {
   __shared__ floatx4_t slots[max_bwd_waves(NP) * Frag<NP, EXACT>::NM * 64];
-  if (blockIdx.x < nk) dkv_f32_body<NP, EXACT>(p, blockIdx.x, slots);
-  else dq_f32_body<NP, EXACT>(p, blockIdx.x - nk, slots);
+  const bool rows_first = run.n > 1;
+  const uint32_t n_first = rows_first ? nq : nk;
+  const bool second = blockIdx.x >= n_first;
+  const uint32_t block = blockIdx.x - (second ? n_first : 0u);
+  if (second != rows_first) {
+    dq_f32_body<NP, EXACT>(p, run, block, slots);
+  } else {
+    const uint32_t step = block / nk;
+    dkv_f32_body<NP, EXACT>(p, run, (int)step, block - step * nk, slots);
+  }
 }
 
 F32Params make_params(const loong_step_desc& d, const StepGeom& g) {
@@ -546,7 +574,7 @@ int launch_fwd(F32Params& p, int cus, hipStream_t st) {
 }
 
 template <int NP, bool EXACT>
-int launch_bwd(F32Params& p, bool do_dq, bool do_dkv, hipStream_t st) {
+int launch_bwd(F32Params& p, const F32Run& run, bool do_dq, bool do_dkv, hipStream_t st) {
   tile_rows(p, kT);
   for (int a = 0; a < 2; ++a) {
     p.ktile[a] = a < p.g.nk ? tiles(p.g.k[a].len, kT) : 0;
@@ -554,12 +582,20 @@ int launch_bwd(F32Params& p, bool do_dq, bool do_dkv, hipStream_t st) {
   }
   p.kmap = make_work_map((int64_t)p.B * p.Hkv, p.ktiles);
   const uint32_t nk = do_dkv ? p.kmap.grid : 0, nq = do_dq ? p.rmap.grid : 0;
-  if (((int64_t)nk + nq) * 64 < (int64_t)1 << 32) {
-    const int w = pick_waves((int64_t)nk + nq, max_bwd_waves(NP));
-    bwd_f32_kernel<NP, EXACT><<<dim3(nk + nq), dim3(w * 64), 0, st>>>(p, nk);
-  } else {  // more workgroups than one grid takes
-    bwd_f32_kernel<NP, EXACT><<<dim3(nk), dim3(pick_waves(nk, max_bwd_waves(NP)) * 64), 0, st>>>(p, nk);
-    bwd_f32_kernel<NP, EXACT><<<dim3(nq), dim3(pick_waves(nq, max_bwd_waves(NP)) * 64), 0, st>>>(p, 0);
+  const int64_t grid = (int64_t)nk * run.n + nq;
+  if (grid * 64 < (int64_t)1 << 32) {
+    const int w = pick_waves(grid, max_bwd_waves(NP));
+    bwd_f32_kernel<NP, EXACT><<<dim3((unsigned)grid), dim3(w * 64), 0, st>>>(p, run, nk, nq);
+    return check_launch("loong_attn_step_bwd (fp32)");
+  }
+  // more workgroups than one grid takes: step by step, half by half
+  F32Run one{};
+  one.n = 1;
+  for (int t = 0; t < run.n; ++t) {
+    one.k[0] = run.k[t]; one.v[0] = run.v[t]; one.dk[0] = run.dk[t]; one.dv[0] = run.dv[t]; one.cls[0] = run.cls[t];
+    if (nk) bwd_f32_kernel<NP, EXACT><<<dim3(nk), dim3(pick_waves(nk, max_bwd_waves(NP)) * 64), 0, st>>>(p, one, nk, 0);
+    if (nq) bwd_f32_kernel<NP, EXACT><<<dim3(nq), dim3(pick_waves(nq, max_bwd_waves(NP)) * 64), 0, st>>>(p, one, 0, nq);
+    p.overwrite = 0;
   }
   return check_launch("loong_attn_step_bwd (fp32)");
 }
@@ -582,9 +618,9 @@ int launch_fwd_f32(const loong_step_desc& d, const StepGeom& g, const void* q, c
   return launch_fwd<128, false>(p, dev.cus, st);
 }
 
-int launch_bwd_f32(const loong_step_desc& d, const StepGeom& g, const void* q, const void* k,
-                   const void* v, const void* d_o, const float* lse, const float* delta, float* dq,
-                   float* dk, float* dv, void* stream) {
+int launch_bwd_f32(const loong_step_desc& d, const StepGeom* g, int n, const void* q, const void* const* k,
+                   const void* const* v, const void* d_o, const float* lse, const float* delta, float* dq,
+                   float* const* dk, float* const* dv, void* stream) {
   const int64_t qrows = (int64_t)d.batch * d.n_q_heads * d.q_len;
   const int64_t krows = (int64_t)d.batch * d.n_kv_heads * d.kv_len;
   if (qrows > 0x7fffffff || krows > 0x7fffffff)
@@ -592,14 +628,21 @@ int launch_bwd_f32(const loong_step_desc& d, const StepGeom& g, const void* q, c
   const bool do_dq = !(d.flags & LOONG_BWD_ONLY_DKV) && qrows > 0 && (krows > 0 || (d.flags & LOONG_OVERWRITE_DQ));
   const bool do_dkv = !(d.flags & LOONG_BWD_ONLY_DQ) && krows > 0;
   if (!do_dq && !do_dkv) return LOONG_OK;
-  F32Params p = make_params(d, g);
-  p.q = (const float*)q; p.k = (const float*)k; p.v = (const float*)v; p.d_o = (const float*)d_o;
-  p.lse_in = lse; p.delta = delta; p.dq = dq; p.dk = dk; p.dv = dv;
+  F32Params p = make_params(d, g[0]);
+  p.q = (const float*)q; p.d_o = (const float*)d_o;
+  p.lse_in = lse; p.delta = delta; p.dq = dq;
+  F32Run run{};
+  run.n = n;
+  for (int t = 0; t < n; ++t) {
+    run.k[t] = (const float*)k[t]; run.v[t] = (const float*)v[t];
+    if (do_dkv) { run.dk[t] = dk[t]; run.dv[t] = dv[t]; }
+    run.cls[t] = g[t].cls[0][0] | g[t].cls[0][1] << 2 | g[t].cls[1][0] << 4 | g[t].cls[1][1] << 6;
+  }
   hipStream_t st = static_cast<hipStream_t>(stream);
-  if (d.head_dim == 32) return launch_bwd<32, true>(p, do_dq, do_dkv, st);
-  if (d.head_dim == 64) return launch_bwd<64, true>(p, do_dq, do_dkv, st);
-  if (d.head_dim == 128) return launch_bwd<128, true>(p, do_dq, do_dkv, st);
-  return launch_bwd<128, false>(p, do_dq, do_dkv, st);
+  if (d.head_dim == 32) return launch_bwd<32, true>(p, run, do_dq, do_dkv, st);
+  if (d.head_dim == 64) return launch_bwd<64, true>(p, run, do_dq, do_dkv, st);
+  if (d.head_dim == 128) return launch_bwd<128, true>(p, run, do_dq, do_dkv, st);
+  return launch_bwd<128, false>(p, run, do_dq, do_dkv, st);
 }
 
 }  // namespace loong

@@ -39,26 +39,26 @@
 #include "device_utils.h"
 #include "loong_internal.h"
 #include "split_exchange.h"
+#include "step_table.h"
 #include "work_map.h"
 
 namespace loong {
 namespace {
 
 struct DkvParams {
-  const uint16_t *q, *k, *v, *d_o;
+  const uint16_t *q, *d_o;
   const float *lse, *delta;
-  float *dk, *dv;
   int B, Hq, Hkv, G;
   int q_len, kv_len;
   int64_t qs[3], ks[3];
-  StepGeom g;
+  int nq;
+  Segment qseg[2];
   float scale, c;  // softmax scale; scale * log2(e)
   int accumulate;  // 1: the results are added to dk/dv instead of stored
-  int nkt[2], kt_total;
+  int nkt, kt_total;  // key tiles per half; of all seen halves
   int nsplit;      // workgroups that share the query loop of one key tile
   uint32_t* ws_cnt;  // nsplit > 1: counter per (batch, kv head, key tile), zero before and after the launch
   float* ws_part;    // nsplit > 1: partial dK/dV of every (key tile, split), in accumulator layout
-  int zero_start, zero_len;  // keys no query of this step sees, whose gradients this launch clears
   WorkMap map;     // units = batch x kv heads, items = key tiles x splits
 };
 
@@ -83,7 +83,7 @@ struct BwdCfg {
 };
 
 template <class E, int D>
-__device__ __forceinline__ void dkv_body(const DkvParams& p, uint32_t block, unsigned char* smem) {
+__device__ __forceinline__ void dkv_body(const StepTable& tab, const DkvParams& p, uint32_t block, unsigned char* smem) {
   using C = BwdCfg<D>;
   constexpr int BM = C::BM, BN = C::BN, ROWB = C::ROWB, CH = C::CH, LI = C::LI;
   constexpr int NKS = D / 16, NDB = D / 32;
@@ -94,23 +94,22 @@ __device__ __forceinline__ void dkv_body(const DkvParams& p, uint32_t block, uns
   if (!decode_work(p.map, block, bhk, rem)) return;
   const int kt = rem / p.nsplit, sp = rem - kt * p.nsplit;
   const int b = bhk / p.Hkv, hk = bhk - b * p.Hkv;
-  const int kb = kt >= p.nkt[0] ? 1 : 0;
-  const int koff0 = (kb ? kt - p.nkt[0] : kt) * BN;
-  const Segment kseg = kb ? p.g.k[1] : p.g.k[0];
+  const int half_idx = kt / p.nkt, koff0 = (kt - half_idx * p.nkt) * BN;
+  const uint32_t entry = tab.half[half_idx];
+  const int step = entry_step(entry), klen = tab.klen, kstart = entry_half(entry) * klen;
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l32 = lane & 31, hh = lane >> 5;
   const int kg = wave & 3;           // key group: keys koff0 + 32 kg ..
   const bool p_wave = wave < 4;      // waves kg and kg + 4 share a SIMD
   const int my_koff = koff0 + 32 * kg + l32;
-  const bool key_ok = my_koff < kseg.len;
-  const int64_t my_krow = kseg.start + min(my_koff, kseg.len - 1);
+  const bool key_ok = my_koff < klen;
+  const int64_t my_krow = kstart + min(my_koff, klen - 1);
 
   // ---- query tiles that can see this key tile: per q segment, tiles first .. first + cnt - 1
   // (per-segment facts in scalars: the loop never indexes the kernel arguments dynamically)
-  const int clsq0 = kb ? p.g.cls[0][1] : p.g.cls[0][0];
-  const int clsq1 = p.g.nq > 1 ? (kb ? p.g.cls[1][1] : p.g.cls[1][0]) : LOONG_SKIP;
-  const int qlen0 = p.g.q[0].len, qlen1 = p.g.nq > 1 ? p.g.q[1].len : 0;
-  const int qstart0 = p.g.q[0].start, qstart1 = p.g.nq > 1 ? p.g.q[1].start : 0;
+  const int clsq0 = entry_class(entry, 0), clsq1 = p.nq > 1 ? entry_class(entry, 1) : LOONG_SKIP;
+  const int qlen0 = p.qseg[0].len, qlen1 = p.nq > 1 ? p.qseg[1].len : 0;
+  const int qstart0 = p.qseg[0].start, qstart1 = p.nq > 1 ? p.qseg[1].start : 0;
   const int nt0 = (qlen0 + BM - 1) / BM, nt1 = (qlen1 + BM - 1) / BM;
   const int first0 = clsq0 == LOONG_DIAG ? min(koff0 / BM, nt0) : 0;
   const int first1 = clsq1 == LOONG_DIAG ? min(koff0 / BM, nt1) : 0;
@@ -135,7 +134,7 @@ __device__ __forceinline__ void dkv_body(const DkvParams& p, uint32_t block, uns
   // (E wave); row my_krow, columns 16 ks + 8 hh .. +7
   bf16x8_t bfrag[NKS];
   {
-    const uint16_t* row = (p_wave ? p.k : p.v) + b * p.ks[0] + hk * p.ks[1] + my_krow * p.ks[2];
+    const uint16_t* row = (p_wave ? tab.k[step] : tab.v[step]) + b * p.ks[0] + hk * p.ks[1] + my_krow * p.ks[2];
     const uint32_t flip = p_wave ? 0u : 0x80008000u;
 #pragma unroll
     for (int ks = 0; ks < NKS; ++ks) {
@@ -227,19 +226,21 @@ __device__ __forceinline__ void dkv_body(const DkvParams& p, uint32_t block, uns
   if (it_begin < it_end) issue_tile(cur, 0);
   if (!p_wave) wait_vmcnt<0>();
 
-  // ---- the gradients of keys no query of this step sees: the unit's workgroups clear a share each, from
+  // ---- the gradients of keys no query sees: the unit's workgroups clear a share each, from
   // the P waves (their stores have the first iteration to finish; as a launch of its own this cost
   // 5-7 us a step)
-  if (p.zero_len > 0 && p_wave) {
-    const int64_t off = (((int64_t)b * p.Hkv + hk) * p.kv_len + p.zero_start) * D;
-    float4* zk = reinterpret_cast<float4*>(p.dk + off);
-    float4* zv = reinterpret_cast<float4*>(p.dv + off);
-    const int n4 = p.zero_len * (D / 4), step = p.map.per_unit * 256;
-    for (int i = rem * 256 + tid; i < n4; i += step) {
-      zk[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-      zv[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+  if (p_wave && !p.accumulate)
+    for (int z = tab.n_seen; z < tab.n_halves; ++z) {
+      const uint32_t ze = tab.half[z];
+      const int64_t off = (((int64_t)b * p.Hkv + hk) * p.kv_len + (int64_t)entry_half(ze) * klen) * D;
+      float4* zk = reinterpret_cast<float4*>(tab.dk[entry_step(ze)] + off);
+      float4* zv = reinterpret_cast<float4*>(tab.dv[entry_step(ze)] + off);
+      const int64_t n4 = (int64_t)klen * (D / 4), stride = (int64_t)p.map.per_unit * 256;
+      for (int64_t i = (int64_t)rem * 256 + tid; i < n4; i += stride) {
+        zk[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+        zv[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+      }
     }
-  }
 
   // P and E = P o T packed, two bf16 per word (elements 2 w, 2 w + 1 of block ib).  A P wave keeps
   // its P across the barrier: dV += P^T dO of tile t runs at the top of iteration t + 1.
@@ -258,7 +259,7 @@ __device__ __forceinline__ void dkv_body(const DkvParams& p, uint32_t block, uns
     decode(cur, h, qa, i0);
     const int qlen = qa ? qlen1 : qlen0;
     const bool isdiag = (qa ? clsq1 : clsq0) == LOONG_DIAG;
-    const bool need_mask = i0 + BM > qlen || koff0 + BN > kseg.len || (isdiag && i0 < koff0 + BN - 1);
+    const bool need_mask = i0 + BM > qlen || koff0 + BN > klen || (isdiag && i0 < koff0 + BN - 1);
     const unsigned char* Qt = smem + (p_wave ? st_p : st_e) * C::STAGE_B;
     const unsigned char* Ot = Qt + C::QT_B;
     const float* lse_s = reinterpret_cast<const float*>(Qt + 2 * C::QT_B);
@@ -448,7 +449,7 @@ __device__ __forceinline__ void dkv_body(const DkvParams& p, uint32_t block, uns
   // rate whatever their width (stored one float at a time, this epilogue took 3.2 us of a
   // 74 us launch).  This workgroup is the only one that writes these rows in this launch, so
   // accumulation is a plain read-modify-write.
-  float* base = (p_wave ? p.dv : p.dk) + (((int64_t)b * p.Hkv + hk) * p.kv_len + kseg.start) * D;
+  float* base = (p_wave ? tab.dv[step] : tab.dk[step]) + (((int64_t)b * p.Hkv + hk) * p.kv_len + kstart) * D;
   const float f = p_wave ? 1.f : -p.scale;
   const bool odd = lane & 1, upper = lane & 2;
   const int col4 = (l32 >> 2) * 4, key_in_group = l32 & 3;
@@ -465,7 +466,7 @@ __device__ __forceinline__ void dkv_body(const DkvParams& p, uint32_t block, uns
       float4 x;
       x.x = upper ? q2 : a0; x.y = upper ? q3 : a1; x.z = upper ? a2 : q0; x.w = upper ? a3 : q1;
       const int koff = koff0 + 32 * kg + 8 * vq + 4 * hh + key_in_group;
-      if (koff < kseg.len) {
+      if (koff < klen) {
         float4* dst = reinterpret_cast<float4*>(base + (int64_t)koff * D + db * 32 + col4);
         if (p.accumulate) {
           const float4 y = *dst;

@@ -22,6 +22,7 @@
 #include "device_utils.h"
 #include "loong_internal.h"
 #include "row_tiling.h"
+#include "step_table.h"
 #include "work_map.h"
 
 namespace loong {
@@ -30,19 +31,22 @@ namespace {
 typedef __attribute__((address_space(3))) void lds_void_t;
 
 struct DqParams {
-  const uint16_t *q, *k, *v, *d_o;
+  const uint16_t *q, *d_o;
   const float *lse, *delta;
   float* dq;
   int B, Hq, Hkv, G, GS;
   int64_t qs[3], ks[3], os[3];
   int q_len;
-  StepGeom g;
+  Segment qseg[2];
   float scale, c;  // softmax scale; scale * log2(e)
   int overwrite;   // 1: dq is written, not added to
   int ntile[2];    // q tiles per q segment
   int tiles_total;
   int hgroups;     // Hq / GS
   WorkMap map;     // units = batch x head groups, items = q tiles
+  // both halves in one launch: workgroups of the half that comes first, and whether that is this one
+  uint32_t first_grid;
+  bool rows_first;
 };
 
 template <int D, int KS>
@@ -67,7 +71,7 @@ struct DqCfg {
 };
 
 template <class E, int D, int KS>
-__device__ __forceinline__ void dq_body(const DqParams& p, uint32_t block, unsigned char* smem) {
+__device__ __forceinline__ void dq_body(const StepTable& tab, const DqParams& p, uint32_t block, unsigned char* smem) {
   using C = DqCfg<D, KS>;
   constexpr int NRB = C::NRB, NJB = C::NJB, BNS = C::BNS, TK = C::TK, NBUF = C::NBUF, PD = C::PD, KI = C::KI;
   constexpr int NDB = D / 32, NKS = D / 16, ROWB = C::ROWB, CH = C::CH;
@@ -82,7 +86,7 @@ __device__ __forceinline__ void dq_body(const DqParams& p, uint32_t block, unsig
   const int tile = qa ? tt - p.ntile[0] : tt;
   const int BMH = 32 * NRB / p.GS;
   const int row0_wg = tile * BMH;
-  const Segment qseg = qa ? p.g.q[1] : p.g.q[0];
+  const Segment qseg = qa ? p.qseg[1] : p.qseg[0];
 
   const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, hh = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // in a scalar register: what derives from it stays scalar
@@ -96,16 +100,10 @@ __device__ __forceinline__ void dq_body(const DqParams& p, uint32_t block, unsig
   const int my_row = qseg.start + min(my_off, qseg.len - 1);
   const int last_off_wg = min(row0_wg + BMH, qseg.len) - 1;
 
-  // ---- visible key tiles of this workgroup (per-segment facts kept in scalars: nothing in
-  // the main loop indexes the kernel arguments dynamically)
-  const int cls0 = qa ? p.g.cls[1][0] : p.g.cls[0][0];
-  const int cls1 = p.g.nk > 1 ? (qa ? p.g.cls[1][1] : p.g.cls[0][1]) : LOONG_SKIP;
-  const int klen0 = p.g.k[0].len, klen1 = p.g.nk > 1 ? p.g.k[1].len : 0;
-  const int kstart0 = p.g.k[0].start, kstart1 = p.g.nk > 1 ? p.g.k[1].start : 0;
-  const int kend0 = cls0 == LOONG_SKIP ? 0 : cls0 == LOONG_FULL ? klen0 : min(klen0, last_off_wg + 1);
-  const int kend1 = cls1 == LOONG_SKIP ? 0 : cls1 == LOONG_FULL ? klen1 : min(klen1, last_off_wg + 1);
-  const int ntk0 = (kend0 + TK - 1) / TK, ntk1 = (kend1 + TK - 1) / TK;
-  const int total_t = ntk0 + ntk1;
+  // ---- visible key tiles of this workgroup: the key halves its rows see, one after the other
+  const int klen = tab.klen, kend_diag = min(klen, last_off_wg + 1);  // keys of a whole and of the diagonal half
+  const int n_list = qa ? tab.n_list[1] : tab.n_list[0], n_diag = qa ? tab.n_diag[1] : tab.n_diag[0];
+  const int total_t = (n_list - n_diag) * ((klen + TK - 1) / TK) + n_diag * ((kend_diag + TK - 1) / TK);
   float* const dq_row = p.dq + b * p.os[0] + h * p.os[1] + (int64_t)my_row * p.os[2];
   if (total_t == 0) {  // nothing visible: no share of dQ in this step
     if (p.overwrite && ksp == 0 && row_ok) {
@@ -154,28 +152,45 @@ __device__ __forceinline__ void dq_body(const DqParams& p, uint32_t block, unsig
   // ---- staging: global -> LDS directly.  Load i of this wave fills LDS bytes
   // [(wave + 8 i) * 1024, +1024) of the K (or V) tile: row (wave + 8 i) * RPI + lane / CH,
   // piece position lane % CH, which holds piece (position ^ swizzle(row)) of that row.
-  const unsigned char* kbase = reinterpret_cast<const unsigned char*>(p.k + b * p.ks[0] + hk * p.ks[1]);
-  const unsigned char* vbase = reinterpret_cast<const unsigned char*>(p.v + b * p.ks[0] + hk * p.ks[1]);
   const int64_t rowbytes = p.ks[2] * 2;
   const int ld_row = wave * C::RPI + lane / CH;  // row inside the tile for i = 0; later loads add 8*RPI rows
   const uint32_t ld_piece = (uint32_t)((lane % CH) ^ tile_swizzle<D>(ld_row)) * 16;
   const uint32_t smem_base = (uint32_t)(uintptr_t)(lds_void_t*)smem;  // LDS byte address of the buffers
-  auto tile_of = [&](int t, int& kb, int& j0) {
-    kb = t < ntk0 ? 0 : 1;
-    j0 = (t - (kb ? ntk0 : 0)) * TK;
+  // a place in the list of key halves: entry, first key of the tile, end of the half's visible keys
+  // (advanced tile by tile: the list is read once per half)
+  struct Cursor { uint32_t e; int i, j0, kend; };
+  auto enter = [&](Cursor& cu, int i) {
+    cu.i = i; cu.j0 = 0;
+    cu.e = qa ? tab.row_list[1][i] : tab.row_list[0][i];
+    cu.kend = cu.e & kDiagEntry ? kend_diag : klen;
   };
+  auto advance = [&](Cursor& cu) {  // true: another half begins
+    cu.j0 += TK;
+    if (cu.j0 < cu.kend || cu.i + 1 >= n_list) return false;
+    enter(cu, cu.i + 1);
+    return true;
+  };
+  const int64_t head_off = b * p.ks[0] + hk * p.ks[1];
+  Cursor ahead, cur;  // the tile to stage next, the tile in use
+  const unsigned char *kbase, *vbase;  // first key of the half `ahead` is in
+  auto find_bases = [&] {
+    const int64_t off = head_off + (int64_t)(entry_half(ahead.e) * klen) * p.ks[2];
+    const int step = entry_step(ahead.e);
+    kbase = reinterpret_cast<const unsigned char*>(tab.k[step] + off);
+    vbase = reinterpret_cast<const unsigned char*>(tab.v[step] + off);
+  };
+  enter(ahead, 0);
+  find_bases();
+  cur = ahead;
   // byte offsets of this lane's pieces from the first row of a tile (full tiles only; the
   // 32-bit form needs TK rows to span less than 4 GiB, else every tile takes the general path)
   const bool narrow = rowbytes * TK < (int64_t(1) << 32);
   uint32_t ld_off[KI];
 #pragma unroll
   for (int i = 0; i < KI; ++i) ld_off[i] = (uint32_t)(ld_row + i * 8 * C::RPI) * (uint32_t)rowbytes + ld_piece;
-  auto issue_tile = [&](int t) {
-    int kb, j0;
-    tile_of(t, kb, j0);
-    const int len = kb ? klen1 : klen0, start = kb ? kstart1 : kstart0;
-    const int64_t tb = (int64_t)(start + j0) * rowbytes;
-    const int last = len - 1 - j0;  // last valid row of the tile (>= 0); later rows repeat it
+  auto issue_tile = [&](int t) {  // stages the tile at `ahead` (the t-th of this workgroup) and moves on
+    const int64_t tb = (int64_t)ahead.j0 * rowbytes;
+    const int last = klen - 1 - ahead.j0;  // last valid row of the tile (>= 0); later rows repeat it
     const uint32_t kl = smem_base + (t % NBUF) * C::BUF_B + wave * 1024;
     const uint32_t vl = kl + C::TILE_B;
     if (narrow && last >= TK - 1) {  // whole tile: uniform base in scalar registers + per-lane offset
@@ -193,6 +208,7 @@ __device__ __forceinline__ void dq_body(const DqParams& p, uint32_t block, unsig
         load_to_lds_16(vbase + ro, vl + i * 8192);
       }
     }
+    if (advance(ahead)) find_bases();
   };
 
   // ---- LDS read offsets of this lane (bytes inside a tile; the wave's split and the block
@@ -233,10 +249,9 @@ __device__ __forceinline__ void dq_body(const DqParams& p, uint32_t block, unsig
     __syncthreads();  // every wave's part of tile t is in LDS; everyone has finished tile t-1
     if (t + PD < total_t) issue_tile(t + PD);  // into the buffer tile t-1 used
 
-    int kb, jt;
-    tile_of(t, kb, jt);
-    const int klen = kb ? klen1 : klen0;
-    const bool isdiag = (kb ? cls1 : cls0) == LOONG_DIAG;
+    const int jt = cur.j0;
+    const bool isdiag = cur.e & kDiagEntry;
+    advance(cur);
     const unsigned char* Kt = smem + (t % NBUF) * C::BUF_B + ksp * BNS * ROWB;
     const unsigned char* Vt = Kt + C::TILE_B;
 

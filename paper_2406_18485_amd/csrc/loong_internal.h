@@ -25,6 +25,13 @@ struct StepGeom {
   uint8_t cls[2][2];
 };
 
+// Visible keys of the rows of q segment a, per row (half of a diagonal block)
+inline double keys_of_rows(const StepGeom& g, int a) {
+  double n = 0;
+  for (int kb = 0; kb < g.nk; ++kb) n += g.cls[a][kb] == LOONG_FULL ? g.k[kb].len : g.cls[a][kb] == LOONG_DIAG ? 0.5 * g.k[kb].len : 0.;
+  return n;
+}
+
 // Validate a descriptor (no device access).  Fills `g` when it succeeds.
 int check_step(const loong_step_desc* d, StepGeom* g);
 
@@ -64,13 +71,14 @@ inline int forced_key_splits(int flags) {
 namespace loong {
 int launch_fwd_f32(const loong_step_desc& d, const StepGeom& g, const void* q, const void* k,
                    const void* v, float* out, float* lse, void* stream);
-int launch_bwd_f32(const loong_step_desc& d, const StepGeom& g, const void* q, const void* k,
-                   const void* v, const void* d_o, const float* lse, const float* delta, float* dq,
-                   float* dk, float* dv, void* stream);
 int launch_fwd_bf16(const loong_step_desc& d, const StepGeom& g, const void* q, const void* k,
                     const void* v, float* out, float* lse, void* stream);
-int launch_bwd_bf16(const loong_step_desc& d, const StepGeom& g, const void* q, const void* k,
-                    const void* v, const void* d_o, const float* lse, const float* delta, float* dq,
-                    float* dk, float* dv, void* workspace, int64_t workspace_bytes, void* stream);
-int64_t bwd_workspace_bytes_bf16(const loong_step_desc& d, const StepGeom& g);
+// (`n` micro-steps that differ in the visiting chunk only, one geometry and one k, v, dk, dv each; n <= kMaxSteps)
+int launch_bwd_f32(const loong_step_desc& d, const StepGeom* g, int n, const void* q, const void* const* k,
+                   const void* const* v, const void* d_o, const float* lse, const float* delta, float* dq,
+                   float* const* dk, float* const* dv, void* stream);
+int launch_bwd_bf16(const loong_step_desc& d, const StepGeom* g, int n, const void* q, const void* const* k,
+                    const void* const* v, const void* d_o, const float* lse, const float* delta, float* dq,
+                    float* const* dk, float* const* dv, void* workspace, int64_t workspace_bytes, void* stream);
+int64_t bwd_workspace_bytes_bf16(const loong_step_desc& d, const StepGeom* g, int n);
 }  // namespace loong

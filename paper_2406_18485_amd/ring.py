@@ -45,6 +45,14 @@ def _desc(shape: RingShape, step: dict, flags: int) -> B.StepDesc:
                        flags=flags | shape.extra_flags)
 
 
+def _pointers(chunks, order) -> list[int]:
+    """Device pointers of chunks[src] for every src of `order`; a stacked tensor is not sliced for it."""
+    if isinstance(chunks, torch.Tensor):
+        base, step = chunks.data_ptr(), chunks.stride(0) * chunks.element_size()
+        return [base + src * step for src in order]
+    return [chunks[src].data_ptr() for src in order]
+
+
 class RingReplay:
     """Buffers and launch sequence of the forward and backward replay for one rank.
 
@@ -69,8 +77,12 @@ class RingReplay:
         self.dv = torch.empty(s.cp, s.batch, s.hkv, s.L, s.d, **f32)
         self.block_out = None
         self.block_lse = None
-        # caller-owned scratch of the backward steps: the largest any micro-step asks for
-        need = max(B.workspace_bytes(_desc(s, step, 0)) for step in self.plan)
+        self._order = [step["src_rank"] for step in self.plan]
+        # the backward steps of a pass: the first forms delta and writes dq, and all are one run
+        flags = B.WORKSPACE_CLEAN | B.COMPUTE_DELTA | B.OVERWRITE_DQ
+        self._bwd_descs = (B.StepDesc * s.cp)(*(_desc(s, step, flags) for step in self.plan))
+        # caller-owned scratch of the backward steps: the largest any micro-step, or all in one run, ask for
+        need = max(B.workspace_bytes_steps(self._bwd_descs), *(B.workspace_bytes(_desc(s, step, 0)) for step in self.plan))
         # (zero once: every call leaves its counters zero, so none has to clear them)
         self.workspace = torch.zeros(max(need, 16), dtype=torch.uint8, device=self.dev)
 
@@ -94,15 +106,11 @@ class RingReplay:
                 B.lse_merge(self.rows, s.d, self.out, self.lse, self.block_out, self.block_lse, stream)
         B.finalize_out(self.rows, s.d, self.out, self.o, s.dtype, stream)
 
-    # ---- backward from the stored O and LSE: delta once, then cp step kernels
+    # ---- backward from the stored O and LSE: delta once, then the cp steps, whose chunks are all here, as one run
     def backward(self, q, k_by_src, v_by_src, d_o, stream=None):
-        s = self.shape
-        for t, step in enumerate(self.plan):
-            src = step["src_rank"]
-            # the first step also forms delta and writes dq, the later ones add to it
-            flags = B.WORKSPACE_CLEAN | (0 if t else B.COMPUTE_DELTA | B.OVERWRITE_DQ)
-            B.attn_step_bwd(_desc(s, step, flags), q, k_by_src[src], v_by_src[src], self.o, d_o, self.lse,
-                            self.delta, self.dq, self.dk[src], self.dv[src], self.workspace, stream=stream)
+        k, v, dk, dv = (_pointers(x, self._order) for x in (k_by_src, v_by_src, self.dk, self.dv))
+        B.attn_steps_bwd(self._bwd_descs, q, k, v, self.o, d_o, self.lse, self.delta, self.dq, dk, dv, self.workspace,
+                         stream=stream)
 
     # ---- forward with the receive buffers of Alg. 2: the chunk of the next micro-step arrives
     # in an inner-ring buffer while the current one is used, and the first chunk of the next

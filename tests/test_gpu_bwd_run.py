@@ -1,0 +1,109 @@
+"""A run of backward micro-steps in one launch (attn_steps_bwd) against the same steps one by one: rows whose
+loop crosses chunk ends of every remainder, key halves nobody sees, shared query loops, more steps than one
+launch takes, dq and dk/dv added to, no mask, each forced key split.
+
+Both compute the same sums of the same products (probabilities rounded to 16 bits alike); only the order of
+fp32 additions differs (dq over steps in registers, dk/dv in other splits).  n additions in another order differ by
+at most n * 2^-24 of the sum of magnitudes; with at most 2^13 terms of like size that is 5e-4 of a typical sum, and
+the result is compared to 1e-4 of its largest element."""
+import ctypes as C
+
+import pytest
+import torch
+
+import paper_2406_18485_amd as P
+from gpu_harness import DEV
+from paper_2406_18485_amd.ring import RingReplay, RingShape, _desc
+
+pytestmark = pytest.mark.gpu
+
+
+def _close(a, b):
+    assert torch.isfinite(a).all()
+    assert float((a - b).abs().max()) <= 1e-4 * float(b.abs().max())
+
+
+def _replay(cp, w, rank, hq, hkv, d, c, batch, flags=0, dtype=torch.bfloat16, code=P.BF16):
+    rep = RingReplay(RingShape(cp=cp, w=w, rank=rank, hq=hq, hkv=hkv, d=d, c=c, dtype=code, scale=d ** -0.5, batch=batch,
+                               extra_flags=flags), DEV)
+    g = torch.Generator(device=DEV).manual_seed(cp * 1000 + c)
+    mk = lambda *s: (torch.randn(*s, device=DEV, generator=g) * 0.5).to(dtype)
+    q, d_o = mk(batch, hq, 2 * c, d), mk(batch, hq, 2 * c, d)
+    k, v = mk(cp, batch, hkv, 2 * c, d), mk(cp, batch, hkv, 2 * c, d)
+    rep.forward(q, k, v)
+    return rep, q, k, v, d_o
+
+
+@pytest.mark.parametrize("cp,w,rank,hq,hkv,d,c,batch,ks", [
+    (4, 2, 2, 4, 1, 128, 200, 1, 0), (4, 4, 0, 2, 2, 64, 33, 2, 0), (3, 3, 2, 6, 2, 64, 129, 1, 0), (2, 1, 1, 8, 8, 128, 1, 1, 0),
+    (8, 4, 7, 3, 1, 128, 65, 1, 1), (8, 8, 4, 4, 2, 64, 127, 1, 2), (5, 5, 3, 8, 1, 128, 96, 1, 4), (40, 8, 11, 2, 1, 64, 40, 1, 0),
+    (8, 8, 3, 8, 8, 128, 640, 1, 0), (6, 3, 5, 8, 4, 64, 512, 3, 0), (1, 1, 0, 4, 2, 128, 300, 1, 0)])
+def test_run_equals_its_steps(cp, w, rank, hq, hkv, d, c, batch, ks):
+    rep, q, k, v, d_o = _replay(cp, w, rank, hq, hkv, d, c, batch, P.key_splits(ks))
+    for t in (rep.dq, rep.dk, rep.dv):
+        t.fill_(9.0)
+    rep.backward(q, k, v, d_o)
+    got = [t.clone() for t in (rep.dq, rep.dk, rep.dv)]
+    assert int(rep.workspace[:P.binding.WORKSPACE_HEAD].max()) == 0   # counters are left clean
+    rep.backward(q, k, v, d_o)
+    assert all(torch.equal(a, b) for a, b in zip(got, (rep.dq, rep.dk, rep.dv)))
+    for t, step in enumerate(rep.plan):
+        src = step["src_rank"]
+        P.attn_step_bwd(_desc(rep.shape, step, 0 if t else P.OVERWRITE_DQ), q, k[src], v[src], rep.o, d_o, rep.lse, rep.delta,
+                        rep.dq, rep.dk[src], rep.dv[src], rep.workspace)
+    for a, b in zip(got, (rep.dq, rep.dk, rep.dv)):
+        _close(a, b)
+    rep.workspace.zero_()
+
+
+@pytest.mark.parametrize("cp,rank,hq,hkv,d,c,batch", [(4, 0, 2, 2, 64, 128, 1), (3, 2, 4, 1, 128, 17, 2), (4, 1, 2, 2, 100, 40, 1),
+                                                        (34, 5, 1, 1, 32, 9, 1)])
+def test_fp32_run_equals_its_steps(cp, rank, hq, hkv, d, c, batch):
+    rep, q, k, v, d_o = _replay(cp, cp, rank, hq, hkv, d, c, batch, dtype=torch.float32, code=P.FP32)
+    for t in (rep.dq, rep.dk, rep.dv):
+        t.fill_(9.0)
+    rep.backward(q, k, v, d_o)
+    got = [t.clone() for t in (rep.dq, rep.dk, rep.dv)]
+    for t, step in enumerate(rep.plan):
+        src = step["src_rank"]
+        P.attn_step_bwd(_desc(rep.shape, step, 0 if t else P.OVERWRITE_DQ), q, k[src], v[src], rep.o, d_o, rep.lse, rep.delta,
+                        rep.dq, rep.dk[src], rep.dv[src])
+    for a, b in zip(got, (rep.dq, rep.dk, rep.dv)):
+        _close(a, b)
+
+
+def test_run_adds_to_what_is_there_and_halves_run_alone():
+    rep, q, k, v, d_o = _replay(4, 2, 1, 4, 2, 64, 161, 1)
+    rep.backward(q, k, v, d_o)
+    want = [t.clone() for t in (rep.dq, rep.dk, rep.dv)]
+    order = [s["src_rank"] for s in rep.plan]
+    for only in (P.BWD_ONLY_DQ, P.BWD_ONLY_DKV):
+        descs = (P.StepDesc * 4)(*(_desc(rep.shape, s, only | P.binding.ACCUM_DKV) for s in rep.plan))
+        ws = torch.randint(0, 255, (max(P.workspace_bytes_steps(descs), 16),), dtype=torch.uint8, device=DEV)
+        P.attn_steps_bwd(descs, q, [k[s] for s in order], [v[s] for s in order], None, d_o, rep.lse, rep.delta, rep.dq,
+                         [rep.dk[s] for s in order], [rep.dv[s] for s in order], ws)
+    for a, b in zip((rep.dq, rep.dk, rep.dv), want):
+        _close(a, 2 * b)
+
+
+def test_run_without_mask():
+    d, lq, lk, n = 128, 130, 333, 3
+    g = torch.Generator(device=DEV).manual_seed(3)
+    mk = lambda *s: (torch.randn(*s, device=DEV, generator=g) * 0.5).to(torch.float16)
+    q, d_o, o, k, v = mk(1, 4, lq, d), mk(1, 4, lq, d), mk(1, 4, lq, d), mk(n, 1, 2, lk, d), mk(n, 1, 2, lk, d)
+    lse, delta = torch.full((1, 4, lq), 7.0, device=DEV), torch.zeros(1, 4, lq, device=DEV)
+    desc = P.make_desc(batch=1, n_q_heads=4, n_kv_heads=2, head_dim=d, q_len=lq, kv_len=lk, dtype=P.FP16, softmax_scale=d ** -0.5)
+    res = []
+    for run in (True, False):
+        dq = torch.zeros(1, 4, lq, d, device=DEV)
+        dk, dv = torch.empty(n, 1, 2, lk, d, device=DEV), torch.empty(n, 1, 2, lk, d, device=DEV)
+        descs = (P.StepDesc * n)(*(desc for _ in range(n)))
+        ws = torch.empty(max(P.workspace_bytes_steps(descs), P.workspace_bytes(desc), 16), dtype=torch.uint8, device=DEV)
+        if run:
+            P.attn_steps_bwd(descs, q, k, v, o, d_o, lse, delta, dq, dk, dv, ws)
+        else:
+            for t in range(n):
+                P.attn_step_bwd(desc, q, k[t], v[t], o, d_o, lse, delta, dq, dk[t], dv[t], ws)
+        res.append((dq, dk, dv))
+    for a, b in zip(*res):
+        _close(a, b)

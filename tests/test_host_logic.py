@@ -216,3 +216,25 @@ def test_package_fails_loudly_without_the_library(tmp_path):
             "try:\n    P.version()\n    print('NO ERROR')\nexcept ImportError as e:\n    print('ImportError', 'no fallback' in str(e))\n")
     r = subprocess.run([sys.executable, "-c", code], cwd=tmp_path, capture_output=True, text=True, timeout=120)
     assert r.stdout.strip() == "ImportError True", r.stdout + r.stderr
+
+
+def test_a_run_of_steps_is_refused_when_its_steps_do_not_belong_together():
+    import ctypes as C
+    lib, vp = P.binding.lib, C.c_void_p
+    one = dict(batch=1, n_q_heads=4, n_kv_heads=2, head_dim=64, q_len=64, kv_len=64, dtype=P.BF16, softmax_scale=0.1, causal=True,
+               chunk_len=32, q_chunk=(0, 3))
+    need = C.c_int64(0)
+
+    def call(descs, dk=(0x10000, 0x20000), dv=(0x30000, 0x40000), n=2):
+        arr = lambda x: (vp * 2)(*x)
+        return lib.loong_attn_steps_bwd(descs, n, 0x1000, arr((0x1000, 0x2000)), arr((0x1000, 0x2000)), None, 0x1000, 0x1000, 0x1000,
+                                        0x1000, arr(dk), arr(dv), None, 0, None)
+
+    good = (P.StepDesc * 2)(P.make_desc(**one, kv_chunk=(0, 3)), P.make_desc(**one, kv_chunk=(1, 2)))
+    assert lib.loong_workspace_bytes_steps(good, 2, C.byref(need)) == P.OK
+    assert call(good, n=0) == P.E_SHAPE
+    assert call(good, dk=(0x10000, 0x10000)) == P.E_SHAPE and call(good, dk=(0x10000, 0x30000)) == P.E_SHAPE
+    assert call(good, dv=(0x30000, 0)) == P.E_NULL and call(good, dv=(0x30000, 0x40008)) == P.E_ALIGN
+    for field, value in (("q_chunk", (1, 2)), ("softmax_scale", 0.2), ("n_kv_heads", 4), ("dtype", P.FP16)):
+        bad = (P.StepDesc * 2)(good[0], P.make_desc(**{**one, field: value}, kv_chunk=(1, 2)))
+        assert call(bad) == P.E_SHAPE and lib.loong_workspace_bytes_steps(bad, 2, C.byref(need)) == P.E_SHAPE
