@@ -128,6 +128,16 @@ LOONG_API int loong_attn_step_fwd(const loong_step_desc* desc, const void* q, co
                         float* out, float* lse, void* stream);
 
 /*
+ * A run of forward micro-steps whose visiting chunks are all resident: loong_attn_step_fwd for step 0, with
+ * LOONG_FUSE_MERGE for every later one, and, if `o` is not NULL, loong_finalize_out of the result (the same
+ * kernels in the same order: bit for bit the same (out, lse, o)); the last step stores the 16-bit `o` beside
+ * `out`.  `descs` are equal in all but kv_chunk (LOONG_E_SHAPE otherwise); k, v are host arrays of n_steps device
+ * pointers; `o` [B,Hq,q_len,d] contiguous in desc->dtype, 16-byte aligned (fp32: `out` contiguous too).
+ */
+LOONG_API int loong_attn_steps_fwd(const loong_step_desc* descs, int32_t n_steps, const void* q, const void* const* k,
+                         const void* const* v, float* out, float* lse, void* o, void* stream);
+
+/*
  * `Update(out, lse, block_out, block_lse)` of Alg. 2, in place on (out, lse):
  *   lse' = log(exp(lse) + exp(block_lse)),
  *   out' = exp(lse - lse') out + exp(block_lse - lse') block_out.

@@ -31,7 +31,7 @@ EXPORTS = (
     "loong_bwd_delta", "loong_init_running", "loong_finalize_out", "loong_validate_step",
     "loong_last_error", "loong_version", "loong_mfma_probe", "loong_cost_model", "loong_cost_search",
     "loong_permute_rows", "loong_reduce_replicas", "loong_workspace_bytes", "loong_attn_step_bwd_static",
-    "loong_attn_steps_bwd", "loong_workspace_bytes_steps",
+    "loong_attn_steps_fwd", "loong_attn_steps_bwd", "loong_workspace_bytes_steps",
 )
 
 
@@ -89,6 +89,7 @@ lib.loong_attn_step_fwd.argtypes = [C.POINTER(StepDesc), _vp, _vp, _vp, _vp, _vp
 lib.loong_lse_merge.argtypes = [_i64, _i32, _vp, _vp, _vp, _vp, _vp]
 lib.loong_attn_step_bwd.argtypes = [C.POINTER(StepDesc)] + [_vp] * 11 + [_i64, _vp]
 lib.loong_attn_step_bwd_static.argtypes = [C.POINTER(StepDesc)] + [_vp] * 11
+lib.loong_attn_steps_fwd.argtypes = [C.POINTER(StepDesc), _i32, _vp, C.POINTER(_vp), C.POINTER(_vp)] + [_vp] * 4
 lib.loong_attn_steps_bwd.argtypes = ([C.POINTER(StepDesc), _i32, _vp, C.POINTER(_vp), C.POINTER(_vp)] + [_vp] * 5 +
                                      [C.POINTER(_vp)] * 2 + [_vp, _i64, _vp])
 lib.loong_workspace_bytes_steps.argtypes = [C.POINTER(StepDesc), _i32, C.POINTER(C.c_int64)]
@@ -120,7 +121,10 @@ def _ptr(x):
 def _stream(stream):
     if stream is None:
         import torch
-        return torch.cuda.current_stream().cuda_stream if torch.cuda.is_available() else None
+        # (asking whether there is a device costs more than the rest of a call: only until torch has used it)
+        if torch.cuda.is_initialized() or torch.cuda.is_available():
+            return torch.cuda.current_stream().cuda_stream
+        return None
     if isinstance(stream, int):
         return stream
     return stream.cuda_stream
@@ -221,6 +225,12 @@ def zigzag_mask(cp: int, inner_w: int, rank: int, step: int) -> dict:
 
 def attn_step_fwd(desc: StepDesc, q, k, v, out, lse, stream=None):
     _check(lib.loong_attn_step_fwd(C.byref(desc), _ptr(q), _ptr(k), _ptr(v), _ptr(out), _ptr(lse), _stream(stream)))
+
+
+def attn_steps_fwd(descs, q, k, v, out, lse, o=None, stream=None):
+    """loong_attn_steps_fwd: `descs` is a ctypes array of StepDesc; k, v hold one tensor (or pointer) per step."""
+    kp, vp = ((_vp * len(descs))(*map(_ptr, x)) for x in (k, v))
+    _check(lib.loong_attn_steps_fwd(descs, len(descs), _ptr(q), kp, vp, _ptr(out), _ptr(lse), _ptr(o), _stream(stream)))
 
 
 def lse_merge(rows: int, head_dim: int, out, lse, block_out, block_lse, stream=None):

@@ -52,15 +52,38 @@ extern "C" {
 
 int loong_attn_step_fwd(const loong_step_desc* desc, const void* q, const void* k, const void* v,
                         float* out, float* lse, void* stream) {
+  return loong_attn_steps_fwd(desc, 1, q, &k, &v, out, lse, nullptr, stream);
+}
+
+int loong_attn_steps_fwd(const loong_step_desc* descs, int32_t n_steps, const void* q, const void* const* k,
+                         const void* const* v, float* out, float* lse, void* o, void* stream) {
   clear_error();
+  if (n_steps < 1) return fail(LOONG_E_SHAPE, "loong_attn_steps_fwd: %d steps", n_steps);
   StepGeom g;
-  if (int rc = check_step(desc, &g)) return rc;
+  for (int t = 0; t < n_steps; ++t)  // every step is validated before anything is enqueued
+    if (int rc = check_run(descs, t, &g)) return rc;
   if (!q || !k || !v || !out || !lse) return fail(LOONG_E_NULL, "loong_attn_step_fwd: NULL tensor");
-  if (!aligned16(q) || !aligned16(k) || !aligned16(v) || !aligned16(out))
-    return fail(LOONG_E_ALIGN, "loong_attn_step_fwd: q/k/v/out must be 16-byte aligned");
-  if (desc->batch == 0 || desc->q_len == 0) return LOONG_OK;
-  return desc->dtype == LOONG_FP32 ? launch_fwd_f32(*desc, g, q, k, v, out, lse, stream)
-                                   : launch_fwd_bf16(*desc, g, q, k, v, out, lse, stream);
+  bool aligned = aligned16(q) && aligned16(out) && aligned16(o);
+  for (int t = 0; t < n_steps; ++t) {
+    if (!k[t] || !v[t]) return fail(LOONG_E_NULL, "loong_attn_step_fwd: NULL tensor");
+    aligned = aligned && aligned16(k[t]) && aligned16(v[t]);
+  }
+  if (!aligned) return fail(LOONG_E_ALIGN, "loong_attn_step_fwd: q/k/v/out must be 16-byte aligned");
+  loong_step_desc d = *descs;
+  const bool half = d.dtype != LOONG_FP32;
+  const int64_t rows = (int64_t)d.batch * d.n_q_heads * d.q_len;
+  if (o && !half && (d.o_stride[2] != d.head_dim || d.o_stride[1] != (int64_t)d.q_len * d.head_dim ||
+                     (d.batch > 1 && d.o_stride[0] != d.n_q_heads * d.o_stride[1])))
+    return fail(LOONG_E_UNSUPPORTED, "loong_attn_steps_fwd: the fp32 copy needs a contiguous out");
+  if (rows == 0) return LOONG_OK;
+  for (int t = 0; t < n_steps; ++t) {
+    if (t > 0) d.flags |= LOONG_FUSE_MERGE;
+    if (int rc = check_step(&descs[t], &g)) return rc;
+    if (int rc = half ? launch_fwd_bf16(d, g, q, k[t], v[t], out, lse, t == n_steps - 1 ? o : nullptr, stream)
+                      : launch_fwd_f32(d, g, q, k[t], v[t], out, lse, stream))
+      return rc;
+  }
+  return o && !half ? loong_finalize_out(rows, d.head_dim, out, o, d.dtype, stream) : LOONG_OK;
 }
 
 int loong_attn_step_bwd(const loong_step_desc* desc, const void* q, const void* k, const void* v,

@@ -46,6 +46,7 @@ typedef __attribute__((address_space(3))) void lds_void_t;
 struct FwdParams {
   const uint16_t *q, *k, *v;
   float *out, *lse;
+  uint16_t* stored;  // the last step of a run: `out` is also stored rounded to 16 bits, [B,Hq,q_len,D] contiguous
   int B, Hq, Hkv, G, GS;
   int64_t qs[3], ks[3], os[3];
   int q_len;
@@ -125,7 +126,23 @@ __global__ __launch_bounds__(kFwdWaves * 64) void fwd_kernel(const FwdParams p) 
   float* out_row = p.out + b * p.os[0] + h * p.os[1] + (int64_t)my_row * p.os[2];
   float* lse_ptr = p.lse + ((int64_t)b * p.Hq + h) * p.q_len + my_row;
 
+  // four columns of the stored copy of this lane's row (beside the 16 bytes of `out`: a pass of its own over
+  // `out` took 6 us behind 8 steps of 8 heads x 2048 rows)
+  auto store16 = [&](int col, float4 x) {
+    uint16_t* dst = p.stored + (((int64_t)b * p.Hq + h) * p.q_len + my_row) * D + col;
+    *reinterpret_cast<uint2*>(dst) = make_uint2(E::pack2(x.x, x.y), E::pack2(x.z, x.w));
+  };
+
   if (total_t == 0) {  // nothing visible: neutral partial result, or leave the running one
+    if (p.stored && ksp == 0 && row_ok) {
+#pragma unroll
+      for (int db = 0; db < NDB; ++db)
+#pragma unroll
+        for (int vq = 0; vq < 4; ++vq) {
+          const int col = db * 32 + 8 * vq + 4 * hh;
+          store16(col, p.fuse ? *reinterpret_cast<const float4*>(out_row + col) : make_float4(0.f, 0.f, 0.f, 0.f));
+        }
+    }
     if (!p.fuse && ksp == 0 && row_ok) {
 #pragma unroll
       for (int db = 0; db < NDB; ++db)
@@ -422,8 +439,9 @@ __global__ __launch_bounds__(kFwdWaves * 64) void fwd_kernel(const FwdParams p) 
             const float4 xv = slots[((sp * NRB + rb) * C::SLOT_F4 + db * 4 + vq) * 64 + lane];
             acc.x += xv.x * w[sp]; acc.y += xv.y * w[sp]; acc.z += xv.z * w[sp]; acc.w += xv.w * w[sp];
           }
-          *reinterpret_cast<float4*>(out_row + db * 32 + 8 * vq + 4 * hh) =
-              make_float4(acc.x * inv, acc.y * inv, acc.z * inv, acc.w * inv);
+          acc = make_float4(acc.x * inv, acc.y * inv, acc.z * inv, acc.w * inv);
+          *reinterpret_cast<float4*>(out_row + db * 32 + 8 * vq + 4 * hh) = acc;
+          if (p.stored) store16(db * 32 + 8 * vq + 4 * hh, acc);
         }
       }
       if (ksp == 0 && hh == 0) *lse_ptr = l_tot > 0.f ? (m_all + fast_log2(l_tot)) * kLn2 : -INFINITY;
@@ -438,16 +456,18 @@ __global__ __launch_bounds__(kFwdWaves * 64) void fwd_kernel(const FwdParams p) 
 #pragma unroll
     for (int db = 0; db < NDB; ++db)
 #pragma unroll
-      for (int vq = 0; vq < 4; ++vq)
-        *reinterpret_cast<float4*>(out_row + db * 32 + 8 * vq + 4 * hh) =
-            make_float4(o[db][4 * vq] * inv, o[db][4 * vq + 1] * inv, o[db][4 * vq + 2] * inv, o[db][4 * vq + 3] * inv);
+      for (int vq = 0; vq < 4; ++vq) {
+        const float4 x = make_float4(o[db][4 * vq] * inv, o[db][4 * vq + 1] * inv, o[db][4 * vq + 2] * inv, o[db][4 * vq + 3] * inv);
+        *reinterpret_cast<float4*>(out_row + db * 32 + 8 * vq + 4 * hh) = x;
+        if (p.stored) store16(db * 32 + 8 * vq + 4 * hh, x);
+      }
     if (hh == 0) *lse_ptr = l_tot > 0.f ? (m_run + fast_log2(l_tot)) * kLn2 : -INFINITY;
   }
 }
 
 template <class E, int D, int KS>
 int launch_cfg(FwdParams& p, hipStream_t st) {
-  const RowTiling rt = make_row_tiling(p.g, p.G, p.Hq, p.B, kFwdWaves / KS, /*list_blind=*/!p.fuse);  // unfused: blind rows get the neutral result
+  const RowTiling rt = make_row_tiling(p.g, p.G, p.Hq, p.B, kFwdWaves / KS, /*list_blind=*/!p.fuse || p.stored);  // unfused: blind rows get the neutral result
   p.GS = rt.GS; p.ntile[0] = rt.ntile[0]; p.ntile[1] = rt.ntile[1];
   p.tiles_total = rt.tiles_total; p.hgroups = rt.hgroups;
   const int64_t total = rt.total_wg;
@@ -473,10 +493,10 @@ int pick_cfg(FwdParams& p, int head_dim, int ks, hipStream_t st) {
 }  // namespace
 
 int launch_fwd_bf16(const loong_step_desc& d, const StepGeom& g, const void* q, const void* k,
-                    const void* v, float* out, float* lse, void* stream) {
+                    const void* v, float* out, float* lse, void* stored, void* stream) {
   FwdParams p{};
   p.q = (const uint16_t*)q; p.k = (const uint16_t*)k; p.v = (const uint16_t*)v;
-  p.out = out; p.lse = lse;
+  p.out = out; p.lse = lse; p.stored = (uint16_t*)stored;
   p.B = d.batch; p.Hq = d.n_q_heads; p.Hkv = d.n_kv_heads; p.G = d.n_q_heads / d.n_kv_heads;
   for (int i = 0; i < 3; ++i) { p.qs[i] = d.q_stride[i]; p.ks[i] = d.kv_stride[i]; p.os[i] = d.o_stride[i]; }
   p.q_len = d.q_len; p.g = g; p.c = d.softmax_scale * kLog2e; p.fuse = (d.flags & LOONG_FUSE_MERGE) ? 1 : 0;

@@ -78,6 +78,7 @@ class RingReplay:
         self.block_out = None
         self.block_lse = None
         self._order = [step["src_rank"] for step in self.plan]
+        self._fwd_descs = (B.StepDesc * s.cp)(*(_desc(s, step, 0) for step in self.plan))
         # the backward steps of a pass: the first forms delta and writes dq, and all are one run
         flags = B.WORKSPACE_CLEAN | B.COMPUTE_DELTA | B.OVERWRITE_DQ
         self._bwd_descs = (B.StepDesc * s.cp)(*(_desc(s, step, flags) for step in self.plan))
@@ -89,21 +90,19 @@ class RingReplay:
     # ---- forward: cp x (Attention [+ Update]) then the cast to the stored activation type
     def forward(self, q, k_by_src, v_by_src, fuse_merge=True, stream=None):
         s = self.shape
-        if not fuse_merge:
-            B.init_running(self.rows, s.d, self.out, self.lse, stream)
-            if self.block_out is None:
-                self.block_out = torch.empty_like(self.out)
-                self.block_lse = torch.empty_like(self.lse)
-        for t, step in enumerate(self.plan):
-            src = step["src_rank"]
-            if fuse_merge:
-                # the first visit writes the running result (rows that see nothing get the neutral
-                # element), the later ones merge into it: no separate initialisation
-                B.attn_step_fwd(_desc(s, step, B.FUSE_MERGE if t else 0), q, k_by_src[src], v_by_src[src],
-                                self.out, self.lse, stream)
-            else:
-                B.attn_step_fwd(_desc(s, step, 0), q, k_by_src[src], v_by_src[src], self.block_out, self.block_lse, stream)
-                B.lse_merge(self.rows, s.d, self.out, self.lse, self.block_out, self.block_lse, stream)
+        if fuse_merge:
+            # the first visit writes the running result (rows that see nothing get the neutral
+            # element), the later ones merge into it (no separate initialisation), the last stores o too
+            k, v = (_pointers(x, self._order) for x in (k_by_src, v_by_src))
+            B.attn_steps_fwd(self._fwd_descs, q, k, v, self.out, self.lse, self.o, stream)
+            return
+        B.init_running(self.rows, s.d, self.out, self.lse, stream)
+        if self.block_out is None:
+            self.block_out = torch.empty_like(self.out)
+            self.block_lse = torch.empty_like(self.lse)
+        for desc, src in zip(self._fwd_descs, self._order):
+            B.attn_step_fwd(desc, q, k_by_src[src], v_by_src[src], self.block_out, self.block_lse, stream)
+            B.lse_merge(self.rows, s.d, self.out, self.lse, self.block_out, self.block_lse, stream)
         B.finalize_out(self.rows, s.d, self.out, self.o, s.dtype, stream)
 
     # ---- backward from the stored O and LSE: delta once, then the cp steps, whose chunks are all here, as one run

@@ -1,0 +1,45 @@
+"""A run of forward micro-steps (attn_steps_fwd) against the same steps one by one and the cast of the result: the
+same kernels in the same order, so out, lse and o must be equal bit for bit.  Ranks whose last step leaves
+rows without keys, ragged tiles, each forced key split, head groups, a run that continues an earlier one."""
+import pytest
+import torch
+
+import paper_2406_18485_amd as P
+from gpu_harness import DEV
+from paper_2406_18485_amd.ring import RingReplay, RingShape, _desc
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("dtype,code", [(torch.bfloat16, P.BF16), (torch.float16, P.FP16), (torch.float32, P.FP32)])
+@pytest.mark.parametrize("cp,w,rank,hq,hkv,d,c,batch,ks", [
+    (4, 2, 0, 4, 1, 128, 200, 1, 0), (4, 4, 3, 2, 2, 64, 33, 2, 4), (3, 3, 1, 6, 2, 128, 129, 1, 2), (2, 1, 1, 8, 8, 64, 1, 1, 1),
+    (1, 1, 0, 4, 2, 128, 65, 1, 0), (2, 2, 0, 2, 1, 64, 300, 3, 1)])
+def test_run_equals_its_steps_and_the_cast(cp, w, rank, hq, hkv, d, c, batch, ks, dtype, code):
+    rep = RingReplay(RingShape(cp=cp, w=w, rank=rank, hq=hq, hkv=hkv, d=d, c=c, dtype=code, scale=d ** -0.5, batch=batch,
+                               extra_flags=P.key_splits(ks)), DEV)
+    g = torch.Generator(device=DEV).manual_seed(c)
+    mk = lambda *s: torch.randn(*s, device=DEV, generator=g).to(dtype)
+    q, k, v = mk(batch, hq, 2 * c, d), mk(cp, batch, hkv, 2 * c, d), mk(cp, batch, hkv, 2 * c, d)
+    for t in (rep.out, rep.lse, rep.o):
+        t.fill_(5.0)
+    rep.forward(q, k, v)
+    got = [t.clone() for t in (rep.out, rep.lse, rep.o)]
+
+    def step_by_step(first):
+        for t, step in enumerate(rep.plan):
+            src = step["src_rank"]
+            P.attn_step_fwd(_desc(rep.shape, step, P.FUSE_MERGE if first or t else 0), q, k[src], v[src], rep.out, rep.lse)
+        P.finalize_out(rep.rows, d, rep.out, rep.o, code)
+
+    step_by_step(0)
+    assert all(torch.equal(a, b) for a, b in zip(got, (rep.out, rep.lse, rep.o)))
+    # continuing from that result: the first step merges too
+    start = [t.clone() for t in (rep.out, rep.lse)]
+    step_by_step(1)
+    want = [t.clone() for t in (rep.out, rep.lse, rep.o)]
+    rep.out.copy_(start[0]); rep.lse.copy_(start[1])
+    order = [s["src_rank"] for s in rep.plan]
+    descs = (P.StepDesc * cp)(*(_desc(rep.shape, s, P.FUSE_MERGE) for s in rep.plan))
+    P.attn_steps_fwd(descs, q, [k[s] for s in order], [v[s] for s in order], rep.out, rep.lse, rep.o)
+    assert all(torch.equal(a, b) for a, b in zip(want, (rep.out, rep.lse, rep.o)))
