@@ -2,6 +2,9 @@
 // (the forward step and the dQ pass of the backward step).  A workgroup has eight waves =
 // NRB row blocks of 32 rows x KS key splits; GS heads of one kv group share a workgroup.
 #pragma once
+#include <algorithm>
+#include <cmath>
+
 #include "loong_internal.h"
 
 namespace loong {
@@ -52,6 +55,35 @@ inline int pick_key_splits(const StepGeom& g, int G, int Hq, int B, int forced, 
     if (n >= want) return ks_opts[i];
   }
   return 4;
+}
+
+// Key splits of a forward step.  Without a diagonal block all its workgroups are equally long, so a launch
+// takes as many rounds as its workgroups fill the chip, and a round costs nearly the same whether it is
+// full or not: fixed + per key (ns; measured at 1000 and 4096 keys with 1, 2, 4 splits).  At head_dim 64 two
+// workgroups share a unit and a pair of rounds costs less than two.  The split with the least time is taken
+// (ties: the taller tiles, which read K and V less often).  Against the smallest split that nearly fills the chip, 8 heads,
+// 4096 keys, head_dim 128: 2304 rows 79.7 -> 66.7 us, 3000 rows 79.1 -> 67.8, 4500 rows 134 -> 106, 9000 rows 223 -> 209.
+inline int pick_fwd_key_splits(const StepGeom& g, int G, int Hq, int B, int head_dim, int forced, int cus) {
+  bool diag = false;
+  double keys = 0;
+  for (int a = 0; a < g.nq; ++a) {
+    for (int kb = 0; kb < g.nk; ++kb) diag |= g.cls[a][kb] == LOONG_DIAG;
+    keys = std::max(keys, keys_of_rows(g, a));
+  }
+  if (forced || diag) return pick_key_splits(g, G, Hq, B, forced, cus);
+  struct Cost { double fixed, per_key; };
+  const Cost one128[3] = {{9400, 23.1}, {9300, 13.95}, {8000, 7.8}};
+  const Cost one64[3] = {{6500, 17.1}, {6500, 11.0}, {5800, 5.9}}, two64[3] = {{12200, 26.8}, {9900, 18.1}, {7800, 9.7}};
+  int best = 4;
+  double least = INFINITY;
+  for (int i = 2; i >= 0; --i) {
+    const int ks = 1 << i, nrb = kRowWaves / ks, gs = pick_gs(G, nrb);
+    const int64_t n = busy_row_tiles(g, 32 * nrb / gs) * (Hq / gs) * B, rounds = (n + cus - 1) / cus;
+    auto time = [&](const Cost& c) { return c.fixed + c.per_key * keys; };
+    const double t = head_dim == 64 ? (rounds / 2) * time(two64[i]) + (rounds % 2) * time(one64[i]) : rounds * time(one128[i]);
+    if (t <= least) { least = t; best = ks; }
+  }
+  return best;
 }
 
 // Placement of the row tiles of a launch with NRB row blocks per workgroup.  With

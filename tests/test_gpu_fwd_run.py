@@ -43,3 +43,23 @@ def test_run_equals_its_steps_and_the_cast(cp, w, rank, hq, hkv, d, c, batch, ks
     descs = (P.StepDesc * cp)(*(_desc(rep.shape, s, P.FUSE_MERGE) for s in rep.plan))
     P.attn_steps_fwd(descs, q, [k[s] for s in order], [v[s] for s in order], rep.out, rep.lse, rep.o)
     assert all(torch.equal(a, b) for a, b in zip(want, (rep.out, rep.lse, rep.o)))
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("lq,hq,hkv", [(2048, 8, 8), (2049, 8, 8), (2304, 8, 2), (4500, 6, 2), (9000, 8, 8)])
+def test_a_step_of_any_number_of_rounds_takes_one_of_the_key_splits(lq, hq, hkv, d):
+    """Row counts either side of one, two and more rounds of workgroups: the split chosen for them must be one of the
+    three forms (bit for bit), and those agree to what rounding P to 16 bits relative to other maxima leaves."""
+    lk = 333
+    g = torch.Generator(device=DEV).manual_seed(lq + d)
+    mk = lambda *s: (torch.randn(*s, device=DEV, generator=g) * 0.5).to(torch.bfloat16)
+    q, k, v = mk(1, hq, lq, d), mk(1, hkv, lk, d), mk(1, hkv, lk, d)
+    res = []
+    for ks in (0, 1, 2, 4):
+        out, lse = torch.full((1, hq, lq, d), 3.0, device=DEV), torch.empty(1, hq, lq, device=DEV)
+        P.attn_step_fwd(P.make_desc(batch=1, n_q_heads=hq, n_kv_heads=hkv, head_dim=d, q_len=lq, kv_len=lk, dtype=P.BF16,
+                                    softmax_scale=d ** -0.5, flags=P.key_splits(ks)), q, k, v, out, lse)
+        res.append((out, lse))
+    assert any(torch.equal(res[0][0], o) and torch.equal(res[0][1], l) for o, l in res[1:])
+    for o, l in res[1:]:
+        assert float((o - res[0][0]).abs().max()) < 4e-3 and float((l - res[0][1]).abs().max()) < 1e-5
