@@ -109,6 +109,9 @@ for _n in EXPORTS:
         getattr(lib, _n).restype = C.c_int
 
 
+_i64x3 = _i64 * 3
+
+
 def _ptr(x):
     """Device pointer of a torch tensor, or an int / None passed through."""
     if x is None:
@@ -118,13 +121,28 @@ def _ptr(x):
     return x.data_ptr()
 
 
+_current_stream = None  # what _find_current_stream found
+
+
+def _find_current_stream():
+    """A cheap query of torch's current stream.  `torch.cuda.current_stream()` builds two Python objects
+    (2.7 us of a 10 us call, measured on a 64-row copy; the raw handle 0.1 us)."""
+    global _current_stream
+    import torch
+    if not torch.cuda.is_available():
+        return lambda: None
+    torch.cuda.current_stream()  # initialises torch's side once
+    raw, device = getattr(torch._C, "_cuda_getCurrentRawStream", None), getattr(torch._C, "_cuda_getDevice", None)
+    if raw is None or device is None:
+        _current_stream = lambda: torch.cuda.current_stream().cuda_stream
+    else:
+        _current_stream = lambda: raw(device())
+    return _current_stream
+
+
 def _stream(stream):
     if stream is None:
-        import torch
-        # (asking whether there is a device costs more than the rest of a call: only until torch has used it)
-        if torch.cuda.is_initialized() or torch.cuda.is_available():
-            return torch.cuda.current_stream().cuda_stream
-        return None
+        return (_current_stream or _find_current_stream())()
     if isinstance(stream, int):
         return stream
     return stream.cuda_stream
@@ -170,8 +188,7 @@ def cost_search(d_sp: int, max_w: int, **kw) -> dict:
 
 def permute_rows(n, in_stride, out_stride, row_bytes: int, src, dst, stream=None):
     """loong_permute_rows: n, in_stride, out_stride are 3-sequences (strides in bytes)."""
-    a3 = _i64 * 3
-    _check(lib.loong_permute_rows(a3(*n), a3(*in_stride), a3(*out_stride), row_bytes, _ptr(src), _ptr(dst), _stream(stream)))
+    _check(lib.loong_permute_rows(_i64x3(*n), _i64x3(*in_stride), _i64x3(*out_stride), row_bytes, _ptr(src), _ptr(dst), _stream(stream)))
 
 
 def reduce_replicas(heads: int, rep: int, elems_per_head: int, src, dst, stream=None):
