@@ -68,3 +68,25 @@ def test_empty_and_error_paths():
         P.reduce_replicas(2, 0, 4, z, z)
     with pytest.raises(P.LoongError):
         P.reduce_replicas(2, 2, 6, z, z)
+
+
+@pytest.mark.parametrize("n,row_bytes,kind", [
+    ((3, 5, 7), 48, "pack"), ((1, 1, 1), 16, "pack"), ((2, 3, 257), 256, "pack"), ((3, 4, 127), 256, "pack"), ((3, 4, 129), 256, "pack"), ((2, 2, 2100), 128, "pack"), ((2, 2, 40), 4096, "pack"), ((2, 2, 40), 4112, "pack"), ((2, 4, 1023), 16, "dense"), ((4, 2, 4097), 256, "dense"),
+    ((2, 3, 40000), 256, "copies"), ((8, 2, 4096), 512, "copies"), ((2, 300, 3), 16, "copies"), ((1, 7, 1025), 1008, "copies")])
+def test_permuted_rows_of_every_form(n, row_bytes, kind):
+    """Rows with gaps, replication above and below the size where a piece is read once; row lengths and counts either side of
+    what a workgroup takes as a chunk.  Bytes must be equal, gaps untouched."""
+    a, b, c = n
+    row = torch.randint(0, 255, (a, b, c, row_bytes), dtype=torch.uint8, device="cuda:0")
+    if kind == "pack":      # rows (c, a, b) in, (a, b, c) with a gap of one piece after each out
+        src = row.permute(2, 0, 1, 3).contiguous()
+        ins, out_row = (b * row_bytes, row_bytes, a * b * row_bytes), row_bytes + 16
+    elif kind == "dense":
+        src, ins, out_row = row, (b * c * row_bytes, c * row_bytes, row_bytes), row_bytes
+    else:
+        src = row[:, 0].contiguous()
+        row = src[:, None].expand(a, b, c, row_bytes)
+        ins, out_row = (c * row_bytes, 0, row_bytes), row_bytes
+    dst = torch.full((a, b, c, out_row), 7, dtype=torch.uint8, device="cuda:0")
+    P.permute_rows(n, ins, (b * c * out_row, c * out_row, out_row), row_bytes, src, dst)
+    assert torch.equal(dst[..., :row_bytes], row) and bool((dst[..., row_bytes:] == 7).all())
