@@ -1,9 +1,10 @@
 """Single-GPU replay of one device's share of Double-Ring-Attention.
 
 The ring is simulated by visiting the K/V chunks, all resident in HBM, in the order in
-which the inner and outer rings of Alg. 2 would deliver them to the simulated rank; each
-visit is one call of the library's step kernels.  torch is used for device memory and
-the stream only.
+which the inner and outer rings of Alg. 2 would deliver them to the simulated rank.  The
+forward is one launch of the step kernel per visit, in that order; the backward, whose visits
+only share sums, takes runs of visits per launch, since every chunk is there.  torch is used
+for device memory and the stream only.
 """
 from __future__ import annotations
 
@@ -80,12 +81,14 @@ class RingReplay:
         self._order = [step["src_rank"] for step in self.plan]
         self._fwd_descs = (B.StepDesc * s.cp)(*(_desc(s, step, 0) for step in self.plan))
         # the backward steps of a pass: the first forms delta and writes dq, and all are one run
-        flags = B.WORKSPACE_CLEAN | B.COMPUTE_DELTA | B.OVERWRITE_DQ
-        self._bwd_descs = (B.StepDesc * s.cp)(*(_desc(s, step, flags) for step in self.plan))
+        self._bwd_descs = (B.StepDesc * s.cp).from_buffer_copy(self._fwd_descs)
+        for desc in self._bwd_descs:
+            desc.flags |= B.WORKSPACE_CLEAN | B.COMPUTE_DELTA | B.OVERWRITE_DQ
         # caller-owned scratch of the backward steps: the largest any micro-step, or all in one run, ask for
-        need = max(B.workspace_bytes_steps(self._bwd_descs), *(B.workspace_bytes(_desc(s, step, 0)) for step in self.plan))
-        # (zero once: every call leaves its counters zero, so none has to clear them)
-        self.workspace = torch.zeros(max(need, 16), dtype=torch.uint8, device=self.dev)
+        need = max(B.workspace_bytes_steps(self._bwd_descs), *(B.workspace_bytes(desc) for desc in self._fwd_descs))
+        # (its counters zero once: every call leaves them zero, so none has to clear them)
+        self.workspace = torch.empty(max(need, 16), dtype=torch.uint8, device=self.dev)
+        self.workspace[:B.WORKSPACE_HEAD].zero_()
 
     # ---- forward: cp x (Attention [+ Update]) then the cast to the stored activation type
     def forward(self, q, k_by_src, v_by_src, fuse_merge=True, stream=None):
