@@ -505,7 +505,7 @@ int launch_fwd_bf16(const loong_step_desc& d, const StepGeom& g, const void* q, 
   hipStream_t st = static_cast<hipStream_t>(stream);
   DeviceFacts dev;
   if (int rc = device_facts(&dev)) return rc;
-  const int ks = pick_fwd_key_splits(g, p.G, p.Hq, p.B, d.head_dim, forced_key_splits(d.flags), dev.cus);
+  const int ks = pick_key_splits(g, p.G, p.Hq, p.B, forced_key_splits(d.flags), dev.cus);
   if (d.dtype == LOONG_FP16) return pick_cfg<Fp16>(p, d.head_dim, ks, st);
   return pick_cfg<Bf16>(p, d.head_dim, ks, st);
 }

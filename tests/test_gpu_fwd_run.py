@@ -63,3 +63,20 @@ def test_a_step_of_any_number_of_rounds_takes_one_of_the_key_splits(lq, hq, hkv,
     assert any(torch.equal(res[0][0], o) and torch.equal(res[0][1], l) for o, l in res[1:])
     for o, l in res[1:]:
         assert float((o - res[0][0]).abs().max()) < 4e-3 and float((l - res[0][1]).abs().max()) < 1e-5
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("lq,hq,hkv,ks", [(2048, 8, 8, 4), (2304, 8, 8, 4), (3000, 8, 2, 4), (4500, 8, 8, 2), (9000, 8, 8, 1)])
+def test_the_split_is_the_smallest_that_fills_the_chip(lq, hq, hkv, ks, d):
+    """The key split decides the result's last bits: it is the smallest that puts a workgroup of 32 * 8 / ks rows on at least 7/8
+    of 256 units, here 32 * 8 = 256, 288, 376, 288 and 288 workgroups (72 to 192 with the next smaller one)."""
+    g = torch.Generator(device=DEV).manual_seed(lq + d)
+    mk = lambda *s: (torch.randn(*s, device=DEV, generator=g) * 0.5).to(torch.bfloat16)
+    q, k, v = mk(1, hq, lq, d), mk(1, hkv, 700, d), mk(1, hkv, 700, d)
+    res = []
+    for forced in (0, ks):
+        out, lse = torch.empty(1, hq, lq, d, device=DEV), torch.empty(1, hq, lq, device=DEV)
+        P.attn_step_fwd(P.make_desc(batch=1, n_q_heads=hq, n_kv_heads=hkv, head_dim=d, q_len=lq, kv_len=700, dtype=P.BF16,
+                                    softmax_scale=d ** -0.5, flags=P.key_splits(forced)), q, k, v, out, lse)
+        res.append((out, lse))
+    assert torch.equal(res[0][0], res[1][0]) and torch.equal(res[0][1], res[1][1])
