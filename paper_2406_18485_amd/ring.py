@@ -49,6 +49,8 @@ def _desc(shape: RingShape, step: dict, flags: int) -> B.StepDesc:
 def _pointers(chunks, order) -> list[int]:
     """Device pointers of chunks[src] for every src of `order`; a stacked tensor is not sliced for it."""
     if isinstance(chunks, torch.Tensor):
+        if max(order) >= chunks.shape[0]:
+            raise IndexError(f"source rank {max(order)} is out of range of {chunks.shape[0]} chunks")
         base, step = chunks.data_ptr(), chunks.stride(0) * chunks.element_size()
         return [base + src * step for src in order]
     return [chunks[src].data_ptr() for src in order]
