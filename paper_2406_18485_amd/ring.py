@@ -46,14 +46,15 @@ def _desc(shape: RingShape, step: dict, flags: int) -> B.StepDesc:
                        flags=flags | shape.extra_flags)
 
 
-def _pointers(chunks, order) -> list[int]:
-    """Device pointers of chunks[src] for every src of `order`; a stacked tensor is not sliced for it."""
+def _visited(chunks, order) -> list:
+    """chunks[src] for every src of `order`, of a stacked tensor their device pointers (it is not sliced for it).  The
+    items themselves are returned, not their pointers: one that `chunks` made for this call lives until it has been used."""
     if isinstance(chunks, torch.Tensor):
         if max(order) >= chunks.shape[0]:
             raise IndexError(f"source rank {max(order)} is out of range of {chunks.shape[0]} chunks")
         base, step = chunks.data_ptr(), chunks.stride(0) * chunks.element_size()
         return [base + src * step for src in order]
-    return [chunks[src].data_ptr() for src in order]
+    return [chunks[src] for src in order]
 
 
 class RingReplay:
@@ -98,7 +99,7 @@ class RingReplay:
         if fuse_merge:
             # the first visit writes the running result (rows that see nothing get the neutral
             # element), the later ones merge into it (no separate initialisation), the last stores o too
-            k, v = (_pointers(x, self._order) for x in (k_by_src, v_by_src))
+            k, v = (_visited(x, self._order) for x in (k_by_src, v_by_src))
             B.attn_steps_fwd(self._fwd_descs, q, k, v, self.out, self.lse, self.o, stream)
             return
         B.init_running(self.rows, s.d, self.out, self.lse, stream)
@@ -112,7 +113,7 @@ class RingReplay:
 
     # ---- backward from the stored O and LSE: delta once, then the cp steps, whose chunks are all here, as one run
     def backward(self, q, k_by_src, v_by_src, d_o, stream=None):
-        k, v, dk, dv = (_pointers(x, self._order) for x in (k_by_src, v_by_src, self.dk, self.dv))
+        k, v, dk, dv = (_visited(x, self._order) for x in (k_by_src, v_by_src, self.dk, self.dv))
         B.attn_steps_bwd(self._bwd_descs, q, k, v, self.o, d_o, self.lse, self.delta, self.dq, dk, dv, self.workspace,
                          stream=stream)
 

@@ -1,5 +1,7 @@
 """What RingReplay hands to the library, without a GPU: its buffers are on the CPU and the library's step
 calls are replaced by ones that look at their arguments."""
+import weakref
+
 import pytest
 import torch
 
@@ -56,3 +58,41 @@ def test_too_few_chunks_are_refused_before_any_call(replay, have, form):
     replay.forward(q, full, full)
     replay.backward(q, full, full, q)
     assert replay.calls == ["loong_attn_steps_fwd", "loong_attn_steps_bwd"]
+
+
+def test_chunks_made_for_the_call_live_through_it(replay):
+    q, full = _inputs(CP)
+
+    class Lazy:   # e.g. chunks kept in another form and widened when they are asked for
+        def __init__(self):
+            self.made = []
+
+        def __getitem__(self, src):
+            x = full[src].clone()
+            self.made.append((weakref.ref(x), x.data_ptr()))
+            return x
+
+    k, v = Lazy(), Lazy()
+
+    def look(name, args):
+        for lazy, pointers in ((k, args[3]), (v, args[4])):
+            assert len(lazy.made) == CP and all(ref() is not None for ref, _ in lazy.made)
+            assert list(pointers) == [p for _, p in lazy.made]
+    replay.look = look
+    replay.forward(q, k, v)
+    k.made, v.made = [], []
+    replay.backward(q, k, v, q)
+    assert len(replay.calls) == 2
+
+
+def test_lists_may_hold_raw_pointers(replay):
+    q, full = _inputs(CP)
+    order = [step["src_rank"] for step in replay.plan]
+    pointers = [full[src].data_ptr() for src in range(CP)]
+
+    def look(name, args):
+        assert list(args[3]) == list(args[4]) == [pointers[src] for src in order]
+    replay.look = look
+    replay.forward(q, pointers, pointers)
+    replay.backward(q, pointers, pointers, q)
+    assert len(replay.calls) == 2
