@@ -70,8 +70,10 @@ extern "C" {
 #define LOONG_BWD_ONLY_DKV   8    /* bwd: compute dk/dv only (dq may be NULL and is not touched) */
 #define LOONG_BWD_ONLY_DQ    16   /* bwd: compute this step's share of dq only (dk, dv may be NULL) */
 #define LOONG_OVERWRITE_DQ   32   /* bwd: dq is written (rows that see no key get 0) instead of added to: the first step */
-#define LOONG_WORKSPACE_CLEAN 64  /* bwd: the first LOONG_WORKSPACE_HEAD bytes of `workspace` are zero on entry, as every call
-                                     leaves them: the caller cleared them once, the call need not */
+#define LOONG_WORKSPACE_CLEAN 64  /* bwd: the first LOONG_WORKSPACE_HEAD bytes of `workspace` are zero when the call's kernels start,
+                                     so the call need not clear them.  The caller answers for it: it zeroes ALL of them itself,
+                                     ordered before its first call on the stream; a call leaves a zero head zero.  (A call
+                                     without the flag clears the head first if it counts there, and leaves it alone if not.) */
 #define LOONG_WORKSPACE_HEAD 65536
 /* Tuning/testing knob of the 16-bit kernels that own query rows (forward, dQ): bits 8..10 of
  * `flags` hold 1, 2 or 4 to force that many key splits per workgroup (waves that share the
@@ -163,8 +165,8 @@ LOONG_API int loong_lse_merge(int64_t rows, int32_t head_dim, float* out, float*
  * arrive adds their partial sums in a fixed order.  Those partial sums and their arrival
  * counters live in `workspace`, device memory of the caller's, 16-byte aligned, at least
  * loong_workspace_bytes(desc) bytes (that may be 0: then `workspace` may be NULL).  It
- * may hold anything on entry (the call clears what it counts in with a kernel of its own on
- * `stream`; with LOONG_WORKSPACE_CLEAN it need not) and holds nothing of value afterwards; calls that share one workspace must be
+ * may hold anything on entry (a call that counts clears the counters on `stream` before it does, unless the caller
+ * vouches for them: LOONG_WORKSPACE_CLEAN) and holds nothing of value afterwards; calls that share one workspace must be
  * ordered on one stream.  A missing or too small workspace is LOONG_E_NULL / LOONG_E_SHAPE
  * and nothing is enqueued.  The bf16/fp16 kernels only; the fp32 kernels need none.
  * The two halves run as one launch on `stream`; LOONG_BWD_ONLY_DKV / LOONG_BWD_ONLY_DQ
@@ -201,7 +203,8 @@ LOONG_API int loong_workspace_bytes_steps(const loong_step_desc* descs, int32_t 
  * refused with LOONG_E_UNSUPPORTED and nothing is enqueued: use loong_attn_step_bwd.  All
  * calls on one GPU share that GPU's array: calls that overlap on one GPU (two streams, two
  * threads) race on it and must be ordered by the caller; the array keeps the last call's
- * contents, and each call clears what it counts in on `stream` before its kernels use it.
+ * contents, and each call clears its counters on `stream` before its kernels use them
+ * (LOONG_WORKSPACE_CLEAN means nothing here).
  */
 #define LOONG_STATIC_SCRATCH_BYTES (((int64_t)64 << 20) + 65536)
 LOONG_API int loong_attn_step_bwd_static(const loong_step_desc* desc, const void* q, const void* k, const void* v,

@@ -122,6 +122,7 @@ int loong_attn_steps_bwd(const loong_step_desc* descs, int32_t n_steps, const vo
         return fail(LOONG_E_SHAPE, "loong_attn_steps_bwd: steps %d and %d have the same dk or dv", u, t);
   if (workspace_bytes < 0) return fail(LOONG_E_SHAPE, "loong_attn_step_bwd: negative workspace size");
   if (desc->batch == 0) return LOONG_OK;
+  void* head = nullptr;             // counters to clear, once for all launches of the run: each leaves them zero
   if (desc->dtype != LOONG_FP32) {  // scratch for shared query loops: checked before anything is enqueued
     int64_t need = 0;
     if (int rc = loong_workspace_bytes_steps(descs, n_steps, &need)) return rc;
@@ -133,10 +134,14 @@ int loong_attn_steps_bwd(const loong_step_desc* descs, int32_t n_steps, const vo
       if (workspace_bytes < need)
         return fail(LOONG_E_SHAPE, "loong_attn_step_bwd: workspace of %lld bytes, this step needs %lld (loong_workspace_bytes)",
                     (long long)workspace_bytes, (long long)need);
+      if (!(desc->flags & LOONG_WORKSPACE_CLEAN)) head = workspace;
     }
   }
-  if (want_delta)
-    if (int rc = loong_bwd_delta(desc, o, d_o, delta, stream)) return rc;
+  if (want_delta) {
+    if (int rc = launch_delta(*desc, o, d_o, delta, head, stream)) return rc;
+  } else if (head) {
+    if (int rc = launch_clear_head(head, stream)) return rc;
+  }
   const int per_launch = steps_per_launch(descs, n_steps);
   for (int t0 = 0; t0 < n_steps; t0 += per_launch) {
     const int n = std::min(n_steps - t0, per_launch);

@@ -27,13 +27,6 @@ __global__ __launch_bounds__(256) void zero_kernel(int64_t n4, float4* a, float4
   }
 }
 
-// The arrival counters a launch with shared query loops uses start from zero: cleared on the
-// caller's stream right before it (a fill kernel, so the call can be captured in a graph).
-__global__ __launch_bounds__(256) void clear_counters_kernel(int n, uint32_t* cnt) {
-  const int i = blockIdx.x * 256 + threadIdx.x;
-  if (i < n) cnt[i] = 0u;
-}
-
 // Work list of a launch over `n` micro-steps that differ in the visiting chunk only: the key halves some
 // row sees and those nobody sees (their gradients are cleared), and how many workgroups share the query
 // loop of a key tile.
@@ -189,10 +182,6 @@ int plan_dkv(StepLaunch& s, const SplitPlan& plan, int n, int flags, int D, void
       return fail(LOONG_E_SHAPE, "loong_attn_step_bwd: workspace too small");
     p.ws_cnt = static_cast<uint32_t*>(workspace);
     p.ws_part = reinterpret_cast<float*>(static_cast<unsigned char*>(workspace) + kWsHeadBytes);
-    if (!(flags & LOONG_WORKSPACE_CLEAN)) {
-      clear_counters_kernel<<<dim3((unsigned)((plan.busy + 255) / 256)), dim3(256), 0, st>>>((int)plan.busy, p.ws_cnt);
-      if (int rc = check_launch("loong_attn_step_bwd (clear counters)")) return rc;
-    }
   }
   s.do_kv = true;
   return LOONG_OK;

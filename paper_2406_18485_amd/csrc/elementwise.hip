@@ -75,14 +75,24 @@ __global__ __launch_bounds__(kThreads) void copy_f32_kernel(int64_t n4, const fl
   if (i < n4) o[i] = in[i];
 }
 
+// ---- arrival counters of the backward step: the head of its workspace ----------------------
+// Cleared on the caller's stream (by a kernel, so the call can be captured in a graph).
+__device__ __forceinline__ void clear_head(uint4* head) {
+  const int64_t threads = (int64_t)gridDim.x * kThreads;
+  for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < kWsHeadBytes / 16; i += threads) head[i] = make_uint4(0, 0, 0, 0);
+}
+__global__ __launch_bounds__(kThreads) void clear_head_kernel(uint4* head) { clear_head(head); }
+
 // ---- delta_i = sum_k dO_ik O_ik ----------------------------------------------------------
 // LPR lanes per row, each lane 16 bytes at a time; rows are (batch, head, token) with strides.
+// `head`: NULL, or the counters that the step after this one uses: they are cleared on the side.
 template <class E, int LPR>  // E = Bf16, Fp16, or float for fp32 storage
 __global__ __launch_bounds__(kThreads) void delta_kernel(int64_t rows, int heads, int len, int dvec,
                                                          int64_t s0, int64_t s1, int64_t s2,
                                                          const void* __restrict__ o_,
                                                          const void* __restrict__ do_,
-                                                         float* __restrict__ delta) {
+                                                         float* __restrict__ delta, uint4* head) {
+  if (head) clear_head(head);
   constexpr int RPB = kThreads / LPR;
   const int sub = threadIdx.x % LPR;
   int64_t row = (int64_t)blockIdx.x * RPB + threadIdx.x / LPR;
@@ -121,6 +131,41 @@ int pow2_lanes(int pieces) {
 int64_t blocks_for(int64_t items, int per_block) { return (items + per_block - 1) / per_block; }
 
 }  // namespace
+
+int launch_clear_head(void* head, void* stream) {
+  clear_head_kernel<<<dim3((unsigned)(kWsHeadBytes / 16 / kThreads)), dim3(kThreads), 0, static_cast<hipStream_t>(stream)>>>(
+      static_cast<uint4*>(head));
+  return check_launch("loong_attn_step_bwd (clear counters)");
+}
+
+int launch_delta(const loong_step_desc& d, const void* o, const void* d_o, float* delta, void* head, void* stream) {
+  const int64_t rows = (int64_t)d.batch * d.n_q_heads * d.q_len;
+  if (rows == 0) return head ? launch_clear_head(head, stream) : LOONG_OK;
+  const int dvec = d.head_dim / (d.dtype == LOONG_FP32 ? 4 : 8);
+  const int lpr = pow2_lanes(dvec);
+  const int64_t nb = blocks_for(rows, kThreads / lpr);
+  if (nb > 0x7fffffff) return fail(LOONG_E_UNSUPPORTED, "loong_bwd_delta: grid too large");
+  dim3 grid((unsigned)nb), block(kThreads);
+  hipStream_t st = static_cast<hipStream_t>(stream);
+  const int64_t* s = d.q_stride;
+#define LOONG_DELTA(BF, L)                                                                          \
+  delta_kernel<BF, L><<<grid, block, 0, st>>>(rows, d.n_q_heads, d.q_len, dvec, s[0], s[1], s[2], \
+                                               o, d_o, delta, static_cast<uint4*>(head))
+#define LOONG_DELTA_L(BF)              \
+  switch (lpr) {                       \
+    case 1: LOONG_DELTA(BF, 1); break; \
+    case 2: LOONG_DELTA(BF, 2); break; \
+    case 4: LOONG_DELTA(BF, 4); break; \
+    case 8: LOONG_DELTA(BF, 8); break; \
+    case 16: LOONG_DELTA(BF, 16); break; \
+    default: LOONG_DELTA(BF, 32); break; \
+  }
+  if (d.dtype == LOONG_BF16) { LOONG_DELTA_L(Bf16) } else if (d.dtype == LOONG_FP16) { LOONG_DELTA_L(Fp16) } else { LOONG_DELTA_L(float) }
+#undef LOONG_DELTA_L
+#undef LOONG_DELTA
+  return check_launch("loong_bwd_delta");
+}
+
 }  // namespace loong
 
 using namespace loong;
@@ -204,31 +249,7 @@ int loong_bwd_delta(const loong_step_desc* desc, const void* o, const void* d_o,
   if (int rc = check_step(desc, nullptr)) return rc;
   if (!o || !d_o || !delta) return fail(LOONG_E_NULL, "loong_bwd_delta: NULL tensor");
   if (!aligned16(o) || !aligned16(d_o)) return fail(LOONG_E_ALIGN, "loong_bwd_delta: o/d_o not 16-byte aligned");
-  const int64_t rows = (int64_t)desc->batch * desc->n_q_heads * desc->q_len;
-  if (rows == 0) return LOONG_OK;
-  const int dvec = desc->head_dim / (desc->dtype == LOONG_FP32 ? 4 : 8);
-  const int lpr = pow2_lanes(dvec);
-  const int64_t nb = blocks_for(rows, kThreads / lpr);
-  if (nb > 0x7fffffff) return fail(LOONG_E_UNSUPPORTED, "loong_bwd_delta: grid too large");
-  dim3 grid((unsigned)nb), block(kThreads);
-  hipStream_t st = static_cast<hipStream_t>(stream);
-  const int64_t* s = desc->q_stride;
-#define LOONG_DELTA(BF, L)                                                                               \
-  delta_kernel<BF, L><<<grid, block, 0, st>>>(rows, desc->n_q_heads, desc->q_len, dvec, s[0], s[1], s[2], \
-                                               o, d_o, delta)
-#define LOONG_DELTA_L(BF)              \
-  switch (lpr) {                       \
-    case 1: LOONG_DELTA(BF, 1); break; \
-    case 2: LOONG_DELTA(BF, 2); break; \
-    case 4: LOONG_DELTA(BF, 4); break; \
-    case 8: LOONG_DELTA(BF, 8); break; \
-    case 16: LOONG_DELTA(BF, 16); break; \
-    default: LOONG_DELTA(BF, 32); break; \
-  }
-  if (desc->dtype == LOONG_BF16) { LOONG_DELTA_L(Bf16) } else if (desc->dtype == LOONG_FP16) { LOONG_DELTA_L(Fp16) } else { LOONG_DELTA_L(float) }
-#undef LOONG_DELTA_L
-#undef LOONG_DELTA
-  return check_launch("loong_bwd_delta");
+  return launch_delta(*desc, o, d_o, delta, nullptr, stream);
 }
 
 }  // extern "C"

@@ -53,8 +53,9 @@ constexpr int kDefaultCus = 256;
 int planning_cus();
 
 // Workspace of the backward step (caller-owned device memory): kWsCounters 32-bit arrival
-// counters, then the partial sums.  The step clears the counters it uses with a kernel of its
-// own before the kernel that counts, so the memory may hold anything when it is handed in.
+// counters, then the partial sums.  A call that counts clears the counters on its own stream first (beside
+// the delta it forms, else with a kernel of its own), so the memory may hold anything when it is handed in;
+// with LOONG_WORKSPACE_CLEAN they are the caller's to have cleared.
 constexpr int kWsCounters = 16384;
 constexpr int64_t kWsHeadBytes = (int64_t)kWsCounters * 4;
 
@@ -82,4 +83,7 @@ int launch_bwd_bf16(const loong_step_desc& d, const StepGeom* g, int n, const vo
                     const void* const* v, const void* d_o, const float* lse, const float* delta, float* dq,
                     float* const* dk, float* const* dv, void* workspace, int64_t workspace_bytes, void* stream);
 int64_t bwd_workspace_bytes_bf16(const loong_step_desc& d, const StepGeom* g, int n);
+// delta of every row, and with `head` the counters of a workspace cleared; these alone
+int launch_delta(const loong_step_desc& d, const void* o, const void* d_o, float* delta, void* head, void* stream);
+int launch_clear_head(void* head, void* stream);
 }  // namespace loong

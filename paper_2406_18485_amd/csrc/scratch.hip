@@ -63,7 +63,9 @@ __attribute__((visibility("default"))) int loong_attn_step_bwd_static(const loon
   void* ptr = nullptr;
   if (need > 0)
     if (int rc = scratch_address(&ptr)) return rc;
-  return loong_attn_step_bwd(desc, q, k, v, o, d_o, lse, delta, dq, dk, dv, ptr, need > 0 ? kScratchBytes : 0, stream);
+  loong_step_desc d = *desc;
+  d.flags &= ~LOONG_WORKSPACE_CLEAN;  // the array is shared by every caller: nobody can answer for its counters
+  return loong_attn_step_bwd(&d, q, k, v, o, d_o, lse, delta, dq, dk, dv, ptr, need > 0 ? kScratchBytes : 0, stream);
 }
 
 }  // extern "C"

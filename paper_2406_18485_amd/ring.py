@@ -86,10 +86,11 @@ class RingReplay:
         # the backward steps of a pass: the first forms delta and writes dq, and all are one run
         self._bwd_descs = (B.StepDesc * s.cp).from_buffer_copy(self._fwd_descs)
         for desc in self._bwd_descs:
-            desc.flags |= B.WORKSPACE_CLEAN | B.COMPUTE_DELTA | B.OVERWRITE_DQ
+            desc.flags |= B.COMPUTE_DELTA | B.OVERWRITE_DQ
         # caller-owned scratch of the backward steps: the largest any micro-step, or all in one run, ask for
         need = max(B.workspace_bytes_steps(self._bwd_descs), *(B.workspace_bytes(desc) for desc in self._fwd_descs))
-        # (its counters zero once: every call leaves them zero, so none has to clear them)
+        # (every call clears the counters on its own stream, which may be another than this one; zero from the start, a
+        # program that has waited for that may also lend the workspace to steps with WORKSPACE_CLEAN)
         self.workspace = torch.empty(max(need, 16), dtype=torch.uint8, device=self.dev)
         self.workspace[:B.WORKSPACE_HEAD].zero_()
 

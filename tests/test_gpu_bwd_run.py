@@ -107,3 +107,34 @@ def test_run_without_mask():
         res.append((dq, dk, dv))
     for a, b in zip(*res):
         _close(a, b)
+
+
+@pytest.mark.parametrize("cp,hq,hkv,d,c", [(4, 4, 1, 128, 200), (8, 8, 8, 128, 640), (1, 2, 1, 64, 33)])
+def test_a_backward_needs_nothing_of_its_workspace(cp, hq, hkv, d, c):
+    """Runs with the delta (which clears the counters on the side), without it (a kernel of its own does), and the static
+    scratch array, whose counters a caller cannot vouch for: all on a stream other than the workspace's, all from junk."""
+    rep, q, k, v, d_o = _replay(cp, cp, cp // 2, hq, hkv, d, c, 1)
+    rep.backward(q, k, v, d_o)
+    want = [t.clone() for t in (rep.dq, rep.dk, rep.dv)]
+    order = [s["src_rank"] for s in rep.plan]
+    side = torch.cuda.Stream()
+    for delta in (True, False):
+        for t in (rep.dq, rep.dk, rep.dv):
+            t.fill_(9.0)
+        rep.workspace.fill_(0xA5)
+        side.wait_stream(torch.cuda.current_stream())
+        if delta:
+            rep.backward(q, k, v, d_o, stream=side)
+        else:
+            descs = (P.StepDesc * cp)(*(_desc(rep.shape, s, P.OVERWRITE_DQ) for s in rep.plan))
+            P.attn_steps_bwd(descs, q, [k[s] for s in order], [v[s] for s in order], None, d_o, rep.lse, rep.delta, rep.dq,
+                             [rep.dk[s] for s in order], [rep.dv[s] for s in order], rep.workspace, stream=side)
+        torch.cuda.current_stream().wait_stream(side)
+        assert all(torch.equal(a, b) for a, b in zip(want, (rep.dq, rep.dk, rep.dv)))
+    step, src = rep.plan[0], order[0]
+    res = []
+    for flags in (0, P.WORKSPACE_CLEAN):
+        g = [torch.empty_like(t) for t in (rep.dq, rep.dk[src], rep.dv[src])]
+        P.attn_step_bwd_static(_desc(rep.shape, step, flags | P.OVERWRITE_DQ), q, k[src], v[src], None, d_o, rep.lse, rep.delta, *g)
+        res.append(g)
+    assert all(torch.equal(a, b) for a, b in zip(*res))

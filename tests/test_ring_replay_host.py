@@ -96,3 +96,12 @@ def test_lists_may_hold_raw_pointers(replay):
     replay.forward(q, pointers, pointers)
     replay.backward(q, pointers, pointers, q)
     assert len(replay.calls) == 2
+
+
+def test_no_backward_vouches_for_counters_cleared_on_another_stream(replay):
+    """The stream of a backward is the caller's choice, so its counters are cleared there and not at construction."""
+    q, full = _inputs(CP)
+    seen = []
+    replay.look = lambda name, args: seen.extend(args[0][t].flags for t in range(CP))
+    replay.backward(q, full, full, q)
+    assert len(seen) == CP and not any(flags & P.WORKSPACE_CLEAN for flags in seen)
