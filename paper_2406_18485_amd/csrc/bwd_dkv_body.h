@@ -220,7 +220,8 @@ __device__ __forceinline__ void dkv_body(const StepTable& tab, const DkvParams& 
   // shared query loop: who gathers
   const int tile_id = bhk * p.kt_total + kt;
   int* const role = reinterpret_cast<int*>(smem + C::ROLE_OFF);
-  if (p.nsplit > 1 && tid == 0) *role = claim_gather(p.ws_cnt + tile_id, p.nsplit);
+  constexpr int kLeaves = 0, kGathers = 1, kAllHere = 2, kPartsMissing = 3;
+  if (p.nsplit > 1 && tid == 0) *role = claim_gather(p.ws_cnt + tile_id, p.nsplit) ? kGathers : kLeaves;
 
   wait_vmcnt<0>();  // the K / V fragments are in: no counter wait of the compiler's lands in the loop
   if (it_begin < it_end) issue_tile(cur, 0);
@@ -403,7 +404,7 @@ __device__ __forceinline__ void dkv_body(const StepTable& tab, const DkvParams& 
     unsigned char* parts = reinterpret_cast<unsigned char*>(p.ws_part) + (int64_t)tile_id * p.nsplit * (kBwdWaves * WAVE_B);
     const __amdgpu_buffer_rsrc_t buf = part_buffer(parts);
     const uint32_t mine = wave * WAVE_B + lane * 16;
-    if (!*role) {
+    if (*role == kLeaves) {
 #pragma unroll
       for (int db = 0; db < NDB; ++db)
 #pragma unroll
@@ -415,13 +416,14 @@ __device__ __forceinline__ void dkv_body(const StepTable& tab, const DkvParams& 
       if (tid == 0) publish_part(p.ws_cnt + tile_id);
       return;
     }
-    if (tid == 0) await_parts(p.ws_cnt + tile_id, p.nsplit);
+    if (tid == 0) *role = await_parts(p.ws_cnt + tile_id, p.nsplit, it_end - it_begin) ? kAllHere : kPartsMissing;
     __syncthreads();
+    const float start = *role == kAllHere ? 0.f : NAN;
     floatx16_t sum[NDB];
 #pragma unroll
     for (int db = 0; db < NDB; ++db)
 #pragma unroll
-      for (int v = 0; v < 16; ++v) sum[db][v] = 0.f;
+      for (int v = 0; v < 16; ++v) sum[db][v] = start;
     for (int s2 = 0; s2 < p.nsplit; ++s2) {
       if (s2 == sp) {
 #pragma unroll

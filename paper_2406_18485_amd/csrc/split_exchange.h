@@ -16,7 +16,9 @@
 // loads are issued after it has seen every part published.
 //
 // Counter of a tile: low half = tickets drawn, high half = parts published.  It must be zero
-// before the launch and the gatherer leaves it zero.
+// before the launch and the gatherer leaves it zero.  If it is not (memory that two unordered calls share, or a
+// caller that vouched for counters it never cleared), the tile's result is wrong, but nothing is read or written elsewhere and
+// every wait ends; a wait that runs out stores NaN, so that most such mistakes show.
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -26,10 +28,11 @@ namespace loong {
 
 constexpr uint32_t kPublished = 0x10000u;
 
-// One thread of the workgroup: draw a ticket; true for the gatherer of `n` workgroups.
+// One thread of the workgroup: draw a ticket; true for the gatherer of `n` workgroups (the last ticket; later ones are
+// drawn from wrong counters only).
 __device__ __forceinline__ bool claim_gather(uint32_t* cnt, int n) {
   const uint32_t before = __hip_atomic_fetch_add(cnt, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  return (before & (kPublished - 1)) == (uint32_t)n - 1;
+  return (before & (kPublished - 1)) >= (uint32_t)n - 1;
 }
 
 // One thread: this workgroup's part is in memory (every wave has waited for its stores, and a
@@ -38,10 +41,19 @@ __device__ __forceinline__ void publish_part(uint32_t* cnt) {
   __hip_atomic_fetch_add(cnt, kPublished, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// One thread of the gatherer: wait for the other n - 1 parts and put the counter back to zero.
-__device__ __forceinline__ void await_parts(uint32_t* cnt, int n) {
-  while ((__hip_atomic_load(cnt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >> 16) != (uint32_t)n - 1) __builtin_amdgcn_s_sleep(2);
+// One thread of the gatherer: wait for the other n - 1 parts and put the counter back to zero; false if they did not
+// come.  The others started before this workgroup drew its ticket and have as many iterations of their loop left at most as it
+// has done, so the wait is limited by that: 1024 looks per iteration and four million for everything else, which take 0.18 us
+// each: 0.2 ms for an iteration of about 2 us, and 0.8 s.  (Looks are counted, not time: a wave that is taken off the device does not run out of them.)
+constexpr int64_t kPolls = 1 << 22;
+__device__ __forceinline__ bool await_parts(uint32_t* cnt, int n, int iterations) {
+  bool all = false;
+  for (int64_t left = kPolls + (int64_t)1024 * iterations; left > 0 && !all; --left) {
+    all = (__hip_atomic_load(cnt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >> 16) == (uint32_t)n - 1;
+    if (!all) __builtin_amdgcn_s_sleep(2);
+  }
   __hip_atomic_store(cnt, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  return all;
 }
 
 // 16 bytes per lane with device scope, as buffer accesses (the compiler counts them like any
