@@ -43,7 +43,8 @@ int steps_per_launch(const loong_step_desc* descs, int n_steps) {
   const double flops = 14. * d.head_dim * pairs * d.n_q_heads * d.batch;
   const double per_launch = 9.4e9 * d.head_dim;
   const int launches = (int)std::max(std::min(std::ceil(flops / per_launch), (double)n_steps), std::ceil(n_steps / (double)kMaxSteps));
-  return (n_steps + launches - 1) / launches;
+  const int per = (n_steps + launches - 1) / launches;
+  return d.dtype == LOONG_FP32 ? per : (int)std::min<int64_t>(per, bwd_steps_that_fit_bf16(d, g));  // (every step has as many keys)
 }
 
 }  // namespace
@@ -122,7 +123,8 @@ int loong_attn_steps_bwd(const loong_step_desc* descs, int32_t n_steps, const vo
         return fail(LOONG_E_SHAPE, "loong_attn_steps_bwd: steps %d and %d have the same dk or dv", u, t);
   if (workspace_bytes < 0) return fail(LOONG_E_SHAPE, "loong_attn_step_bwd: negative workspace size");
   if (desc->batch == 0) return LOONG_OK;
-  void* head = nullptr;             // counters to clear, once for all launches of the run: each leaves them zero
+  // (the counters are cleared once for all launches of the run: each leaves them zero)
+  BwdPrologue before{want_delta ? o : nullptr, d_o, delta, nullptr};
   if (desc->dtype != LOONG_FP32) {  // scratch for shared query loops: checked before anything is enqueued
     int64_t need = 0;
     if (int rc = loong_workspace_bytes_steps(descs, n_steps, &need)) return rc;
@@ -134,14 +136,11 @@ int loong_attn_steps_bwd(const loong_step_desc* descs, int32_t n_steps, const vo
       if (workspace_bytes < need)
         return fail(LOONG_E_SHAPE, "loong_attn_step_bwd: workspace of %lld bytes, this step needs %lld (loong_workspace_bytes)",
                     (long long)workspace_bytes, (long long)need);
-      if (!(desc->flags & LOONG_WORKSPACE_CLEAN)) head = workspace;
+      if (!(desc->flags & LOONG_WORKSPACE_CLEAN)) before.head = workspace;
     }
   }
-  if (want_delta) {
-    if (int rc = launch_delta(*desc, o, d_o, delta, head, stream)) return rc;
-  } else if (head) {
-    if (int rc = launch_clear_head(head, stream)) return rc;
-  }
+  if (desc->dtype == LOONG_FP32)
+    if (int rc = launch_prologue(*desc, before, stream)) return rc;
   const int per_launch = steps_per_launch(descs, n_steps);
   for (int t0 = 0; t0 < n_steps; t0 += per_launch) {
     const int n = std::min(n_steps - t0, per_launch);
@@ -152,7 +151,7 @@ int loong_attn_steps_bwd(const loong_step_desc* descs, int32_t n_steps, const vo
     float *const *dk_t = only_dq ? nullptr : dk + t0, *const *dv_t = only_dq ? nullptr : dv + t0;
     if (int rc = desc->dtype == LOONG_FP32
                      ? launch_bwd_f32(d, g, n, q, k + t0, v + t0, d_o, lse, delta, dq, dk_t, dv_t, stream)
-                     : launch_bwd_bf16(d, g, n, q, k + t0, v + t0, d_o, lse, delta, dq, dk_t, dv_t, workspace, workspace_bytes, stream))
+                     : launch_bwd_bf16(d, g, n, t0 ? nullptr : &before, q, k + t0, v + t0, d_o, lse, delta, dq, dk_t, dv_t, workspace, workspace_bytes, stream))
       return rc;
   }
   return LOONG_OK;

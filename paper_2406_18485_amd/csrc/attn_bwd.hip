@@ -155,10 +155,14 @@ struct StepLaunch {
   DqParams q;
   StepGeom rows;   // the q segments, and which of them see keys in any step
   bool do_kv, do_q;
+  bool clear;      // nobody sees any key: dk and dv of all steps are cleared
 };
 
-// Key-owning half: work list, workspace and what is enqueued before it.
-int plan_dkv(StepLaunch& s, const SplitPlan& plan, int n, int flags, int D, void* workspace, int64_t workspace_bytes, hipStream_t st) {
+// Workgroups that a launch has room for.
+constexpr int64_t kMaxGrid = (kLaunchThreads - 1) / (kBwdWaves * 64);
+
+// Key-owning half: work list and workspace.
+int plan_dkv(StepLaunch& s, const SplitPlan& plan, int flags, int D, void* workspace, int64_t workspace_bytes) {
   DkvParams& p = s.kv;
   s.do_kv = false;
   // Only key tiles that some query can see are listed (eight equal ranges of the list, one
@@ -167,16 +171,13 @@ int plan_dkv(StepLaunch& s, const SplitPlan& plan, int n, int flags, int D, void
   p.nsplit = plan.nsplit;
   p.accumulate = (flags & LOONG_ACCUM_DKV) ? 1 : 0;
   const int64_t total = plan.busy * plan.nsplit;
-  if (total > 0x3ffffff0) return fail(LOONG_E_UNSUPPORTED, "backward grid too large");
+  if (total > kMaxGrid) return fail(LOONG_E_UNSUPPORTED, "backward grid too large");
   if (total == 0) {
-    if (p.accumulate) return LOONG_OK;
-    const int64_t n4 = (int64_t)p.B * p.Hkv * p.kv_len * D / 4;
-    for (int t = 0; t < n; ++t)
-      zero_kernel<<<dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, st>>>(n4, reinterpret_cast<float4*>(s.tab.dk[t]),
-                                                                            reinterpret_cast<float4*>(s.tab.dv[t]));
-    return check_launch("loong_attn_step_bwd (clear dk/dv)");
+    s.clear = !p.accumulate;
+    return LOONG_OK;
   }
   p.map = make_work_map((int64_t)p.Hkv * p.B, (int64_t)p.kt_total * plan.nsplit);
+  if (p.map.grid > kMaxGrid) return fail(LOONG_E_UNSUPPORTED, "backward grid too large");
   if (plan.nsplit > 1) {  // (size and alignment were checked by the entry point, against the same plan)
     if (!workspace || workspace_bytes < kWsHeadBytes + (int64_t)partial_bytes(plan, D))
       return fail(LOONG_E_SHAPE, "loong_attn_step_bwd: workspace too small");
@@ -187,19 +188,24 @@ int plan_dkv(StepLaunch& s, const SplitPlan& plan, int n, int flags, int D, void
   return LOONG_OK;
 }
 
+// Row-owning half with `ks` key splits: work list.
+int plan_dq(StepLaunch& s, int ks) {
+  DqParams& p = s.q;
+  const RowTiling rt = make_row_tiling(s.rows, p.G, p.Hq, p.B, kRowWaves / ks, /*list_blind=*/p.overwrite);
+  p.GS = rt.GS; p.ntile[0] = rt.ntile[0]; p.ntile[1] = rt.ntile[1];
+  p.tiles_total = rt.tiles_total; p.hgroups = rt.hgroups;
+  s.do_q = rt.total_wg > 0;
+  if (!s.do_q) return LOONG_OK;
+  if (rt.total_wg > kMaxGrid) return fail(LOONG_E_UNSUPPORTED, "backward (dQ) grid too large");
+  p.map = make_work_map((int64_t)p.B * rt.hgroups, rt.tiles_total);
+  if (p.map.grid > kMaxGrid) return fail(LOONG_E_UNSUPPORTED, "backward (dQ) grid too large");
+  return LOONG_OK;
+}
+
 template <class E, int D, int KS>
 int launch_cfg(StepLaunch& s, hipStream_t st) {
-  if (s.do_q) {
-    DqParams& p = s.q;
-    const RowTiling rt = make_row_tiling(s.rows, p.G, p.Hq, p.B, kRowWaves / KS, /*list_blind=*/p.overwrite);
-    p.GS = rt.GS; p.ntile[0] = rt.ntile[0]; p.ntile[1] = rt.ntile[1];
-    p.tiles_total = rt.tiles_total; p.hgroups = rt.hgroups;
-    if (rt.total_wg > 0x3ffffff0) return fail(LOONG_E_UNSUPPORTED, "backward (dQ) grid too large");
-    p.map = make_work_map((int64_t)p.B * rt.hgroups, rt.tiles_total);
-    s.do_q = rt.total_wg > 0;
-  }
   const dim3 block(kBwdWaves * 64);
-  if (s.do_kv && s.do_q && (int64_t)s.kv.map.grid + s.q.map.grid < 0x40000000) {
+  if (s.do_kv && s.do_q && (int64_t)s.kv.map.grid + s.q.map.grid <= kMaxGrid) {
     s.q.first_grid = s.q.rows_first ? s.q.map.grid : s.kv.map.grid;
     bwd_step_kernel<E, D, KS><<<dim3(s.kv.map.grid + s.q.map.grid), block, 0, st>>>(s.tab, s.kv, s.q);
   } else {
@@ -223,7 +229,7 @@ int pick_cfg(StepLaunch& s, int head_dim, int ks, hipStream_t st) {
 
 }  // namespace
 
-int launch_bwd_bf16(const loong_step_desc& d, const StepGeom* g, int n, const void* q, const void* const* k,
+int launch_bwd_bf16(const loong_step_desc& d, const StepGeom* g, int n, const BwdPrologue* before, const void* q, const void* const* k,
                     const void* const* v, const void* d_o, const float* lse, const float* delta, float* dq,
                     float* const* dk, float* const* dv, void* workspace, int64_t workspace_bytes, void* stream) {
   hipStream_t st = static_cast<hipStream_t>(stream);
@@ -251,7 +257,7 @@ int launch_bwd_bf16(const loong_step_desc& d, const StepGeom* g, int n, const vo
     for (int i = 0; i < 3; ++i) { p.qs[i] = d.q_stride[i]; p.ks[i] = d.kv_stride[i]; }
     p.nq = g[0].nq; p.qseg[0] = g[0].q[0]; p.qseg[1] = g[0].q[1];
     p.scale = d.softmax_scale; p.c = d.softmax_scale * kLog2e;
-    if (int rc = plan_dkv(s, plan, n, d.flags, d.head_dim, workspace, workspace_bytes, st)) return rc;
+    if (int rc = plan_dkv(s, plan, d.flags, d.head_dim, workspace, workspace_bytes)) return rc;
   }
   if (s.do_q) {
     DqParams& p = s.q;
@@ -264,7 +270,6 @@ int launch_bwd_bf16(const loong_step_desc& d, const StepGeom* g, int n, const vo
     p.overwrite = (d.flags & LOONG_OVERWRITE_DQ) ? 1 : 0;
     p.rows_first = n > 1;
   }
-  if (!s.do_kv && !s.do_q) return LOONG_OK;
   int ks = forced_key_splits(d.flags);
   if (!ks && n > 1) {
     // several steps: the tallest row tiles whose loop still fits beside the other work of a unit
@@ -272,8 +277,26 @@ int launch_bwd_bf16(const loong_step_desc& d, const StepGeom* g, int n, const vo
     if (!s.do_kv) ks = 0;
   }
   if (!ks) ks = pick_key_splits(s.rows, G, d.n_q_heads, d.batch, 0, dev.cus);
+  if (s.do_q)
+    if (int rc = plan_dq(s, ks)) return rc;
+  // ---- the launch fits: from here on work is enqueued
+  if (before)
+    if (int rc = launch_prologue(d, *before, stream)) return rc;
+  if (s.clear) {
+    const int64_t n4 = (int64_t)d.batch * d.n_kv_heads * d.kv_len * d.head_dim / 4;
+    for (int t = 0; t < n; ++t)
+      zero_kernel<<<dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, st>>>(n4, reinterpret_cast<float4*>(dk[t]), reinterpret_cast<float4*>(dv[t]));
+    if (int rc = check_launch("loong_attn_step_bwd (clear dk/dv)")) return rc;
+  }
+  if (!s.do_kv && !s.do_q) return LOONG_OK;
   if (d.dtype == LOONG_FP16) return pick_cfg<Fp16>(s, d.head_dim, ks, st);
   return pick_cfg<Bf16>(s, d.head_dim, ks, st);
+}
+
+// (all its keys counted as seen, and as many workgroups as make_work_map may add)
+int64_t bwd_steps_that_fit_bf16(const loong_step_desc& d, const StepGeom& g) {
+  const int64_t per_step = (int64_t)g.nk * ((g.k[0].len + kBwdBN - 1) / kBwdBN) * d.n_kv_heads * d.batch;
+  return std::max<int64_t>((kMaxGrid - 8) / std::max<int64_t>(per_step, 1), 1);
 }
 
 int64_t bwd_workspace_bytes_bf16(const loong_step_desc& d, const StepGeom* g, int n) {

@@ -166,6 +166,11 @@ int launch_delta(const loong_step_desc& d, const void* o, const void* d_o, float
   return check_launch("loong_bwd_delta");
 }
 
+int launch_prologue(const loong_step_desc& d, const BwdPrologue& p, void* stream) {
+  if (p.o) return launch_delta(d, p.o, p.d_o, p.delta, p.head, stream);
+  return p.head ? launch_clear_head(p.head, stream) : LOONG_OK;
+}
+
 }  // namespace loong
 
 using namespace loong;

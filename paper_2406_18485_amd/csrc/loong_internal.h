@@ -41,6 +41,9 @@ inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 
 // Map a hipError_t (as int) of the last launch to the ABI status.
 int check_launch(const char* what);
 
+// A launch takes fewer threads than this (the runtime refuses it otherwise).
+constexpr int64_t kLaunchThreads = (int64_t)1 << 32;
+
 // Facts of the current device, looked up once per device (device.hip).  device_facts fails with
 // LOONG_E_HIP when there is no device and LOONG_E_UNSUPPORTED when it is not a gfx950 part.
 struct DeviceFacts {
@@ -79,9 +82,20 @@ int launch_fwd_bf16(const loong_step_desc& d, const StepGeom& g, const void* q, 
 int launch_bwd_f32(const loong_step_desc& d, const StepGeom* g, int n, const void* q, const void* const* k,
                    const void* const* v, const void* d_o, const float* lse, const float* delta, float* dq,
                    float* const* dk, float* const* dv, void* stream);
-int launch_bwd_bf16(const loong_step_desc& d, const StepGeom* g, int n, const void* q, const void* const* k,
+// What a backward call enqueues before its first launch: delta from `o`, unless that is NULL, and the counters at
+// `head` cleared, unless that is NULL.
+struct BwdPrologue {
+  const void *o, *d_o;
+  float* delta;
+  void* head;
+};
+int launch_prologue(const loong_step_desc& d, const BwdPrologue& p, void* stream);
+// (`before`: enqueued first, once the launch is known to fit; or NULL)
+int launch_bwd_bf16(const loong_step_desc& d, const StepGeom* g, int n, const BwdPrologue* before, const void* q, const void* const* k,
                     const void* const* v, const void* d_o, const float* lse, const float* delta, float* dq,
                     float* const* dk, float* const* dv, void* workspace, int64_t workspace_bytes, void* stream);
+// steps of a run that one launch has room for
+int64_t bwd_steps_that_fit_bf16(const loong_step_desc& d, const StepGeom& g);
 int64_t bwd_workspace_bytes_bf16(const loong_step_desc& d, const StepGeom* g, int n);
 // delta of every row, and with `head` the counters of a workspace cleared; these alone
 int launch_delta(const loong_step_desc& d, const void* o, const void* d_o, float* delta, void* head, void* stream);

@@ -44,7 +44,8 @@ __device__ __forceinline__ void publish_part(uint32_t* cnt) {
 // One thread of the gatherer: wait for the other n - 1 parts and put the counter back to zero; false if they did not
 // come.  The others started before this workgroup drew its ticket and have as many iterations of their loop left at most as it
 // has done, so the wait is limited by that: 1024 looks per iteration and four million for everything else, which take 0.18 us
-// each: 0.2 ms for an iteration of about 2 us, and 0.8 s.  (Looks are counted, not time: a wave that is taken off the device does not run out of them.)
+// each: 0.2 ms for an iteration of about 2 us, and 0.8 s.  (Looks are counted, not time: a wave that is taken off the device does not
+// run out of them.)
 constexpr int64_t kPolls = 1 << 22;
 __device__ __forceinline__ bool await_parts(uint32_t* cnt, int n, int iterations) {
   bool all = false;

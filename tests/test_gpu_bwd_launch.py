@@ -84,3 +84,44 @@ def test_a_wait_for_parts_that_do_not_come_ends_in_nan(word):
     assert torch.equal(got[0], want[0]) and torch.isnan(got[1]).all() and torch.isnan(got[2]).all()
     again = _run(t, desc(0), torch.zeros(t["q"].shape, device=DEV), ws)
     assert all(torch.equal(a, b) for a, b in zip(again, want))
+
+
+def _many(n, batch, d=64):
+    """One query and one key per batch element, n steps that share them: a workgroup each in either half."""
+    g = torch.Generator(device=DEV).manual_seed(n)
+    mk = lambda: torch.randn(batch, 1, 1, d, device=DEV, generator=g, dtype=torch.bfloat16) * 0.5
+    q, k, v, d_o = mk(), mk(), mk(), mk()
+    lse, delta = torch.zeros(batch, 1, 1, device=DEV), torch.zeros(batch, 1, 1, device=DEV)
+    f32 = dict(dtype=torch.float32, device=DEV)
+    dq, dk, dv = torch.full((batch, 1, 1, d), 5.0, **f32), torch.empty(n, batch, 1, 1, d, **f32), torch.empty(n, batch, 1, 1, d, **f32)
+    descs = (P.StepDesc * n)(*(P.make_desc(batch=batch, n_q_heads=1, n_kv_heads=1, head_dim=d, q_len=1, kv_len=1, dtype=P.BF16,
+                                           softmax_scale=0.125, flags=P.OVERWRITE_DQ) for _ in range(n)))
+    return descs, q, k, v, d_o, lse, delta, dq, dk, dv
+
+
+@pytest.mark.parametrize("n,batch", [(1, 1 << 22), (32, 1 << 18)])
+def test_more_workgroups_than_one_launch_takes(n, batch):
+    """A launch takes fewer than 2^32 threads, 2^23 workgroups of 512: the two halves of the first case have that many together,
+    the key tiles of the second's 32 steps alone.  With one key P = exp(scale q.k - lse), dS = P (dO.v - delta)."""
+    descs, q, k, v, d_o, lse, delta, dq, dk, dv = _many(n, batch)
+    ws = torch.empty(max(P.workspace_bytes_steps(descs), 16), dtype=torch.uint8, device=DEV)
+    P.attn_steps_bwd(descs, q, [k] * n, [v] * n, None, d_o, lse, delta, dq, dk, dv, ws)
+    torch.cuda.synchronize()
+    for part in (slice(0, 1 << 16), slice(batch // 2, batch // 2 + (1 << 16)), slice(batch - (1 << 16), batch)):
+        qf, kf, vf, of = (t[part].float() for t in (q, k, v, d_o))
+        p = torch.exp((qf * kf).sum(-1, keepdim=True) * 0.125)
+        ds = p * (of * vf).sum(-1, keepdim=True) * 0.125
+        for t in {0, n - 1}:
+            # P, dS and the scaled operand of the exponent are rounded to 8 bits: 2^-9 each, products of size one
+            assert float((dv[t, part] - p * of).abs().max()) < 2e-2 and float((dk[t, part] - ds * qf).abs().max()) < 2e-2
+        assert float((dq[part] - n * ds * kf).abs().max()) < n * 2e-2
+
+
+def test_a_step_too_large_for_a_launch_is_refused_before_anything_runs():
+    (desc,), q, k, v, d_o, lse, delta, dq, dk, dv = _many(1, 1 << 23)
+    desc.flags |= P.COMPUTE_DELTA
+    delta.fill_(3.0)
+    with pytest.raises(P.LoongError) as e:
+        P.attn_step_bwd(desc, q, k, v, q, d_o, lse, delta, dq, dk[0], dv[0])
+    torch.cuda.synchronize()
+    assert e.value.code == P.E_UNSUPPORTED and bool((delta == 3.0).all()) and bool((dq == 5.0).all())
