@@ -88,14 +88,17 @@ int loong_permute_rows(const int64_t n[3], const int64_t in_stride[3], const int
   if (blocks > 0x7fffffff) return fail(LOONG_E_UNSUPPORTED, "loong_permute_rows: more than 2^31-1 workgroups");
   // by chunks while a row fits a workgroup, c gives every (a, b) several and few threads are left without a piece;
   // but not rows that are dense on both sides and too many for the memory-side cache: each (a, b) is then one stream
-  // already, and 32 of them at once cost more than one (4096 tokens unpacked 12.5 -> 10.8 us, 16000 tokens 45.3 -> 49.6)
+  // already, and 32 of them at once cost more than one (4096 tokens unpacked 12.5 -> 10.8 us, 16000 tokens 45.3 -> 49.6);
+  // nor where the threads left without a piece take the launch past its limit
   const bool streams = p.is2 == row_bytes && p.os2 == row_bytes && !(p.is1 == 0 && n[1] > 1) && p.total > ((int64_t)4 << 20);
   const int64_t rows = p.pieces <= 256 ? 256 / p.pieces : 0;
   const int64_t chunks = rows ? (p.n2 + rows - 1) / rows : 0, ab = n[0] * n[1];
-  if (!streams && chunks >= 8 && rows * p.pieces >= 224 && p.n2 < ((int64_t)1 << 30) && ab < ((int64_t)1 << 30) && chunks * ab <= 0x7fffffff) {
+  const bool once = p.is1 == 0 && n[1] > 1 && chunks * n[0] >= 1024;  // (where what is read still gives every unit workgroups)
+  if (!streams && chunks >= 8 && rows * p.pieces >= 224 && p.n2 < ((int64_t)1 << 30) && ab < ((int64_t)1 << 30) &&
+      chunks * (once ? n[0] : ab) < kLaunchThreads / 256) {
     ChunkParams c{(uint32_t)rows, (uint32_t)ab, (uint32_t)n[1], (uint32_t)n[2], (uint32_t)p.pieces,
                   p.is0, p.is1, p.is2, p.os0, p.os1, p.os2, 1};
-    if (p.is1 == 0 && n[1] > 1 && chunks * n[0] >= 1024) {  // (where what is read still gives every unit workgroups)
+    if (once) {
       c.copies = (uint32_t)n[1]; c.n1 = 1; c.ab = (uint32_t)n[0];
     }
     permute_chunks_kernel<<<dim3((unsigned)(chunks * c.ab)), dim3(256), 0, static_cast<hipStream_t>(stream)>>>(

@@ -90,3 +90,14 @@ def test_permuted_rows_of_every_form(n, row_bytes, kind):
     dst = torch.full((a, b, c, out_row), 7, dtype=torch.uint8, device="cuda:0")
     P.permute_rows(n, ins, (b * c * out_row, c * out_row, out_row), row_bytes, src, dst)
     assert torch.equal(dst[..., :row_bytes], row) and bool((dst[..., row_bytes:] == 7).all())
+
+
+def test_rows_whose_chunks_exceed_one_launch():
+    """2^24 rows of 225 pieces: dealt out as chunks, a row to a workgroup of 256 threads, they would be the 2^32 threads that a
+    launch does not take; piece by piece they are fewer.  The rows of one column are read again and again, 60 GB are written."""
+    b, c, row_bytes = 4096, 4096, 3600
+    src = torch.randint(0, 255, (b, row_bytes), dtype=torch.uint8, device=DEV)
+    dst = torch.empty(b, c, row_bytes, dtype=torch.uint8, device=DEV)
+    dst[:, ::511] = 0
+    P.permute_rows((1, b, c), (0, row_bytes, 0), (0, c * row_bytes, row_bytes), row_bytes, src, dst)
+    assert torch.equal(dst[:, ::511], src[:, None].expand(-1, 9, -1))
