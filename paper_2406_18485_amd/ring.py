@@ -8,7 +8,7 @@ for device memory and the stream only.
 """
 from __future__ import annotations
 
-from dataclasses import dataclass
+from dataclasses import dataclass, replace
 
 import torch
 
@@ -81,22 +81,38 @@ class RingReplay:
         self.dv = torch.empty(s.cp, s.batch, s.hkv, s.L, s.d, **f32)
         self.block_out = None
         self.block_lse = None
+        self.workspace = None
+        self._prepare()
+
+    # ---- what the calls take of the shape and the plan, kept between them
+    def _prepare(self):
+        s = self.shape
+        self._prepared = replace(s), [dict(step) for step in self.plan]
         self._order = [step["src_rank"] for step in self.plan]
-        self._fwd_descs = (B.StepDesc * s.cp)(*(_desc(s, step, 0) for step in self.plan))
+        descs = B.StepDesc * len(self.plan)
+        self._fwd_descs = descs(*(_desc(s, step, 0) for step in self.plan))
         # the backward steps of a pass: the first forms delta and writes dq, and all are one run
-        self._bwd_descs = (B.StepDesc * s.cp).from_buffer_copy(self._fwd_descs)
+        self._bwd_descs = descs.from_buffer_copy(self._fwd_descs)
         for desc in self._bwd_descs:
             desc.flags |= B.COMPUTE_DELTA | B.OVERWRITE_DQ
         # caller-owned scratch of the backward steps: the largest any micro-step, or all in one run, ask for
-        need = max(B.workspace_bytes_steps(self._bwd_descs), *(B.workspace_bytes(desc) for desc in self._fwd_descs))
+        need = max(B.workspace_bytes_steps(self._bwd_descs), *(B.workspace_bytes(desc) for desc in self._fwd_descs), 16)
+        if self.workspace is not None and self.workspace.numel() >= need:
+            return
         # (every call clears the counters on its own stream, which may be another than this one; zero from the start, a
         # program that has waited for that may also lend the workspace to steps with WORKSPACE_CLEAN)
-        self.workspace = torch.empty(max(need, 16), dtype=torch.uint8, device=self.dev)
+        self.workspace = torch.empty(need, dtype=torch.uint8, device=self.dev)
         self.workspace[:B.WORKSPACE_HEAD].zero_()
+
+    def _follow(self):
+        """The program may have changed `shape` (its scale, its extra flags) or `plan` since the last call."""
+        if (self.shape, self.plan) != self._prepared:
+            self._prepare()
 
     # ---- forward: cp x (Attention [+ Update]) then the cast to the stored activation type
     def forward(self, q, k_by_src, v_by_src, fuse_merge=True, stream=None):
         s = self.shape
+        self._follow()
         if fuse_merge:
             # the first visit writes the running result (rows that see nothing get the neutral
             # element), the later ones merge into it (no separate initialisation), the last stores o too
@@ -114,6 +130,7 @@ class RingReplay:
 
     # ---- backward from the stored O and LSE: delta once, then the cp steps, whose chunks are all here, as one run
     def backward(self, q, k_by_src, v_by_src, d_o, stream=None):
+        self._follow()
         k, v, dk, dv = (_visited(x, self._order) for x in (k_by_src, v_by_src, self.dk, self.dv))
         B.attn_steps_bwd(self._bwd_descs, q, k, v, self.o, d_o, self.lse, self.delta, self.dq, dk, dv, self.workspace,
                          stream=stream)

@@ -105,3 +105,37 @@ def test_no_backward_vouches_for_counters_cleared_on_another_stream(replay):
     replay.look = lambda name, args: seen.extend(args[0][t].flags for t in range(CP))
     replay.backward(q, full, full, q)
     assert len(seen) == CP and not any(flags & P.WORKSPACE_CLEAN for flags in seen)
+
+
+@pytest.mark.parametrize("fused", [True, False])
+def test_changes_of_shape_and_plan_reach_the_next_call(replay, fused):
+    """`shape` and `plan` are public and plain: a scale, extra flags or an order of visits set after construction count."""
+    q, full = _inputs(CP)
+    seen = []
+
+    def look(name, args):
+        if name == "loong_attn_step_fwd":   # one descriptor by reference, one K pointer
+            seen.append((args[0]._obj.softmax_scale, args[0]._obj.flags, args[2]))
+        elif name in ("loong_attn_steps_fwd", "loong_attn_steps_bwd"):
+            seen.extend((args[0][t].softmax_scale, args[0][t].flags, args[3][t]) for t in range(args[1]))
+    replay.look = look
+
+    def passes():
+        seen.clear()
+        replay.forward(q, full, full, fuse_merge=fused)
+        replay.backward(q, full, full, q)
+        return list(seen)
+
+    first = passes()
+    assert len(first) == 2 * CP and {scale for scale, _, _ in first} == {0.125}
+    replay.shape.scale = 0.25
+    replay.shape.extra_flags = P.key_splits(2)
+    assert passes() == [(0.25, flags | P.key_splits(2), k) for _, flags, k in first]
+    replay.plan.reverse()
+    half = replay.plan[:2]
+    assert [k for _, _, k in passes()] == [k for _, _, k in first[CP - 1::-1] + first[:CP - 1:-1]]
+    replay.plan = half
+    assert [k for _, _, k in passes()] == [first[CP - 1][2], first[CP - 2][2]] * 2
+    made = replay._fwd_descs
+    passes()
+    assert replay._fwd_descs is made   # nothing changed, nothing made again
