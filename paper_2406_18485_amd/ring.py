@@ -81,7 +81,7 @@ class RingReplay:
         self.dv = torch.empty(s.cp, s.batch, s.hkv, s.L, s.d, **f32)
         self.block_out = None
         self.block_lse = None
-        self.workspace = None
+        self.workspace, self._workspaces = None, []   # (one that was outgrown may be in use on some stream: it is kept)
         self._prepare()
 
     # ---- what the calls take of the shape and the plan, kept between them
@@ -96,13 +96,14 @@ class RingReplay:
         for desc in self._bwd_descs:
             desc.flags |= B.COMPUTE_DELTA | B.OVERWRITE_DQ
         # caller-owned scratch of the backward steps: the largest any micro-step, or all in one run, ask for
-        need = max(B.workspace_bytes_steps(self._bwd_descs), *(B.workspace_bytes(desc) for desc in self._fwd_descs), 16)
+        need = max(B.workspace_bytes_steps(self._bwd_descs), *(B.workspace_bytes(desc) for desc in self._fwd_descs))
         if self.workspace is not None and self.workspace.numel() >= need:
             return
-        # (every call clears the counters on its own stream, which may be another than this one; zero from the start, a
-        # program that has waited for that may also lend the workspace to steps with WORKSPACE_CLEAN)
-        self.workspace = torch.empty(need, dtype=torch.uint8, device=self.dev)
-        self.workspace[:B.WORKSPACE_HEAD].zero_()
+        # (nothing is cleared here: every call clears its counters on its own stream, and a clearing on this one could come
+        # while a call on another counts.  Where no step needs any: 16 bytes that none of them touches.)
+        self._workspaces.append(torch.empty(need, dtype=torch.uint8, device=self.dev) if need else
+                                torch.zeros(16, dtype=torch.uint8, device=self.dev))
+        self.workspace = self._workspaces[-1]
 
     def _follow(self):
         """The program may have changed `shape` (its scale, its extra flags) or `plan` since the last call."""

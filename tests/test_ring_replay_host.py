@@ -139,3 +139,20 @@ def test_changes_of_shape_and_plan_reach_the_next_call(replay, fused):
     made = replay._fwd_descs
     passes()
     assert replay._fwd_descs is made   # nothing changed, nothing made again
+
+
+def test_construction_clears_no_memory_that_calls_count_in(monkeypatch):
+    """It would be cleared on the stream of the construction, at a time that calls on other streams know nothing of."""
+    junk = lambda *size, **kw: torch.full(size, 0xA5 if kw["dtype"] == torch.uint8 else 7, **kw)
+    monkeypatch.setattr(torch, "empty", junk)
+    shape = RingShape(cp=CP, w=2, rank=1, hq=4, hkv=1, d=128, c=200, dtype=P.BF16, scale=0.125)
+    rep = RingReplay(shape, "cpu")
+    assert rep.workspace.numel() > B.WORKSPACE_HEAD and bool((rep.workspace == 0xA5).all())
+    # a plan that asks for more: the first workspace, which another stream may be using, is kept beside the new one
+    plan, rep.plan = rep.plan, rep.plan[:1]
+    rep.workspace, rep._workspaces = None, []
+    rep._follow()
+    first, small = weakref.ref(rep.workspace), rep.workspace.numel()
+    rep.plan = plan
+    rep._follow()
+    assert rep.workspace.numel() > small and first() is not None
