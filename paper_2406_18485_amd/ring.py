@@ -132,6 +132,8 @@ class RingReplay:
     # ---- backward from the stored O and LSE: delta once, then the cp steps, whose chunks are all here, as one run
     def backward(self, q, k_by_src, v_by_src, d_o, stream=None):
         self._follow()
+        if self.shape.extra_flags & B.BWD_ONLY_DKV:   # (the steps leave dq alone)
+            self.dq.zero_()
         k, v, dk, dv = (_visited(x, self._order) for x in (k_by_src, v_by_src, self.dk, self.dv))
         B.attn_steps_bwd(self._bwd_descs, q, k, v, self.o, d_o, self.lse, self.delta, self.dq, dk, dv, self.workspace,
                          stream=stream)

@@ -156,3 +156,14 @@ def test_construction_clears_no_memory_that_calls_count_in(monkeypatch):
     rep.plan = plan
     rep._follow()
     assert rep.workspace.numel() > small and first() is not None
+
+
+def test_dq_is_zero_when_the_steps_leave_it_alone(replay):
+    """Extra flags that ask for dK and dV only: dq is what no step has added to, not what the memory held."""
+    q, full = _inputs(CP)
+    replay.dq.fill_(7.0)
+    replay.backward(q, full, full, q)
+    assert bool((replay.dq == 7.0).all())    # the steps write it (here they are not the library's)
+    replay.shape.extra_flags = P.BWD_ONLY_DKV
+    replay.backward(q, full, full, q)
+    assert bool((replay.dq == 0.0).all())
