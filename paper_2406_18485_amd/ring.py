@@ -91,6 +91,10 @@ class RingReplay:
         self._order = [step["src_rank"] for step in self.plan]
         descs = B.StepDesc * len(self.plan)
         self._fwd_descs = descs(*(_desc(s, step, 0) for step in self.plan))
+        # the same where every step is a call: the first writes the running result, the others merge into it
+        self._merge_descs = descs.from_buffer_copy(self._fwd_descs)
+        for desc in self._merge_descs[1:]:
+            desc.flags |= B.FUSE_MERGE
         # the backward steps of a pass: the first forms delta and writes dq, and all are one run
         self._bwd_descs = descs.from_buffer_copy(self._fwd_descs)
         for desc in self._bwd_descs:
@@ -152,33 +156,40 @@ class RingReplay:
             self._kv_bufs = [(torch.empty(shp, dtype=self.store_dtype, device=self.dev),
                               torch.empty(shp, dtype=self.store_dtype, device=self.dev)) for _ in range(3)]
             self._comm = (torch.cuda.Stream(self.dev), torch.cuda.Stream(self.dev))   # inner ring, outer ring
-        bufs, (inner, outer) = self._kv_bufs, self._comm
-        filled = [torch.cuda.Event() for _ in range(3)]
-        released = [torch.cuda.Event() for _ in range(3)]
+            self._events = [torch.cuda.Event() for _ in range(3)], [torch.cuda.Event() for _ in range(3)]
+        self._follow()
+        bufs, (inner, outer), (filled, released) = self._kv_bufs, self._comm, self._events
 
+        # (this path is bound by the host where chunks are short, and a stream context costs 8 us: more than the step's launch)
         def receive(stream, b, src):
             stream.wait_event(released[b])          # the buffer's last reader has finished
-            with torch.cuda.stream(stream):
+            torch.cuda.set_stream(stream)
+            try:
                 bufs[b][0].copy_(k_by_src[src], non_blocking=True)
                 bufs[b][1].copy_(v_by_src[src], non_blocking=True)
-                filled[b].record(stream)
+            finally:
+                torch.cuda.set_stream(main)
+            filled[b].record(stream)
 
         for ev in released:
             ev.record(main)
         cur, nxt, out = 0, 1, 2
         receive(inner, cur, self.plan[0]["src_rank"])   # the own chunk
         n_outer = s.cp // s.w
-        for t, step in enumerate(self.plan):
+        for t in range(len(self.plan)):
             a, b = divmod(t, s.w)
             if b == 0 and a + 1 < n_outer:
                 receive(outer, out, self.plan[(a + 1) * s.w]["src_rank"])
             if b + 1 < s.w:
                 receive(inner, nxt, self.plan[t + 1]["src_rank"])
             main.wait_event(filled[cur])
-            B.attn_step_fwd(_desc(s, step, B.FUSE_MERGE if t else 0), q, bufs[cur][0], bufs[cur][1], self.out, self.lse)
+            if t + 1 < len(self.plan):
+                B.attn_step_fwd(self._merge_descs[t], q, bufs[cur][0], bufs[cur][1], self.out, self.lse)
+            else:   # the last one stores o too
+                last = (B.StepDesc * 1)(self._merge_descs[t])
+                B.attn_steps_fwd(last, q, bufs[cur][:1], bufs[cur][1:], self.out, self.lse, self.o)
             released[cur].record(main)
             if b + 1 < s.w:
                 cur, nxt = nxt, cur
             else:
                 cur, out = out, cur
-        B.finalize_out(self.rows, s.d, self.out, self.o, s.dtype)
