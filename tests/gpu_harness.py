@@ -30,6 +30,13 @@ def workspace_for(desc) -> torch.Tensor:
     return torch.empty(max(P.workspace_bytes(desc), 16), dtype=torch.uint8, device=DEV)
 
 
+def token_major(x, gap):
+    """[batch, head, token, d] as a view of [batch, token, head, d + gap] memory, with its strides; what is in the gaps is NaN."""
+    b, h, n, d = x.shape
+    y = torch.full((b, n, h, d + gap), float("nan"), dtype=x.dtype, device=x.device)[..., :d].permute(0, 2, 1, 3)
+    return y.copy_(x), y.stride()[:3]
+
+
 def shape_of(cfg: RingConfig, extra_flags: int = 0) -> RingShape:
     return RingShape(cp=cfg.cp, w=cfg.w, rank=cfg.rank, hq=cfg.hq, hkv=cfg.hkv, d=cfg.d, c=cfg.c,
                      dtype={"bf16": P.BF16, "fp16": P.FP16, "fp32": P.FP32}[cfg.dtype], scale=cfg.scale,

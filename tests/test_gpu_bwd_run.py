@@ -3,24 +3,25 @@ loop crosses chunk ends of every remainder, key halves nobody sees, shared query
 launch takes, dq and dk/dv added to, no mask, each forced key split.
 
 Both compute the same sums of the same products (probabilities rounded to 16 bits alike); only the order of
-fp32 additions differs (dq over steps in registers, dk/dv in other splits).  n additions in another order differ by
-at most n * 2^-24 of the sum of magnitudes; with at most 2^13 terms of like size that is 5e-4 of a typical sum, and
-the result is compared to 1e-4 of its largest element."""
+fp32 additions differs (dq over steps in registers, dk/dv in other splits).  An element is a chain of one addition per 16
+products (4 in fp32 storage, dealt over four or eight waves): at most 640 here (8 steps x 1280 keys), each rounded by at
+most 2^-24 of the running sum, so two orders differ by at most 2 * 640 * 2^-24 = 7.6e-5 of the largest running sum, which
+is about the largest element; the result is compared to 1e-4 of that."""
 import ctypes as C
 
 import pytest
 import torch
 
 import paper_2406_18485_amd as P
-from gpu_harness import DEV
+from gpu_harness import DEV, token_major
 from paper_2406_18485_amd.ring import RingReplay, RingShape, _desc
 
 pytestmark = pytest.mark.gpu
 
 
-def _close(a, b):
+def _close(a, b, tol=1e-4):
     assert torch.isfinite(a).all()
-    assert float((a - b).abs().max()) <= 1e-4 * float(b.abs().max())
+    assert float((a - b).abs().max()) <= tol * float(b.abs().max())
 
 
 def _replay(cp, w, rank, hq, hkv, d, c, batch, flags=0, dtype=torch.bfloat16, code=P.BF16):
@@ -138,3 +139,33 @@ def test_a_backward_needs_nothing_of_its_workspace(cp, hq, hkv, d, c):
         P.attn_step_bwd_static(_desc(rep.shape, step, flags | P.OVERWRITE_DQ), q, k[src], v[src], None, d_o, rep.lse, rep.delta, *g)
         res.append(g)
     assert all(torch.equal(a, b) for a, b in zip(*res))
+
+
+# (the last two are cut by their work: 7.2e11 operations at head_dim 64 where a launch aims at 6e11, 1.7e12 at 128 where it aims at 1.2e12)
+@pytest.mark.parametrize("cp,rank,hq,hkv,d,c,batch,dtype,code", [
+    (4, 2, 4, 1, 128, 200, 1, torch.bfloat16, P.BF16), (3, 0, 2, 2, 64, 33, 2, torch.float16, P.FP16), (4, 1, 2, 1, 100, 40, 1, torch.float32, P.FP32),
+    (3, 1, 32, 8, 64, 2048, 1, torch.float16, P.FP16), (4, 2, 28, 4, 128, 2048, 1, torch.bfloat16, P.BF16)])
+def test_strided_run_gives_the_same_bits_and_a_cut_one_the_same_sums(cp, rank, hq, hkv, d, c, batch, dtype, code):
+    """Token-major q, k, v, o, d_o and dq with gaps between the rows; a run long enough for several launches against its steps."""
+    rep, q, k, v, d_o = _replay(cp, cp, rank, hq, hkv, d, c, batch, dtype=dtype, code=code)
+    rep.backward(q, k, v, d_o)
+    want = [t.clone() for t in (rep.dq, rep.dk, rep.dv)]
+    (qs, stride), (os_, _), (dos, _) = (token_major(t, 8) for t in (q, rep.o, d_o))
+    ks_, vs_ = ([token_major(x, 16)[0] for x in y] for y in (k, v))
+    dq, o_stride = token_major(torch.full_like(rep.dq, 5.0), 4)
+    descs = (P.StepDesc * cp)(*(_desc(rep.shape, step, P.COMPUTE_DELTA | P.OVERWRITE_DQ) for step in rep.plan))
+    for desc in descs:
+        desc.q_stride[:], desc.kv_stride[:], desc.o_stride[:] = stride, ks_[0].stride()[:3], o_stride
+    order = [s["src_rank"] for s in rep.plan]
+    for t in (rep.dk, rep.dv, rep.delta):
+        t.fill_(5.0)
+    P.attn_steps_bwd(descs, qs, [ks_[s] for s in order], [vs_[s] for s in order], os_, dos, rep.lse, rep.delta, dq,
+                     [rep.dk[s] for s in order], [rep.dv[s] for s in order], rep.workspace)
+    assert all(torch.equal(a, b) for a, b in zip(want, (dq, rep.dk, rep.dv)))
+    for t, step in enumerate(rep.plan):
+        src = step["src_rank"]
+        P.attn_step_bwd(_desc(rep.shape, step, 0 if t else P.OVERWRITE_DQ), q, k[src], v[src], None, d_o, rep.lse, rep.delta,
+                        rep.dq, rep.dk[src], rep.dv[src], rep.workspace)
+    longest = max(cp * 2 * c, 2 * c * hq // hkv) // 16   # additions in the longest chain: a row's keys, a key's rows
+    for a, b in zip(want, (rep.dq, rep.dk, rep.dv)):
+        _close(a, b, max(1e-4, 2 * longest * 2.0 ** -24))

@@ -5,7 +5,7 @@ import pytest
 import torch
 
 import paper_2406_18485_amd as P
-from gpu_harness import DEV
+from gpu_harness import DEV, token_major
 from paper_2406_18485_amd.ring import RingReplay, RingShape, _desc
 
 pytestmark = pytest.mark.gpu
@@ -80,3 +80,30 @@ def test_the_split_is_the_smallest_that_fills_the_chip(lq, hq, hkv, ks, d):
                                     softmax_scale=d ** -0.5, flags=P.key_splits(forced)), q, k, v, out, lse)
         res.append((out, lse))
     assert torch.equal(res[0][0], res[1][0]) and torch.equal(res[0][1], res[1][1])
+
+
+@pytest.mark.parametrize("dtype,code", [(torch.bfloat16, P.BF16), (torch.float16, P.FP16)])
+@pytest.mark.parametrize("cp,rank,hq,hkv,d,c,batch,ks", [(4, 2, 4, 1, 128, 200, 1, 0), (2, 0, 2, 2, 64, 33, 2, 4), (3, 1, 6, 2, 128, 129, 1, 2), (2, 1, 8, 8, 64, 97, 1, 1)])
+def test_strided_tensors_on_another_stream_give_the_same_bits(cp, rank, hq, hkv, d, c, batch, ks, dtype, code):
+    """Token-major q, k, v and `out` with gaps between the rows, and the contiguous `o` that the last step stores beside them."""
+    shape = RingShape(cp=cp, w=cp, rank=rank, hq=hq, hkv=hkv, d=d, c=c, dtype=code, scale=d ** -0.5, batch=batch, extra_flags=P.key_splits(ks))
+    rep = RingReplay(shape, DEV)
+    g = torch.Generator(device=DEV).manual_seed(c)
+    mk = lambda h: torch.randn(batch, h, 2 * c, d, device=DEV, generator=g).to(dtype)
+    q, k, v = mk(hq), [mk(hkv) for _ in range(cp)], [mk(hkv) for _ in range(cp)]
+    rep.forward(q, k, v)
+    qs, q_stride = token_major(q, 8)
+    ks_, vs_ = ([token_major(x, 16)[0] for x in y] for y in (k, v))
+    out, o_stride = token_major(torch.full_like(rep.out, 5.0), 4)
+    lse, o = torch.full_like(rep.lse, 5.0), torch.full_like(rep.o, 5.0)
+    descs = (P.StepDesc * cp)(*(_desc(shape, step, 0) for step in rep.plan))
+    for desc in descs:
+        desc.q_stride[:], desc.kv_stride[:], desc.o_stride[:] = q_stride, ks_[0].stride()[:3], o_stride
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    order = [s["src_rank"] for s in rep.plan]
+    P.attn_steps_fwd(descs, qs, [ks_[s] for s in order], [vs_[s] for s in order], out, lse, o, stream=side)
+    torch.cuda.current_stream().wait_stream(side)
+    assert torch.equal(out, rep.out) and torch.equal(lse, rep.lse) and torch.equal(o, rep.o)
+    gaps = out.permute(0, 2, 1, 3).as_strided((batch, 2 * c, hq, 4), (out.stride(0), out.stride(2), out.stride(1), 1), d)
+    assert bool(gaps.isnan().all())

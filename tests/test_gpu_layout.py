@@ -72,6 +72,7 @@ def test_empty_and_error_paths():
 
 @pytest.mark.parametrize("n,row_bytes,kind", [
     ((3, 5, 7), 48, "pack"), ((1, 1, 1), 16, "pack"), ((2, 3, 257), 256, "pack"), ((3, 4, 127), 256, "pack"), ((3, 4, 129), 256, "pack"), ((2, 2, 2100), 128, "pack"), ((2, 2, 40), 4096, "pack"), ((2, 2, 40), 4112, "pack"), ((2, 4, 1023), 16, "dense"), ((4, 2, 4097), 256, "dense"),
+    ((4, 2, 32768), 256, "dense"), ((4, 2, 32769), 256, "dense"),   # 64 MiB, and the streams that more of it are taken as
     ((2, 3, 40000), 256, "copies"), ((8, 2, 4096), 512, "copies"), ((2, 300, 3), 16, "copies"), ((1, 7, 1025), 1008, "copies")])
 def test_permuted_rows_of_every_form(n, row_bytes, kind):
     """Rows with gaps, replication above and below the size where a piece is read once; row lengths and counts either side of
