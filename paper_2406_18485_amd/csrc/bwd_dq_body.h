@@ -322,13 +322,15 @@ __device__ __forceinline__ void dq_body(const StepTable& tab, const DqParams& p,
   for (int db = 0; db < NDB; ++db)
 #pragma unroll
     for (int vq = 0; vq < 4; ++vq) old[db][vq] = make_float4(0.f, 0.f, 0.f, 0.f);
+  // (One branch around all the loads: with one around each, they are waited for one by one, 8192 rows x 100 keys
+  // x 8 heads without a split 31.9 us instead of 24.6.)
+  if (ksp == 0 && row_ok && !p.overwrite) {
+#pragma unroll
+    for (int db = 0; db < NDB; ++db)
+#pragma unroll
+      for (int vq = 0; vq < 4; ++vq) old[db][vq] = *reinterpret_cast<const float4*>(dq_row + db * 32 + 8 * vq + 4 * hh);
+  }
   if (KS > 1) {
-    if (ksp == 0 && row_ok && !p.overwrite) {
-#pragma unroll
-      for (int db = 0; db < NDB; ++db)
-#pragma unroll
-        for (int vq = 0; vq < 4; ++vq) old[db][vq] = *reinterpret_cast<const float4*>(dq_row + db * 32 + 8 * vq + 4 * hh);
-    }
     __syncthreads();  // all reads of the last tile are done: the tile buffers are reused
     float4* slots = reinterpret_cast<float4*>(smem);
     if (ksp > 0) {
@@ -363,7 +365,6 @@ __device__ __forceinline__ void dq_body(const StepTable& tab, const DqParams& p,
       for (int vq = 0; vq < 4; ++vq) {
         float4* dst = reinterpret_cast<float4*>(dq_row + db * 32 + 8 * vq + 4 * hh);
         float4 x = old[db][vq];
-        if (KS == 1 && !p.overwrite) x = *dst;
         x.x = fmaf(acc[db][4 * vq + 0], p.scale, x.x); x.y = fmaf(acc[db][4 * vq + 1], p.scale, x.y);
         x.z = fmaf(acc[db][4 * vq + 2], p.scale, x.z); x.w = fmaf(acc[db][4 * vq + 3], p.scale, x.w);
         *dst = x;
