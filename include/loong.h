@@ -74,7 +74,7 @@ extern "C" {
                                      so the call need not clear them.  The caller answers for it: it zeroes ALL of them itself,
                                      ordered before its first call on the stream; a call leaves a zero head zero.  (A call
                                      without the flag clears the head first if it counts there, and leaves it alone if not.)
-                                     Counters that were not zero make dk and dv wrong (NaN where a wait ran out: it is bounded) */
+                                     Counters that were not zero make dk and dv wrong (NaN for most values they may hold) */
 #define LOONG_WORKSPACE_HEAD 65536
 /* Tuning/testing knob of the 16-bit kernels that own query rows (forward, dQ): bits 8..10 of
  * `flags` hold 1, 2 or 4 to force that many key splits per workgroup (waves that share the

@@ -77,7 +77,7 @@ struct BwdCfg {
   static constexpr int STAGE_B = 2 * QT_B + 2 * BM * 4;  // Q, dO, lse, delta
   static constexpr int NSTAGE = 3;                 // tile being staged, tile of the P waves, tile of the E waves
   static constexpr int XCH_B = 4 * 2 * 2 * 1024;   // P hand-over: 4 key groups x 2 blocks x 2 halves x 64 lanes x 16 B
-  static constexpr int ROLE_OFF = NSTAGE * STAGE_B + 2 * XCH_B;  // shared loops: whether this workgroup gathers
+  static constexpr int ROLE_OFF = NSTAGE * STAGE_B + 2 * XCH_B;  // shared loops: what arrive() said
   static constexpr int SMEM_BYTES = ROLE_OFF + 16;
   static_assert(LI >= 1 && LI * 1024 * 4 == QT_B, "tile must split evenly over the staging waves");
 };
@@ -216,12 +216,6 @@ __device__ __forceinline__ void dkv_body(const StepTable& tab, const DkvParams& 
   cur.gq = it_begin / max(per_g, 1);
   cur.r = it_begin - cur.gq * per_g;
   nxt = cur;
-
-  // shared query loop: who gathers
-  const int tile_id = bhk * p.kt_total + kt;
-  int* const role = reinterpret_cast<int*>(smem + C::ROLE_OFF);
-  constexpr int kLeaves = 0, kGathers = 1, kAllHere = 2, kPartsMissing = 3;
-  if (p.nsplit > 1 && tid == 0) *role = claim_gather(p.ws_cnt + tile_id, p.nsplit) ? kGathers : kLeaves;
 
   wait_vmcnt<0>();  // the K / V fragments are in: no counter wait of the compiler's lands in the loop
   if (it_begin < it_end) issue_tile(cur, 0);
@@ -396,29 +390,27 @@ __device__ __forceinline__ void dkv_body(const StepTable& tab, const DkvParams& 
     st_e = st_p; st_p = st_n; st_n = freed;
   }
 
-  // ---- several workgroups share this key tile's query loop: all but one park their partial sums,
-  // and that one adds them up in split order (split_exchange.h)
+  // ---- several workgroups share this key tile's query loop: all park their partial sums, and the
+  // last to arrive adds them up in split order (split_exchange.h)
   if (p.nsplit > 1) {
-    __syncthreads();  // (a workgroup without iterations has not met the loop's barrier)
+    int* const role = reinterpret_cast<int*>(smem + C::ROLE_OFF);
+    const int tile_id = bhk * p.kt_total + kt;
     constexpr int WAVE_B = NDB * 16 * 64 * 4;  // bytes per wave and part
     unsigned char* parts = reinterpret_cast<unsigned char*>(p.ws_part) + (int64_t)tile_id * p.nsplit * (kBwdWaves * WAVE_B);
     const __amdgpu_buffer_rsrc_t buf = part_buffer(parts);
     const uint32_t mine = wave * WAVE_B + lane * 16;
-    if (*role == kLeaves) {
 #pragma unroll
-      for (int db = 0; db < NDB; ++db)
+    for (int db = 0; db < NDB; ++db)
 #pragma unroll
-        for (int vq = 0; vq < 4; ++vq)
-          store_part(buf, sp * (kBwdWaves * WAVE_B) + mine + (db * 4 + vq) * 1024,
-                     floatx4_t{acc[db][4 * vq], acc[db][4 * vq + 1], acc[db][4 * vq + 2], acc[db][4 * vq + 3]});
-      wait_vmcnt<0>();
-      __syncthreads();
-      if (tid == 0) publish_part(p.ws_cnt + tile_id);
-      return;
-    }
-    if (tid == 0) *role = await_parts(p.ws_cnt + tile_id, p.nsplit, it_end - it_begin) ? kAllHere : kPartsMissing;
+      for (int vq = 0; vq < 4; ++vq)
+        store_part(buf, sp * (kBwdWaves * WAVE_B) + mine + (db * 4 + vq) * 1024,
+                   floatx4_t{acc[db][4 * vq], acc[db][4 * vq + 1], acc[db][4 * vq + 2], acc[db][4 * vq + 3]});
+    wait_vmcnt<0>();
     __syncthreads();
-    const float start = *role == kAllHere ? 0.f : NAN;
+    if (tid == 0) *role = arrive(p.ws_cnt + tile_id, p.nsplit);
+    __syncthreads();
+    if (*role == kLeaves) return;
+    const float start = *role == kGathers ? 0.f : NAN;
     floatx16_t sum[NDB];
 #pragma unroll
     for (int db = 0; db < NDB; ++db)

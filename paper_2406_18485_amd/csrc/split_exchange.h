@@ -1,24 +1,24 @@
 // Exchange of partial results between the workgroups that share one tile's loop (several
-// workgroups walk over parts of it; one adds the parts up).  Who adds is decided when the
-// workgroups START: each claims a ticket, and the one that draws the last gathers.  All the others
-// are running by then, so its wait for them ends whatever the order of dispatch; they park their
-// parts in the caller's workspace, publish, and leave, while the gatherer keeps its own part in
-// registers.  (Deciding at the end, by arrival, made every workgroup park its part and wait for the
-// stores before it could count itself, and put the ticket's round trip after the loop instead
-// of beside the first loads.)  The parts are added in split order, so the result does not depend on
-// who gathers.
+// workgroups walk over parts of it; one adds the parts up).  Every workgroup parks its part in the
+// caller's workspace and then counts itself; the last to arrive adds the others' parts to its own,
+// which it still has in registers, in split order, so the result does not depend on who that is.
+// No workgroup waits for another: a launch ends whatever the counters hold.
+//
+// (Letting the last to START gather, chosen by a ticket drawn in the prologue, saves its parking but puts the
+// ticket's round trip before the loop and needs a wait for the others' parts.  dK/dV alone, 4096 rows x 1024 keys, 8 heads on 2,
+// head_dim 64: 45.9 us against 41.6 by arrival; 2 x 8 x 512 x 512: 18.3 against 15.3; whole backward steps 1-5 % longer.  Runs
+// of steps go either way: 4 of 8 heads x 3998 rows 477 against 485, 4 of 16 heads x 606 rows 110 against 105.)
 //
 // The parts cross between XCDs, whose L2s are not coherent for ordinary accesses.  A device-scope
 // fence would do (release: write back the XCD's L2, acquire: invalidate it), but every workgroup
 // would pay for the whole cache (measured: 1.4-1.8x the time of a step).  Instead every word is
 // stored and loaded with device scope (sc1), i.e. written through to and read from the level all
-// XCDs share; the stores are waited for (vmcnt) before the workgroup publishes, and the gatherer's
-// loads are issued after it has seen every part published.
+// XCDs share; the stores are waited for (vmcnt) before the workgroup counts itself, and the gatherer's
+// loads are issued after its count has returned.
 //
-// Counter of a tile: low half = tickets drawn, high half = parts published.  It must be zero
-// before the launch and the gatherer leaves it zero.  If it is not (memory that two unordered calls share, or a
-// caller that vouched for counters it never cleared), the tile's result is wrong, but nothing is read or written elsewhere and
-// every wait ends; a wait that runs out stores NaN, so that most such mistakes show.
+// The counter of a tile is zero before the launch and the last to arrive leaves it zero.  If it is not
+// zero (memory that two unordered calls share, or a caller that vouched for counters it never cleared), the
+// tile's result is wrong, but nothing is read or written elsewhere, and a count past the last gives NaN.
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -26,35 +26,15 @@
 
 namespace loong {
 
-constexpr uint32_t kPublished = 0x10000u;
+constexpr int kLeaves = 0, kGathers = 1, kCountsWrong = 2;
 
-// One thread of the workgroup: draw a ticket; true for the gatherer of `n` workgroups (the last ticket; later ones are
-// drawn from wrong counters only).
-__device__ __forceinline__ bool claim_gather(uint32_t* cnt, int n) {
+// One thread of the workgroup, whose part is in memory (every wave has waited for its stores, and a
+// workgroup barrier has been passed since): what it does next.
+__device__ __forceinline__ int arrive(uint32_t* cnt, int n) {
   const uint32_t before = __hip_atomic_fetch_add(cnt, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  return (before & (kPublished - 1)) >= (uint32_t)n - 1;
-}
-
-// One thread: this workgroup's part is in memory (every wave has waited for its stores, and a
-// workgroup barrier has been passed since).
-__device__ __forceinline__ void publish_part(uint32_t* cnt) {
-  __hip_atomic_fetch_add(cnt, kPublished, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-// One thread of the gatherer: wait for the other n - 1 parts and put the counter back to zero; false if they did not
-// come.  The others started before this workgroup drew its ticket and have as many iterations of their loop left at most as it
-// has done, so the wait is limited by that: 1024 looks per iteration and four million for everything else, which take 0.18 us
-// each: 0.2 ms for an iteration of about 2 us, and 0.8 s.  (Looks are counted, not time: a wave that is taken off the device does not
-// run out of them.)
-constexpr int64_t kPolls = 1 << 22;
-__device__ __forceinline__ bool await_parts(uint32_t* cnt, int n, int iterations) {
-  bool all = false;
-  for (int64_t left = kPolls + (int64_t)1024 * iterations; left > 0 && !all; --left) {
-    all = (__hip_atomic_load(cnt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >> 16) == (uint32_t)n - 1;
-    if (!all) __builtin_amdgcn_s_sleep(2);
-  }
+  if (before < (uint32_t)n - 1) return kLeaves;
   __hip_atomic_store(cnt, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  return all;
+  return before == (uint32_t)n - 1 ? kGathers : kCountsWrong;
 }
 
 // 16 bytes per lane with device scope, as buffer accesses (the compiler counts them like any
