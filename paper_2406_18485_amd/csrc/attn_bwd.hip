@@ -56,7 +56,7 @@ SplitPlan plan_split(const StepGeom* g, int n, int G, int Hkv, int B, int q_len,
         if (cls == LOONG_SKIP || g[t].q[a].len == 0) continue;
         seen += g[t].q[a].len;
         diag |= cls == LOONG_DIAG;
-        if (tab) tab->row_list[a][n_list[a]] = (uint32_t)t | (uint32_t)kb << 8 | (cls == LOONG_DIAG ? kDiagEntry : 0u);
+        if (tab) tab->row[a][n_list[a]] = (uint32_t)t | (uint32_t)kb << 8 | (cls == LOONG_DIAG ? kDiagEntry : 0u);
         ++n_list[a];
         n_diag[a] += cls == LOONG_DIAG;
       }
@@ -84,6 +84,10 @@ SplitPlan plan_split(const StepGeom* g, int n, int G, int Hkv, int B, int q_len,
     tab->klen = klen; tab->n_seen = n_seen; tab->n_halves = n_halves;
     for (int i = 0; i < n_halves; ++i) tab->half[i] = entry[i];
     for (int a = 0; a < 2; ++a) { tab->n_list[a] = n_list[a]; tab->n_diag[a] = n_diag[a]; }
+    for (int i = 0; i < 2; ++i) {
+      tab->first_half[i] = tab->half[i];
+      for (int a = 0; a < 2; ++a) tab->first_row[a][i] = tab->row[a][i];
+    }
   }
   int nsplit = 1;
   const int64_t q_tiles = std::max<int64_t>((int64_t)G * ((q_len + BM - 1) / BM), 1);
@@ -240,8 +244,9 @@ int launch_bwd_bf16(const loong_step_desc& d, const StepGeom* g, int n, const Bw
   s.do_kv = !(d.flags & LOONG_BWD_ONLY_DQ) && d.kv_len > 0;
   s.do_q = !(d.flags & LOONG_BWD_ONLY_DKV) && d.q_len > 0 && (d.kv_len > 0 || (d.flags & LOONG_OVERWRITE_DQ));
   for (int t = 0; t < n; ++t) {
-    s.tab.k[t] = (const uint16_t*)k[t]; s.tab.v[t] = (const uint16_t*)v[t];
-    if (s.do_kv) { s.tab.dk[t] = dk[t]; s.tab.dv[t] = dv[t]; }
+    StepTable::Chunk& c = s.tab.step[t];
+    c.k = (const uint16_t*)k[t]; c.v = (const uint16_t*)v[t];
+    if (s.do_kv) { c.dk = dk[t]; c.dv = dv[t]; }
   }
   const SplitPlan plan = plan_split(g, n, G, d.n_kv_heads, d.batch, d.q_len, planning_cus(), &s.tab);
   s.rows = g[0];

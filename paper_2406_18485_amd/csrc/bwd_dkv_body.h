@@ -95,12 +95,15 @@ __device__ __forceinline__ void dkv_body(const StepTable& tab, const DkvParams& 
   const int kt = rem / p.nsplit, sp = rem - kt * p.nsplit;
   const int b = bhk / p.Hkv, hk = bhk - b * p.Hkv;
   const int half_idx = kt / p.nkt, koff0 = (kt - half_idx * p.nkt) * BN;
-  const uint32_t entry = tab.half[half_idx];
+  const uint32_t entry0 = scalar_now(tab.first_half[0]), entry1 = scalar_now(tab.first_half[1]);
+  uint32_t entry = half_idx == 1 ? entry1 : entry0;
+  if (half_idx > 1) entry = tab.half[half_idx];
   const int step = entry_step(entry), klen = tab.klen, kstart = entry_half(entry) * klen;
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l32 = lane & 31, hh = lane >> 5;
   const int kg = wave & 3;           // key group: keys koff0 + 32 kg ..
   const bool p_wave = wave < 4;      // waves kg and kg + 4 share a SIMD
+  const bool p_wave_s = scalar_now(p_wave);  // (the same in a scalar register, where it chooses a pointer)
   const int my_koff = koff0 + 32 * kg + l32;
   const bool key_ok = my_koff < klen;
   const int64_t my_krow = kstart + min(my_koff, klen - 1);
@@ -131,21 +134,28 @@ __device__ __forceinline__ void dkv_body(const StepTable& tab, const DkvParams& 
   };
 
   // ---- the wave's B operand: its K rows (P wave) or its V rows with the sign bits flipped
-  // (E wave); row my_krow, columns 16 ks + 8 hh .. +7
+  // (E wave); row my_krow, columns 16 ks + 8 hh .. +7.  All of it is requested before any of it is used.
   bf16x8_t bfrag[NKS];
   {
-    const uint16_t* row = (p_wave ? tab.k[step] : tab.v[step]) + b * p.ks[0] + hk * p.ks[1] + my_krow * p.ks[2];
-    const uint32_t flip = p_wave ? 0u : 0x80008000u;
+    const uint16_t *kp = scalar_now(tab.step[0].k), *vp = scalar_now(tab.step[0].v);
+    if (step) { kp = scalar_now(tab.step[step].k); vp = scalar_now(tab.step[step].v); }
+    const uint16_t* row = (p_wave_s ? kp : vp) + b * p.ks[0] + hk * p.ks[1] + my_krow * p.ks[2];
+#pragma unroll
+    for (int ks = 0; ks < NKS; ++ks) bfrag[ks] = as_bf16x8(*reinterpret_cast<const uint4*>(row + ks * 16 + hh * 8));
+  }
+  // K comes with scale * log2 e folded in (rounded to 16 bits again): the score product then ends
+  // in the exponent's units and its chains can start from the rows' offsets, which takes the
+  // multiply-add per element off the vector port (4 % of the kernel).  The second rounding
+  // changes P by less than rounding P itself to 16 bits does.
+  if (p_wave_s) {
+#pragma unroll
+    for (int ks = 0; ks < NKS; ++ks) bfrag[ks] = scaled_fragment<E>(bfrag[ks], p.c);
+  } else {
 #pragma unroll
     for (int ks = 0; ks < NKS; ++ks) {
-      uint4 x = *reinterpret_cast<const uint4*>(row + ks * 16 + hh * 8);
-      x.x ^= flip; x.y ^= flip; x.z ^= flip; x.w ^= flip;
+      uint4 x = __builtin_bit_cast(uint4, bfrag[ks]);
+      x.x ^= 0x80008000u; x.y ^= 0x80008000u; x.z ^= 0x80008000u; x.w ^= 0x80008000u;
       bfrag[ks] = as_bf16x8(x);
-      // K comes with scale * log2 e folded in (rounded to 16 bits again): the score product then ends
-      // in the exponent's units and its chains can start from the rows' offsets, which takes the
-      // multiply-add per element off the vector port (4 % of the kernel).  The second rounding
-      // changes P by less than rounding P itself to 16 bits does.
-      if (p_wave) bfrag[ks] = scaled_fragment<E>(bfrag[ks], p.c);
     }
   }
 
@@ -226,10 +236,10 @@ __device__ __forceinline__ void dkv_body(const StepTable& tab, const DkvParams& 
   // 5-7 us a step)
   if (p_wave && !p.accumulate)
     for (int z = tab.n_seen; z < tab.n_halves; ++z) {
-      const uint32_t ze = tab.half[z];
+      const uint32_t ze = z == 1 ? entry1 : tab.half[z];
       const int64_t off = (((int64_t)b * p.Hkv + hk) * p.kv_len + (int64_t)entry_half(ze) * klen) * D;
-      float4* zk = reinterpret_cast<float4*>(tab.dk[entry_step(ze)] + off);
-      float4* zv = reinterpret_cast<float4*>(tab.dv[entry_step(ze)] + off);
+      float4* zk = reinterpret_cast<float4*>(tab.step[entry_step(ze)].dk + off);
+      float4* zv = reinterpret_cast<float4*>(tab.step[entry_step(ze)].dv + off);
       const int64_t n4 = (int64_t)klen * (D / 4), stride = (int64_t)p.map.per_unit * 256;
       for (int64_t i = (int64_t)rem * 256 + tid; i < n4; i += stride) {
         zk[i] = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -443,7 +453,7 @@ __device__ __forceinline__ void dkv_body(const StepTable& tab, const DkvParams& 
   // rate whatever their width (stored one float at a time, this epilogue took 3.2 us of a
   // 74 us launch).  This workgroup is the only one that writes these rows in this launch, so
   // accumulation is a plain read-modify-write.
-  float* base = (p_wave ? tab.dv[step] : tab.dk[step]) + (((int64_t)b * p.Hkv + hk) * p.kv_len + kstart) * D;
+  float* base = (p_wave_s ? tab.step[step].dv : tab.step[step].dk) + (((int64_t)b * p.Hkv + hk) * p.kv_len + kstart) * D;
   const float f = p_wave ? 1.f : -p.scale;
   const bool odd = lane & 1, upper = lane & 2;
   const int col4 = (l32 >> 2) * 4, key_in_group = l32 & 3;

@@ -102,7 +102,12 @@ __device__ __forceinline__ void dq_body(const StepTable& tab, const DqParams& p,
 
   // ---- visible key tiles of this workgroup: the key halves its rows see, one after the other
   const int klen = tab.klen, kend_diag = min(klen, last_off_wg + 1);  // keys of a whole and of the diagonal half
-  const int n_list = qa ? tab.n_list[1] : tab.n_list[0], n_diag = qa ? tab.n_diag[1] : tab.n_diag[0];
+  const uint32_t n_list0 = scalar_now(tab.n_list[0]), n_list1 = scalar_now(tab.n_list[1]);
+  const uint32_t n_diag0 = scalar_now(tab.n_diag[0]), n_diag1 = scalar_now(tab.n_diag[1]);
+  const uint32_t e00 = scalar_now(tab.first_row[0][0]), e01 = scalar_now(tab.first_row[0][1]);  // the first two entries of either
+  const uint32_t e10 = scalar_now(tab.first_row[1][0]), e11 = scalar_now(tab.first_row[1][1]);
+  const uint32_t first = qa ? e10 : e00, second = qa ? e11 : e01;
+  const int n_list = (int)(qa ? n_list1 : n_list0), n_diag = (int)(qa ? n_diag1 : n_diag0);
   const int total_t = (n_list - n_diag) * ((klen + TK - 1) / TK) + n_diag * ((kend_diag + TK - 1) / TK);
   float* const dq_row = p.dq + b * p.os[0] + h * p.os[1] + (int64_t)my_row * p.os[2];
   if (total_t == 0) {  // nothing visible: no share of dQ in this step
@@ -161,7 +166,8 @@ __device__ __forceinline__ void dq_body(const StepTable& tab, const DqParams& p,
   struct Cursor { uint32_t e; int i, j0, kend; };
   auto enter = [&](Cursor& cu, int i) {
     cu.i = i; cu.j0 = 0;
-    cu.e = qa ? tab.row_list[1][i] : tab.row_list[0][i];
+    cu.e = i ? second : first;
+    if (i > 1) cu.e = qa ? tab.row[1][i] : tab.row[0][i];
     cu.kend = cu.e & kDiagEntry ? kend_diag : klen;
   };
   auto advance = [&](Cursor& cu) {  // true: another half begins
@@ -170,14 +176,17 @@ __device__ __forceinline__ void dq_body(const StepTable& tab, const DqParams& p,
     enter(cu, cu.i + 1);
     return true;
   };
+  const uint16_t *const k0 = scalar_now(tab.step[0].k), *const v0 = scalar_now(tab.step[0].v);
   const int64_t head_off = b * p.ks[0] + hk * p.ks[1];
   Cursor ahead, cur;  // the tile to stage next, the tile in use
   const unsigned char *kbase, *vbase;  // first key of the half `ahead` is in
   auto find_bases = [&] {
     const int64_t off = head_off + (int64_t)(entry_half(ahead.e) * klen) * p.ks[2];
     const int step = entry_step(ahead.e);
-    kbase = reinterpret_cast<const unsigned char*>(tab.k[step] + off);
-    vbase = reinterpret_cast<const unsigned char*>(tab.v[step] + off);
+    const uint16_t *k = k0, *v = v0;
+    if (step) { k = scalar_now(tab.step[step].k); v = scalar_now(tab.step[step].v); }
+    kbase = reinterpret_cast<const unsigned char*>(k + off);
+    vbase = reinterpret_cast<const unsigned char*>(v + off);
   };
   enter(ahead, 0);
   find_bases();

@@ -1,6 +1,11 @@
 // The visiting chunks a backward launch works on: one micro-step, or a run of micro-steps whose chunks
 // are all resident.  The kernels take the table by value and index it with workgroup-uniform values
 // (scalar loads, once per chunk).
+//
+// A kernel argument comes from memory that no cache holds when a launch begins, about a microsecond a look, and a look
+// that needs the last one's answer pays again: entry, then step, then pointer made a key tile's prologue three looks
+// longer.  So what a launch over one step reads (two entries, one step) lies at fixed places, is loaded together
+// (scalar_now keeps the compiler from choosing an address first and loading then) and only later entries are looked up.
 #pragma once
 #include <stdint.h>
 
@@ -10,15 +15,18 @@ constexpr int kMaxSteps = 32;              // micro-steps per launch; longer run
 constexpr int kMaxHalves = 2 * kMaxSteps;  // key halves of their chunks
 
 struct StepTable {
-  const uint16_t *k[kMaxSteps], *v[kMaxSteps];
-  float *dk[kMaxSteps], *dv[kMaxSteps];
   int klen;                        // keys per half; half 1 of a chunk starts at token klen
+  int n_seen, n_halves;            // entries in `half`: those some row sees, all
+  int n_list[2], n_diag[2];        // entries in `row` per q segment, and the diagonal ones among them
+  uint32_t first_half[2], first_row[2][2];  // the first two of each list again, beside the counts
+  struct Chunk {
+    const uint16_t *k, *v;
+    float *dk, *dv;
+  } step[kMaxSteps];
   // key halves, those some row sees first: step | half << 8 | class for q segment 0 << 10 | q segment 1 << 12
   uint32_t half[kMaxHalves];
-  int n_seen, n_halves;
   // per q segment the halves it sees, in visit order: step | half << 8 | diagonal << 9
-  uint32_t row_list[2][kMaxHalves];
-  int n_list[2], n_diag[2];
+  uint32_t row[2][kMaxHalves];
 };
 
 constexpr uint32_t kDiagEntry = 1u << 9;
@@ -27,6 +35,12 @@ constexpr uint32_t kDiagEntry = 1u << 9;
 __device__ __forceinline__ int entry_step(uint32_t e) { return (int)(e & 0xff); }
 __device__ __forceinline__ int entry_half(uint32_t e) { return (int)(e >> 8) & 1; }
 __device__ __forceinline__ int entry_class(uint32_t e, int qa) { return (int)(e >> (10 + 2 * qa)) & 3; }
+__device__ __forceinline__ uint32_t scalar_now(uint32_t x) { return (uint32_t)__builtin_amdgcn_readfirstlane(x); }
+template <class T>
+__device__ __forceinline__ T* scalar_now(T* p) {
+  const uint64_t a = reinterpret_cast<uint64_t>(p);
+  return reinterpret_cast<T*>((uint64_t)scalar_now((uint32_t)(a >> 32)) << 32 | scalar_now((uint32_t)a));
+}
 #endif
 
 }  // namespace loong
