@@ -86,15 +86,21 @@ int loong_permute_rows(const int64_t n[3], const int64_t in_stride[3], const int
   if (p.total == 0) return LOONG_OK;
   const int64_t blocks = (p.total + 255) / 256;
   if (blocks > 0x7fffffff) return fail(LOONG_E_UNSUPPORTED, "loong_permute_rows: more than 2^31-1 workgroups");
-  // by chunks while a row fits a workgroup, c gives every (a, b) several and few threads are left without a piece;
-  // but not rows that are dense on both sides and too many for the memory-side cache: each (a, b) is then one stream
-  // already, and 32 of them at once cost more than one (4096 tokens unpacked 12.5 -> 10.8 us, 16000 tokens 45.3 -> 49.6);
-  // nor where the threads left without a piece take the launch past its limit
-  const bool streams = p.is2 == row_bytes && p.os2 == row_bytes && !(p.is1 == 0 && n[1] > 1) && p.total > ((int64_t)4 << 20);
-  const int64_t rows = p.pieces <= 256 ? 256 / p.pieces : 0;
+  // By chunks where that is faster (against piece by piece, rows of 64 to 4096 bytes, 20 MB to 1 GB):
+  //   heads and messages    rows up to 512 bytes: token-major heads read 0.70 to 0.98 of the time, written 0.83 to 0.97; at 1 KB 0.86
+  //                         to 1.10, at 2 to 4 KB 0.75 to 1.16.  Not more than 64 MiB where the rows of an (a, b) are read as one
+  //                         stream: 32 of them at once cost more than one then (dense on both sides 45.3 -> 49.6 us at 16000
+  //                         tokens, token-major heads written 37 -> 41 us at 131 MB)
+  //   replication           rows up to 1 KB: 0.54 to 0.97; at 2 to 4 KB up to 1.38.  Not more than 192 MiB (0.77 to 1.18 above)
+  // and c gives every (a, b) several chunks, few threads are left without a piece, and those do not take the launch
+  // past its limit.
+  const bool replicated = p.is1 == 0 && n[1] > 1;
+  const bool pays = replicated ? p.pieces <= 64 && p.total <= ((int64_t)12 << 20)
+                               : p.pieces <= 32 && !(p.is2 == row_bytes && p.total > ((int64_t)4 << 20));
+  const int64_t rows = pays ? 256 / p.pieces : 0;
   const int64_t chunks = rows ? (p.n2 + rows - 1) / rows : 0, ab = n[0] * n[1];
-  const bool once = p.is1 == 0 && n[1] > 1 && chunks * n[0] >= 1024;  // (where what is read still gives every unit workgroups)
-  if (!streams && chunks >= 8 && rows * p.pieces >= 224 && p.n2 < ((int64_t)1 << 30) && ab < ((int64_t)1 << 30) &&
+  const bool once = replicated && chunks * n[0] >= 1024;  // (where what is read still gives every unit workgroups)
+  if (chunks >= 8 && rows * p.pieces >= 224 && p.n2 < ((int64_t)1 << 30) && ab < ((int64_t)1 << 30) &&
       chunks * (once ? n[0] : ab) < kLaunchThreads / 256) {
     ChunkParams c{(uint32_t)rows, (uint32_t)ab, (uint32_t)n[1], (uint32_t)n[2], (uint32_t)p.pieces,
                   p.is0, p.is1, p.is2, p.os0, p.os1, p.os2, 1};

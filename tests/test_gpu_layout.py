@@ -72,7 +72,9 @@ def test_empty_and_error_paths():
 
 @pytest.mark.parametrize("n,row_bytes,kind", [
     ((3, 5, 7), 48, "pack"), ((1, 1, 1), 16, "pack"), ((2, 3, 257), 256, "pack"), ((3, 4, 127), 256, "pack"), ((3, 4, 129), 256, "pack"), ((2, 2, 2100), 128, "pack"), ((2, 2, 40), 4096, "pack"), ((2, 2, 40), 4112, "pack"), ((2, 4, 1023), 16, "dense"), ((4, 2, 4097), 256, "dense"),
-    ((4, 2, 32768), 256, "dense"), ((4, 2, 32769), 256, "dense"),   # 64 MiB, and the streams that more of it are taken as
+    # either side of the sizes that chunks are taken up to: 64 MiB of streams, 512 and 1024 bytes a row, 192 MiB of copies
+    ((4, 2, 32768), 256, "dense"), ((4, 2, 32769), 256, "dense"), ((2, 3, 300), 512, "pack"), ((2, 3, 300), 528, "pack"),
+    ((40, 2, 300), 1024, "copies"), ((40, 2, 300), 1040, "copies"), ((6, 2, 65536), 256, "copies"), ((6, 2, 65537), 256, "copies"),
     ((2, 3, 40000), 256, "copies"), ((8, 2, 4096), 512, "copies"), ((2, 300, 3), 16, "copies"), ((1, 7, 1025), 1008, "copies")])
 def test_permuted_rows_of_every_form(n, row_bytes, kind):
     """Rows with gaps, replication above and below the size where a piece is read once; row lengths and counts either side of
@@ -94,11 +96,11 @@ def test_permuted_rows_of_every_form(n, row_bytes, kind):
 
 
 def test_rows_whose_chunks_exceed_one_launch():
-    """2^24 rows of 225 pieces: dealt out as chunks, a row to a workgroup of 256 threads, they would be the 2^32 threads that a
-    launch does not take; piece by piece they are fewer.  The rows of one column are read again and again, 60 GB are written."""
-    b, c, row_bytes = 4096, 4096, 3600
+    """13000 x 13000 rows of 25 pieces: dealt out as chunks, ten rows to a workgroup of 256 threads, they would be more than the
+    2^32 threads that a launch takes; piece by piece they are fewer.  One column of rows is read again and again, 68 GB are written."""
+    b, c, row_bytes = 13000, 13000, 400
     src = torch.randint(0, 255, (b, row_bytes), dtype=torch.uint8, device=DEV)
     dst = torch.empty(b, c, row_bytes, dtype=torch.uint8, device=DEV)
-    dst[:, ::511] = 0
+    dst[:, ::1625] = 0
     P.permute_rows((1, b, c), (0, row_bytes, 0), (0, c * row_bytes, row_bytes), row_bytes, src, dst)
-    assert torch.equal(dst[:, ::511], src[:, None].expand(-1, 9, -1))
+    assert torch.equal(dst[:, ::1625], src[:, None].expand(-1, 8, -1))
