@@ -163,7 +163,7 @@ struct StepLaunch {
 };
 
 // Workgroups that a launch has room for.
-constexpr int64_t kMaxGrid = (kLaunchThreads - 1) / (kBwdWaves * 64);
+constexpr int64_t kMaxGrid = kLaunchThreads / (kBwdWaves * 64) - 1;
 
 // Key-owning half: work list and workspace.
 int plan_dkv(StepLaunch& s, const SplitPlan& plan, int flags, int D, void* workspace, int64_t workspace_bytes) {
@@ -284,13 +284,14 @@ int launch_bwd_bf16(const loong_step_desc& d, const StepGeom* g, int n, const Bw
   if (!ks) ks = pick_key_splits(s.rows, G, d.n_q_heads, d.batch, 0, dev.cus);
   if (s.do_q)
     if (int rc = plan_dq(s, ks)) return rc;
+  const int64_t n4 = (int64_t)d.batch * d.n_kv_heads * d.kv_len * d.head_dim / 4, clear_grid = (n4 + 255) / 256;
+  if (s.clear && !launch_fits(clear_grid, 256)) return fail(LOONG_E_UNSUPPORTED, "backward grid too large");
   // ---- the launch fits: from here on work is enqueued
   if (before)
     if (int rc = launch_prologue(d, *before, stream)) return rc;
   if (s.clear) {
-    const int64_t n4 = (int64_t)d.batch * d.n_kv_heads * d.kv_len * d.head_dim / 4;
     for (int t = 0; t < n; ++t)
-      zero_kernel<<<dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, st>>>(n4, reinterpret_cast<float4*>(dk[t]), reinterpret_cast<float4*>(dv[t]));
+      zero_kernel<<<dim3((unsigned)clear_grid), dim3(256), 0, st>>>(n4, reinterpret_cast<float4*>(dk[t]), reinterpret_cast<float4*>(dv[t]));
     if (int rc = check_launch("loong_attn_step_bwd (clear dk/dv)")) return rc;
   }
   if (!s.do_kv && !s.do_q) return LOONG_OK;

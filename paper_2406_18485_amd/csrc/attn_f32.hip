@@ -564,10 +564,12 @@ int launch_fwd(F32Params& p, int cus, hipStream_t st) {
   const int64_t wide = (int64_t)p.B * p.Hq * p.rtiles;
   if (wide >= 2 * cus) {
     const int w = pick_waves(p.rmap.grid, 4);
+    if (!launch_fits(p.rmap.grid, w * 64)) return fail(LOONG_E_UNSUPPORTED, "fp32 path: forward grid too large");
     fwd_f32_kernel<NP, EXACT, 2><<<dim3(p.rmap.grid), dim3(w * 64), 0, st>>>(p);
   } else {
     tile_rows(p, kT);
     const int w = pick_waves(p.rmap.grid, (int64_t)p.rmap.grid * kMaxWaves <= (int64_t)cus * 8 ? kMaxWaves : 4);
+    if (!launch_fits(p.rmap.grid, w * 64)) return fail(LOONG_E_UNSUPPORTED, "fp32 path: forward grid too large");
     fwd_f32_kernel<NP, EXACT, 1><<<dim3(p.rmap.grid), dim3(w * 64), 0, st>>>(p);
   }
   return check_launch("loong_attn_step_fwd (fp32)");
@@ -582,6 +584,7 @@ int launch_bwd(F32Params& p, const F32Run& run, bool do_dq, bool do_dkv, hipStre
   }
   p.kmap = make_work_map((int64_t)p.B * p.Hkv, p.ktiles);
   const uint32_t nk = do_dkv ? p.kmap.grid : 0, nq = do_dq ? p.rmap.grid : 0;
+  if (!launch_fits(nk, 64) || !launch_fits(nq, 64)) return fail(LOONG_E_UNSUPPORTED, "fp32 path: backward grid too large");
   const int64_t grid = (int64_t)nk * run.n + nq;
   if (grid * 64 < (int64_t)1 << 32) {
     const int w = pick_waves(grid, max_bwd_waves(NP));

@@ -474,7 +474,7 @@ int launch_cfg(FwdParams& p, hipStream_t st) {
   p.tiles_total = rt.tiles_total; p.hgroups = rt.hgroups;
   const int64_t total = rt.total_wg;
   if (total == 0) return LOONG_OK;
-  if (total > 0x3ffffff0) return fail(LOONG_E_UNSUPPORTED, "forward grid too large");
+  if (!launch_fits(total + 7, kFwdWaves * 64)) return fail(LOONG_E_UNSUPPORTED, "forward grid too large");  // (padded to eight)
   p.map = make_work_map((int64_t)p.B * rt.hgroups, rt.tiles_total);
   fwd_kernel<E, D, KS><<<dim3(p.map.grid), dim3(kFwdWaves * 64), 0, st>>>(p);
   return check_launch("loong_attn_step_fwd (bf16)");

@@ -144,7 +144,7 @@ int launch_delta(const loong_step_desc& d, const void* o, const void* d_o, float
   const int dvec = d.head_dim / (d.dtype == LOONG_FP32 ? 4 : 8);
   const int lpr = pow2_lanes(dvec);
   const int64_t nb = blocks_for(rows, kThreads / lpr);
-  if (nb > 0x7fffffff) return fail(LOONG_E_UNSUPPORTED, "loong_bwd_delta: grid too large");
+  if (!launch_fits(nb, kThreads)) return fail(LOONG_E_UNSUPPORTED, "loong_bwd_delta: grid too large");
   dim3 grid((unsigned)nb), block(kThreads);
   hipStream_t st = static_cast<hipStream_t>(stream);
   const int64_t* s = d.q_stride;
@@ -190,7 +190,7 @@ int loong_lse_merge(int64_t rows, int32_t head_dim, float* out, float* lse, cons
   const int d4 = head_dim / 4;
   const int lpr = pow2_lanes(d4);
   const int64_t nb = blocks_for(rows, kThreads / lpr);
-  if (nb > 0x7fffffff) return fail(LOONG_E_UNSUPPORTED, "loong_lse_merge: grid too large");
+  if (!launch_fits(nb, kThreads)) return fail(LOONG_E_UNSUPPORTED, "loong_lse_merge: grid too large");
   dim3 grid((unsigned)nb), block(kThreads);
   switch (lpr) {
     case 1: merge_kernel<1><<<grid, block, 0, st>>>(rows, d4, out, lse, block_out, block_lse); break;
@@ -214,7 +214,7 @@ int loong_init_running(int64_t rows, int32_t head_dim, float* out, float* lse, v
   if (rows == 0) return LOONG_OK;
   const int64_t n4 = rows * (head_dim / 4);
   const int64_t nb = blocks_for(n4, kThreads);
-  if (nb > 0x7fffffff) return fail(LOONG_E_UNSUPPORTED, "loong_init_running: grid too large");
+  if (!launch_fits(nb, kThreads)) return fail(LOONG_E_UNSUPPORTED, "loong_init_running: grid too large");
   init_running_kernel<<<dim3((unsigned)nb), dim3(kThreads), 0, static_cast<hipStream_t>(stream)>>>(
       n4, rows, reinterpret_cast<float4*>(out), lse);
   return check_launch("loong_init_running");
@@ -234,7 +234,7 @@ int loong_finalize_out(int64_t rows, int32_t head_dim, const float* out, void* o
   if (rows == 0) return LOONG_OK;
   const int64_t n = rows * (head_dim / vec);
   const int64_t nb = blocks_for(n, kThreads);
-  if (nb > 0x7fffffff) return fail(LOONG_E_UNSUPPORTED, "loong_finalize_out: grid too large");
+  if (!launch_fits(nb, kThreads)) return fail(LOONG_E_UNSUPPORTED, "loong_finalize_out: grid too large");
   hipStream_t st = static_cast<hipStream_t>(stream);
   if (dtype == LOONG_BF16)
     cast_half_kernel<Bf16><<<dim3((unsigned)nb), dim3(kThreads), 0, st>>>(n, reinterpret_cast<const float4*>(out),

@@ -85,7 +85,7 @@ int loong_permute_rows(const int64_t n[3], const int64_t in_stride[3], const int
   p.total = n[0] * n[1] * n[2] * p.pieces;
   if (p.total == 0) return LOONG_OK;
   const int64_t blocks = (p.total + 255) / 256;
-  if (blocks > 0x7fffffff) return fail(LOONG_E_UNSUPPORTED, "loong_permute_rows: more than 2^31-1 workgroups");
+  if (!launch_fits(blocks, 256)) return fail(LOONG_E_UNSUPPORTED, "loong_permute_rows: more than 2^32-1 pieces of 16 bytes");
   // By chunks where that is faster (against piece by piece, rows of 64 to 4096 bytes, 20 MB to 1 GB):
   //   heads and messages    rows up to 512 bytes: token-major heads read 0.70 to 0.98 of the time, written 0.83 to 0.97; at 1 KB 0.86
   //                         to 1.10, at 2 to 4 KB 0.75 to 1.16.  Not more than 64 MiB where the rows of an (a, b) are read as one
@@ -101,7 +101,7 @@ int loong_permute_rows(const int64_t n[3], const int64_t in_stride[3], const int
   const int64_t chunks = rows ? (p.n2 + rows - 1) / rows : 0, ab = n[0] * n[1];
   const bool once = replicated && chunks * n[0] >= 1024;  // (where what is read still gives every unit workgroups)
   if (chunks >= 8 && rows * p.pieces >= 224 && p.n2 < ((int64_t)1 << 30) && ab < ((int64_t)1 << 30) &&
-      chunks * (once ? n[0] : ab) < kLaunchThreads / 256) {
+      launch_fits(chunks * (once ? n[0] : ab), 256)) {
     ChunkParams c{(uint32_t)rows, (uint32_t)ab, (uint32_t)n[1], (uint32_t)n[2], (uint32_t)p.pieces,
                   p.is0, p.is1, p.is2, p.os0, p.os1, p.os2, 1};
     if (once) {
@@ -125,7 +125,7 @@ int loong_reduce_replicas(int64_t heads, int32_t rep, int64_t elems_per_head, co
   const int64_t total = heads * (elems_per_head / 4);
   if (total == 0) return LOONG_OK;
   const int64_t blocks = (total + 255) / 256;
-  if (blocks > 0x7fffffff) return fail(LOONG_E_UNSUPPORTED, "loong_reduce_replicas: more than 2^31-1 workgroups");
+  if (!launch_fits(blocks, 256)) return fail(LOONG_E_UNSUPPORTED, "loong_reduce_replicas: more than 2^32-1 pieces of 16 bytes");
   reduce_replicas_kernel<<<dim3((unsigned)blocks), dim3(256), 0, static_cast<hipStream_t>(stream)>>>(
       heads, rep, elems_per_head / 4, reinterpret_cast<const float4*>(in), reinterpret_cast<float4*>(out));
   return check_launch("loong_reduce_replicas");

@@ -41,8 +41,10 @@ inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 
 // Map a hipError_t (as int) of the last launch to the ABI status.
 int check_launch(const char* what);
 
-// A launch takes fewer threads than this (the runtime refuses it otherwise).
+// A launch takes fewer threads than this.  (The runtime refuses this very number; of larger ones it has run a part and
+// reported success.)
 constexpr int64_t kLaunchThreads = (int64_t)1 << 32;
+inline bool launch_fits(int64_t workgroups, int threads) { return workgroups < kLaunchThreads / threads; }
 
 // Facts of the current device, looked up once per device (device.hip).  device_facts fails with
 // LOONG_E_HIP when there is no device and LOONG_E_UNSUPPORTED when it is not a gfx950 part.

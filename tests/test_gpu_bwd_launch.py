@@ -124,3 +124,7 @@ def test_a_step_too_large_for_a_launch_is_refused_before_anything_runs():
         P.attn_step_bwd(desc, q, k, v, q, d_o, lse, delta, dq, dk[0], dv[0])
     torch.cuda.synchronize()
     assert e.value.code == P.E_UNSUPPORTED and bool((delta == 3.0).all()) and bool((dq == 5.0).all())
+    with pytest.raises(P.LoongError) as e:
+        P.attn_step_fwd(desc, q, k, v, dq, lse)
+    torch.cuda.synchronize()
+    assert e.value.code == P.E_UNSUPPORTED and bool((dq == 5.0).all())

@@ -238,3 +238,22 @@ def test_a_run_of_steps_is_refused_when_its_steps_do_not_belong_together():
     for field, value in (("q_chunk", (1, 2)), ("softmax_scale", 0.2), ("n_kv_heads", 4), ("dtype", P.FP16)):
         bad = (P.StepDesc * 2)(good[0], P.make_desc(**{**one, field: value}, kv_chunk=(1, 2)))
         assert call(bad) == P.E_SHAPE and lib.loong_workspace_bytes_steps(bad, 2, C.byref(need)) == P.E_SHAPE
+
+
+def test_more_rows_than_a_launch_has_threads_for_are_refused():
+    """The runtime has run a part of a launch of more than 2^32 threads and reported success; the library says no before it.
+    (Pointers that are only looked at: nothing is launched.)"""
+    p = 1 << 20
+    half, f32 = _good(), _good(dtype=P.FP32, head_dim=64, n_q_heads=2, n_kv_heads=2, q_len=256, kv_len=256, chunk_len=128)
+    rows = (1 << 32) // 32          # 32 lanes a row at head_dim 128
+    calls = [lambda: P.lse_merge(rows, 128, p, p, p, p, 0), lambda: P.init_running(rows, 128, p, p, 0),
+             lambda: P.finalize_out(2 * rows, 128, p, p, P.BF16, 0),
+             lambda: P.permute_rows((1 << 14, 1 << 14, 1), (256, 256, 256), (256, 256, 256), 256, p, p, 0),
+             lambda: P.reduce_replicas(1 << 20, 2, 1 << 14, p, p, 0)]
+    for desc, batch in ((half, 1 << 24), (f32, 1 << 24)):
+        desc.batch = batch
+        calls.append(lambda desc=desc: P.bwd_delta(desc, p, p, p, 0))
+    for call in calls:
+        with pytest.raises(P.LoongError) as e:
+            call()
+        assert e.value.code == P.E_UNSUPPORTED
