@@ -59,7 +59,8 @@ struct FwdParams {
   WorkMap map;     // units = batch x head groups, items = q tiles
 };
 
-template <int D, int KS>
+// WGS: workgroups that are to share a unit
+template <int D, int KS, int WGS>
 struct FwdCfg {
   static constexpr int NT = kFwdWaves * 64;
   static constexpr int NRB = kFwdWaves / KS;       // 32-row blocks per workgroup
@@ -70,9 +71,9 @@ struct FwdCfg {
   static constexpr int RP = 256 / ROWB;            // rows per 256 bytes (one sweep over all LDS banks)
   static constexpr int TILE_B = TK * ROWB;         // bytes of one K (or V) tile
   static constexpr int BUF_B = 2 * TILE_B;
-  // (head_dim 64: 64 KB of tiles and 128 registers, so that two workgroups share a unit: 4096 rows x 4096 keys x 8 heads
+  // (two workgroups per unit, head_dim 64: 64 KB of tiles and 128 registers; 4096 rows x 4096 keys x 8 heads
   // with four splits 57.7 -> 48.5 us, 9000 rows with one split 153 -> 120)
-  static constexpr int NBUF = BUF_B * 4 <= (D == 64 ? 65536 : 131072) ? 4 : 2;
+  static constexpr int NBUF = BUF_B * 4 <= (WGS == 2 ? 65536 : 131072) ? 4 : 2;
   static constexpr int PD = NBUF - 1;              // tiles in flight ahead of the one being used
   static constexpr int RPI = 1024 / ROWB;          // rows filled by one wave-level load
   static constexpr int KI = TILE_B / 1024 / kFwdWaves;  // loads per wave per K (or V) tile
@@ -83,9 +84,9 @@ struct FwdCfg {
   static_assert(KI >= 1 && KI * 1024 * kFwdWaves == TILE_B, "tile must split evenly over the waves");
 };
 
-template <class E, int D, int KS>
-__global__ __launch_bounds__(kFwdWaves * 64, D == 64 ? 4 : 2) void fwd_kernel(const FwdParams p) {
-  using C = FwdCfg<D, KS>;
+template <class E, int D, int KS, int WGS>
+__global__ __launch_bounds__(kFwdWaves * 64, 2 * WGS) void fwd_kernel(const FwdParams p) {
+  using C = FwdCfg<D, KS, WGS>;
   constexpr int NRB = C::NRB, BNS = C::BNS, TK = C::TK, NBUF = C::NBUF, PD = C::PD, KI = C::KI;
   constexpr int NJB = BNS / 32, NDB = D / 32, NKS = D / 16, ROWB = C::ROWB, CH = C::CH, RP = C::RP;
   __shared__ __attribute__((aligned(1024))) unsigned char smem[C::SMEM_BYTES];
@@ -468,7 +469,7 @@ __global__ __launch_bounds__(kFwdWaves * 64, D == 64 ? 4 : 2) void fwd_kernel(co
 }
 
 template <class E, int D, int KS>
-int launch_cfg(FwdParams& p, hipStream_t st) {
+int launch_cfg(FwdParams& p, int cus, hipStream_t st) {
   const RowTiling rt = make_row_tiling(p.g, p.G, p.Hq, p.B, kFwdWaves / KS, /*list_blind=*/!p.fuse || p.stored);  // unfused: blind rows get the neutral result
   p.GS = rt.GS; p.ntile[0] = rt.ntile[0]; p.ntile[1] = rt.ntile[1];
   p.tiles_total = rt.tiles_total; p.hgroups = rt.hgroups;
@@ -476,20 +477,28 @@ int launch_cfg(FwdParams& p, hipStream_t st) {
   if (total == 0) return LOONG_OK;
   if (!launch_fits(total + 7, kFwdWaves * 64)) return fail(LOONG_E_UNSUPPORTED, "forward grid too large");  // (padded to eight)
   p.map = make_work_map((int64_t)p.B * rt.hgroups, rt.tiles_total);
-  fwd_kernel<E, D, KS><<<dim3(p.map.grid), dim3(kFwdWaves * 64), 0, st>>>(p);
+  // two workgroups share a unit where the tiles of both fit (head_dim 64) and there are more than units; if not, the tiles
+  // of one are staged four deep instead of two (2048 rows x 16384 keys x 4 heads, four splits, 128 workgroups: 102.7 -> 99 us)
+  const dim3 grid(p.map.grid), block(kFwdWaves * 64);
+  if constexpr (D == 64) {
+    if (KS < 4 || total > cus) fwd_kernel<E, D, KS, 2><<<grid, block, 0, st>>>(p);
+    else fwd_kernel<E, D, 4, 1><<<grid, block, 0, st>>>(p);
+  } else {
+    fwd_kernel<E, D, KS, 1><<<grid, block, 0, st>>>(p);
+  }
   return check_launch("loong_attn_step_fwd (bf16)");
 }
 
 template <class E>
-int pick_cfg(FwdParams& p, int head_dim, int ks, hipStream_t st) {
+int pick_cfg(FwdParams& p, int head_dim, int ks, int cus, hipStream_t st) {
   if (head_dim == 128) {
-    if (ks == 1) return launch_cfg<E, 128, 1>(p, st);
-    if (ks == 2) return launch_cfg<E, 128, 2>(p, st);
-    return launch_cfg<E, 128, 4>(p, st);
+    if (ks == 1) return launch_cfg<E, 128, 1>(p, cus, st);
+    if (ks == 2) return launch_cfg<E, 128, 2>(p, cus, st);
+    return launch_cfg<E, 128, 4>(p, cus, st);
   }
-  if (ks == 1) return launch_cfg<E, 64, 1>(p, st);
-  if (ks == 2) return launch_cfg<E, 64, 2>(p, st);
-  return launch_cfg<E, 64, 4>(p, st);
+  if (ks == 1) return launch_cfg<E, 64, 1>(p, cus, st);
+  if (ks == 2) return launch_cfg<E, 64, 2>(p, cus, st);
+  return launch_cfg<E, 64, 4>(p, cus, st);
 }
 
 }  // namespace
@@ -506,8 +515,8 @@ int launch_fwd_bf16(const loong_step_desc& d, const StepGeom& g, const void* q, 
   DeviceFacts dev;
   if (int rc = device_facts(&dev)) return rc;
   const int ks = pick_key_splits(g, p.G, p.Hq, p.B, forced_key_splits(d.flags), dev.cus);
-  if (d.dtype == LOONG_FP16) return pick_cfg<Fp16>(p, d.head_dim, ks, st);
-  return pick_cfg<Bf16>(p, d.head_dim, ks, st);
+  if (d.dtype == LOONG_FP16) return pick_cfg<Fp16>(p, d.head_dim, ks, dev.cus, st);
+  return pick_cfg<Bf16>(p, d.head_dim, ks, dev.cus, st);
 }
 
 }  // namespace loong

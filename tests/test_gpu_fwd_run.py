@@ -107,3 +107,23 @@ def test_strided_tensors_on_another_stream_give_the_same_bits(cp, rank, hq, hkv,
     assert torch.equal(out, rep.out) and torch.equal(lse, rep.lse) and torch.equal(o, rep.o)
     gaps = out.permute(0, 2, 1, 3).as_strided((batch, 2 * c, hq, 4), (out.stride(0), out.stride(2), out.stride(1), 1), d)
     assert bool(gaps.isnan().all())
+
+
+@pytest.mark.parametrize("lq", [1, 64, 2048, 2049])
+@pytest.mark.parametrize("lk", [1, 127, 128, 129, 300, 513, 1000])
+def test_either_depth_of_staged_tiles_gives_the_same_bits(lq, lk):
+    """head_dim 64 with four key splits: tiles four deep in up to 256 workgroups of 64 rows, two deep in more.  The head of a launch
+    of the first kind equals the same head in one of the second, key counts either side of one to four tiles of 128."""
+    g = torch.Generator(device=DEV).manual_seed(lq + lk)
+    mk = lambda n: (torch.randn(1, n, 64, device=DEV, generator=g) * 0.5).to(torch.bfloat16)
+    q, k, v = mk(lq), mk(lk), mk(lk)
+    res = []
+    for batch in (1, -(-257 // (-(-lq // 64)))):   # `batch` copies of the first head are more than 256 workgroups
+        rep = lambda x: x[:1].expand(batch, -1, -1)[:, None].contiguous()
+        out, lse = torch.empty(batch, 1, lq, 64, device=DEV), torch.empty(batch, 1, lq, device=DEV)
+        P.attn_step_fwd(P.make_desc(batch=batch, n_q_heads=1, n_kv_heads=1, head_dim=64, q_len=lq, kv_len=lk, dtype=P.BF16,
+                                    softmax_scale=0.125, flags=P.key_splits(4)), rep(q), rep(k), rep(v), out, lse)
+        res.append((out[0], lse[0], out[-1], lse[-1]))
+    assert all(torch.equal(a, b) for a, b in zip(*res))
+    s = (q[0].double() @ k[0].double().t().contiguous()) * 0.125
+    assert float((res[0][0][0] - torch.softmax(s, -1) @ v[0].double()).abs().max()) < 2e-2
