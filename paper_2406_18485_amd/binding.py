@@ -121,6 +121,18 @@ def _ptr(x):
     return x.data_ptr()
 
 
+def pointer_array(addresses):
+    """Host array of device addresses (ints), as the calls over several steps take it."""
+    return (_vp * len(addresses))(*addresses)
+
+
+def _ptrs(items, n):
+    """The same of n tensors or pointers; one that is already made is passed through."""
+    if isinstance(items, C.Array) and len(items) == n:
+        return items
+    return (_vp * n)(*map(_ptr, items))   # (of fewer the rest is NULL, of more this fails)
+
+
 _current_stream = None  # what _find_current_stream found
 
 
@@ -246,8 +258,8 @@ def attn_step_fwd(desc: StepDesc, q, k, v, out, lse, stream=None):
 
 def attn_steps_fwd(descs, q, k, v, out, lse, o=None, stream=None):
     """loong_attn_steps_fwd: `descs` is a ctypes array of StepDesc; k, v hold one tensor (or pointer) per step."""
-    kp, vp = ((_vp * len(descs))(*map(_ptr, x)) for x in (k, v))
-    _check(lib.loong_attn_steps_fwd(descs, len(descs), _ptr(q), kp, vp, _ptr(out), _ptr(lse), _ptr(o), _stream(stream)))
+    n = len(descs)
+    _check(lib.loong_attn_steps_fwd(descs, n, _ptr(q), _ptrs(k, n), _ptrs(v, n), _ptr(out), _ptr(lse), _ptr(o), _stream(stream)))
 
 
 def lse_merge(rows: int, head_dim: int, out, lse, block_out, block_lse, stream=None):
@@ -274,9 +286,9 @@ def workspace_bytes_steps(descs) -> int:
 
 def attn_steps_bwd(descs, q, k, v, o, d_o, lse, delta, dq, dk, dv, workspace, stream=None):
     """loong_attn_steps_bwd: `descs` is a ctypes array of StepDesc; k, v, dk, dv hold one tensor (or pointer) per step."""
-    ptrs = [(_vp * len(descs))(*map(_ptr, x)) for x in (k, v, dk, dv)]
-    _check(lib.loong_attn_steps_bwd(descs, len(descs), _ptr(q), ptrs[0], ptrs[1], _ptr(o), _ptr(d_o), _ptr(lse), _ptr(delta),
-                                    _ptr(dq), ptrs[2], ptrs[3], _ptr(workspace), workspace.numel() * workspace.element_size(),
+    n = len(descs)
+    _check(lib.loong_attn_steps_bwd(descs, n, _ptr(q), _ptrs(k, n), _ptrs(v, n), _ptr(o), _ptr(d_o), _ptr(lse), _ptr(delta),
+                                    _ptr(dq), _ptrs(dk, n), _ptrs(dv, n), _ptr(workspace), workspace.numel() * workspace.element_size(),
                                     _stream(stream)))
 
 

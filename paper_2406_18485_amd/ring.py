@@ -8,7 +8,7 @@ for device memory and the stream only.
 """
 from __future__ import annotations
 
-from dataclasses import dataclass, replace
+from dataclasses import dataclass
 
 import torch
 
@@ -46,14 +46,14 @@ def _desc(shape: RingShape, step: dict, flags: int) -> B.StepDesc:
                        flags=flags | shape.extra_flags)
 
 
-def _visited(chunks, order) -> list:
-    """chunks[src] for every src of `order`, of a stacked tensor their device pointers (it is not sliced for it).  The
+def _visited(chunks, order, last):
+    """chunks[src] for every src of `order` (the largest is `last`), of a stacked tensor their device pointers (it is not sliced for it).  The
     items themselves are returned, not their pointers: one that `chunks` made for this call lives until it has been used."""
     if isinstance(chunks, torch.Tensor):
-        if max(order) >= chunks.shape[0]:
-            raise IndexError(f"source rank {max(order)} is out of range of {chunks.shape[0]} chunks")
+        if last >= chunks.shape[0]:
+            raise IndexError(f"source rank {last} is out of range of {chunks.shape[0]} chunks")
         base, step = chunks.data_ptr(), chunks.stride(0) * chunks.element_size()
-        return [base + src * step for src in order]
+        return B.pointer_array([base + src * step for src in order])
     return [chunks[src] for src in order]
 
 
@@ -87,8 +87,9 @@ class RingReplay:
     # ---- what the calls take of the shape and the plan, kept between them
     def _prepare(self):
         s = self.shape
-        self._prepared = replace(s), [dict(step) for step in self.plan]
+        self._prepared = dict(vars(s)), [dict(step) for step in self.plan]
         self._order = [step["src_rank"] for step in self.plan]
+        self._last = max(self._order)
         descs = B.StepDesc * len(self.plan)
         self._fwd_descs = descs(*(_desc(s, step, 0) for step in self.plan))
         # the same where every step is a call: the first writes the running result, the others merge into it
@@ -111,7 +112,7 @@ class RingReplay:
 
     def _follow(self):
         """The program may have changed `shape` (its scale, its extra flags) or `plan` since the last call."""
-        if (self.shape, self.plan) != self._prepared:
+        if vars(self.shape) != self._prepared[0] or self.plan != self._prepared[1]:
             self._prepare()
 
     # ---- forward: cp x (Attention [+ Update]) then the cast to the stored activation type
@@ -121,7 +122,7 @@ class RingReplay:
         if fuse_merge:
             # the first visit writes the running result (rows that see nothing get the neutral
             # element), the later ones merge into it (no separate initialisation), the last stores o too
-            k, v = (_visited(x, self._order) for x in (k_by_src, v_by_src))
+            k, v = (_visited(x, self._order, self._last) for x in (k_by_src, v_by_src))
             B.attn_steps_fwd(self._fwd_descs, q, k, v, self.out, self.lse, self.o, stream)
             return
         B.init_running(self.rows, s.d, self.out, self.lse, stream)
@@ -138,7 +139,7 @@ class RingReplay:
         self._follow()
         if self.shape.extra_flags & B.BWD_ONLY_DKV:   # (the steps leave dq alone)
             self.dq.zero_()
-        k, v, dk, dv = (_visited(x, self._order) for x in (k_by_src, v_by_src, self.dk, self.dv))
+        k, v, dk, dv = (_visited(x, self._order, self._last) for x in (k_by_src, v_by_src, self.dk, self.dv))
         B.attn_steps_bwd(self._bwd_descs, q, k, v, self.o, d_o, self.lse, self.delta, self.dq, dk, dv, self.workspace,
                          stream=stream)
 
