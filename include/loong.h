@@ -52,9 +52,9 @@ extern "C" {
 
 /* storage type of q, k, v, o, d_o */
 #define LOONG_BF16 0              /* bf16 MFMA kernels, head_dim 64 or 128 */
-#define LOONG_FP32 1              /* fp32 storage, head_dim <= 128, multiple of 4: a correctness path for small
-                                     cases (one wave per row, plain fp32 multiply-adds, no matrix cores, no
-                                     tiling): far from any roofline and not meant for long sequences */
+#define LOONG_FP32 1              /* fp32 storage, head_dim <= 128, multiple of 4: a correctness path for small cases on
+                                     the fp32 matrix instruction (nothing is rounded to a shorter type), a sixteenth of the
+                                     16-bit rate at best and not meant for long sequences */
 #define LOONG_FP16 2              /* the MFMA kernels on IEEE half storage (the 16-bit type Sec. "Performance
                                      Analysis" sizes the tensors in), head_dim 64 or 128 */
 

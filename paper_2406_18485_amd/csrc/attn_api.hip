@@ -27,11 +27,12 @@ int check_run(const loong_step_desc* descs, int t, StepGeom* g) {
 }
 
 // Steps of a valid run that go into one launch.  More steps hide more ramps and ragged ends, but the
-// key-owning workgroups of a long launch drift apart and no longer find each other's query tiles in L2: a
-// launch takes steps up to about 1.3 ms of work (the rate at head_dim 64 is 0.6 of that at 128), and never splits one.  Backward passes with 1 / 2 / 4 / all steps per
-// launch: 8 steps of 98 us (4 heads x 4096 rows) 781 / 676 / 525 / 472 us, 8 of 425 us (8 x 8192 rows, one kv
-// head) 3398 / 3365 / 3247 / 3313, 8 of 820 us (4 x 16384) 6541 / 6477 / 6503 / 6707, 4 of 1090 us
-// (8 x 16000 rows, head_dim 64) 4352 / 4727 / 5118 / 5066.
+// key-owning workgroups of a long launch drift apart and no longer find each other's query tiles in L2.  The run is
+// cut into as many launches as its operations hold budgets of 9.4e9 head_dim (1.2e12 at 128, some 1.3 ms), and the steps
+// are dealt out evenly, rounded up: no launch splits a step, and one may hold up to two budgets (two steps
+// of 820 us below).  Backward passes with 1 / 2 / 4 / all steps per launch, and by the rule: 8 steps of 98 us (4 heads
+// x 4096 rows) 788 / 693 / 546 / 469 us, 469; 8 of 420 us (8 x 8192 rows, one kv head) 3365 / 3336 / 3231 / 3341, 3342; 8 of 800
+// us (4 x 16384) 6424 / 6436 / 6513 / 6779, 6437; 4 of 1010 us (8 x 16000 rows, head_dim 64) 4052 / 4510 / 4777 / 4817, 4058.
 int steps_per_launch(const loong_step_desc* descs, int n_steps) {
   const loong_step_desc& d = descs[0];
   double pairs = 0;

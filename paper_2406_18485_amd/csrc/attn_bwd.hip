@@ -119,14 +119,14 @@ size_t partial_bytes(const SplitPlan& s, int head_dim) {
 // key-owning workgroups come first (they are the longer ones) and the row-owning ones fill the compute
 // units as these finish: no gap and no second ramp between the halves, and where neither half has
 // a workgroup for every unit they run side by side.  A whole step, two launches (and the passes that
-// cleared counters and unseen keys) -> one: 2048 rows x 4096 keys x 8 heads 119.5 -> 116.2 us, the step
-// of the same work whose keys are half unseen 135.3 -> 116.0, 3000 x 5000 without mask 315 -> 216,
-// 400 rows x 200 keys x 4 heads 45 -> 19, 32768 x 16384 x 4 heads 3030 -> 3012.
+// cleared counters and unseen keys) -> one: 2048 rows x 4096 keys x 8 heads 125.1 -> 118.3 us, the step
+// of the same work whose keys are half unseen 136.6 -> 124.5, 3000 x 5000 without mask 317 -> 211,
+// 400 rows x 200 keys x 4 heads 33 -> 20, 32768 x 16384 x 4 heads 3123 -> 3084.
 // With several steps in the launch the row-owning workgroups are the longer ones (their loop runs over the
 // keys of every step, dQ stays in registers throughout) and come first; the key tiles of all
 // steps fill the chip, so few query loops are shared and one ramp and one ragged end serve all steps.
-// A backward pass step by step -> as a run: 8 steps of 2048 rows x 4096 keys x 8 heads 1036 -> 850 us, 32 steps of
-// 2048 rows x 4 heads, one kv head 1522 -> 510, 4 steps of 400 rows x 4 heads 163 -> 81 (with its forward).
+// A backward pass, a launch per step -> the run: 8 steps of 2048 rows x 4096 keys x 8 heads 1003 -> 851 us, 32 steps of
+// 2048 rows x 4 heads, one kv head 1395 -> 529, 4 steps of 400 rows x 4 heads 158 -> 77 (with its forward).
 // (Key-owning workgroups first in a run: 7 % slower at 8 x 2048 rows.  A split so fine that a key tile's loop
 // is 0.15 of a unit's time, not 0.3: 1 % slower there, 3 % at 8 heads x 3998 rows, head_dim 64.)
 template <class E, int D>

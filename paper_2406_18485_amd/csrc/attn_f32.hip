@@ -20,7 +20,10 @@
 //
 // Against one wave per row with vector multiply-adds (a pass of a replay): 2 x 256 rows, 4 x 256 keys, d = 64,
 // forward and backward 580 -> 102 us; 16 heads x 1024 rows, 2 x 1024 keys, d = 128 forward 1914 -> 130 us,
-// backward 8494 -> 464 us.  The distance from 64-bit results fell too (gradients 5.0e-7 -> 4.3e-7 relative).
+// backward 8494 -> 464 us.  Head dimensions other than 32, 64 and 128 take the kernels of 128 with the pieces past
+// the end masked: up to 3.5 times the products (head_dim 36), the 16-row forward holds 37 registers of a lane in memory,
+// the backward runs one wave per SIMD; still below one wave per row (4 heads x 500 rows, head_dim 36, forward 82.1 -> 25.5 us,
+// backward 198 -> 37.8).  The distance from 64-bit results fell too (gradients 5.0e-7 -> 4.3e-7 relative).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>

@@ -28,7 +28,7 @@ __global__ __launch_bounds__(256) void permute_rows_kernel(PermuteParams p, cons
 // flight at one time then read and write the same few c of every (a, b).  Token-major heads are so read as whole
 // tokens, where c innermost read one head of many tokens, 256 bytes in every 8 KB.  A piece whose source does not
 // depend on b (replication) is read once.  Bound by HBM and, at these sizes, by the call: 32 heads x 4096 tokens x 256
-// bytes packed 14.2 -> 11.0 us (a plain copy of the bytes: 9.1), x 16000 tokens 52.2 -> 48.0, replicated twice
+// bytes packed 14.2 -> 11.1 us (a plain copy of the bytes: 9.1), x 16000 tokens 52.2 -> 47.6, replicated four times
 // 36.2 -> 33.7.  (Two or four pieces per thread in the c-innermost order: 22 us for the first.)
 struct ChunkParams {
   uint32_t rows, ab, n1, n2, pieces;   // rows per workgroup; n0 * n1

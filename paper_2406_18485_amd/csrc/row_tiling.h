@@ -36,9 +36,10 @@ inline int64_t busy_row_tiles(const StepGeom& g, int bmh) {
 // split that puts a workgroup on (nearly) every compute unit is taken (measured on
 // 32K..1M-token shapes: one more split than that is always slower, one fewer leaves units idle).
 // (A forward step timed by rounds of workgroups would take other splits at some sizes, 8 heads x 2304 rows x 4096 keys
-// 79.7 -> 66.7 us with two, not four; but the split decides where the lagging maxima stand and in which order a row's exponentials are
-// added, and its results lie further from 64 bits then: LSE 2.2e-7 -> 3.0e-7 at 3 heads x 11212 rows, 16 steps, out
-// 1.614e-3 -> 1.619e-3 at groups of three heads x 1554 rows, 3 steps.)
+// 79.7 -> 66.7 us with two, not four, a replay of 8 steps of 2 heads x 23670 rows 3231 -> 2799; but the split decides where
+// the lagging maxima stand and in which order a row's exponentials are added, and the results lie further from 64 bits
+// then: LSE 2.2e-7 -> 3.0e-7 at 3 heads x 11212 rows, 16 steps, out 1.614e-3 -> 1.619e-3 at groups of three heads x
+// 1554 rows, 3 steps.)
 // `forced` (1, 2 or 4, from the descriptor's flags) overrides the choice; `cus` is the device's
 // number of compute units.
 inline int pick_key_splits(const StepGeom& g, int G, int Hq, int B, int forced, int cus) {
