@@ -89,7 +89,7 @@ class RingReplay:
         s = self.shape
         self._prepared = dict(vars(s)), [dict(step) for step in self.plan]
         self._order = [step["src_rank"] for step in self.plan]
-        self._last = max(self._order)
+        self._last, self._repeats = max(self._order), len(set(self._order)) < len(self._order)
         descs = B.StepDesc * len(self.plan)
         self._fwd_descs = descs(*(_desc(s, step, 0) for step in self.plan))
         # the same where every step is a call: the first writes the running result, the others merge into it
@@ -140,6 +140,14 @@ class RingReplay:
         if self.shape.extra_flags & B.BWD_ONLY_DKV:   # (the steps leave dq alone)
             self.dq.zero_()
         k, v, dk, dv = (_visited(x, self._order, self._last) for x in (k_by_src, v_by_src, self.dk, self.dv))
+        if self._repeats:   # the steps of a run need gradients of their own: one after the other
+            for t, desc in enumerate(self._bwd_descs):
+                step = B.StepDesc.from_buffer_copy(desc)
+                if t:
+                    step.flags &= ~(B.COMPUTE_DELTA | B.OVERWRITE_DQ)
+                B.attn_step_bwd(step, q, k[t], v[t], self.o, d_o, self.lse, self.delta, self.dq, dk[t], dv[t], self.workspace,
+                                stream=stream)
+            return
         B.attn_steps_bwd(self._bwd_descs, q, k, v, self.o, d_o, self.lse, self.delta, self.dq, dk, dv, self.workspace,
                          stream=stream)
 

@@ -169,3 +169,16 @@ def test_strided_run_gives_the_same_bits_and_a_cut_one_the_same_sums(cp, rank, h
     longest = max(cp * 2 * c, 2 * c * hq // hkv) // 16   # additions in the longest chain: a row's keys, a key's rows
     for a, b in zip(want, (rep.dq, rep.dk, rep.dv)):
         _close(a, b, max(1e-4, 2 * longest * 2.0 ** -24))
+
+
+def test_a_source_visited_twice_counts_twice():
+    """The second visit writes the same dk and dv again and adds its share of dq to the first's."""
+    rep, q, k, v, d_o = _replay(3, 3, 1, 4, 2, 64, 161, 1)
+    plan = rep.plan
+    rep.plan = [plan[1]]
+    rep.backward(q, k, v, d_o)
+    want = rep.dq.clone()
+    rep.plan = [plan[1], plan[1]]
+    rep.backward(q, k, v, d_o)
+    assert torch.isfinite(rep.dk[plan[1]["src_rank"]]).all()
+    _close(rep.dq, 2 * want)

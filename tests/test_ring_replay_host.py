@@ -167,3 +167,21 @@ def test_dq_is_zero_when_the_steps_leave_it_alone(replay):
     replay.shape.extra_flags = P.BWD_ONLY_DKV
     replay.backward(q, full, full, q)
     assert bool((replay.dq == 0.0).all())
+
+
+def test_a_plan_that_visits_a_source_again_runs_step_by_step(replay):
+    """Two steps of a run may not share dk and dv; one after the other they may, each writing or adding in its turn."""
+    q, full = _inputs(CP)
+    replay.plan = [replay.plan[1], replay.plan[0], replay.plan[1]]
+    seen = []
+
+    def look(name, args):
+        assert name != "loong_attn_steps_bwd"
+        if name == "loong_attn_step_bwd":
+            seen.append((args[0]._obj.flags & (P.COMPUTE_DELTA | P.OVERWRITE_DQ), args[2], args[9]))
+    replay.look = look
+    replay.backward(q, full, full, q)
+    order = [step["src_rank"] for step in replay.plan]
+    assert [k for _, k, _ in seen] == [full[src].data_ptr() for src in order]
+    assert [dk for _, _, dk in seen] == [replay.dk[src].data_ptr() for src in order]
+    assert [flags for flags, _, _ in seen] == [P.COMPUTE_DELTA | P.OVERWRITE_DQ, 0, 0]
