@@ -2,10 +2,11 @@
 // are all resident.  The kernels take the table by value and index it with workgroup-uniform values
 // (scalar loads, once per chunk).
 //
-// A kernel argument comes from memory that no cache holds when a launch begins, about a microsecond a look, and a look
-// that needs the last one's answer pays again: entry, then step, then pointer made a key tile's prologue three looks
-// longer.  So what a launch over one step reads (two entries, one step) lies at fixed places, is loaded together
-// (scalar_now keeps the compiler from choosing an address first and loading then) and only later entries are looked up.
+// A look at a kernel argument is a round trip to memory, and one that needs the last one's answer pays again: entry,
+// then step, then pointer made a key tile's prologue three looks longer.  So what a launch over one step reads (two
+// entries, one step) lies at fixed places, is loaded together (scalar_now keeps the compiler from choosing an address
+// first and loading then) and only later entries are looked up.  A whole step of 64 x 8 heads, 1 row x 1024 keys, head_dim 128:
+// 321 -> 271 us, with the fragments of bwd_dkv_body.h requested together.
 #pragma once
 #include <stdint.h>
 
