@@ -16,6 +16,9 @@
 namespace loong {
 namespace {
 
+// workgroups that run on a compute unit together (registers, LDS)
+constexpr int wgs_per_unit(int head_dim) { return head_dim == 64 ? 2 : 1; }
+
 constexpr double kLoopShare = 0.3;  // several steps per launch: a key tile's loop over the time of a unit
 constexpr double kRowShare = 0.8;   // the same for the loop of a row-owning workgroup, which starts first
 
@@ -36,7 +39,7 @@ struct SplitPlan {
   double per_cu, longest_loop, longest_row;  // multiply-adds per head_dim: all / CUs; of a key tile's loop; of a row's keys
 };
 
-SplitPlan plan_split(const StepGeom* g, int n, int G, int Hkv, int B, int q_len, int cus, StepTable* tab) {
+SplitPlan plan_split(const StepGeom* g, int n, int G, int Hkv, int B, int q_len, int cus, int per_unit, StepTable* tab) {
   constexpr int BM = kBwdBM, BN = kBwdBN;
   SplitPlan s{};
   uint32_t entry[kMaxHalves];
@@ -95,7 +98,13 @@ SplitPlan plan_split(const StepGeom* g, int n, int G, int Hkv, int B, int q_len,
     // one step: more than one workgroup when the listed tiles are fewer than the compute units, and
     // twice as many when a diagonal block makes the loop lengths uneven
     if (s.busy > 0 && s.busy < cus) nsplit = (int)std::min<int64_t>((cus + s.busy - 1) / s.busy, 16);
-    if (diag && s.busy * nsplit <= 2 * cus) nsplit *= 2;
+    // Where the chip holds more workgroups than units (head_dim 64), loops that stay long are split until it is full; the exchange
+    // costs some 12 us.  dK/dV alone, a workgroup per unit / a full chip: 128 tiles in a loop, 8 heads on 2 x 2000 rows x 20000 keys
+    // 247 / 219 us; 256 tiles in either of two, 8192 x 8192 310 / 276; 32 and 24 tiles 67 / 69 and 53 / 53; 8 tiles (8 heads on 2 x
+    // 121 x 20787) 23 / 35.
+    if (s.busy > 0 && s.busy * nsplit < (int64_t)per_unit * cus && q_tiles / nsplit >= 48)
+      nsplit = (int)std::min<int64_t>((per_unit * cus + s.busy - 1) / s.busy, 16);
+    if (diag && s.busy * nsplit <= 2 * cus) nsplit *= 2;  // (at head_dim 64 at most 1024 parts of 64 KB: the static scratch holds them)
   } else if (s.busy > 0) {
     // several steps: the tiles fill the chip, the split keeps the longest loop a small part of a unit's time
     nsplit = (int)std::min(std::max(std::ceil(s.longest_loop / (kLoopShare * s.per_cu)), 1.), 16.);
@@ -130,19 +139,19 @@ size_t partial_bytes(const SplitPlan& s, int head_dim) {
 // (Key-owning workgroups first in a run: 7 % slower at 8 x 2048 rows.  A split so fine that a key tile's loop
 // is 0.15 of a unit's time, not 0.3: 1 % slower there, 3 % at 8 heads x 3998 rows, head_dim 64.)
 template <class E, int D>
-__global__ __launch_bounds__(kBwdWaves * 64) void bwd_dkv_kernel(const StepTable tab, const DkvParams p) {
+__global__ __launch_bounds__(kBwdWaves * 64, 2 * wgs_per_unit(D)) void bwd_dkv_kernel(const StepTable tab, const DkvParams p) {
   __shared__ __attribute__((aligned(1024))) unsigned char smem[BwdCfg<D>::SMEM_BYTES];
   dkv_body<E, D>(tab, p, blockIdx.x, smem);
 }
 
 template <class E, int D, int KS>
-__global__ __launch_bounds__(kRowWaves * 64) void dq_kernel(const StepTable tab, const DqParams p) {
+__global__ __launch_bounds__(kRowWaves * 64, 2 * wgs_per_unit(D)) void dq_kernel(const StepTable tab, const DqParams p) {
   __shared__ __attribute__((aligned(1024))) unsigned char smem[DqCfg<D, KS>::SMEM_BYTES];
   dq_body<E, D, KS>(tab, p, blockIdx.x, smem);
 }
 
 template <class E, int D, int KS>
-__global__ __launch_bounds__(kBwdWaves * 64) void bwd_step_kernel(const StepTable tab, const DkvParams pk, const DqParams pq) {
+__global__ __launch_bounds__(kBwdWaves * 64, 2 * wgs_per_unit(D)) void bwd_step_kernel(const StepTable tab, const DkvParams pk, const DqParams pq) {
   constexpr int BYTES = BwdCfg<D>::SMEM_BYTES > DqCfg<D, KS>::SMEM_BYTES ? BwdCfg<D>::SMEM_BYTES : DqCfg<D, KS>::SMEM_BYTES;
   static_assert(kBwdWaves == kRowWaves, "one workgroup size for both halves");
   __shared__ __attribute__((aligned(1024))) unsigned char smem[BYTES];
@@ -248,7 +257,7 @@ int launch_bwd_bf16(const loong_step_desc& d, const StepGeom* g, int n, const Bw
     c.k = (const uint16_t*)k[t]; c.v = (const uint16_t*)v[t];
     if (s.do_kv) { c.dk = dk[t]; c.dv = dv[t]; }
   }
-  const SplitPlan plan = plan_split(g, n, G, d.n_kv_heads, d.batch, d.q_len, planning_cus(), &s.tab);
+  const SplitPlan plan = plan_split(g, n, G, d.n_kv_heads, d.batch, d.q_len, planning_cus(), wgs_per_unit(d.head_dim), &s.tab);
   s.rows = g[0];
   for (int t = 1; t < n; ++t)  // (which segments see keys at all is what the row tiling asks)
     for (int a = 0; a < g[t].nq; ++a)
@@ -281,7 +290,7 @@ int launch_bwd_bf16(const loong_step_desc& d, const StepGeom* g, int n, const Bw
     for (ks = 1; ks < 4 && s.do_kv && plan.longest_row * (32 * kRowWaves / ks) > kRowShare * plan.per_cu;) ks *= 2;
     if (!s.do_kv) ks = 0;
   }
-  if (!ks) ks = pick_key_splits(s.rows, G, d.n_q_heads, d.batch, 0, dev.cus);
+  if (!ks) ks = pick_key_splits(s.rows, G, d.n_q_heads, d.batch, 0, dev.cus * wgs_per_unit(d.head_dim));
   if (s.do_q)
     if (int rc = plan_dq(s, ks)) return rc;
   const int64_t n4 = (int64_t)d.batch * d.n_kv_heads * d.kv_len * d.head_dim / 4, clear_grid = (n4 + 255) / 256;
@@ -307,7 +316,7 @@ int64_t bwd_steps_that_fit_bf16(const loong_step_desc& d, const StepGeom& g) {
 
 int64_t bwd_workspace_bytes_bf16(const loong_step_desc& d, const StepGeom* g, int n) {
   if (d.kv_len == 0 || d.batch == 0 || (d.flags & LOONG_BWD_ONLY_DQ)) return 0;
-  const SplitPlan plan = plan_split(g, n, d.n_q_heads / d.n_kv_heads, d.n_kv_heads, d.batch, d.q_len, planning_cus(), nullptr);
+  const SplitPlan plan = plan_split(g, n, d.n_q_heads / d.n_kv_heads, d.n_kv_heads, d.batch, d.q_len, planning_cus(), wgs_per_unit(d.head_dim), nullptr);
   return plan.nsplit > 1 ? kWsHeadBytes + (int64_t)partial_bytes(plan, d.head_dim) : 0;
 }
 

@@ -74,10 +74,25 @@ struct BwdCfg {
   static constexpr int RPI = 1024 / ROWB;          // rows filled by one wave-level load
   static constexpr int QT_B = BM * ROWB;           // bytes of a Q (or dO) tile
   static constexpr int LI = QT_B / 1024 / 4;       // loads per staging wave (the four E waves) per Q (or dO) tile
-  static constexpr int STAGE_B = 2 * QT_B + 2 * BM * 4;  // Q, dO, lse, delta
-  static constexpr int NSTAGE = 3;                 // tile being staged, tile of the P waves, tile of the E waves
+  // head_dim 64 runs two workgroups per unit: one's prologue, epilogue and exchange of partial sums run beside the other's
+  // loop, and four waves per SIMD leave the vector port idle less.  That takes at most 128 registers (operands requested three
+  // steps ahead, not four) and half the LDS: the Q rows keep three stages (tile being staged, tile of the P waves, tile of the E
+  // waves), but both roles use the dO rows of the E waves' tile only, so these are staged an iteration later, in two (LATE_O).
+  // There the P waves, whose exponentials weigh twice as much beside their matrix work, are the longer path, so the exponent
+  // offsets of a tile's rows are formed once, by the E wave that fetches their LSE (OFFSETS).  dK/dV alone, one workgroup per
+  // unit -> two -> with OFFSETS: 1500 rows x 4100 keys x 2 x 8 heads 116 -> 101 -> 87 us, 8192 x 8192 x 8 heads on 2
+  // 298 -> 310 -> 275 (the last with twice the workgroups per query loop), 16384 x 16384 x 8 1165 -> 1040 -> 1023.
+  // At head_dim 128 (registers for one workgroup) both cost: late dO 874 -> 905 us (16384 x 16384 x 4 heads), OFFSETS 516 -> 545
+  // (8 steps of 2048 rows x 8 heads): the E waves' path is the longer one there.
+  static constexpr bool LATE_O = D == 64, OFFSETS = D == 64;
+  static constexpr int NSTAGE_Q = 3, NSTAGE_O = LATE_O ? 2 : 3;
+  static constexpr int Q_STRIDE = (LATE_O ? 1 : 2) * (QT_B + BM * 4), O_STRIDE = Q_STRIDE;
+  static constexpr int O_OFF = LATE_O ? NSTAGE_Q * Q_STRIDE : QT_B;            // first dO stage
+  static constexpr int LSE_OFF = LATE_O ? QT_B : 2 * QT_B;                     // from the start of a Q stage
+  static constexpr int DELTA_OFF = LATE_O ? QT_B : QT_B + BM * 4;              // from the start of a dO stage
+  static constexpr int XCH_OFF = LATE_O ? O_OFF + NSTAGE_O * O_STRIDE : NSTAGE_Q * Q_STRIDE;
   static constexpr int XCH_B = 4 * 2 * 2 * 1024;   // P hand-over: 4 key groups x 2 blocks x 2 halves x 64 lanes x 16 B
-  static constexpr int ROLE_OFF = NSTAGE * STAGE_B + 2 * XCH_B;  // shared loops: what arrive() said
+  static constexpr int ROLE_OFF = XCH_OFF + 2 * XCH_B;  // shared loops: what arrive() said
   static constexpr int SMEM_BYTES = ROLE_OFF + 16;
   static_assert(LI >= 1 && LI * 1024 * 4 == QT_B, "tile must split evenly over the staging waves");
 };
@@ -168,22 +183,18 @@ __device__ __forceinline__ void dkv_body(const StepTable& tab, const DkvParams& 
   uint32_t ld_off[LI];  // byte offset of this lane's piece from the tile's first row
 #pragma unroll
   for (int i = 0; i < LI; ++i) ld_off[i] = (uint32_t)(ld_row + i * 4 * C::RPI) * q_rowbytes + ld_piece;
-  // A operand of S / T: row l32 (+32 ib), pieces 2 ks + hh
-  uint32_t row_rd[NKS];
+  // A operand of S / T: row l32 (+32 ib), pieces 2 ks + hh; transposing reads of a row-major tile: run of four rows starting
+  // at 4 hh (+8 for the second run; +16 sl, +32 ib as constants), 16-column strip (lane >> 4) & 1 of block db
+  uint32_t row_rd[NKS], tr_lo[NDB], tr_hi[NDB];
 #pragma unroll
-  for (int ks = 0; ks < NKS; ++ks) row_rd[ks] = l32 * ROWB + ((2 * ks + hh) ^ tile_swizzle<D>(l32)) * 16;
-  // transposing reads of a row-major tile: run of four rows starting at 4 hh (+8 for the
-  // second run; +16 sl, +32 ib as constants), 16-column strip (lane >> 4) & 1 of block db
-  const int i16 = lane & 15, tr_r = i16 >> 2, tr_q = i16 & 3, strip = (lane >> 4) & 1;
-  uint32_t tr_lo[NDB], tr_hi[NDB];
+  for (int ks = 0; ks < NKS; ++ks) row_rd[ks] = row_read_base<D>(lane) ^ row_read_xor(ks);
 #pragma unroll
   for (int db = 0; db < NDB; ++db) {
-    const int piece = db * 4 + strip * 2 + (tr_q >> 1);
-    tr_lo[db] = (4 * hh + tr_r) * ROWB + (piece ^ tile_swizzle<D>(4 * hh + tr_r)) * 16 + (tr_q & 1) * 8;
-    tr_hi[db] = (4 * hh + tr_r + 8) * ROWB + (piece ^ tile_swizzle<D>(4 * hh + tr_r + 8)) * 16 + (tr_q & 1) * 8;
+    tr_lo[db] = tr_read_base<D>(lane) ^ tr_read_xor(db, 0);
+    tr_hi[db] = (tr_read_base<D>(lane) ^ tr_read_xor(db, 1)) + 8 * ROWB;
   }
   // P hand-over slot of this key group: [block][half of the block's 16 elements][lane] x 16 bytes
-  unsigned char* const xch = smem + C::NSTAGE * C::STAGE_B + kg * 4096 + lane * 16;
+  unsigned char* const xch = smem + C::XCH_OFF + kg * 4096 + lane * 16;
 
   floatx16_t acc[NDB];  // dV (P wave) or dK / -scale (E wave) of the wave's 32 keys
 #pragma unroll
@@ -191,36 +202,51 @@ __device__ __forceinline__ void dkv_body(const StepTable& tab, const DkvParams& 
 #pragma unroll
     for (int v = 0; v < 16; ++v) acc[db][v] = 0.f;
 
-  // ---- staging of one query tile by the E waves: Q, dO rows and their LSE / delta, global -> LDS
-  auto issue_tile = [&](const Cursor& cu, int stage) {
+  // ---- staging of one query tile by the E waves, global -> LDS: Q rows into the stage at byte `at_q`, dO rows and their
+  // delta into the one at `at_o` (either may be left out); with OFFSETS the rows' LSE goes to a register of E wave 0
+  float lse_ahead = 0.f;
+  auto issue_tile = [&](const Cursor& cu, auto want_q, auto want_o, uint32_t at_q, uint32_t at_o) {
     if (p_wave) return;
     int h, qa, i0;
     decode(cu, h, qa, i0);
     const int qlen = qa ? qlen1 : qlen0, qstart = qa ? qstart1 : qstart0;
     const int last = qlen - 1 - i0;
-    const uint32_t st = smem_base + stage * C::STAGE_B;
     const int64_t tile_off = b * p.qs[0] + h * p.qs[1] + (int64_t)(qstart + i0) * p.qs[2];
     const unsigned char* qb = reinterpret_cast<const unsigned char*>(p.q + tile_off);
     const unsigned char* ob = reinterpret_cast<const unsigned char*>(p.d_o + tile_off);
+    const uint32_t sq = smem_base + at_q, so = smem_base + at_o;
     if (last >= BM - 1) {
 #pragma unroll
       for (int i = 0; i < LI; ++i) {
-        load_to_lds_16(qb, ld_off[i], st + (kg + 4 * i) * 1024);
-        load_to_lds_16(ob, ld_off[i], st + C::QT_B + (kg + 4 * i) * 1024);
+        if constexpr (want_q.value) load_to_lds_16(qb, ld_off[i], sq + (kg + 4 * i) * 1024);
+        if constexpr (want_o.value) load_to_lds_16(ob, ld_off[i], so + (kg + 4 * i) * 1024);
       }
     } else {  // ragged end of a segment: rows past the last one repeat it
 #pragma unroll
       for (int i = 0; i < LI; ++i) {
         const uint32_t off = (uint32_t)min(ld_row + i * 4 * C::RPI, last) * q_rowbytes + ld_piece;
-        load_to_lds_16(qb, off, st + (kg + 4 * i) * 1024);
-        load_to_lds_16(ob, off, st + C::QT_B + (kg + 4 * i) * 1024);
+        if constexpr (want_q.value) load_to_lds_16(qb, off, sq + (kg + 4 * i) * 1024);
+        if constexpr (want_o.value) load_to_lds_16(ob, off, so + (kg + 4 * i) * 1024);
       }
     }
-    if (kg < 2) {  // E wave 0: the 64 rows' LSE, E wave 1: their delta
-      const int64_t row = ((int64_t)b * p.Hq + h) * p.q_len + qstart + i0 + min(lane, last);
-      load_to_lds_4((kg ? p.delta : p.lse) + row, st + 2 * C::QT_B + kg * BM * 4);
+    const int64_t row = ((int64_t)b * p.Hq + h) * p.q_len + qstart + i0 + min(lane, last);
+    if constexpr (C::OFFSETS) {
+      if constexpr (want_q.value)
+        if (kg == 0) lse_ahead = lane <= last ? p.lse[row] : -INFINITY;
+      if constexpr (want_o.value)
+        if (kg == 1) load_to_lds_4(p.delta + row, so + C::DELTA_OFF);
+    } else {
+      if (kg < 2) load_to_lds_4((kg ? p.delta : p.lse) + row, sq + C::LSE_OFF + kg * BM * 4);  // E wave 0: the LSE, E wave 1: delta
     }
   };
+  // E wave 0, once the LSE of a staged tile is there: the exponent offsets its rows' score chains start from, -LSE log2 e, and -inf
+  // (P = 0) for rows past the end of the segment and rows that saw no key in the whole attention
+  auto store_offsets = [&](int stage) {
+    if (C::OFFSETS && wave == 4)
+      *reinterpret_cast<float*>(smem + stage * C::Q_STRIDE + C::LSE_OFF + lane * 4) = lse_ahead == -INFINITY ? -INFINITY : lse_ahead * -kLog2e;
+  };
+  constexpr std::true_type yes;
+  constexpr std::false_type no;
 
   Cursor cur, nxt;
   cur.gq = it_begin / max(per_g, 1);
@@ -228,8 +254,12 @@ __device__ __forceinline__ void dkv_body(const StepTable& tab, const DkvParams& 
   nxt = cur;
 
   wait_vmcnt<0>();  // the K / V fragments are in: no counter wait of the compiler's lands in the loop
-  if (it_begin < it_end) issue_tile(cur, 0);
+  if (it_begin < it_end) {
+    if constexpr (C::LATE_O) issue_tile(cur, yes, no, 0, 0);
+    else issue_tile(cur, yes, yes, 0, C::O_OFF);
+  }
   if (!p_wave) wait_vmcnt<0>();
+  store_offsets(0);
 
   // ---- the gradients of keys no query sees: the unit's workgroups clear a share each, from
   // the P waves (their stores have the first iteration to finish; as a launch of its own this cost
@@ -250,25 +280,30 @@ __device__ __forceinline__ void dkv_body(const StepTable& tab, const DkvParams& 
   // P and E = P o T packed, two bf16 per word (elements 2 w, 2 w + 1 of block ib).  A P wave keeps
   // its P across the barrier: dV += P^T dO of tile t runs at the top of iteration t + 1.
   uint32_t w2[2][8];
-  constexpr int PF = 4;  // LDS operands are requested PF matrix steps ahead
-  // Iteration j: the P waves work on tile j, the E waves on tile j - 1, tile j + 1 is staged.
-  int st_p = 0, st_e = 2, st_n = 1;  // LDS stages of those three tiles
+  constexpr int PF = D == 64 ? 3 : 4;  // LDS operands are requested PF matrix steps ahead
+  // Iteration j: the P waves work on tile j, the E waves on tile j - 1; the Q rows of tile j + 1 and the dO rows of
+  // tile j are staged.
+  int st_p = 0, st_e = 2, st_n = 1;  // LDS stages of the Q rows of tiles j, j - 1 and j + 1
+  int so_e = 1, so_n = 0;            // and of the dO rows of tiles j - 1 and j
   for (int it = it_begin; it <= it_end && it_begin < it_end; ++it) {
     __syncthreads();  // tile `it` is in LDS, P of tile it - 1 is handed over, tile it - 2 is finished with
     if (it + 1 < it_end) {
       advance(nxt);
-      issue_tile(nxt, st_n);
+      if constexpr (C::LATE_O) issue_tile(nxt, yes, no, st_n * C::Q_STRIDE, 0);
+      else issue_tile(nxt, yes, yes, st_n * C::Q_STRIDE, st_n * C::Q_STRIDE + C::O_OFF);
     }
+    if constexpr (C::LATE_O)
+      if (it < it_end) issue_tile(cur, no, yes, 0, C::O_OFF + so_n * C::O_STRIDE);
     const bool p_active = p_wave && it < it_end, e_active = !p_wave && it > it_begin;
     int h, qa, i0;
     decode(cur, h, qa, i0);
     const int qlen = qa ? qlen1 : qlen0;
     const bool isdiag = (qa ? clsq1 : clsq0) == LOONG_DIAG;
-    const bool need_mask = i0 + BM > qlen || koff0 + BN > klen || (isdiag && i0 < koff0 + BN - 1);
-    const unsigned char* Qt = smem + (p_wave ? st_p : st_e) * C::STAGE_B;
-    const unsigned char* Ot = Qt + C::QT_B;
-    const float* lse_s = reinterpret_cast<const float*>(Qt + 2 * C::QT_B);
-    const float* dl_s = lse_s + BM;
+    const bool need_mask = (!C::OFFSETS && i0 + BM > qlen) || koff0 + BN > klen || (isdiag && i0 < koff0 + BN - 1);
+    const unsigned char* Qt = smem + (p_wave ? st_p : st_e) * C::Q_STRIDE;
+    const unsigned char* Ot = smem + C::O_OFF + (C::LATE_O ? so_e : st_e) * C::O_STRIDE;  // of tile j - 1
+    const float* nl_s = reinterpret_cast<const float*>(Qt + C::LSE_OFF);
+    const float* dl_s = reinterpret_cast<const float*>(Ot + C::DELTA_OFF);
     unsigned char* const xch_w = xch + ((it - it_begin) & 1) * C::XCH_B;        // P of tile `it`
     const unsigned char* const xch_r = xch + ((it - it_begin + 1) & 1) * C::XCH_B;  // P of tile it - 1
 
@@ -320,7 +355,7 @@ __device__ __forceinline__ void dkv_body(const StepTable& tab, const DkvParams& 
     };
 
     // dV += P^T dO of tile it - 1 (its dO is still staged: the E waves work on that tile now)
-    if (p_wave && it > it_begin) cols_product(smem + st_e * C::STAGE_B + C::QT_B, [](auto) {});
+    if (p_wave && it > it_begin) cols_product(Ot, [](auto) {});
     if (p_active) {
       // exponent offsets -LSE log2 e, where the score chains start; masked pairs get -inf: P = 0
       // whatever the score
@@ -329,21 +364,27 @@ __device__ __forceinline__ void dkv_body(const StepTable& tab, const DkvParams& 
       for (int ib = 0; ib < 2; ++ib)
 #pragma unroll
         for (int vq = 0; vq < 4; ++vq) {
-          const float4 L = *reinterpret_cast<const float4*>(&lse_s[ib * 32 + 8 * vq + 4 * hh]);
-          nl[ib][4 * vq + 0] = L.x * -kLog2e; nl[ib][4 * vq + 1] = L.y * -kLog2e;
-          nl[ib][4 * vq + 2] = L.z * -kLog2e; nl[ib][4 * vq + 3] = L.w * -kLog2e;
+          const float4 L = *reinterpret_cast<const float4*>(&nl_s[ib * 32 + 8 * vq + 4 * hh]);
+          constexpr float f = C::OFFSETS ? 1.f : -kLog2e;
+          nl[ib][4 * vq + 0] = L.x * f; nl[ib][4 * vq + 1] = L.y * f;
+          nl[ib][4 * vq + 2] = L.z * f; nl[ib][4 * vq + 3] = L.w * f;
         }
       // a row whose LSE is -inf saw no key in the whole attention: its offset came out as +inf
       // and must be -inf (P = 0).  One look at the tile's 64 staged values per wave finds the case.
-      const bool blind_row = __builtin_amdgcn_ballot_w64(lse_s[lane] == -INFINITY) != 0;
+      const bool blind_row = !C::OFFSETS && __builtin_amdgcn_ballot_w64(nl_s[lane] == -INFINITY) != 0;
       if (need_mask || blind_row) {
 #pragma unroll
         for (int ib = 0; ib < 2; ++ib)
 #pragma unroll
           for (int v = 0; v < 16; ++v) {
             const int i_off = i0 + ib * 32 + acc_row(v, hh);
-            const bool ok = key_ok && i_off < qlen && (!isdiag || my_koff <= i_off) && nl[ib][v] < INFINITY;
-            nl[ib][v] = ok ? nl[ib][v] : -INFINITY;
+            if constexpr (C::OFFSETS) {  // (the rows' own reasons are in the offset already, and testing them again took 12 us of 99)
+              const bool ok = key_ok && (!isdiag || my_koff <= i_off);
+              nl[ib][v] = ok ? nl[ib][v] : -INFINITY;
+            } else {
+              const bool ok = key_ok && i_off < qlen && (!isdiag || my_koff <= i_off) && nl[ib][v] < INFINITY;
+              nl[ib][v] = ok ? nl[ib][v] : -INFINITY;
+            }
           }
       }
       auto exps = [&](int ib, int w) {  // elements 2 w, 2 w + 1 of block ib
@@ -395,9 +436,12 @@ __device__ __forceinline__ void dkv_body(const StepTable& tab, const DkvParams& 
       });
     }
     wait_vmcnt<0>();  // this wave's part of the next tile, issued a whole iteration ago
+    store_offsets(st_n);
     if (it < it_end) advance(cur);
     const int freed = st_e;
     st_e = st_p; st_p = st_n; st_n = freed;
+    const int freed_o = so_e;
+    so_e = so_n; so_n = freed_o;
   }
 
   // ---- several workgroups share this key tile's query loop: all park their partial sums, and the

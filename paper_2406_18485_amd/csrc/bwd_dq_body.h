@@ -59,7 +59,7 @@ struct DqCfg {
   static constexpr int CH = D / 8;                 // 16-byte pieces per row
   static constexpr int TILE_B = TK * ROWB;         // bytes of one K (or V) tile
   static constexpr int BUF_B = 2 * TILE_B;
-  static constexpr int NBUF = BUF_B * 4 <= 131072 ? 4 : 2;
+  static constexpr int NBUF = BUF_B * 4 <= (D == 64 ? 65536 : 131072) ? 4 : 2;  // (head_dim 64: two workgroups per unit)
   static constexpr int PD = NBUF - 1;              // tiles in flight ahead of the one being used
   static constexpr int RPI = 1024 / ROWB;          // rows filled by one wave-level load
   static constexpr int KI = TILE_B / 1024 / kRowWaves;  // loads per wave per K (or V) tile
@@ -75,6 +75,13 @@ __device__ __forceinline__ void dq_body(const StepTable& tab, const DqParams& p,
   using C = DqCfg<D, KS>;
   constexpr int NRB = C::NRB, NJB = C::NJB, BNS = C::BNS, TK = C::TK, NBUF = C::NBUF, PD = C::PD, KI = C::KI;
   constexpr int NDB = D / 32, NKS = D / 16, ROWB = C::ROWB, CH = C::CH;
+  // head_dim 64 runs two workgroups per unit (four waves per SIMD), in at most 128 registers: the chains' starting values are
+  // made by the matrix cores each time (spread) instead of kept in 32 registers, LDS offsets are two registers
+  // (row_read_base), one operand is requested ahead, not four, and what only the end needs is found there.  dQ alone, one
+  // workgroup per unit -> two: 16384 x 16384 x 8 heads 730 -> 707 us, 1500 x 4100 x 2 x 8 58.8 -> 52.3, 8192 x 8192 x 8
+  // 188 -> 195 (256 workgroups); with the offsets added on the vector port instead 728, 57, 205; two operands ahead
+  // spilled: 64 us for the second.
+  constexpr bool LEAN = D == 64;
 
   // ---- which (batch, head group, q tile): within a head group the tiles with the most
   // visible keys come first
@@ -109,9 +116,10 @@ __device__ __forceinline__ void dq_body(const StepTable& tab, const DqParams& p,
   const uint32_t first = qa ? e10 : e00, second = qa ? e11 : e01;
   const int n_list = (int)(qa ? n_list1 : n_list0), n_diag = (int)(qa ? n_diag1 : n_diag0);
   const int total_t = (n_list - n_diag) * ((klen + TK - 1) / TK) + n_diag * ((kend_diag + TK - 1) / TK);
-  float* const dq_row = p.dq + b * p.os[0] + h * p.os[1] + (int64_t)my_row * p.os[2];
+  auto find_dq_row = [&](int off) { return p.dq + b * p.os[0] + h * p.os[1] + (int64_t)(qseg.start + min(off, qseg.len - 1)) * p.os[2]; };
   if (total_t == 0) {  // nothing visible: no share of dQ in this step
     if (p.overwrite && ksp == 0 && row_ok) {
+      float* const dq_row = find_dq_row(my_off);
 #pragma unroll
       for (int db = 0; db < NDB; ++db)
 #pragma unroll
@@ -147,7 +155,8 @@ __device__ __forceinline__ void dq_body(const StepTable& tab, const DqParams& p,
   floatx16_t ndl;  // -delta of the lane's row in every element: where the dP chains start
   floatx16_t nlt;  // -LSE log2 e of the lane's row in every element: where the score chains start
 #pragma unroll
-  for (int v = 0; v < 16; ++v) { ndl[v] = -dl; nlt[v] = nl; }
+  for (int v = 0; v < 16; ++v) { ndl[v] = -dl; nlt[v] = nl; }  // (LEAN: not used)
+  const s16x4_t nl_pieces = pieces_of(nl, lane), ndl_pieces = pieces_of(-dl, lane);
   floatx16_t acc[NDB];  // dQ^T of the wave's rows (without the softmax scale)
 #pragma unroll
   for (int db = 0; db < NDB; ++db)
@@ -158,8 +167,8 @@ __device__ __forceinline__ void dq_body(const StepTable& tab, const DqParams& p,
   // [(wave + 8 i) * 1024, +1024) of the K (or V) tile: row (wave + 8 i) * RPI + lane / CH,
   // piece position lane % CH, which holds piece (position ^ swizzle(row)) of that row.
   const int64_t rowbytes = p.ks[2] * 2;
-  const int ld_row = wave * C::RPI + lane / CH;  // row inside the tile for i = 0; later loads add 8*RPI rows
-  const uint32_t ld_piece = (uint32_t)((lane % CH) ^ tile_swizzle<D>(ld_row)) * 16;
+  auto staged_row = [&](int lane) { return wave * C::RPI + lane / CH; };  // inside the tile for i = 0; later loads add 8*RPI rows
+  auto staged_piece = [&](int lane) { return (uint32_t)((lane % CH) ^ tile_swizzle<D>(staged_row(lane))) * 16; };
   const uint32_t smem_base = (uint32_t)(uintptr_t)(lds_void_t*)smem;  // LDS byte address of the buffers
   // a place in the list of key halves: entry, first key of the tile, end of the half's visible keys
   // (advanced tile by tile: the list is read once per half)
@@ -194,9 +203,7 @@ __device__ __forceinline__ void dq_body(const StepTable& tab, const DqParams& p,
   // byte offsets of this lane's pieces from the first row of a tile (full tiles only; the
   // 32-bit form needs TK rows to span less than 4 GiB, else every tile takes the general path)
   const bool narrow = rowbytes * TK < (int64_t(1) << 32);
-  uint32_t ld_off[KI];
-#pragma unroll
-  for (int i = 0; i < KI; ++i) ld_off[i] = (uint32_t)(ld_row + i * 8 * C::RPI) * (uint32_t)rowbytes + ld_piece;
+  const uint32_t ld_off = (uint32_t)staged_row(lane) * (uint32_t)rowbytes + staged_piece(lane);
   auto issue_tile = [&](int t) {  // stages the tile at `ahead` (the t-th of this workgroup) and moves on
     const int64_t tb = (int64_t)ahead.j0 * rowbytes;
     const int last = klen - 1 - ahead.j0;  // last valid row of the tile (>= 0); later rows repeat it
@@ -205,14 +212,15 @@ __device__ __forceinline__ void dq_body(const StepTable& tab, const DqParams& p,
     if (narrow && last >= TK - 1) {  // whole tile: uniform base in scalar registers + per-lane offset
 #pragma unroll
       for (int i = 0; i < KI; ++i) {
-        load_to_lds_16(kbase + tb, ld_off[i], kl + i * 8192);
-        load_to_lds_16(vbase + tb, ld_off[i], vl + i * 8192);
+        load_to_lds_16(kbase + tb + i * 8 * C::RPI * rowbytes, ld_off, kl + i * 8192);
+        load_to_lds_16(vbase + tb + i * 8 * C::RPI * rowbytes, ld_off, vl + i * 8192);
       }
     } else {
+      const int ln = lane_again();
 #pragma unroll
       for (int i = 0; i < KI; ++i) {
-        const int r = min(ld_row + i * 8 * C::RPI, last);
-        const int64_t ro = tb + (int64_t)r * rowbytes + ld_piece;
+        const int r = min(staged_row(ln) + i * 8 * C::RPI, last);
+        const int64_t ro = tb + (int64_t)r * rowbytes + staged_piece(ln);
         load_to_lds_16(kbase + ro, kl + i * 8192);
         load_to_lds_16(vbase + ro, vl + i * 8192);
       }
@@ -222,23 +230,15 @@ __device__ __forceinline__ void dq_body(const StepTable& tab, const DqParams& p,
 
   // ---- LDS read offsets of this lane (bytes inside a tile; the wave's split and the block
   // and slice indices are added as constants: the swizzle repeats every 16 rows)
-  // row operand: row l32 (+32 jb), pieces 2 ks + hh
-  uint32_t row_rd[NKS];
+  // (row operands: row l32 (+32 jb), pieces 2 ks + hh; K^T operands: runs of four keys 4 hh .. 4 hh + 3 and 8 keys on)
+  const uint32_t row_rd = row_read_base<D>(lane), tr_rd = tr_read_base<D>(lane);
+  uint32_t row_rds[NKS], tr_lo[NDB], tr_hi[NDB];
 #pragma unroll
-  for (int ks = 0; ks < NKS; ++ks) row_rd[ks] = l32 * ROWB + ((2 * ks + hh) ^ tile_swizzle<D>(l32)) * 16;
-  // K^T operand via transposing reads: in a group of 16 lanes, lane i points at row i / 4
-  // of a run of four keys and at columns 4 (i % 4) .. +3 of a 16-column strip; it receives
-  // the four keys of column i of the strip.  Lanes 0-31 / 32-63 take runs 4 hh .. 4 hh + 3,
-  // and the run 8 keys on.
-  uint32_t tr_lo[NDB], tr_hi[NDB];
-  {
-    const int i16 = lane & 15, r = i16 >> 2, qd = i16 & 3, strip = (lane >> 4) & 1;
+  for (int ks = 0; ks < NKS; ++ks) row_rds[ks] = row_rd ^ row_read_xor(ks);
 #pragma unroll
-    for (int db = 0; db < NDB; ++db) {
-      const int piece = db * 4 + strip * 2 + (qd >> 1);
-      tr_lo[db] = (4 * hh + r) * ROWB + (piece ^ tile_swizzle<D>(4 * hh + r)) * 16 + (qd & 1) * 8;
-      tr_hi[db] = (4 * hh + r + 8) * ROWB + (piece ^ tile_swizzle<D>(4 * hh + r + 8)) * 16 + (qd & 1) * 8;
-    }
+  for (int db = 0; db < NDB; ++db) {
+    tr_lo[db] = tr_rd ^ tr_read_xor(db, 0);
+    tr_hi[db] = (tr_rd ^ tr_read_xor(db, 1)) + 8 * ROWB;
   }
 
   // ---- pipeline: PD tiles in flight.  Everything loaded so far is waited for here, so that
@@ -261,16 +261,14 @@ __device__ __forceinline__ void dq_body(const StepTable& tab, const DqParams& p,
     const int jt = cur.j0;
     const bool isdiag = cur.e & kDiagEntry;
     advance(cur);
-    const unsigned char* Kt = smem + (t % NBUF) * C::BUF_B + ksp * BNS * ROWB;
-    const unsigned char* Vt = Kt + C::TILE_B;
+    const uint32_t Kt = (t % NBUF) * C::BUF_B + ksp * BNS * ROWB;
 
 #pragma unroll
     for (int jb = 0; jb < NJB; ++jb) {
       // A wave skips a block whose keys lie past the end of the segment or past all of its rows.
       const int j0 = jt + ksp * BNS + jb * 32;
       if (!wave_live || j0 >= klen || (isdiag && j0 > wrow0 + 31)) continue;
-      const unsigned char* Kb = Kt + jb * 32 * ROWB;
-      const unsigned char* Vb = Vt + jb * 32 * ROWB;
+      const uint32_t Kb = Kt + jb * 32 * ROWB, row_at = Kb + row_rd, tr_at = Kb + tr_rd;
 
       // ---- S^T = K Q^T, dP^T = V dO^T (keys x rows: a lane holds one query row).  The K and V
       // row operands are requested PF products ahead (in program order, held there by the
@@ -278,12 +276,13 @@ __device__ __forceinline__ void dq_body(const StepTable& tab, const DqParams& p,
       // pair of products then waits out a full LDS latency.
       floatx16_t s, dp;
       {
-        constexpr int NIT = 2 * NKS, PF = 4;
+        constexpr int NIT = 2 * NKS, PF = LEAN ? 1 : 4;
         auto row_frag = [&](int it) {
-          return as_bf16x8(*reinterpret_cast<const uint4*>(((it & 1) ? Vb : Kb) + row_rd[it >> 1]));
+          return as_bf16x8(*reinterpret_cast<const uint4*>(smem + (LEAN ? row_at ^ row_read_xor(it >> 1) : Kb + row_rds[it >> 1]) + ((it & 1) ? C::TILE_B : 0)));
         };
         bf16x8_t ring[PF + 1];
         static_for<0, PF>([&](auto i) { ring[i.value] = row_frag(i.value); });
+        if constexpr (LEAN) { s = spread(nl_pieces); dp = spread(ndl_pieces); }
         // (the dP chain starts from -delta of the lane's row, so it ends as dP - delta; the score
         // chain from -LSE log2 e, so it ends as the exponent of P: two vector instructions per
         // element that the matrix cores do on the side)
@@ -291,8 +290,8 @@ __device__ __forceinline__ void dq_body(const StepTable& tab, const DqParams& p,
           constexpr int it = i.value, ks = it >> 1;
           if constexpr (it + PF < NIT) ring[(it + PF) % (PF + 1)] = row_frag(it + PF);
           __builtin_amdgcn_sched_barrier(0);
-          if constexpr (it & 1) dp = E::mfma(ring[it % (PF + 1)], dof[ks], ks ? dp : ndl);
-          else s = E::mfma(ring[it % (PF + 1)], qf[ks], ks ? s : nlt);
+          if constexpr (it & 1) dp = E::mfma(ring[it % (PF + 1)], dof[ks], ks || LEAN ? dp : ndl);
+          else s = E::mfma(ring[it % (PF + 1)], qf[ks], ks || LEAN ? s : nlt);
         });
       }
       // ---- dS^T = P^T (dP^T - delta), the softmax scale is applied to the sums at the end
@@ -300,10 +299,11 @@ __device__ __forceinline__ void dq_body(const StepTable& tab, const DqParams& p,
 #pragma unroll
       for (int v = 0; v < 16; ++v) e[v] = fast_exp2(s[v]) * dp[v];
       if (j0 + 32 > klen || (isdiag && j0 + 31 > wrow0)) {  // diagonal or ragged end only
+        const int ln = lane_again(), off = wrow0 + (ln & 31);
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
-          const int key = j0 + acc_row(v, hh);
-          const bool ok = key < klen && (!isdiag || key <= my_off);
+          const int key = j0 + acc_row(v, ln >> 5);
+          const bool ok = key < klen && (!isdiag || key <= off);
           e[v] = ok ? e[v] : 0.f;
         }
       }
@@ -318,14 +318,20 @@ __device__ __forceinline__ void dq_body(const StepTable& tab, const DqParams& p,
       for (int sl = 0; sl < 2; ++sl)
 #pragma unroll
         for (int db = 0; db < NDB; ++db) {
-          const unsigned char* kp = Kb + sl * 16 * ROWB;
-          acc[db] = E::mfma(read_tr_pair(kp + tr_lo[db], kp + tr_hi[db]), as_bf16x8(pk[sl]), acc[db]);
+          const unsigned char* kp = smem + sl * 16 * ROWB;
+          const bf16x8_t k_cols = LEAN ? read_tr_pair(kp + (tr_at ^ tr_read_xor(db, 0)), kp + 8 * ROWB + (tr_at ^ tr_read_xor(db, 1)))
+                                       : read_tr_pair(kp + Kb + tr_lo[db], kp + Kb + tr_hi[db]);
+          acc[db] = E::mfma(k_cols, as_bf16x8(pk[sl]), acc[db]);
         }
     }
   }
 
   // ---- sum the key splits: splits 1.. park their dQ^T in LDS, split 0 adds them in order.
   // Split 0 requests its rows of dQ first: the round trip to memory runs while the others park.
+  // (the lane's place is found anew: at head_dim 64 the loop has no register to spare for it)
+  const int end_lane = lane_again(), end_off = wrow0 + (end_lane & 31), end_hh = end_lane >> 5;
+  const bool end_ok = end_off < qseg.len;
+  float* const dq_row = find_dq_row(end_off);
   float4 old[NDB][4];
 #pragma unroll
   for (int db = 0; db < NDB; ++db)
@@ -333,17 +339,17 @@ __device__ __forceinline__ void dq_body(const StepTable& tab, const DqParams& p,
     for (int vq = 0; vq < 4; ++vq) old[db][vq] = make_float4(0.f, 0.f, 0.f, 0.f);
   // (One branch around all the loads: with one around each, they are waited for one by one, 8192 rows x 100 keys
   // x 8 heads without a split 31.9 us instead of 24.6.)
-  if (ksp == 0 && row_ok && !p.overwrite) {
+  if (ksp == 0 && end_ok && !p.overwrite) {
 #pragma unroll
     for (int db = 0; db < NDB; ++db)
 #pragma unroll
-      for (int vq = 0; vq < 4; ++vq) old[db][vq] = *reinterpret_cast<const float4*>(dq_row + db * 32 + 8 * vq + 4 * hh);
+      for (int vq = 0; vq < 4; ++vq) old[db][vq] = *reinterpret_cast<const float4*>(dq_row + db * 32 + 8 * vq + 4 * end_hh);
   }
   if (KS > 1) {
     __syncthreads();  // all reads of the last tile are done: the tile buffers are reused
     float4* slots = reinterpret_cast<float4*>(smem);
     if (ksp > 0) {
-      float4* mine = slots + ((ksp - 1) * NRB + rb) * C::SLOT_F4 * 64 + lane;
+      float4* mine = slots + ((ksp - 1) * NRB + rb) * C::SLOT_F4 * 64 + end_lane;
 #pragma unroll
       for (int db = 0; db < NDB; ++db)
 #pragma unroll
@@ -354,7 +360,7 @@ __device__ __forceinline__ void dq_body(const StepTable& tab, const DqParams& p,
     if (ksp > 0) return;
 #pragma unroll 1
     for (int sp = 1; sp < KS; ++sp) {
-      const float4* theirs = slots + ((sp - 1) * NRB + rb) * C::SLOT_F4 * 64 + lane;
+      const float4* theirs = slots + ((sp - 1) * NRB + rb) * C::SLOT_F4 * 64 + end_lane;
 #pragma unroll
       for (int db = 0; db < NDB; ++db)
 #pragma unroll
@@ -367,12 +373,12 @@ __device__ __forceinline__ void dq_body(const StepTable& tab, const DqParams& p,
   }
 
   // ---- dQ row += scale * sum: register 4 vq + r of block db is column 32 db + 8 vq + 4 hh + r
-  if (row_ok) {
+  if (end_ok) {
 #pragma unroll
     for (int db = 0; db < NDB; ++db)
 #pragma unroll
       for (int vq = 0; vq < 4; ++vq) {
-        float4* dst = reinterpret_cast<float4*>(dq_row + db * 32 + 8 * vq + 4 * hh);
+        float4* dst = reinterpret_cast<float4*>(dq_row + db * 32 + 8 * vq + 4 * end_hh);
         float4 x = old[db][vq];
         x.x = fmaf(acc[db][4 * vq + 0], p.scale, x.x); x.y = fmaf(acc[db][4 * vq + 1], p.scale, x.y);
         x.z = fmaf(acc[db][4 * vq + 2], p.scale, x.z); x.w = fmaf(acc[db][4 * vq + 3], p.scale, x.w);

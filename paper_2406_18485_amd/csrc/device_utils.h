@@ -40,6 +40,25 @@ __device__ __forceinline__ floatx16_t mfma32(bf16x8_t a, bf16x8_t b, floatx16_t 
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
 }
 
+// The start of an accumulator whose column (lane & 31) is all x, from the matrix cores: the lane's fragment holds x in three
+// bf16 pieces, which add up to all of its bits, and is multiplied by ones.
+typedef short s16x4_t __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ s16x4_t pieces_of(float x, int lane) {
+  const __bf16 a = (__bf16)x;
+  const float r = __builtin_isinf(x) ? 0.f : x - (float)a;
+  const __bf16 b = (__bf16)r, c = (__bf16)(r - (float)b);
+  const s16x4_t f = {__builtin_bit_cast(short, a), __builtin_bit_cast(short, b), __builtin_bit_cast(short, c), 0};
+  const s16x4_t none = {0, 0, 0, 0};
+  return lane < 32 ? f : none;
+}
+__device__ __forceinline__ floatx16_t spread(s16x4_t pieces) {
+  const s16x4_t ones = {0x3f80, 0x3f80, 0x3f80, 0x3f80};
+  floatx16_t zero;
+#pragma unroll
+  for (int v = 0; v < 16; ++v) zero[v] = 0.f;
+  return __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(ones, pieces, zero, 0, 0, 0);
+}
+
 // ---- 16-bit storage types.  The kernels keep operand fragments as eight 16-bit lanes in a
 // bf16x8_t whatever the element type is; the element class says how the matrix instruction
 // reads them and how fp32 values are rounded into them (nearest even for both).
@@ -158,6 +177,34 @@ __device__ __forceinline__ constexpr int tile_swizzle(int row) {
   if (D == 128) return ((row & 3) << 2) | ((row >> 2) & 3);
   const int m = (row >> 1) & 7;  // D == 64: two rows per 256 bytes
   return ((m & 1) << 2) | ((m >> 1) & 3);
+}
+
+// LDS byte offsets of a lane's reads inside such a tile.  Every read is one of two offsets with a constant XORed in, whatever
+// the tile's place (tiles lie at multiples of 256 bytes), so two registers can serve all of them at one instruction
+// per read.  (Where registers are not short, an offset of its own per read is 1 % faster: the addition of the tile's place is
+// shared by the reads of its blocks.)
+//   row operand: row (lane & 31), pieces 2 ks + (lane >> 5)  ->  row_read_base ^ row_read_xor(ks)
+//   transposed operand: in a group of 16 lanes, lane i points at row i / 4 of a run of four rows and at columns
+//   4 (i % 4) .. +3 of a 16-column strip of the 32-column block db; lanes 0-31 / 32-63 take the runs that start at row 0 / 4
+//   ->  tr_read_base ^ tr_read_xor(db, 0), and the run 8 rows on  ->  (tr_read_base ^ tr_read_xor(db, 1)) + 8 rows
+template <int D>
+__device__ __forceinline__ uint32_t row_read_base(int lane) {
+  const int row = lane & 31;
+  return row * (D * 2) + (((lane >> 5) ^ tile_swizzle<D>(row)) * 16);
+}
+__device__ __forceinline__ constexpr uint32_t row_read_xor(int ks) { return 32 * ks; }
+template <int D>
+__device__ __forceinline__ uint32_t tr_read_base(int lane) {
+  const int i16 = lane & 15, row = 4 * (lane >> 5) + (i16 >> 2), qd = i16 & 3, strip = (lane >> 4) & 1;
+  return row * (D * 2) + (((strip * 2 + (qd >> 1)) ^ tile_swizzle<D>(row)) * 16) + (qd & 1) * 8;
+}
+__device__ __forceinline__ constexpr uint32_t tr_read_xor(int db, int later_run) { return 64 * db ^ 32 * later_run; }
+
+// The lane's number, counted anew wherever this is called: what rare paths derive from it is not kept in registers.
+__device__ __forceinline__ int lane_again() {
+  int lane;
+  asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(lane));
+  return lane;
 }
 
 // f(integral_constant<int, I>) for I = First .. Last - 1, unrolled by instantiation (does not

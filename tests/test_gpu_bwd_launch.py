@@ -128,3 +128,37 @@ def test_a_step_too_large_for_a_launch_is_refused_before_anything_runs():
         P.attn_step_fwd(desc, q, k, v, dq, lse)
     torch.cuda.synchronize()
     assert e.value.code == P.E_UNSUPPORTED and bool((dq == 5.0).all())
+
+
+@pytest.mark.parametrize("dtype", [P.BF16, P.FP16])
+@pytest.mark.parametrize("lq,lk,hq,hkv", [(1, 1, 1, 1), (31, 129, 2, 1), (64, 64, 1, 1), (65, 127, 4, 2), (200, 700, 3, 1), (513, 257, 8, 8)])
+@pytest.mark.parametrize("ks", [1, 2, 4])
+def test_head_dim_64_gradients_at_the_edges_of_tiles(lq, lk, hq, hkv, ks, dtype):
+    """Two workgroups per unit: offsets formed once per query row (rows past the end and rows with LSE = -inf give nothing),
+    starting values spread by the matrix cores (a row with an LSE and a delta beyond the half's range among them), tiles two and
+    four deep.  Against fp64 from the same LSE and delta; the bound is what rounding P, dS, K and Q to 16 bits leaves: about 2^-9
+    (2^-12) of the terms' root sum of squares, eight times that for the largest of some 1e5 values."""
+    g = torch.Generator(device="cpu").manual_seed(lq * 7 + lk)
+    mk = lambda h, n: (torch.randn(1, h, n, 64, generator=g) * 0.5).to(TORCH[dtype])
+    q, k, v, d_o = mk(hq, lq), mk(hkv, lk), mk(hkv, lk), mk(hq, lq)
+    x = lambda t: t.double().repeat_interleave(hq // t.shape[1], 1)
+    s = (x(q) @ x(k).transpose(-1, -2)) * 0.125
+    lse = torch.logsumexp(s, -1).float()
+    p = torch.exp(s - lse.double()[..., None])
+    delta = (x(d_o) * (p @ x(v))).sum(-1).float()
+    if lq > 1:
+        lse[0, 0, 0], lse[0, -1, -1], delta[0, -1, -1] = -math.inf, 1e6, -1e6   # no key at all; probabilities of zero
+        p[0, 0, 0], p[0, -1, -1] = 0.0, 0.0
+    ds = p * (x(d_o) @ x(v).transpose(-1, -2) - delta.double()[..., None]) * 0.125
+    group = lambda t: t.reshape(1, hkv, hq // hkv, lk, 64).sum(2)
+    want = ds @ x(k), group(ds.transpose(-1, -2) @ x(q)), group(p.transpose(-1, -2) @ x(d_o))
+    terms = (ds.abs().square() @ x(k).square()).sqrt(), group(ds.square().transpose(-1, -2) @ x(q).square()).sqrt(), group(
+        p.square().transpose(-1, -2) @ x(d_o).square()).sqrt()
+    desc = P.make_desc(batch=1, n_q_heads=hq, n_kv_heads=hkv, head_dim=64, q_len=lq, kv_len=lk, dtype=dtype, softmax_scale=0.125,
+                       flags=P.key_splits(ks))
+    t = dict(q=q.to(DEV), k=k.to(DEV), v=v.to(DEV), d_o=d_o.to(DEV), lse=lse.to(DEV), delta=delta.to(DEV))
+    got = _run(t, desc, torch.zeros(q.shape, device=DEV), workspace_for(desc))
+    eps = 2.0 ** (-9 if dtype == P.BF16 else -12)
+    for a, b, scale in zip(got, want, terms):
+        err = (a.cpu().double() - b).abs()
+        assert bool((err <= 8 * eps * (scale + scale.max() / 8) + 1e-6).all()), float((err / (scale + scale.max() / 8) / eps).max())
