@@ -78,14 +78,13 @@ int loong_attn_steps_fwd(const loong_step_desc* descs, int32_t n_steps, const vo
                      (d.batch > 1 && d.o_stride[0] != d.n_q_heads * d.o_stride[1])))
     return fail(LOONG_E_UNSUPPORTED, "loong_attn_steps_fwd: the fp32 copy needs a contiguous out");
   if (rows == 0) return LOONG_OK;
+  if (half) return launch_fwd_bf16(descs, n_steps, q, k, v, out, lse, o, stream);
   for (int t = 0; t < n_steps; ++t) {
     if (t > 0) d.flags |= LOONG_FUSE_MERGE;
     if (int rc = check_step(&descs[t], &g)) return rc;
-    if (int rc = half ? launch_fwd_bf16(d, g, q, k[t], v[t], out, lse, t == n_steps - 1 ? o : nullptr, stream)
-                      : launch_fwd_f32(d, g, q, k[t], v[t], out, lse, stream))
-      return rc;
+    if (int rc = launch_fwd_f32(d, g, q, k[t], v[t], out, lse, stream)) return rc;
   }
-  return o && !half ? loong_finalize_out(rows, d.head_dim, out, o, d.dtype, stream) : LOONG_OK;
+  return o ? loong_finalize_out(rows, d.head_dim, out, o, d.dtype, stream) : LOONG_OK;
 }
 
 int loong_attn_step_bwd(const loong_step_desc* desc, const void* q, const void* k, const void* v,

@@ -33,6 +33,7 @@
 #include "device_utils.h"
 #include "loong_internal.h"
 #include "row_tiling.h"
+#include "step_table.h"
 #include "work_map.h"
 
 namespace loong {
@@ -43,8 +44,22 @@ constexpr int kFwdWaves = kRowWaves;
 
 typedef __attribute__((address_space(3))) void lds_void_t;
 
+// The visiting chunks of a launch, in visit order: one micro-step, or a run of up to N whose chunks are all resident.
+struct FwdStep {
+  const uint16_t *k, *v;
+  uint32_t cls, unused;      // class of (q segment a, key half b) at bits 4 a + 2 b
+};
+template <int N>
+struct FwdSteps {
+  uint32_t seen[2];          // per q segment: bit t is set if its rows see a key of step t
+  // (No array of bytes beside the pointers: the compiler adds the one index to the base and seven times it as the offset of the
+  // other's scalar load, which drops the low two bits of each)
+  FwdStep step[N];
+};
+static_assert(kMaxSteps <= 32, "`seen` has a bit per step");
+
 struct FwdParams {
-  const uint16_t *q, *k, *v;
+  const uint16_t* q;
   float *out, *lse;
   uint16_t* stored;  // the last step of a run: `out` is also stored rounded to 16 bits, [B,Hq,q_len,D] contiguous
   int B, Hq, Hkv, G, GS;
@@ -84,8 +99,8 @@ struct FwdCfg {
   static_assert(KI >= 1 && KI * 1024 * kFwdWaves == TILE_B, "tile must split evenly over the waves");
 };
 
-template <class E, int D, int KS, int WGS>
-__global__ __launch_bounds__(kFwdWaves * 64, 2 * WGS) void fwd_kernel(const FwdParams p) {
+template <class E, int D, int KS, int WGS, int N>
+__global__ __launch_bounds__(kFwdWaves * 64, 2 * WGS) void fwd_kernel(const FwdSteps<N> steps, const FwdParams p) {
   using C = FwdCfg<D, KS, WGS>;
   constexpr int NRB = C::NRB, BNS = C::BNS, TK = C::TK, NBUF = C::NBUF, PD = C::PD, KI = C::KI;
   constexpr int NJB = BNS / 32, NDB = D / 32, NKS = D / 16, ROWB = C::ROWB, CH = C::CH, RP = C::RP;
@@ -112,19 +127,29 @@ __global__ __launch_bounds__(kFwdWaves * 64, 2 * WGS) void fwd_kernel(const FwdP
   const int my_off = wrow0 + l32;
   const bool wave_live = wrow0 < qseg.len;
   const bool row_ok = my_off < qseg.len;
-  const int my_row = qseg.start + min(my_off, qseg.len - 1);
+  const int vis_off = min(my_off, qseg.len - 1);  // (lanes past the end do exactly what the last row's lane does)
+  const int my_row = qseg.start + vis_off;
   const int last_off_wg = min(row0_wg + BMH, qseg.len) - 1;
 
-  // ---- visible key tiles of this workgroup (per-segment facts kept in scalars: nothing in
+  // ---- visible key tiles of this workgroup in the step it is in (per-segment facts kept in scalars: nothing in
   // the main loop indexes the kernel arguments dynamically)
-  const int cls0 = qa ? p.g.cls[1][0] : p.g.cls[0][0];
-  const int cls1 = p.g.nk > 1 ? (qa ? p.g.cls[1][1] : p.g.cls[0][1]) : LOONG_SKIP;
   const int klen0 = p.g.k[0].len, klen1 = p.g.nk > 1 ? p.g.k[1].len : 0;
   const int kstart0 = p.g.k[0].start, kstart1 = p.g.nk > 1 ? p.g.k[1].start : 0;
-  const int kend0 = cls0 == LOONG_SKIP ? 0 : cls0 == LOONG_FULL ? klen0 : min(klen0, last_off_wg + 1);
-  const int kend1 = cls1 == LOONG_SKIP ? 0 : cls1 == LOONG_FULL ? klen1 : min(klen1, last_off_wg + 1);
-  const int ntk0 = (kend0 + TK - 1) / TK, ntk1 = (kend1 + TK - 1) / TK;
-  const int total_t = ntk0 + ntk1;
+  uint32_t todo = scalar_now(qa ? steps.seen[1] : steps.seen[0]);  // the steps still to do
+  int cls0, cls1, ntk0, total_t;
+  const unsigned char *kbase, *vbase;
+  auto enter_step = [&] {
+    const int t = N == 1 ? 0 : __builtin_ctz(todo);
+    todo &= todo - 1;
+    const uint32_t cls = steps.step[t].cls >> (4 * qa);
+    cls0 = cls & 3; cls1 = p.g.nk > 1 ? (cls >> 2) & 3 : LOONG_SKIP;
+    const int kend0 = cls0 == LOONG_SKIP ? 0 : cls0 == LOONG_FULL ? klen0 : min(klen0, last_off_wg + 1);
+    const int kend1 = cls1 == LOONG_SKIP ? 0 : cls1 == LOONG_FULL ? klen1 : min(klen1, last_off_wg + 1);
+    ntk0 = (kend0 + TK - 1) / TK;
+    total_t = ntk0 + (kend1 + TK - 1) / TK;
+    kbase = reinterpret_cast<const unsigned char*>(scalar_now(steps.step[t].k + b * p.ks[0] + hk * p.ks[1]));
+    vbase = reinterpret_cast<const unsigned char*>(scalar_now(steps.step[t].v + b * p.ks[0] + hk * p.ks[1]));
+  };
 
   float* out_row = p.out + b * p.os[0] + h * p.os[1] + (int64_t)my_row * p.os[2];
   float* lse_ptr = p.lse + ((int64_t)b * p.Hq + h) * p.q_len + my_row;
@@ -136,7 +161,7 @@ __global__ __launch_bounds__(kFwdWaves * 64, 2 * WGS) void fwd_kernel(const FwdP
     *reinterpret_cast<uint2*>(dst) = make_uint2(E::pack2(x.x, x.y), E::pack2(x.z, x.w));
   };
 
-  if (total_t == 0) {  // nothing visible: neutral partial result, or leave the running one
+  if (todo == 0) {  // nothing visible: neutral partial result, or leave the running one
     if (p.stored && ksp == 0 && row_ok) {
 #pragma unroll
       for (int db = 0; db < NDB; ++db)
@@ -160,8 +185,6 @@ __global__ __launch_bounds__(kFwdWaves * 64, 2 * WGS) void fwd_kernel(const FwdP
   // ---- staging: global -> LDS directly.  Load i of this wave fills LDS bytes
   // [(wave + 8 i) * 1024, +1024) of the K (or V) tile: row (wave + 8 i) * RPI + lane / CH,
   // piece position lane % CH, which holds piece (position ^ swizzle(row)) of that row.
-  const unsigned char* kbase = reinterpret_cast<const unsigned char*>(p.k + b * p.ks[0] + hk * p.ks[1]);
-  const unsigned char* vbase = reinterpret_cast<const unsigned char*>(p.v + b * p.ks[0] + hk * p.ks[1]);
   const int64_t rowbytes = p.ks[2] * 2;
   const int ld_row = wave * C::RPI + lane / CH;  // row inside the tile for i = 0; later loads add 8*RPI rows
   const int ld_pos = lane % CH;
@@ -244,9 +267,13 @@ __global__ __launch_bounds__(kFwdWaves * 64, 2 * WGS) void fwd_kernel(const FwdP
   // and the running state, so that the three latencies overlap; everything is then waited
   // for before the loop, so that no counter wait of the compiler's own ends up inside it,
   // where it would also wait for the tiles in flight.
+  auto issue_first_tiles = [&] {
 #pragma unroll
-  for (int t = 0; t < PD; ++t)
-    if (t < total_t) issue_tile(t);
+    for (int t = 0; t < PD; ++t)
+      if (t < total_t) issue_tile(t);
+  };
+  enter_step();
+  issue_first_tiles();
 
   // ---- Q fragments (B operand of S^T = K Q^T): row my_row, columns 16*ks + 8*hh .. +7
   bf16x8_t qf[NKS];
@@ -288,6 +315,8 @@ __global__ __launch_bounds__(kFwdWaves * 64, 2 * WGS) void fwd_kernel(const FwdP
   wait_vmcnt<0>();
   const bool stage_late = PD == 1 && wave >= kFwdWaves / 2;  // waves w and w + 4 share a SIMD
 
+  // ---- the steps, one after the other
+  for (;;) {
   for (int t = 0; t < total_t; ++t) {
     // this wave's loads of tile t have landed when at most the later tiles' are outstanding
     const int later = min(PD - 1, total_t - 1 - t);
@@ -342,7 +371,7 @@ __global__ __launch_bounds__(kFwdWaves * 64, 2 * WGS) void fwd_kernel(const FwdP
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
           const int key = j0 + jb * 32 + acc_row(v, hh);
-          const bool ok = key < klen && (!isdiag || key <= my_off);
+          const bool ok = key < klen && (!isdiag || key <= vis_off);
           s[jb][v] = ok ? s[jb][v] : -INFINITY;
         }
     }
@@ -390,6 +419,77 @@ __global__ __launch_bounds__(kFwdWaves * 64, 2 * WGS) void fwd_kernel(const FwdP
           const unsigned char* vp = Vt + (jb * 32 + sl * 16) * ROWB + v_rd[db];
           o[db] = E::mfma(read_tr_pair(vp, vp + 8 * ROWB), as_bf16x8(pk[jb][sl]), o[db]);
         }
+  }
+
+    if (N == 1 || todo == 0) break;
+    // ---- another step follows: the running result as the next one would find it in memory, in the registers of split 0
+    // (the arithmetic of the combination below, so a run gives the bits of its steps)
+    __syncthreads();  // all reads of the last tile are done: the tile buffers are reused
+    float m_all = m_run, l_all = l_run;
+    if constexpr (KS > 1) {
+      float4* slots = reinterpret_cast<float4*>(smem);
+      if (ksp > 0) {
+        float4* mine = slots + ((ksp - 1) * NRB + rb) * C::SLOT_F4 * 64 + lane;
+#pragma unroll
+        for (int db = 0; db < NDB; ++db)
+#pragma unroll
+          for (int vq = 0; vq < 4; ++vq)
+            mine[(db * 4 + vq) * 64] = make_float4(o[db][4 * vq], o[db][4 * vq + 1], o[db][4 * vq + 2], o[db][4 * vq + 3]);
+        mine[(NDB * 4) * 64] = make_float4(m_run, l_run, 0.f, 0.f);
+      }
+      __syncthreads();
+      if (ksp == 0) {
+        float ms[KS], ls[KS];
+        ms[0] = m_run; ls[0] = l_run;
+#pragma unroll
+        for (int sp = 1; sp < KS; ++sp) {
+          const float4 st = slots[(((sp - 1) * NRB + rb) * C::SLOT_F4 + NDB * 4) * 64 + lane];
+          ms[sp] = st.x; ls[sp] = st.y;
+          m_all = fmaxf(m_all, st.x);
+        }
+        const float m_ref = m_all == -INFINITY ? 0.f : m_all;
+        float w[KS];
+        l_all = 0.f;
+#pragma unroll
+        for (int sp = 0; sp < KS; ++sp) {
+          w[sp] = fast_exp2(ms[sp] - m_ref);
+          l_all += ls[sp] * w[sp];
+        }
+#pragma unroll
+        for (int db = 0; db < NDB; ++db)
+#pragma unroll
+          for (int vq = 0; vq < 4; ++vq) {
+            float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+            for (int sp = 0; sp < KS; ++sp) {
+              const float4 xv = sp == 0 ? make_float4(o[db][4 * vq], o[db][4 * vq + 1], o[db][4 * vq + 2], o[db][4 * vq + 3])
+                                        : slots[(((sp - 1) * NRB + rb) * C::SLOT_F4 + db * 4 + vq) * 64 + lane];
+              acc.x += xv.x * w[sp]; acc.y += xv.y * w[sp]; acc.z += xv.z * w[sp]; acc.w += xv.w * w[sp];
+            }
+            o[db][4 * vq] = acc.x; o[db][4 * vq + 1] = acc.y; o[db][4 * vq + 2] = acc.z; o[db][4 * vq + 3] = acc.w;
+          }
+      }
+    }
+    if (ksp == 0) {
+      const float l_tot = sum_with_other_half(l_all);
+      const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
+      const float prev = l_tot > 0.f ? (m_all + fast_log2(l_tot)) * kLn2 : -INFINITY;
+#pragma unroll
+      for (int db = 0; db < NDB; ++db)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) o[db][v] = prev != -INFINITY ? o[db][v] * inv : 0.f;
+      m_run = prev != -INFINITY ? prev * kLog2e : -INFINITY;
+      l_run = prev != -INFINITY && hh == 0 ? 1.f : 0.f;
+    } else {
+      m_run = -INFINITY; l_run = 0.f;
+#pragma unroll
+      for (int db = 0; db < NDB; ++db)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) o[db][v] = 0.f;
+    }
+    if (KS > 1) __syncthreads();  // the parked results have been read
+    enter_step();
+    issue_first_tiles();
   }
 
   // ---- combine the key splits through LDS: every split parks (m, l, O^T); split j then
@@ -468,9 +568,9 @@ __global__ __launch_bounds__(kFwdWaves * 64, 2 * WGS) void fwd_kernel(const FwdP
   }
 }
 
-template <class E, int D, int KS>
-int launch_cfg(FwdParams& p, int cus, hipStream_t st) {
-  const RowTiling rt = make_row_tiling(p.g, p.G, p.Hq, p.B, kFwdWaves / KS, /*list_blind=*/!p.fuse || p.stored);  // unfused: blind rows get the neutral result
+template <class E, int D, int KS, int N>
+int launch_cfg(const FwdSteps<N>& steps, const StepGeom& rows, FwdParams& p, int cus, hipStream_t st) {
+  const RowTiling rt = make_row_tiling(rows, p.G, p.Hq, p.B, kFwdWaves / KS, /*list_blind=*/!p.fuse || p.stored);  // unfused: blind rows get the neutral result
   p.GS = rt.GS; p.ntile[0] = rt.ntile[0]; p.ntile[1] = rt.ntile[1];
   p.tiles_total = rt.tiles_total; p.hgroups = rt.hgroups;
   const int64_t total = rt.total_wg;
@@ -481,42 +581,101 @@ int launch_cfg(FwdParams& p, int cus, hipStream_t st) {
   // of one are staged four deep instead of two (2048 rows x 16384 keys x 4 heads, four splits, 128 workgroups: 102.7 -> 99 us)
   const dim3 grid(p.map.grid), block(kFwdWaves * 64);
   if constexpr (D == 64) {
-    if (KS < 4 || total > cus) fwd_kernel<E, D, KS, 2><<<grid, block, 0, st>>>(p);
-    else fwd_kernel<E, D, 4, 1><<<grid, block, 0, st>>>(p);
+    if (KS < 4 || total > cus) fwd_kernel<E, D, KS, 2, N><<<grid, block, 0, st>>>(steps, p);
+    else fwd_kernel<E, D, 4, 1, N><<<grid, block, 0, st>>>(steps, p);
   } else {
-    fwd_kernel<E, D, KS, 1><<<grid, block, 0, st>>>(p);
+    fwd_kernel<E, D, KS, 1, N><<<grid, block, 0, st>>>(steps, p);
   }
   return check_launch("loong_attn_step_fwd (bf16)");
 }
 
-template <class E>
-int pick_cfg(FwdParams& p, int head_dim, int ks, int cus, hipStream_t st) {
+template <class E, int N>
+int pick_cfg(const FwdSteps<N>& steps, const StepGeom& rows, FwdParams& p, int head_dim, int ks, int cus, hipStream_t st) {
   if (head_dim == 128) {
-    if (ks == 1) return launch_cfg<E, 128, 1>(p, cus, st);
-    if (ks == 2) return launch_cfg<E, 128, 2>(p, cus, st);
-    return launch_cfg<E, 128, 4>(p, cus, st);
+    if (ks == 1) return launch_cfg<E, 128, 1>(steps, rows, p, cus, st);
+    if (ks == 2) return launch_cfg<E, 128, 2>(steps, rows, p, cus, st);
+    return launch_cfg<E, 128, 4>(steps, rows, p, cus, st);
   }
-  if (ks == 1) return launch_cfg<E, 64, 1>(p, cus, st);
-  if (ks == 2) return launch_cfg<E, 64, 2>(p, cus, st);
-  return launch_cfg<E, 64, 4>(p, cus, st);
+  if (ks == 1) return launch_cfg<E, 64, 1>(steps, rows, p, cus, st);
+  if (ks == 2) return launch_cfg<E, 64, 2>(steps, rows, p, cus, st);
+  return launch_cfg<E, 64, 4>(steps, rows, p, cus, st);
+}
+
+template <int N>
+int launch_steps(const FwdSteps<N>& steps, const StepGeom& rows, FwdParams& p, const loong_step_desc& d, int ks, int cus, hipStream_t st) {
+  if (d.dtype == LOONG_FP16) return pick_cfg<Fp16>(steps, rows, p, d.head_dim, ks, cus, st);
+  return pick_cfg<Bf16>(steps, rows, p, d.head_dim, ks, cus, st);
+}
+
+// May this step share a launch with its neighbours in a run?  A launch, its ramp and the first round trip to memory cost some 8 us
+// a step; a run pays for one.  Forward replays, a launch per step -> runs: 8 steps of 8 heads x 2048 rows x 4096 keys 362 -> 322 us,
+// 16 of 8 x 300 (head_dim 64) 142 -> 83, 32 of 2 x 200 321 -> 198, 8 of 64 x 1000 240 -> 185, 4 of 32 x 6000 1236 -> 1121.
+// What longer steps may lose is each other: the workgroups of one kv head share its tiles in L2 as long as they
+// walk in step, and the parts of a diagonal block, of unequal length, put them out of step for the rest of the launch (4 steps of 4
+// heads x 32000 rows 3690 us step by step, 3880 as one run, 3640 with the diagonal step apart; 32 steps 30100 / 31800 /
+// 29750).  And with two key splits long runs lose where the launches do not (8 steps of 4 x 16000 rows, head_dim 64,
+// 1503 -> 1585, 16 of 4 x 20000 rows, 9130 -> 9300; the loops are the same instructions, the cause was not found).
+bool joins_run(const loong_step_desc& d, const StepGeom& g, int ks) {
+  double pairs = 0;
+  bool diag = false;
+  for (int a = 0; a < g.nq; ++a) {
+    pairs += keys_of_rows(g, a) * g.q[a].len;
+    for (int kb = 0; kb < g.nk; ++kb) diag |= g.cls[a][kb] == LOONG_DIAG;
+  }
+  const bool is_short = 4. * d.head_dim * pairs * d.n_q_heads * d.batch < 1.4e11;  // (some 130 us)
+  return is_short || (ks != 2 && !diag);
 }
 
 }  // namespace
 
-int launch_fwd_bf16(const loong_step_desc& d, const StepGeom& g, const void* q, const void* k,
-                    const void* v, float* out, float* lse, void* stored, void* stream) {
+int launch_fwd_bf16(const loong_step_desc* descs, int n, const void* q, const void* const* k, const void* const* v,
+                    float* out, float* lse, void* stored, void* stream) {
+  const loong_step_desc& d = descs[0];
   FwdParams p{};
-  p.q = (const uint16_t*)q; p.k = (const uint16_t*)k; p.v = (const uint16_t*)v;
-  p.out = out; p.lse = lse; p.stored = (uint16_t*)stored;
+  p.q = (const uint16_t*)q;
+  p.out = out; p.lse = lse;
   p.B = d.batch; p.Hq = d.n_q_heads; p.Hkv = d.n_kv_heads; p.G = d.n_q_heads / d.n_kv_heads;
   for (int i = 0; i < 3; ++i) { p.qs[i] = d.q_stride[i]; p.ks[i] = d.kv_stride[i]; p.os[i] = d.o_stride[i]; }
-  p.q_len = d.q_len; p.g = g; p.c = d.softmax_scale * kLog2e; p.fuse = (d.flags & LOONG_FUSE_MERGE) ? 1 : 0;
+  p.q_len = d.q_len; p.c = d.softmax_scale * kLog2e; p.fuse = (d.flags & LOONG_FUSE_MERGE) ? 1 : 0;
   hipStream_t st = static_cast<hipStream_t>(stream);
   DeviceFacts dev;
   if (int rc = device_facts(&dev)) return rc;
-  const int ks = pick_key_splits(g, p.G, p.Hq, p.B, forced_key_splits(d.flags), dev.cus);
-  if (d.dtype == LOONG_FP16) return pick_cfg<Fp16>(p, d.head_dim, ks, dev.cus, st);
-  return pick_cfg<Bf16>(p, d.head_dim, ks, dev.cus, st);
+  StepGeom g;
+  if (int rc = check_step(&descs[0], &g)) return rc;
+  auto splits = [&] { return pick_key_splits(g, p.G, p.Hq, p.B, forced_key_splits(d.flags), dev.cus); };
+  int ks = splits();
+  bool joins = joins_run(d, g, ks);
+  for (int t = 0; t < n;) {
+    FwdSteps<kMaxSteps> steps{};
+    StepGeom rows = g;  // which segments see keys at all is what the row tiling asks
+    const int launch_ks = ks;
+    bool more;
+    int m = 0;
+    do {
+      for (int a = 0; a < g.nq; ++a)
+        if (segment_sees_keys(g, a)) {
+          steps.seen[a] |= 1u << m;
+          rows.cls[a][0] = LOONG_FULL;
+        }
+      steps.step[m].k = (const uint16_t*)k[t]; steps.step[m].v = (const uint16_t*)v[t];
+      for (int a = 0; a < g.nq; ++a)
+        for (int kb = 0; kb < g.nk; ++kb) steps.step[m].cls |= (uint32_t)g.cls[a][kb] << (4 * a + 2 * kb);
+      p.g = g;
+      ++m;
+      if (++t == n) break;
+      if (int rc = check_step(&descs[t], &g)) return rc;
+      const bool joined = joins;
+      ks = splits(); joins = joins_run(d, g, ks);
+      more = joined && joins && ks == launch_ks && m < kMaxSteps;
+    } while (more);
+    p.stored = t == n ? (uint16_t*)stored : nullptr;
+    int rc;
+    if (m == 1) rc = launch_steps(FwdSteps<1>{{steps.seen[0], steps.seen[1]}, {steps.step[0]}}, rows, p, d, launch_ks, dev.cus, st);
+    else rc = launch_steps(steps, rows, p, d, launch_ks, dev.cus, st);
+    if (rc) return rc;
+    p.fuse = 1;
+  }
+  return LOONG_OK;
 }
 
 }  // namespace loong

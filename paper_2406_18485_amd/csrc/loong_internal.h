@@ -77,9 +77,9 @@ inline int forced_key_splits(int flags) {
 namespace loong {
 int launch_fwd_f32(const loong_step_desc& d, const StepGeom& g, const void* q, const void* k,
                    const void* v, float* out, float* lse, void* stream);
-// (`stored`: NULL, or where the result rounded to the storage type goes too)
-int launch_fwd_bf16(const loong_step_desc& d, const StepGeom& g, const void* q, const void* k,
-                    const void* v, float* out, float* lse, void* stored, void* stream);
+// (a valid run of `n` steps; `stored`: NULL, or where the result rounded to the storage type goes too)
+int launch_fwd_bf16(const loong_step_desc* descs, int n, const void* q, const void* const* k, const void* const* v,
+                    float* out, float* lse, void* stored, void* stream);
 // (`n` micro-steps that differ in the visiting chunk only, one geometry and one k, v, dk, dv each; n <= kMaxSteps)
 int launch_bwd_f32(const loong_step_desc& d, const StepGeom* g, int n, const void* q, const void* const* k,
                    const void* const* v, const void* d_o, const float* lse, const float* delta, float* dq,

@@ -45,6 +45,16 @@ def test_run_equals_its_steps_and_the_cast(cp, w, rank, hq, hkv, d, c, batch, ks
     assert all(torch.equal(a, b) for a, b in zip(want, (rep.out, rep.lse, rep.o)))
 
 
+@pytest.mark.parametrize("code,dtype", [(P.BF16, torch.bfloat16), (P.FP16, torch.float16)])
+@pytest.mark.parametrize("cp,w,rank,hq,hkv,d,c,batch,ks", [
+    (33, 33, 20, 2, 1, 64, 5, 1, 0), (40, 8, 39, 4, 1, 128, 3, 1, 0),   # more steps than one launch takes
+    (5, 5, 2, 4, 2, 128, 257, 2, 1), (5, 5, 2, 4, 2, 128, 257, 2, 2), (6, 3, 4, 3, 1, 64, 97, 1, 2), (6, 2, 0, 3, 3, 64, 130, 1, 1),
+    (3, 3, 1, 8, 8, 128, 2048, 1, 0)])   # diagonal step with four splits, one with two, one with four: three launches
+def test_runs_over_several_launches_equal_their_steps(cp, w, rank, hq, hkv, d, c, batch, ks, code, dtype):
+    """Steps that share a launch hand the running result on in registers, between launches it goes through memory: the same bits."""
+    test_run_equals_its_steps_and_the_cast(cp, w, rank, hq, hkv, d, c, batch, ks, dtype, code)
+
+
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("lq,hq,hkv", [(2048, 8, 8), (2049, 8, 8), (2304, 8, 2), (4500, 6, 2), (9000, 8, 8)])
 def test_a_step_of_any_number_of_rounds_takes_one_of_the_key_splits(lq, hq, hkv, d):
