@@ -95,11 +95,12 @@ struct FwdCfg {
   static constexpr int SLOT_F4 = (D / 32) * 4 + 1; // float4 per lane of one wave's partial result
   static constexpr int TILE_BYTES = NBUF * BUF_B;
   static constexpr int COMB_BYTES = (KS > 1 ? KS : 0) * NRB * SLOT_F4 * 64 * 16;
-  static constexpr int SMEM_BYTES = TILE_BYTES > COMB_BYTES ? TILE_BYTES : COMB_BYTES;
+  static constexpr int ASK_BYTES = TILE_BYTES + (NBUF == 2 ? 1024 : 0);  // (where the lines asked for ahead go)
+  static constexpr int SMEM_BYTES = ASK_BYTES > COMB_BYTES ? ASK_BYTES : COMB_BYTES;
   static_assert(KI >= 1 && KI * 1024 * kFwdWaves == TILE_B, "tile must split evenly over the waves");
 };
 
-template <class E, int D, int KS, int WGS, int N>
+template <class E, int D, int KS, int WGS, int N, bool AHEAD>
 __global__ __launch_bounds__(kFwdWaves * 64, 2 * WGS) void fwd_kernel(const FwdSteps<N> steps, const FwdParams p) {
   using C = FwdCfg<D, KS, WGS>;
   constexpr int NRB = C::NRB, BNS = C::BNS, TK = C::TK, NBUF = C::NBUF, PD = C::PD, KI = C::KI;
@@ -230,6 +231,21 @@ __global__ __launch_bounds__(kFwdWaves * 64, 2 * WGS) void fwd_kernel(const FwdS
     }
   };
 
+  // ---- with a single tile of look-ahead, 1.2 us, a tile that comes from HBM is late.  AHEAD: the early waves also ask for lines
+  // of the tile three iterations ahead (a load in 16 of them, each workgroup other lines), so that they are in this XCD's L2
+  // when that tile is staged; what arrives goes to a corner of LDS that nobody reads.
+  constexpr int ASK = 3, LPR = ROWB / 128, ASKED = 16, SHARE = TK * LPR / ASKED;  // 128-byte lines per row; lines of the K tile a workgroup asks for
+  static_assert(!AHEAD || PD == 1, "the early waves' loads are counted with one tile in flight");
+  const int ask_line = (int)(blockIdx.x >> 3) % SHARE * ASKED + (wave & 1) * 8 + (lane & 7);
+  const int ask_row = narrow ? ask_line / LPR : 0, ask_col = ask_line % LPR * 128;
+  auto ask_for = [&](int t) {
+    int kb, j0;
+    tile_of(min(t, total_t - 1), kb, j0);
+    const int last = (kb ? klen1 : klen0) - 1 - j0;
+    const unsigned char* base = (wave < 2 ? kbase : vbase) + (int64_t)((kb ? kstart1 : kstart0) + j0) * rowbytes;
+    load_to_lds_4(base, (uint32_t)min(ask_row, last) * (uint32_t)rowbytes + ask_col, smem_base + C::TILE_BYTES + wave * 256);
+  };
+
   // ---- LDS read offsets of this lane (bytes inside a tile; the wave's split and the block
   // and slice indices are added as constants)
   // K operand: row l32 (+32 jb), pieces 2 ks + hh
@@ -322,6 +338,7 @@ __global__ __launch_bounds__(kFwdWaves * 64, 2 * WGS) void fwd_kernel(const FwdS
     const int later = min(PD - 1, total_t - 1 - t);
     if (later >= 2) wait_vmcnt<2 * 2 * KI>();
     else if (later == 1) wait_vmcnt<2 * KI>();
+    else if (AHEAD && !stage_late) wait_vmcnt<1>();  // (the request behind tile t's loads; of tile 0 everything was waited for)
     else wait_vmcnt<0>();
     __syncthreads();  // every wave's part of tile t is in LDS; everyone has finished tile t-1
     // Tile t+PD goes into the buffer tile t-1 used.  A wave is held at each staging load
@@ -331,7 +348,10 @@ __global__ __launch_bounds__(kFwdWaves * 64, 2 * WGS) void fwd_kernel(const FwdS
     // right here, its partner behind its score product, each while the other computes
     // (3-5 % there; with deeper look-ahead staggering measured 7-10 % slower).
     const bool more = t + PD < total_t;
-    if (more && !stage_late) issue_tile(t + PD);
+    if (more && !stage_late) {
+      issue_tile(t + PD);
+      if constexpr (AHEAD) ask_for(t + ASK);
+    }
 
     int j0, klen;
     bool isdiag;
@@ -490,6 +510,7 @@ __global__ __launch_bounds__(kFwdWaves * 64, 2 * WGS) void fwd_kernel(const FwdS
     if (KS > 1) __syncthreads();  // the parked results have been read
     enter_step();
     issue_first_tiles();
+    if constexpr (AHEAD) wait_vmcnt<0>();
   }
 
   // ---- combine the key splits through LDS: every split parks (m, l, O^T); split j then
@@ -581,10 +602,22 @@ int launch_cfg(const FwdSteps<N>& steps, const StepGeom& rows, FwdParams& p, int
   // of one are staged four deep instead of two (2048 rows x 16384 keys x 4 heads, four splits, 128 workgroups: 102.7 -> 99 us)
   const dim3 grid(p.map.grid), block(kFwdWaves * 64);
   if constexpr (D == 64) {
-    if (KS < 4 || total > cus) fwd_kernel<E, D, KS, 2, N><<<grid, block, 0, st>>>(steps, p);
-    else fwd_kernel<E, D, 4, 1, N><<<grid, block, 0, st>>>(steps, p);
+    if (KS < 4 || total > cus) fwd_kernel<E, D, KS, 2, N, false><<<grid, block, 0, st>>>(steps, p);
+    else fwd_kernel<E, D, 4, 1, N, false><<<grid, block, 0, st>>>(steps, p);
   } else {
-    fwd_kernel<E, D, KS, 1, N><<<grid, block, 0, st>>>(steps, p);
+    // Lines are asked for ahead (AHEAD) where every q head has keys of its own, chunks are long and the chip is full: the heads'
+    // tiles, multiples of a chunk apart, then come from HBM together and late.  Replays on inputs that are in no cache, without ->
+    // with: 8 steps of 8 heads x 2048 rows x 4096 keys 394 -> 356 us, of 8 x 1200 x 2400 227 -> 209, 4 x 3500 x 7000 596 -> 534,
+    // 6 x 2000 x 4000 355 -> 318; but 16 x 1000 x 2000 220 -> 224, 8 x 512 x 1024 97 -> 100, 5 x 1300 x 2600 (105 workgroups)
+    // 182 -> 187, two heads 279 -> 286; two q heads per kv head 341 -> 341, four 329 -> 338; head_dim 64 225 -> 239.  On
+    // inputs that are in cache 2 % longer throughout.
+    if constexpr (KS == 4) {
+      if (p.G == 1 && p.B * p.Hkv >= 4 && p.g.nk * p.g.k[0].len >= 2304 && total >= cus * 7 / 8) {
+        fwd_kernel<E, D, KS, 1, N, true><<<grid, block, 0, st>>>(steps, p);
+        return check_launch("loong_attn_step_fwd (bf16)");
+      }
+    }
+    fwd_kernel<E, D, KS, 1, N, false><<<grid, block, 0, st>>>(steps, p);
   }
   return check_launch("loong_attn_step_fwd (bf16)");
 }
