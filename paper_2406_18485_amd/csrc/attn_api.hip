@@ -71,20 +71,14 @@ int loong_attn_steps_fwd(const loong_step_desc* descs, int32_t n_steps, const vo
     aligned = aligned && aligned16(k[t]) && aligned16(v[t]);
   }
   if (!aligned) return fail(LOONG_E_ALIGN, "loong_attn_step_fwd: q/k/v/out must be 16-byte aligned");
-  loong_step_desc d = *descs;
+  const loong_step_desc& d = *descs;
   const bool half = d.dtype != LOONG_FP32;
   const int64_t rows = (int64_t)d.batch * d.n_q_heads * d.q_len;
   if (o && !half && (d.o_stride[2] != d.head_dim || d.o_stride[1] != (int64_t)d.q_len * d.head_dim ||
                      (d.batch > 1 && d.o_stride[0] != d.n_q_heads * d.o_stride[1])))
     return fail(LOONG_E_UNSUPPORTED, "loong_attn_steps_fwd: the fp32 copy needs a contiguous out");
   if (rows == 0) return LOONG_OK;
-  if (half) return launch_fwd_bf16(descs, n_steps, q, k, v, out, lse, o, stream);
-  for (int t = 0; t < n_steps; ++t) {
-    if (t > 0) d.flags |= LOONG_FUSE_MERGE;
-    if (int rc = check_step(&descs[t], &g)) return rc;
-    if (int rc = launch_fwd_f32(d, g, q, k[t], v[t], out, lse, stream)) return rc;
-  }
-  return o ? loong_finalize_out(rows, d.head_dim, out, o, d.dtype, stream) : LOONG_OK;
+  return half ? launch_fwd_bf16(descs, n_steps, q, k, v, out, lse, o, stream) : launch_fwd_f32(descs, n_steps, q, k, v, out, lse, o, stream);
 }
 
 int loong_attn_step_bwd(const loong_step_desc* desc, const void* q, const void* k, const void* v,

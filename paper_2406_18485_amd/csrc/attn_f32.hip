@@ -37,8 +37,9 @@ namespace loong {
 namespace {
 
 struct F32Params {
-  const float *q, *k, *v, *d_o, *lse_in, *delta;   // (k, v: forward)
+  const float *q, *d_o, *lse_in, *delta;
   float *out, *lse, *dq;
+  float* stored;          // forward, or NULL: `out`, contiguous, is also copied here
   int B, Hq, Hkv, G, d, q_len, kv_len;
   int64_t qs[3], ks[3], os[3];
   StepGeom g;
@@ -55,6 +56,14 @@ struct F32Params {
 struct F32Run {
   const float *k[kMaxSteps], *v[kMaxSteps];
   float *dk[kMaxSteps], *dv[kMaxSteps];
+  uint32_t cls[kMaxSteps];
+  int n;
+};
+uint32_t classes(const StepGeom& g) { return g.cls[0][0] | g.cls[0][1] << 2 | g.cls[1][0] << 4 | g.cls[1][1] << 6; }
+// The micro-steps of a forward launch: a step is some 8 us of latencies, of which the launch, the first loads and the way of
+// the running rows through memory are the larger part (4 steps of 2 heads x 256 rows, d = 64: 38 -> 22 us).
+struct F32Steps {
+  const float *k[kMaxSteps], *v[kMaxSteps];
   uint32_t cls[kMaxSteps];
   int n;
 };
@@ -245,12 +254,14 @@ __device__ __forceinline__ void add_waves(typename F::Acc& a, floatx4_t* slots, 
     }
 }
 
-// ---- forward: RB x 16 query rows per workgroup (RB = 2 where rows are many: half the reads of K and V)
+// ---- forward: RB x 16 query rows per workgroup (RB = 2 where rows are many: half the reads of K and V), over the
+// launch's steps.  Between two steps the running result goes through LDS as it would go through memory: the same bits.
 template <int NP, bool EXACT, int RB>
-__global__ __launch_bounds__(kMaxWaves * 64 / RB) void fwd_f32_kernel(const F32Params p) {
+__global__ __launch_bounds__(kMaxWaves * 64 / RB) void fwd_f32_kernel(const F32Params p, const F32Steps steps) {
   using F = Frag<NP, EXACT>;
   constexpr int NM = F::NM;
   __shared__ floatx4_t slots[kMaxWaves * (NM + 1) * 64];
+  __shared__ floatx4_t state[RB * NM * 64];   // the running result between two steps
   int bh, rank;
   if (!decode_work(p.rmap, blockIdx.x, bh, rank)) return;
   const int tt = p.rtiles - 1 - rank;  // late rows see more keys: first
@@ -260,26 +271,39 @@ __global__ __launch_bounds__(kMaxWaves * 64 / RB) void fwd_f32_kernel(const F32P
   const Segment qs = qa ? p.g.q[1] : p.g.q[0];
   const int lane = threadIdx.x & 63, i = lane & 15, g = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), waves = blockDim.x >> 6;
-  const TileList keys = keys_of_rows(p.g, qa, min(row0 + kT * RB, qs.len) - 1);
-  if (keys.total == 0 && p.fuse) return;  // running result untouched
 
-  const float* kbase = p.k + b * p.ks[0] + hk * p.ks[1];
-  const float* vbase = p.v + b * p.ks[0] + hk * p.ks[1];
+  // the next step in which the last of these rows sees a key
+  TileList keys{};
+  const float *kbase = nullptr, *vbase = nullptr;
+  int step = -1;
+  auto next_step = [&] {
+    for (++step; step < steps.n; ++step) {
+      keys = keys_of_rows(with_classes(p.g, steps.cls[step]), qa, min(row0 + kT * RB, qs.len) - 1);
+      if (keys.total == 0) continue;
+      kbase = steps.k[step] + b * p.ks[0] + hk * p.ks[1];
+      vbase = steps.v[step] + b * p.ks[0] + hk * p.ks[1];
+      return true;
+    }
+    return false;
+  };
+  bool more = next_step();
+  if (!more && p.fuse && !p.stored) return;  // running result untouched
+
   typename F::Row qf[RB], kf;
   typename F::Acc o[RB];
   float m[RB], l[RB];
-  float* orow[RB];
+  int64_t orow[RB];
   float* lse_p[RB];
   auto load_k = [&](int t) {
     const TileList::Tile tl = keys.at(min(t, keys.total - 1));
     return F::load_row(kbase + (int64_t)(tl.start + min(tl.j0 + i, tl.len - 1)) * p.ks[2], g, p.d);
   };
-  if (wave < keys.total) kf = load_k(wave);
+  if (more && wave < keys.total) kf = load_k(wave);
 #pragma unroll
   for (int rb = 0; rb < RB; ++rb) {
     const int row = qs.start + min(row0 + rb * kT + i, qs.len - 1);
     qf[rb] = F::load_row(p.q + b * p.qs[0] + h * p.qs[1] + (int64_t)row * p.qs[2], g, p.d);
-    orow[rb] = p.out + b * p.os[0] + h * p.os[1] + (int64_t)row * p.os[2];
+    orow[rb] = b * p.os[0] + h * p.os[1] + (int64_t)row * p.os[2];
     lse_p[rb] = p.lse + ((int64_t)b * p.Hq + h) * p.q_len + row;
     o[rb] = F::zero();
     m[rb] = -INFINITY; l[rb] = 0.f;
@@ -288,16 +312,23 @@ __global__ __launch_bounds__(kMaxWaves * 64 / RB) void fwd_f32_kernel(const F32P
       floatx4_t x[NM];
 #pragma unroll
       for (int pc = 0; pc < NM; ++pc)
-        x[pc] = *reinterpret_cast<const floatx4_t*>(orow[rb] + (EXACT ? F::piece_col(pc, g) : min(F::piece_col(pc, g), p.d - 4)));
+        x[pc] = *reinterpret_cast<const floatx4_t*>(p.out + orow[rb] + (EXACT ? F::piece_col(pc, g) : min(F::piece_col(pc, g), p.d - 4)));
       if (prev != -INFINITY) {
         m[rb] = prev * kLog2e;
         l[rb] = g == 0 ? 1.f : 0.f;
 #pragma unroll
         for (int pc = 0; pc < NM; ++pc) F::set_piece(o[rb], pc, x[pc]);
       }
+      if (!more && row0 + rb * kT + i < qs.len) {  // nothing visible in any step: the copy alone
+#pragma unroll
+        for (int pc = 0; pc < NM; ++pc)
+          if (EXACT || F::piece_col(pc, g) < p.d) *reinterpret_cast<floatx4_t*>(p.stored + orow[rb] + F::piece_col(pc, g)) = x[pc];
+      }
     }
   }
+  if (!more && p.fuse) return;
   const float c = p.scale * kLog2e;
+  for (;;) {
   for (int t = wave; t < keys.total; t += waves) {
     const TileList::Tile tl = keys.at(t);
     const float* vtile = vbase + (int64_t)tl.start * p.ks[2];
@@ -351,26 +382,50 @@ __global__ __launch_bounds__(kMaxWaves * 64 / RB) void fwd_f32_kernel(const F32P
     mine[NM * 64] = floatx4_t{m[rb], l[rb], 0.f, 0.f};
   }
   __syncthreads();
+  more = next_step();
+  if (more && wave < keys.total) kf = load_k(wave);
 #pragma unroll
   for (int rb = 0; rb < RB; ++rb) {
     const floatx4_t* part = slots + rb * (NM + 1) * 64 + lane;
-    const int step = RB * (NM + 1) * 64;
+    const int step_w = RB * (NM + 1) * 64;
     float m_all = -INFINITY, l_all = 0.f;
-    for (int w = 0; w < waves; ++w) m_all = fmaxf(m_all, part[w * step + NM * 64][0]);
+    for (int w = 0; w < waves; ++w) m_all = fmaxf(m_all, part[w * step_w + NM * 64][0]);
     const float m_ref = m_all == -INFINITY ? 0.f : m_all;
     for (int w = 0; w < waves; ++w) {
-      const floatx4_t st = part[w * step + NM * 64];
+      const floatx4_t st = part[w * step_w + NM * 64];
       l_all += st[1] * fast_exp2(st[0] - m_ref);
     }
     const float l_tot = sum_over_groups(l_all);
     const float inv = l_tot != 0.f ? 1.f / l_tot : 0.f;
-    if (row0 + rb * kT + i >= qs.len) continue;
+    const float lse = l_tot != 0.f ? fmaf(m_all, kLn2, fast_log2(l_tot) * kLn2) : -INFINITY;
+    const bool row_ok = row0 + rb * kT + i < qs.len;
     for (int pc = wave; pc < NM; pc += waves) {
       floatx4_t acc = {0.f, 0.f, 0.f, 0.f};
-      for (int w = 0; w < waves; ++w) acc += part[w * step + pc * 64] * fast_exp2(part[w * step + NM * 64][0] - m_ref);
-      if (EXACT || F::piece_col(pc, g) < p.d) *reinterpret_cast<floatx4_t*>(orow[rb] + F::piece_col(pc, g)) = acc * inv;
+      for (int w = 0; w < waves; ++w) acc += part[w * step_w + pc * 64] * fast_exp2(part[w * step_w + NM * 64][0] - m_ref);
+      acc = acc * inv;
+      if (more) {
+        state[(rb * NM + pc) * 64 + lane] = acc;
+      } else if (row_ok && (EXACT || F::piece_col(pc, g) < p.d)) {
+        *reinterpret_cast<floatx4_t*>(p.out + orow[rb] + F::piece_col(pc, g)) = acc;
+        if (p.stored) *reinterpret_cast<floatx4_t*>(p.stored + orow[rb] + F::piece_col(pc, g)) = acc;
+      }
     }
-    if (wave == 0 && g == 0) *lse_p[rb] = l_tot != 0.f ? fmaf(m_all, kLn2, fast_log2(l_tot) * kLn2) : -INFINITY;
+    if (!more && row_ok && wave == 0 && g == 0) *lse_p[rb] = lse;
+    // (the first wave goes on from the result, the others from nothing)
+    const bool some = wave == 0 && lse != -INFINITY;
+    m[rb] = some ? lse * kLog2e : -INFINITY;
+    l[rb] = some && g == 0 ? 1.f : 0.f;
+  }
+  if (!more) return;
+  __syncthreads();
+#pragma unroll
+  for (int rb = 0; rb < RB; ++rb) {
+    o[rb] = F::zero();
+    if (wave == 0 && m[rb] != -INFINITY) {
+#pragma unroll
+      for (int pc = 0; pc < NM; ++pc) F::set_piece(o[rb], pc, state[(rb * NM + pc) * 64 + lane]);
+    }
+  }
   }
 }
 
@@ -559,7 +614,7 @@ int pick_waves(int64_t workgroups, int most) {
 }
 
 template <int NP, bool EXACT>
-int launch_fwd(F32Params& p, int cus, hipStream_t st) {
+int launch_fwd(F32Params& p, const F32Steps& steps, int cus, hipStream_t st) {
   // 32-row workgroups where they still put two on every unit (16384 rows, d = 128, a pass of two steps: 131 us
   // against 156 with two waves per tile).  16-row ones share a tile among eight waves while that is at most two
   // waves per SIMD, else among four (4 heads x 600 rows, d = 128: 35 us with four, 41 with eight, 51 with two).
@@ -568,12 +623,12 @@ int launch_fwd(F32Params& p, int cus, hipStream_t st) {
   if (wide >= 2 * cus) {
     const int w = pick_waves(p.rmap.grid, 4);
     if (!launch_fits(p.rmap.grid, w * 64)) return fail(LOONG_E_UNSUPPORTED, "fp32 path: forward grid too large");
-    fwd_f32_kernel<NP, EXACT, 2><<<dim3(p.rmap.grid), dim3(w * 64), 0, st>>>(p);
+    fwd_f32_kernel<NP, EXACT, 2><<<dim3(p.rmap.grid), dim3(w * 64), 0, st>>>(p, steps);
   } else {
     tile_rows(p, kT);
     const int w = pick_waves(p.rmap.grid, (int64_t)p.rmap.grid * kMaxWaves <= (int64_t)cus * 8 ? kMaxWaves : 4);
     if (!launch_fits(p.rmap.grid, w * 64)) return fail(LOONG_E_UNSUPPORTED, "fp32 path: forward grid too large");
-    fwd_f32_kernel<NP, EXACT, 1><<<dim3(p.rmap.grid), dim3(w * 64), 0, st>>>(p);
+    fwd_f32_kernel<NP, EXACT, 1><<<dim3(p.rmap.grid), dim3(w * 64), 0, st>>>(p, steps);
   }
   return check_launch("loong_attn_step_fwd (fp32)");
 }
@@ -608,20 +663,35 @@ int launch_bwd(F32Params& p, const F32Run& run, bool do_dq, bool do_dkv, hipStre
 
 }  // namespace
 
-int launch_fwd_f32(const loong_step_desc& d, const StepGeom& g, const void* q, const void* k,
-                   const void* v, float* out, float* lse, void* stream) {
+int launch_fwd_f32(const loong_step_desc* descs, int n, const void* q, const void* const* k, const void* const* v,
+                   float* out, float* lse, void* stored, void* stream) {
+  const loong_step_desc& d = descs[0];
   const int64_t rows = (int64_t)d.batch * d.n_q_heads * d.q_len;
   if (rows == 0) return LOONG_OK;
   if (rows > 0x7fffffff) return fail(LOONG_E_UNSUPPORTED, "fp32 path: more than 2^31-1 query rows");
   DeviceFacts dev;
   if (int rc = device_facts(&dev)) return rc;
-  F32Params p = make_params(d, g);
-  p.q = (const float*)q; p.k = (const float*)k; p.v = (const float*)v; p.out = out; p.lse = lse;
   hipStream_t st = static_cast<hipStream_t>(stream);
-  if (d.head_dim == 32) return launch_fwd<32, true>(p, dev.cus, st);
-  if (d.head_dim == 64) return launch_fwd<64, true>(p, dev.cus, st);
-  if (d.head_dim == 128) return launch_fwd<128, true>(p, dev.cus, st);
-  return launch_fwd<128, false>(p, dev.cus, st);
+  StepGeom g;
+  if (int rc = check_step(&descs[0], &g)) return rc;
+  F32Params p = make_params(d, g);
+  p.q = (const float*)q; p.out = out; p.lse = lse;
+  for (int t = 0; t < n;) {
+    F32Steps steps{};
+    for (; t < n && steps.n < kMaxSteps; ++t, ++steps.n) {
+      if (int rc = check_step(&descs[t], &g)) return rc;
+      steps.k[steps.n] = (const float*)k[t]; steps.v[steps.n] = (const float*)v[t];
+      steps.cls[steps.n] = classes(g);
+    }
+    p.stored = t == n ? (float*)stored : nullptr;
+    if (int rc = d.head_dim == 32    ? launch_fwd<32, true>(p, steps, dev.cus, st)
+                 : d.head_dim == 64  ? launch_fwd<64, true>(p, steps, dev.cus, st)
+                 : d.head_dim == 128 ? launch_fwd<128, true>(p, steps, dev.cus, st)
+                                     : launch_fwd<128, false>(p, steps, dev.cus, st))
+      return rc;
+    p.fuse = 1;
+  }
+  return LOONG_OK;
 }
 
 int launch_bwd_f32(const loong_step_desc& d, const StepGeom* g, int n, const void* q, const void* const* k,
@@ -642,7 +712,7 @@ int launch_bwd_f32(const loong_step_desc& d, const StepGeom* g, int n, const voi
   for (int t = 0; t < n; ++t) {
     run.k[t] = (const float*)k[t]; run.v[t] = (const float*)v[t];
     if (do_dkv) { run.dk[t] = dk[t]; run.dv[t] = dv[t]; }
-    run.cls[t] = g[t].cls[0][0] | g[t].cls[0][1] << 2 | g[t].cls[1][0] << 4 | g[t].cls[1][1] << 6;
+    run.cls[t] = classes(g[t]);
   }
   hipStream_t st = static_cast<hipStream_t>(stream);
   if (d.head_dim == 32) return launch_bwd<32, true>(p, run, do_dq, do_dkv, st);

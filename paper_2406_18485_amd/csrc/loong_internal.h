@@ -75,9 +75,9 @@ inline int forced_key_splits(int flags) {
 // Kernel launchers (defined next to their kernels).  All arguments are already validated.
 // The *_bf16 launchers serve both 16-bit storage types (LOONG_BF16 and LOONG_FP16).
 namespace loong {
-int launch_fwd_f32(const loong_step_desc& d, const StepGeom& g, const void* q, const void* k,
-                   const void* v, float* out, float* lse, void* stream);
-// (a valid run of `n` steps; `stored`: NULL, or where the result rounded to the storage type goes too)
+// (a valid run of `n` steps; `stored`: NULL, or where the result in the storage type goes too, contiguous; fp32: only if `out` is)
+int launch_fwd_f32(const loong_step_desc* descs, int n, const void* q, const void* const* k, const void* const* v,
+                   float* out, float* lse, void* stored, void* stream);
 int launch_fwd_bf16(const loong_step_desc* descs, int n, const void* q, const void* const* k, const void* const* v,
                     float* out, float* lse, void* stored, void* stream);
 // (`n` micro-steps that differ in the visiting chunk only, one geometry and one k, v, dk, dv each; n <= kMaxSteps)

@@ -45,7 +45,7 @@ def test_run_equals_its_steps_and_the_cast(cp, w, rank, hq, hkv, d, c, batch, ks
     assert all(torch.equal(a, b) for a, b in zip(want, (rep.out, rep.lse, rep.o)))
 
 
-@pytest.mark.parametrize("code,dtype", [(P.BF16, torch.bfloat16), (P.FP16, torch.float16)])
+@pytest.mark.parametrize("code,dtype", [(P.BF16, torch.bfloat16), (P.FP16, torch.float16), (P.FP32, torch.float32)])
 @pytest.mark.parametrize("cp,w,rank,hq,hkv,d,c,batch,ks", [
     (33, 33, 20, 2, 1, 64, 5, 1, 0), (40, 8, 39, 4, 1, 128, 3, 1, 0),   # more steps than one launch takes
     (5, 5, 2, 4, 2, 128, 257, 2, 1), (5, 5, 2, 4, 2, 128, 257, 2, 2), (6, 3, 4, 3, 1, 64, 97, 1, 2), (6, 2, 0, 3, 3, 64, 130, 1, 1),
