@@ -125,13 +125,16 @@ class RingReplay:
             k, v = (_visited(x, self._order, self._last) for x in (k_by_src, v_by_src))
             B.attn_steps_fwd(self._fwd_descs, q, k, v, self.out, self.lse, self.o, stream)
             return
-        B.init_running(self.rows, s.d, self.out, self.lse, stream)
         if self.block_out is None:
             self.block_out = torch.empty_like(self.out)
             self.block_lse = torch.empty_like(self.lse)
-        for desc, src in zip(self._fwd_descs, self._order):
-            B.attn_step_fwd(desc, q, k_by_src[src], v_by_src[src], self.block_out, self.block_lse, stream)
-            B.lse_merge(self.rows, s.d, self.out, self.lse, self.block_out, self.block_lse, stream)
+        # the first step writes the running result (an update of the neutral element would give its very bits), the
+        # others are merged into it: two launches fewer, 11 us of 97 in 3 steps of 12 heads x 1554 rows
+        for t, (desc, src) in enumerate(zip(self._fwd_descs, self._order)):
+            out, lse = (self.block_out, self.block_lse) if t else (self.out, self.lse)
+            B.attn_step_fwd(desc, q, k_by_src[src], v_by_src[src], out, lse, stream)
+            if t:
+                B.lse_merge(self.rows, s.d, self.out, self.lse, out, lse, stream)
         B.finalize_out(self.rows, s.d, self.out, self.o, s.dtype, stream)
 
     # ---- backward from the stored O and LSE: delta once, then the cp steps, whose chunks are all here, as one run
