@@ -517,6 +517,7 @@ __global__ __launch_bounds__(kFwdWaves * 64, 2 * WGS) void fwd_kernel(const FwdS
   // folds column block j (32 columns) of all splits, so the four waves share the work
   // (with fewer column blocks than splits the surplus waves leave).
   if (KS > 1) {
+    if constexpr (AHEAD) wait_vmcnt<0>();  // (a request may be on its way to a part of LDS that is reused here)
     __syncthreads();  // all reads of the last tile are done: the tile buffers are reused
     float4* slots = reinterpret_cast<float4*>(smem);
     {
