@@ -96,7 +96,9 @@ struct FwdCfg {
   static constexpr int TILE_BYTES = NBUF * BUF_B;
   static constexpr int COMB_BYTES = (KS > 1 ? KS : 0) * NRB * SLOT_F4 * 64 * 16;
   static constexpr int ASK_BYTES = TILE_BYTES + (NBUF == 2 ? 1024 : 0);  // (where the lines asked for ahead go)
-  static constexpr int SMEM_BYTES = ASK_BYTES > COMB_BYTES ? ASK_BYTES : COMB_BYTES;
+  static constexpr int ML_BYTES = ASK_BYTES + (KS == 4 && D == 128 ? (KS - 1) * NRB * 512 : 0);  // (maxima and sums of the splits between two steps)
+  static constexpr int MOST_BYTES = ASK_BYTES > COMB_BYTES ? ASK_BYTES : COMB_BYTES;
+  static constexpr int SMEM_BYTES = MOST_BYTES > ML_BYTES ? MOST_BYTES : ML_BYTES;
   static_assert(KI >= 1 && KI * 1024 * kFwdWaves == TILE_B, "tile must split evenly over the waves");
 };
 
@@ -132,24 +134,28 @@ __global__ __launch_bounds__(kFwdWaves * 64, 2 * WGS) void fwd_kernel(const FwdS
   const int my_row = qseg.start + vis_off;
   const int last_off_wg = min(row0_wg + BMH, qseg.len) - 1;
 
-  // ---- visible key tiles of this workgroup in the step it is in (per-segment facts kept in scalars: nothing in
+  // ---- visible key tiles of this workgroup, step by step (per-segment facts kept in scalars: nothing in
   // the main loop indexes the kernel arguments dynamically)
   const int klen0 = p.g.k[0].len, klen1 = p.g.nk > 1 ? p.g.k[1].len : 0;
   const int kstart0 = p.g.k[0].start, kstart1 = p.g.nk > 1 ? p.g.k[1].start : 0;
   uint32_t todo = scalar_now(qa ? steps.seen[1] : steps.seen[0]);  // the steps still to do
-  int cls0, cls1, ntk0, total_t;
-  const unsigned char *kbase, *vbase;
-  auto enter_step = [&] {
+  struct Step {
+    int cls0, cls1, ntk0, total;   // classes of the key halves; tiles in the first, in both
+    const unsigned char *k, *v;    // first row of this head
+  };
+  auto next_step = [&](uint32_t& todo) {
     const int t = N == 1 ? 0 : __builtin_ctz(todo);
     todo &= todo - 1;
     const uint32_t cls = steps.step[t].cls >> (4 * qa);
-    cls0 = cls & 3; cls1 = p.g.nk > 1 ? (cls >> 2) & 3 : LOONG_SKIP;
-    const int kend0 = cls0 == LOONG_SKIP ? 0 : cls0 == LOONG_FULL ? klen0 : min(klen0, last_off_wg + 1);
-    const int kend1 = cls1 == LOONG_SKIP ? 0 : cls1 == LOONG_FULL ? klen1 : min(klen1, last_off_wg + 1);
-    ntk0 = (kend0 + TK - 1) / TK;
-    total_t = ntk0 + (kend1 + TK - 1) / TK;
-    kbase = reinterpret_cast<const unsigned char*>(scalar_now(steps.step[t].k + b * p.ks[0] + hk * p.ks[1]));
-    vbase = reinterpret_cast<const unsigned char*>(scalar_now(steps.step[t].v + b * p.ks[0] + hk * p.ks[1]));
+    Step s;
+    s.cls0 = cls & 3; s.cls1 = p.g.nk > 1 ? (cls >> 2) & 3 : LOONG_SKIP;
+    const int kend0 = s.cls0 == LOONG_SKIP ? 0 : s.cls0 == LOONG_FULL ? klen0 : min(klen0, last_off_wg + 1);
+    const int kend1 = s.cls1 == LOONG_SKIP ? 0 : s.cls1 == LOONG_FULL ? klen1 : min(klen1, last_off_wg + 1);
+    s.ntk0 = (kend0 + TK - 1) / TK;
+    s.total = s.ntk0 + (kend1 + TK - 1) / TK;
+    s.k = reinterpret_cast<const unsigned char*>(scalar_now(steps.step[t].k + b * p.ks[0] + hk * p.ks[1]));
+    s.v = reinterpret_cast<const unsigned char*>(scalar_now(steps.step[t].v + b * p.ks[0] + hk * p.ks[1]));
+    return s;
   };
 
   float* out_row = p.out + b * p.os[0] + h * p.os[1] + (int64_t)my_row * p.os[2];
@@ -192,9 +198,9 @@ __global__ __launch_bounds__(kFwdWaves * 64, 2 * WGS) void fwd_kernel(const FwdS
   const uint32_t k_piece = (uint32_t)(ld_pos ^ ((ld_row / RP) & (CH - 1))) * 16;
   const uint32_t v_piece = (uint32_t)(ld_pos ^ (((ld_row / RP) & (4 / RP - 1)) * 4)) * 16;
   const uint32_t smem_base = (uint32_t)(uintptr_t)(lds_void_t*)smem;  // LDS byte address of the buffers
-  auto tile_of = [&](int t, int& kb, int& j0) {
-    kb = t < ntk0 ? 0 : 1;
-    j0 = (t - (kb ? ntk0 : 0)) * TK;
+  auto tile_of = [&](const Step& s, int t, int& kb, int& j0) {
+    kb = t < s.ntk0 ? 0 : 1;
+    j0 = (t - (kb ? s.ntk0 : 0)) * TK;
   };
   // byte offsets of this lane's pieces from the first row of a tile (full tiles only; the
   // 32-bit form needs TK rows to span less than 4 GiB, else every tile takes the general path)
@@ -206,27 +212,27 @@ __global__ __launch_bounds__(kFwdWaves * 64, 2 * WGS) void fwd_kernel(const FwdS
     k_off[i] = ro + k_piece;
     v_off[i] = ro + v_piece;
   }
-  auto issue_tile = [&](int t) {
+  auto issue_tile = [&](const Step& s, int t, int nth) {  // tile t of step s, the nth of this workgroup
     int kb, j0;
-    tile_of(t, kb, j0);
+    tile_of(s, t, kb, j0);
     const int len = kb ? klen1 : klen0, start = kb ? kstart1 : kstart0;
     const int64_t tb = (int64_t)(start + j0) * rowbytes;
     const int last = len - 1 - j0;  // last valid row of the tile (>= 0); later rows repeat it
-    const uint32_t kl = smem_base + (t % NBUF) * C::BUF_B + wave * 1024;
+    const uint32_t kl = smem_base + (nth % NBUF) * C::BUF_B + wave * 1024;
     const uint32_t vl = kl + C::TILE_B;
     if (narrow && last >= TK - 1) {  // whole tile: uniform base in scalar registers + per-lane offset
 #pragma unroll
       for (int i = 0; i < KI; ++i) {
-        load_to_lds_16(kbase + tb, k_off[i], kl + i * 8192);
-        load_to_lds_16(vbase + tb, v_off[i], vl + i * 8192);
+        load_to_lds_16(s.k + tb, k_off[i], kl + i * 8192);
+        load_to_lds_16(s.v + tb, v_off[i], vl + i * 8192);
       }
     } else {
 #pragma unroll
       for (int i = 0; i < KI; ++i) {
         const int r = min(ld_row + i * 8 * C::RPI, last);
         const int64_t ro = tb + (int64_t)r * rowbytes;
-        load_to_lds_16(kbase + ro + k_piece, kl + i * 8192);
-        load_to_lds_16(vbase + ro + v_piece, vl + i * 8192);
+        load_to_lds_16(s.k + ro + k_piece, kl + i * 8192);
+        load_to_lds_16(s.v + ro + v_piece, vl + i * 8192);
       }
     }
   };
@@ -238,11 +244,11 @@ __global__ __launch_bounds__(kFwdWaves * 64, 2 * WGS) void fwd_kernel(const FwdS
   static_assert(!AHEAD || PD == 1, "the early waves' loads are counted with one tile in flight");
   const int ask_line = (int)(blockIdx.x >> 3) % SHARE * ASKED + (wave & 1) * 8 + (lane & 7);
   const int ask_row = narrow ? ask_line / LPR : 0, ask_col = ask_line % LPR * 128;
-  auto ask_for = [&](int t) {
+  auto ask_for = [&](const Step& s, int t) {
     int kb, j0;
-    tile_of(min(t, total_t - 1), kb, j0);
+    tile_of(s, min(t, s.total - 1), kb, j0);
     const int last = (kb ? klen1 : klen0) - 1 - j0;
-    const unsigned char* base = (wave < 2 ? kbase : vbase) + (int64_t)((kb ? kstart1 : kstart0) + j0) * rowbytes;
+    const unsigned char* base = (wave < 2 ? s.k : s.v) + (int64_t)((kb ? kstart1 : kstart0) + j0) * rowbytes;
     load_to_lds_4(base, (uint32_t)min(ask_row, last) * (uint32_t)rowbytes + ask_col, smem_base + C::TILE_BYTES + wave * 256);
   };
 
@@ -270,12 +276,12 @@ __global__ __launch_bounds__(kFwdWaves * 64, 2 * WGS) void fwd_kernel(const FwdS
 
   // ---- per-tile pieces.  A wave skips a tile whose keys (its share of the staged tile) lie
   // past the end of the segment or past all of its rows.
-  auto my_keys = [&](int t, int& j0, int& klen, bool& isdiag) {
+  auto my_keys = [&](const Step& s, int t, int& j0, int& klen, bool& isdiag) {
     int kb;
-    tile_of(t, kb, j0);
+    tile_of(s, t, kb, j0);
     j0 += ksp * BNS;
     klen = kb ? klen1 : klen0;
-    isdiag = (kb ? cls1 : cls0) == LOONG_DIAG;
+    isdiag = (kb ? s.cls1 : s.cls0) == LOONG_DIAG;
     return wave_live && j0 < klen && !(isdiag && j0 > wrow0 + 31);
   };
 
@@ -283,13 +289,30 @@ __global__ __launch_bounds__(kFwdWaves * 64, 2 * WGS) void fwd_kernel(const FwdS
   // and the running state, so that the three latencies overlap; everything is then waited
   // for before the loop, so that no counter wait of the compiler's own ends up inside it,
   // where it would also wait for the tiles in flight.
-  auto issue_first_tiles = [&] {
+  // STREAM: the stream of tiles goes on from step to step; while the last tile of one is used, the first of the next is staged.
+  // That is for runs of short steps (32 steps of 2 heads x 200 rows 203 -> 176 us, 8 of 8 x 1024 97 -> 91, 4 of 4 x 400 with
+  // their backward 66 -> 64); what it keeps count of costs the other forms 1-3 % of their loops (head_dim 64, or fewer splits).
+  constexpr bool STREAM = N > 1 && KS == 4 && D == 128;
+  static_assert(!STREAM || PD == 1, "one tile in flight between two steps");
+  Step cur = next_step(todo);
+  Step ahead = cur;                       // STREAM: the step of the tile to stage next, that tile, and how many are staged
+  uint32_t todo_ahead = todo;
+  int t_ahead = 0, staged = 0, nth = 0;   // (nth: tiles used)
+  auto can_stage = [&](int t) { return STREAM ? t_ahead < ahead.total || todo_ahead : t < cur.total; };
+  auto stage = [&](int t) {
+    if constexpr (STREAM) {
+      if (t_ahead == ahead.total) { ahead = next_step(todo_ahead); t_ahead = 0; }
+      issue_tile(ahead, t_ahead++, staged++);
+    } else {
+      issue_tile(cur, t, t);
+    }
+  };
+  auto stage_first = [&] {
 #pragma unroll
     for (int t = 0; t < PD; ++t)
-      if (t < total_t) issue_tile(t);
+      if (can_stage(t)) stage(t);
   };
-  enter_step();
-  issue_first_tiles();
+  stage_first();
 
   // ---- Q fragments (B operand of S^T = K Q^T): row my_row, columns 16*ks + 8*hh .. +7
   bf16x8_t qf[NKS];
@@ -333,34 +356,34 @@ __global__ __launch_bounds__(kFwdWaves * 64, 2 * WGS) void fwd_kernel(const FwdS
 
   // ---- the steps, one after the other
   for (;;) {
-  for (int t = 0; t < total_t; ++t) {
-    // this wave's loads of tile t have landed when at most the later tiles' are outstanding
-    const int later = min(PD - 1, total_t - 1 - t);
+  for (int t = 0; t < cur.total; ++t, ++nth) {
+    // this wave's loads of the tile have landed when at most the later tiles' are outstanding
+    const int later = min(PD - 1, cur.total - 1 - t);
     if (later >= 2) wait_vmcnt<2 * 2 * KI>();
     else if (later == 1) wait_vmcnt<2 * KI>();
-    else if (AHEAD && !stage_late) wait_vmcnt<1>();  // (the request behind tile t's loads; of tile 0 everything was waited for)
+    else if (AHEAD && !stage_late) wait_vmcnt<1>();  // (the request behind the tile's loads; of the first one everything was waited for)
     else wait_vmcnt<0>();
-    __syncthreads();  // every wave's part of tile t is in LDS; everyone has finished tile t-1
-    // Tile t+PD goes into the buffer tile t-1 used.  A wave is held at each staging load
+    __syncthreads();  // every wave's part of the tile is in LDS; everyone has finished the one before
+    // The next tile to stage goes into the buffer of the one before.  A wave is held at each staging load
     // until the address unit has taken it (16 clocks per load, one unit per CU).  With a
     // single tile of look-ahead (the 64 KB tiles of four key splits) that hold is the largest
     // part of an iteration, and the two waves of a SIMD then stage at different times: one
     // right here, its partner behind its score product, each while the other computes
     // (3-5 % there; with deeper look-ahead staggering measured 7-10 % slower).
-    const bool more = t + PD < total_t;
+    const bool more = can_stage(t + PD);
     if (more && !stage_late) {
-      issue_tile(t + PD);
-      if constexpr (AHEAD) ask_for(t + ASK);
+      stage(t + PD);
+      if constexpr (AHEAD) ask_for(cur, t + ASK);
     }
 
     int j0, klen;
     bool isdiag;
-    if (!my_keys(t, j0, klen, isdiag)) {
-      if (more && stage_late) issue_tile(t + PD);
+    if (!my_keys(cur, t, j0, klen, isdiag)) {
+      if (more && stage_late) stage(t + PD);
       continue;
     }
-    const unsigned char* Kt = smem + (t % NBUF) * C::BUF_B + ksp * BNS * ROWB;
-    const unsigned char* Vt = smem + (t % NBUF) * C::BUF_B + C::TILE_B + ksp * BNS * ROWB;
+    const unsigned char* Kt = smem + (STREAM ? nth : t) % NBUF * C::BUF_B + ksp * BNS * ROWB;
+    const unsigned char* Vt = smem + (STREAM ? nth : t) % NBUF * C::BUF_B + C::TILE_B + ksp * BNS * ROWB;
 
     // ---- S^T = K Q^T.  The K operands are requested PF products ahead (in program order, held
     // there by the scheduling barriers): left to itself the compiler keeps two reads in flight
@@ -383,7 +406,7 @@ __global__ __launch_bounds__(kFwdWaves * 64, 2 * WGS) void fwd_kernel(const FwdS
         s[it % NJB] = E::mfma(ring[it % (PF + 1)], qf[it / NJB], it < NJB ? zero : s[it % NJB]);
       });
     }
-    if (more && stage_late) issue_tile(t + PD);
+    if (more && stage_late) stage(t + PD);
     // ---- mask (diagonal or ragged end only)
     if (j0 + BNS > klen || (isdiag && j0 + BNS - 1 > wrow0)) {
 #pragma unroll
@@ -443,19 +466,44 @@ __global__ __launch_bounds__(kFwdWaves * 64, 2 * WGS) void fwd_kernel(const FwdS
 
     if (N == 1 || todo == 0) break;
     // ---- another step follows: the running result as the next one would find it in memory, in the registers of split 0
-    // (the arithmetic of the combination below, so a run gives the bits of its steps)
-    __syncthreads();  // all reads of the last tile are done: the tile buffers are reused
+    // (the arithmetic of the combination below, so a run gives the bits of its steps).  With STREAM the other splits park
+    // theirs in the buffer of the tile just used, half of the columns at a time: the next step's first tile is on its way to
+    // the other buffer.
     float m_all = m_run, l_all = l_run;
+    if (KS > 1 || !STREAM) __syncthreads();  // all reads of the last tile are done
     if constexpr (KS > 1) {
-      float4* slots = reinterpret_cast<float4*>(smem);
-      if (ksp > 0) {
-        float4* mine = slots + ((ksp - 1) * NRB + rb) * C::SLOT_F4 * 64 + lane;
+      constexpr int HALF = STREAM ? NDB / 2 : NDB, PARKED = (KS - 1) * NRB * HALF * 4096;
+      static_assert(!STREAM || PARKED <= C::BUF_B, "half of the columns fit a buffer");
+      float4* slots = reinterpret_cast<float4*>(smem + (STREAM ? (nth - 1) % NBUF * C::BUF_B : 0));
+      float2* ml = reinterpret_cast<float2*>(smem + (STREAM ? C::ASK_BYTES : PARKED));
+      auto park = [&](int db0) {
+        float4* mine = slots + ((ksp - 1) * NRB + rb) * HALF * 4 * 64 + lane;
 #pragma unroll
-        for (int db = 0; db < NDB; ++db)
+        for (int d2 = 0; d2 < HALF; ++d2)
 #pragma unroll
           for (int vq = 0; vq < 4; ++vq)
-            mine[(db * 4 + vq) * 64] = make_float4(o[db][4 * vq], o[db][4 * vq + 1], o[db][4 * vq + 2], o[db][4 * vq + 3]);
-        mine[(NDB * 4) * 64] = make_float4(m_run, l_run, 0.f, 0.f);
+            mine[(d2 * 4 + vq) * 64] = make_float4(o[db0 + d2][4 * vq], o[db0 + d2][4 * vq + 1], o[db0 + d2][4 * vq + 2], o[db0 + d2][4 * vq + 3]);
+      };
+      float w[KS];
+      auto fold = [&](int db0) {
+#pragma unroll
+        for (int d2 = 0; d2 < HALF; ++d2)
+#pragma unroll
+          for (int vq = 0; vq < 4; ++vq) {
+            floatx16_t& od = o[db0 + d2];
+            float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+            for (int sp = 0; sp < KS; ++sp) {
+              const float4 xv = sp == 0 ? make_float4(od[4 * vq], od[4 * vq + 1], od[4 * vq + 2], od[4 * vq + 3])
+                                        : slots[((((sp - 1) * NRB + rb) * HALF + d2) * 4 + vq) * 64 + lane];
+              acc.x += xv.x * w[sp]; acc.y += xv.y * w[sp]; acc.z += xv.z * w[sp]; acc.w += xv.w * w[sp];
+            }
+            od[4 * vq] = acc.x; od[4 * vq + 1] = acc.y; od[4 * vq + 2] = acc.z; od[4 * vq + 3] = acc.w;
+          }
+      };
+      if (ksp > 0) {
+        park(0);
+        ml[((ksp - 1) * NRB + rb) * 64 + lane] = make_float2(m_run, l_run);
       }
       __syncthreads();
       if (ksp == 0) {
@@ -463,31 +511,24 @@ __global__ __launch_bounds__(kFwdWaves * 64, 2 * WGS) void fwd_kernel(const FwdS
         ms[0] = m_run; ls[0] = l_run;
 #pragma unroll
         for (int sp = 1; sp < KS; ++sp) {
-          const float4 st = slots[(((sp - 1) * NRB + rb) * C::SLOT_F4 + NDB * 4) * 64 + lane];
+          const float2 st = ml[((sp - 1) * NRB + rb) * 64 + lane];
           ms[sp] = st.x; ls[sp] = st.y;
           m_all = fmaxf(m_all, st.x);
         }
         const float m_ref = m_all == -INFINITY ? 0.f : m_all;
-        float w[KS];
         l_all = 0.f;
 #pragma unroll
         for (int sp = 0; sp < KS; ++sp) {
           w[sp] = fast_exp2(ms[sp] - m_ref);
           l_all += ls[sp] * w[sp];
         }
-#pragma unroll
-        for (int db = 0; db < NDB; ++db)
-#pragma unroll
-          for (int vq = 0; vq < 4; ++vq) {
-            float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-#pragma unroll
-            for (int sp = 0; sp < KS; ++sp) {
-              const float4 xv = sp == 0 ? make_float4(o[db][4 * vq], o[db][4 * vq + 1], o[db][4 * vq + 2], o[db][4 * vq + 3])
-                                        : slots[(((sp - 1) * NRB + rb) * C::SLOT_F4 + db * 4 + vq) * 64 + lane];
-              acc.x += xv.x * w[sp]; acc.y += xv.y * w[sp]; acc.z += xv.z * w[sp]; acc.w += xv.w * w[sp];
-            }
-            o[db][4 * vq] = acc.x; o[db][4 * vq + 1] = acc.y; o[db][4 * vq + 2] = acc.z; o[db][4 * vq + 3] = acc.w;
-          }
+        fold(0);
+      }
+      if constexpr (STREAM) {
+        __syncthreads();
+        if (ksp > 0) park(HALF);
+        __syncthreads();
+        if (ksp == 0) fold(HALF);
       }
     }
     if (ksp == 0) {
@@ -507,10 +548,9 @@ __global__ __launch_bounds__(kFwdWaves * 64, 2 * WGS) void fwd_kernel(const FwdS
 #pragma unroll
         for (int v = 0; v < 16; ++v) o[db][v] = 0.f;
     }
-    if (KS > 1) __syncthreads();  // the parked results have been read
-    enter_step();
-    issue_first_tiles();
-    if constexpr (AHEAD) wait_vmcnt<0>();
+    if (KS > 1 && !STREAM) __syncthreads();  // the parked results have been read
+    cur = next_step(todo);
+    if constexpr (!STREAM) stage_first();
   }
 
   // ---- combine the key splits through LDS: every split parks (m, l, O^T); split j then
