@@ -73,7 +73,8 @@ extern "C" {
 #define LOONG_WORKSPACE_CLEAN 64  /* bwd: the first LOONG_WORKSPACE_HEAD bytes of `workspace` are zero when the call's kernels start,
                                      so the call need not clear them.  The caller answers for it: it zeroes ALL of them itself,
                                      ordered before its first call on the stream; a call leaves a zero head zero.  (A call
-                                     without the flag clears the head first if it counts there, and leaves it alone if not.)
+                                     without the flag clears the head first if it counts there, and leaves it alone if not;
+                                     a run of several steps that forms the delta clears it wherever there is one.)
                                      Counters that were not zero make dk and dv wrong (NaN for most values they may hold) */
 #define LOONG_WORKSPACE_HEAD 65536
 /* Tuning/testing knob of the 16-bit kernels that own query rows (forward, dQ): bits 8..10 of
@@ -165,7 +166,8 @@ LOONG_API int loong_lse_merge(int64_t rows, int32_t head_dim, float* out, float*
  * fill the chip, several workgroups share a key tile's query loop and the last one to
  * arrive adds their partial sums in a fixed order.  Those partial sums and their arrival
  * counters live in `workspace`, device memory of the caller's, 16-byte aligned, at least
- * loong_workspace_bytes(desc) bytes (that may be 0: then `workspace` may be NULL).  It
+ * loong_workspace_bytes(desc) bytes (that may be 0: then `workspace` may be NULL; where only the keys of few query rows are
+ * shared, partial dQ, a missing or smaller one is not an error: they are not shared then).  It
  * may hold anything on entry (a call that counts clears the counters on `stream` before it does, unless the caller
  * vouches for them: LOONG_WORKSPACE_CLEAN) and holds nothing of value afterwards; calls that share one workspace must be
  * ordered on one stream.  A missing or too small workspace is LOONG_E_NULL / LOONG_E_SHAPE

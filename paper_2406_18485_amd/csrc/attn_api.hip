@@ -48,6 +48,20 @@ int steps_per_launch(const loong_step_desc* descs, int n_steps) {
   return d.dtype == LOONG_FP32 ? per : (int)std::min<int64_t>(per, bwd_steps_that_fit_bf16(d, g));  // (every step has as many keys)
 }
 
+// Bytes of workspace the launches of a valid 16-bit run cannot do without (`least`), or all that they make use of.
+int workspace_of_run(const loong_step_desc* descs, int n_steps, bool least, int64_t* bytes) {
+  StepGeom g[kMaxSteps];
+  *bytes = 0;
+  const int per_launch = steps_per_launch(descs, n_steps);
+  for (int t0 = 0; t0 < n_steps; t0 += per_launch) {
+    const int n = std::min(n_steps - t0, per_launch);
+    for (int t = 0; t < n; ++t)
+      if (int rc = check_step(&descs[t0 + t], &g[t])) return rc;
+    *bytes = std::max(*bytes, bwd_workspace_bytes_bf16(descs[0], g, n, least));
+  }
+  return LOONG_OK;
+}
+
 }  // namespace
 
 extern "C" {
@@ -120,9 +134,17 @@ int loong_attn_steps_bwd(const loong_step_desc* descs, int32_t n_steps, const vo
   // (the counters are cleared once for all launches of the run: each leaves them zero)
   BwdPrologue before{want_delta ? o : nullptr, d_o, delta, nullptr};
   if (desc->dtype != LOONG_FP32) {  // scratch for shared query loops: checked before anything is enqueued
-    int64_t need = 0;
-    if (int rc = loong_workspace_bytes_steps(descs, n_steps, &need)) return rc;
-    if (need > 0) {
+    int64_t need = 0, use = 0;
+    if (int rc = workspace_of_run(descs, n_steps, /*least=*/true, &need)) return rc;
+    if (int rc = workspace_of_run(descs, n_steps, /*least=*/false, &use)) return rc;
+    if (need == 0) {
+      // none is needed; one that is large enough is used (the keys of a row tile are shared then)
+      const bool clears = workspace && aligned16(workspace) && !(desc->flags & LOONG_WORKSPACE_CLEAN);
+      const bool uses = use > 0 && workspace && aligned16(workspace) && workspace_bytes >= use;
+      // (a run leaves the head of its workspace zero whether it counts or not, where the delta it forms can clear it on the side)
+      if (clears && (uses || (n_steps > 1 && want_delta && workspace_bytes >= kWsHeadBytes))) before.head = workspace;
+      if (!uses) workspace = nullptr;
+    } else {
       if (!workspace)
         return fail(LOONG_E_NULL, "loong_attn_step_bwd: this step needs a workspace of %lld bytes (loong_workspace_bytes)",
                     (long long)need);
@@ -158,20 +180,13 @@ int loong_workspace_bytes(const loong_step_desc* desc, int64_t* bytes) {
 int loong_workspace_bytes_steps(const loong_step_desc* descs, int32_t n_steps, int64_t* bytes) {
   clear_error();
   if (n_steps < 1) return fail(LOONG_E_SHAPE, "loong_workspace_bytes_steps: %d steps", n_steps);
-  StepGeom g[kMaxSteps];
+  StepGeom g;
   for (int t = 0; t < n_steps; ++t)
-    if (int rc = check_run(descs, t, &g[0])) return rc;
+    if (int rc = check_run(descs, t, &g)) return rc;
   if (!bytes) return fail(LOONG_E_NULL, "loong_workspace_bytes: NULL result");
   *bytes = 0;
   if (descs->dtype == LOONG_FP32) return LOONG_OK;
-  const int per_launch = steps_per_launch(descs, n_steps);
-  for (int t0 = 0; t0 < n_steps; t0 += per_launch) {
-    const int n = std::min(n_steps - t0, per_launch);
-    for (int t = 0; t < n; ++t)
-      if (int rc = check_step(&descs[t0 + t], &g[t])) return rc;
-    *bytes = std::max(*bytes, bwd_workspace_bytes_bf16(descs[0], g, n));
-  }
-  return LOONG_OK;
+  return workspace_of_run(descs, n_steps, /*least=*/false, bytes);
 }
 
 }  // extern "C"

@@ -36,7 +36,7 @@ __global__ __launch_bounds__(256) void zero_kernel(int64_t n4, float4* a, float4
 struct SplitPlan {
   int nkt, nsplit;
   int64_t busy;  // listed key tiles x kv heads x batch
-  double per_cu, longest_loop, longest_row;  // multiply-adds per head_dim: all / CUs; of a key tile's loop; of a row's keys
+  double per_cu, longest_row;  // multiply-adds per head_dim: all / CUs; of a row's keys
 };
 
 SplitPlan plan_split(const StepGeom* g, int n, int G, int Hkv, int B, int q_len, int cus, int per_unit, StepTable* tab) {
@@ -81,7 +81,6 @@ SplitPlan plan_split(const StepGeom* g, int n, int G, int Hkv, int B, int q_len,
   s.busy = (int64_t)n_seen * s.nkt * Hkv * B;
   // (the dK/dV half does 8 head_dim operations per pair, the dQ half 6)
   s.per_cu = 14. * pairs * G * Hkv * B / cus;
-  s.longest_loop = 8. * BN * most_rows * G;
   s.longest_row = 6. * most_keys;
   if (tab) {
     tab->klen = klen; tab->n_seen = n_seen; tab->n_halves = n_halves;
@@ -106,8 +105,20 @@ SplitPlan plan_split(const StepGeom* g, int n, int G, int Hkv, int B, int q_len,
       nsplit = (int)std::min<int64_t>((per_unit * cus + s.busy - 1) / s.busy, 16);
     if (diag && s.busy * nsplit <= 2 * cus) nsplit *= 2;  // (at head_dim 64 at most 1024 parts of 64 KB: the static scratch holds them)
   } else if (s.busy > 0) {
-    // several steps: the tiles fill the chip, the split keeps the longest loop a small part of a unit's time
-    nsplit = (int)std::min(std::max(std::ceil(s.longest_loop / (kLoopShare * s.per_cu)), 1.), 16.);
+    // Several steps: the tiles fill the chip; as many parts as make the longest loop a small part of a unit's time, or fewer
+    // where these would end later.  An estimate of that: all work over the places the chip has for workgroups and the longest single
+    // workgroup, in tiles of a query loop (some 1.9 us); a workgroup's prologue and stores are worth 3.5, parking and
+    // adding up shared sums half a tile more per part, and another 5 when the whole chip does it.  A backward pass, without the estimate -> with it: 8 steps of 2 heads x 2000 rows
+    // 149 -> 102 us, 16 of 4 x 1000 140 -> 112, 3 of 12 x 1400 (head_dim 64) 69 -> 59, 8 of 8 x 1200 137 -> 120, 4 of 32 x 600
+    // 113 -> 95, 4 of 4 x 400 31.9 -> 32.5.  (The estimate alone makes five parts of four on 8 steps of 4 x 16384 rows: 3.6 % longer.)
+    const int most = (int)std::min(std::max(std::ceil(8. * BN * most_rows * G / (kLoopShare * s.per_cu)), 1.), 16.);
+    const double loops = pairs * G * Hkv * B / ((double)BN * BM), longest = ((double)most_rows / BM + 1.) * G;  // tiles of all loops, of the longest (with its ragged ends)
+    double best = 0;
+    for (int k = 1; k <= most; ++k) {
+      const double all = (loops + s.busy * k * (k == 1 ? 3.5 : 8.5 + 0.5 * k)) / (per_unit * cus), one = longest / k + (k == 1 ? 3.5 : 4. + 0.5 * k);
+      const double time = std::max(all, one) + 0.25 * std::min(all, one);
+      if (k == 1 || time < best) { best = time; nsplit = k; }
+    }
   }
   // The last workgroup of a key tile adds up all its partial sums alone, at one CU's memory
   // rate (about 1.1 us per split), while a split shortens the loop by q_tiles x 1.9 us / n:
@@ -124,6 +135,52 @@ size_t partial_bytes(const SplitPlan& s, int head_dim) {
   return s.nsplit > 1 ? (size_t)s.busy * s.nsplit * kBwdWaves * (head_dim / 32) * 16 * 64 * sizeof(float) : 0;
 }
 
+// The q segments of a launch, and which of them see keys in any of its steps (which is what the row tiling asks).
+StepGeom seen_rows(const StepGeom* g, int n) {
+  StepGeom rows = g[0];
+  for (int t = 1; t < n; ++t)
+    for (int a = 0; a < g[t].nq; ++a)
+      if (segment_sees_keys(g[t], a)) rows.cls[a][0] = LOONG_FULL;
+  return rows;
+}
+
+// How the row-owning half of a launch is divided.  `rows`: the q segments, and which of them see keys in any step.
+struct RowPlan {
+  int ks, parts;          // key splits inside a workgroup; workgroups that share a tile's keys
+  int64_t tiles;          // q tiles x head groups x batch
+};
+
+// bytes of partial dQ it parks, behind the partial sums of the other half
+size_t row_part_bytes(const RowPlan& r, int head_dim) {
+  return r.parts > 1 ? (size_t)r.tiles * r.parts * (kRowWaves / r.ks) * 32 * head_dim * sizeof(float) : 0;
+}
+
+// Few rows and many keys: the loop over the keys of a q tile is the longest thing in the launch and most units have nothing to do,
+// so several workgroups share it.  A part keeps at least 12 tiles: parking and adding up take some 10 us, as long as 8 tiles (24 instead of 12: 115 us for the first run).
+// Whole backward steps, one workgroup -> several per tile: 121 rows x 20787 keys, 8 heads on 2, 232 -> 75 us (head_dim 64: 144 -> 44), 2 x 2
+// heads x 300 x 8000 101 -> 54; runs of 32 steps, 2 heads x 200 rows 115 -> 55, 1 x 600 142 -> 54; 8 x 60 x 3000 26.7 -> 26.9.
+// Only where both halves run: the dQ half alone needs no workspace.
+RowPlan plan_rows(const loong_step_desc& d, const StepGeom& rows, int n, const SplitPlan& plan, bool do_kv, int cus) {
+  const int G = d.n_q_heads / d.n_kv_heads;
+  RowPlan r{};
+  r.ks = forced_key_splits(d.flags);
+  if (!r.ks && n > 1 && do_kv) {
+    // several steps: the tallest row tiles whose loop still fits beside the other work of a unit
+    for (r.ks = 1; r.ks < 4 && plan.longest_row * (32 * kRowWaves / r.ks) > kRowShare * plan.per_cu;) r.ks *= 2;
+  }
+  if (!r.ks) r.ks = pick_key_splits(rows, G, d.n_q_heads, d.batch, 0, cus * wgs_per_unit(d.head_dim));
+  r.tiles = make_row_tiling(rows, G, d.n_q_heads, d.batch, kRowWaves / r.ks, /*list_blind=*/d.flags & LOONG_OVERWRITE_DQ).total_wg;
+  r.parts = 1;
+  if (do_kv && r.tiles > 0 && 2 * r.tiles <= cus) {
+    const double loop = plan.longest_row / 6. / (r.ks == 1 ? 64 : 32 * r.ks);  // tiles of keys
+    r.parts = (int)std::max<int64_t>(std::min<int64_t>({cus / r.tiles, (int64_t)(loop / 12.), 16}), 1);
+    // (a step that fits the static scratch goes on fitting)
+    if (plan.busy + r.tiles > kWsCounters ||
+        kWsHeadBytes + (int64_t)(partial_bytes(plan, d.head_dim) + row_part_bytes(r, d.head_dim)) > LOONG_STATIC_SCRATCH_BYTES) r.parts = 1;
+  }
+  return r;
+}
+
 // ---- kernels: the two halves of a step, alone and in one launch.  In the common launch of one step the
 // key-owning workgroups come first (they are the longer ones) and the row-owning ones fill the compute
 // units as these finish: no gap and no second ramp between the halves, and where neither half has
@@ -136,8 +193,7 @@ size_t partial_bytes(const SplitPlan& s, int head_dim) {
 // steps fill the chip, so few query loops are shared and one ramp and one ragged end serve all steps.
 // A backward pass, a launch per step -> the run: 8 steps of 2048 rows x 4096 keys x 8 heads 1003 -> 851 us, 32 steps of
 // 2048 rows x 4 heads, one kv head 1395 -> 529, 4 steps of 400 rows x 4 heads 158 -> 77 (with its forward).
-// (Key-owning workgroups first in a run: 7 % slower at 8 x 2048 rows.  A split so fine that a key tile's loop
-// is 0.15 of a unit's time, not 0.3: 1 % slower there, 3 % at 8 heads x 3998 rows, head_dim 64.)
+// (Key-owning workgroups first in a run: 7 % slower at 8 x 2048 rows.)
 template <class E, int D>
 __global__ __launch_bounds__(kBwdWaves * 64, 2 * wgs_per_unit(D)) void bwd_dkv_kernel(const StepTable tab, const DkvParams p) {
   __shared__ __attribute__((aligned(1024))) unsigned char smem[BwdCfg<D>::SMEM_BYTES];
@@ -201,16 +257,21 @@ int plan_dkv(StepLaunch& s, const SplitPlan& plan, int flags, int D, void* works
   return LOONG_OK;
 }
 
-// Row-owning half with `ks` key splits: work list.
-int plan_dq(StepLaunch& s, int ks) {
+// Row-owning half: work list and workspace.
+int plan_dq(StepLaunch& s, const RowPlan& plan, int64_t ws_offset, void* workspace) {
   DqParams& p = s.q;
-  const RowTiling rt = make_row_tiling(s.rows, p.G, p.Hq, p.B, kRowWaves / ks, /*list_blind=*/p.overwrite);
+  const RowTiling rt = make_row_tiling(s.rows, p.G, p.Hq, p.B, kRowWaves / plan.ks, /*list_blind=*/p.overwrite);
+  p.parts = plan.parts;
+  if (p.parts > 1) {
+    p.ws_cnt = static_cast<uint32_t*>(workspace) + (kWsCounters - plan.tiles);  // (the other half counts from the front)
+    p.ws_part = reinterpret_cast<float*>(static_cast<unsigned char*>(workspace) + ws_offset);
+  }
   p.GS = rt.GS; p.ntile[0] = rt.ntile[0]; p.ntile[1] = rt.ntile[1];
   p.tiles_total = rt.tiles_total; p.hgroups = rt.hgroups;
   s.do_q = rt.total_wg > 0;
   if (!s.do_q) return LOONG_OK;
-  if (rt.total_wg > kMaxGrid) return fail(LOONG_E_UNSUPPORTED, "backward (dQ) grid too large");
-  p.map = make_work_map((int64_t)p.B * rt.hgroups, rt.tiles_total);
+  if (rt.total_wg * p.parts > kMaxGrid) return fail(LOONG_E_UNSUPPORTED, "backward (dQ) grid too large");
+  p.map = make_work_map((int64_t)p.B * rt.hgroups, (int64_t)rt.tiles_total * p.parts);
   if (p.map.grid > kMaxGrid) return fail(LOONG_E_UNSUPPORTED, "backward (dQ) grid too large");
   return LOONG_OK;
 }
@@ -258,10 +319,7 @@ int launch_bwd_bf16(const loong_step_desc& d, const StepGeom* g, int n, const Bw
     if (s.do_kv) { c.dk = dk[t]; c.dv = dv[t]; }
   }
   const SplitPlan plan = plan_split(g, n, G, d.n_kv_heads, d.batch, d.q_len, planning_cus(), wgs_per_unit(d.head_dim), &s.tab);
-  s.rows = g[0];
-  for (int t = 1; t < n; ++t)  // (which segments see keys at all is what the row tiling asks)
-    for (int a = 0; a < g[t].nq; ++a)
-      if (segment_sees_keys(g[t], a)) s.rows.cls[a][0] = LOONG_FULL;
+  s.rows = seen_rows(g, n);
   if (s.do_kv) {
     DkvParams& p = s.kv;
     p.q = (const uint16_t*)q; p.d_o = (const uint16_t*)d_o;
@@ -284,15 +342,13 @@ int launch_bwd_bf16(const loong_step_desc& d, const StepGeom* g, int n, const Bw
     p.overwrite = (d.flags & LOONG_OVERWRITE_DQ) ? 1 : 0;
     p.rows_first = n > 1;
   }
-  int ks = forced_key_splits(d.flags);
-  if (!ks && n > 1) {
-    // several steps: the tallest row tiles whose loop still fits beside the other work of a unit
-    for (ks = 1; ks < 4 && s.do_kv && plan.longest_row * (32 * kRowWaves / ks) > kRowShare * plan.per_cu;) ks *= 2;
-    if (!s.do_kv) ks = 0;
-  }
-  if (!ks) ks = pick_key_splits(s.rows, G, d.n_q_heads, d.batch, 0, dev.cus * wgs_per_unit(d.head_dim));
+  RowPlan row_plan = plan_rows(d, s.rows, n, plan, s.do_kv, dev.cus);
+  const int ks = row_plan.ks;
+  // (a workspace without room for the partial dQ will do: a tile's keys are not shared then)
+  const int64_t row_parts_at = kWsHeadBytes + (int64_t)partial_bytes(plan, d.head_dim);
+  if (row_plan.parts > 1 && (!workspace || workspace_bytes < row_parts_at + (int64_t)row_part_bytes(row_plan, d.head_dim))) row_plan.parts = 1;
   if (s.do_q)
-    if (int rc = plan_dq(s, ks)) return rc;
+    if (int rc = plan_dq(s, row_plan, row_parts_at, workspace)) return rc;
   const int64_t n4 = (int64_t)d.batch * d.n_kv_heads * d.kv_len * d.head_dim / 4, clear_grid = (n4 + 255) / 256;
   if (s.clear && !launch_fits(clear_grid, 256)) return fail(LOONG_E_UNSUPPORTED, "backward grid too large");
   // ---- the launch fits: from here on work is enqueued
@@ -314,10 +370,14 @@ int64_t bwd_steps_that_fit_bf16(const loong_step_desc& d, const StepGeom& g) {
   return std::max<int64_t>((kMaxGrid - 8) / std::max<int64_t>(per_step, 1), 1);
 }
 
-int64_t bwd_workspace_bytes_bf16(const loong_step_desc& d, const StepGeom* g, int n) {
+int64_t bwd_workspace_bytes_bf16(const loong_step_desc& d, const StepGeom* g, int n, bool least) {
   if (d.kv_len == 0 || d.batch == 0 || (d.flags & LOONG_BWD_ONLY_DQ)) return 0;
   const SplitPlan plan = plan_split(g, n, d.n_q_heads / d.n_kv_heads, d.n_kv_heads, d.batch, d.q_len, planning_cus(), wgs_per_unit(d.head_dim), nullptr);
-  return plan.nsplit > 1 ? kWsHeadBytes + (int64_t)partial_bytes(plan, d.head_dim) : 0;
+  const int64_t keys = plan.nsplit > 1 ? (int64_t)partial_bytes(plan, d.head_dim) : 0;
+  int64_t rows = 0;
+  if (!least && !(d.flags & LOONG_BWD_ONLY_DKV) && d.q_len > 0)
+    rows = (int64_t)row_part_bytes(plan_rows(d, seen_rows(g, n), n, plan, /*do_kv=*/plan.busy > 0, planning_cus()), d.head_dim);
+  return keys + rows > 0 ? kWsHeadBytes + keys + rows : 0;
 }
 
 }  // namespace loong

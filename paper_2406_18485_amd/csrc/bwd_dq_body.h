@@ -22,6 +22,7 @@
 #include "device_utils.h"
 #include "loong_internal.h"
 #include "row_tiling.h"
+#include "split_exchange.h"
 #include "step_table.h"
 #include "work_map.h"
 
@@ -43,7 +44,10 @@ struct DqParams {
   int ntile[2];    // q tiles per q segment
   int tiles_total;
   int hgroups;     // Hq / GS
-  WorkMap map;     // units = batch x head groups, items = q tiles
+  WorkMap map;     // units = batch x head groups, items = q tiles x parts
+  int parts;       // workgroups that share the loop over the keys of a q tile
+  uint32_t* ws_cnt;  // parts > 1: counter per q tile, zero before and after the launch
+  float* ws_part;    // parts > 1: partial dQ of every (q tile, part)
   // both halves in one launch: workgroups of the half that comes first, and whether that is this one
   uint32_t first_grid;
   bool rows_first;
@@ -87,7 +91,8 @@ __device__ __forceinline__ void dq_body(const StepTable& tab, const DqParams& p,
   // visible keys come first
   int bh, rank;
   if (!decode_work(p.map, block, bh, rank)) return;
-  const int tt = p.tiles_total - 1 - rank;
+  const int tile_rank = rank / p.parts, part = rank - tile_rank * p.parts;
+  const int tt = p.tiles_total - 1 - tile_rank;
   const int b = bh / p.hgroups, hg = bh - b * p.hgroups;
   const int qa = tt >= p.ntile[0] ? 1 : 0;
   const int tile = qa ? tt - p.ntile[0] : tt;
@@ -115,10 +120,10 @@ __device__ __forceinline__ void dq_body(const StepTable& tab, const DqParams& p,
   const uint32_t e10 = scalar_now(tab.first_row[1][0]), e11 = scalar_now(tab.first_row[1][1]);
   const uint32_t first = qa ? e10 : e00, second = qa ? e11 : e01;
   const int n_list = (int)(qa ? n_list1 : n_list0), n_diag = (int)(qa ? n_diag1 : n_diag0);
-  const int total_t = (n_list - n_diag) * ((klen + TK - 1) / TK) + n_diag * ((kend_diag + TK - 1) / TK);
+  const int all_t = (n_list - n_diag) * ((klen + TK - 1) / TK) + n_diag * ((kend_diag + TK - 1) / TK);
   auto find_dq_row = [&](int off) { return p.dq + b * p.os[0] + h * p.os[1] + (int64_t)(qseg.start + min(off, qseg.len - 1)) * p.os[2]; };
-  if (total_t == 0) {  // nothing visible: no share of dQ in this step
-    if (p.overwrite && ksp == 0 && row_ok) {
+  if (all_t == 0) {  // nothing visible: no share of dQ in this step
+    if (p.overwrite && ksp == 0 && row_ok && part == 0) {
       float* const dq_row = find_dq_row(my_off);
 #pragma unroll
       for (int db = 0; db < NDB; ++db)
@@ -128,6 +133,8 @@ __device__ __forceinline__ void dq_body(const StepTable& tab, const DqParams& p,
     }
     return;
   }
+
+  const int first_t = (int)((int64_t)all_t * part / p.parts), total_t = (int)((int64_t)all_t * (part + 1) / p.parts) - first_t;
 
   // ---- Q and dO fragments (B operands): row my_row, columns 16 ks + 8 hh .. +7; the row's
   // LSE in log2 units, negated, and its delta.  A row with LSE = -inf sees no key at all.
@@ -198,6 +205,12 @@ __device__ __forceinline__ void dq_body(const StepTable& tab, const DqParams& p,
     vbase = reinterpret_cast<const unsigned char*>(v + off);
   };
   enter(ahead, 0);
+  for (int skip = first_t; skip > 0;) {  // (tile first_t exists)
+    const int n = (ahead.kend + TK - 1) / TK;
+    if (skip < n) ahead.j0 = skip * TK;
+    else enter(ahead, ahead.i + 1);
+    skip = skip < n ? 0 : skip - n;
+  }
   find_bases();
   cur = ahead;
   // byte offsets of this lane's pieces from the first row of a tile (full tiles only; the
@@ -339,12 +352,13 @@ __device__ __forceinline__ void dq_body(const StepTable& tab, const DqParams& p,
     for (int vq = 0; vq < 4; ++vq) old[db][vq] = make_float4(0.f, 0.f, 0.f, 0.f);
   // (One branch around all the loads: with one around each, they are waited for one by one, 8192 rows x 100 keys
   // x 8 heads without a split 31.9 us instead of 24.6.)
-  if (ksp == 0 && end_ok && !p.overwrite) {
+  auto request_old = [&] {
 #pragma unroll
     for (int db = 0; db < NDB; ++db)
 #pragma unroll
       for (int vq = 0; vq < 4; ++vq) old[db][vq] = *reinterpret_cast<const float4*>(dq_row + db * 32 + 8 * vq + 4 * end_hh);
-  }
+  };
+  if (ksp == 0 && end_ok && !p.overwrite && p.parts == 1) request_old();
   if (KS > 1) {
     __syncthreads();  // all reads of the last tile are done: the tile buffers are reused
     float4* slots = reinterpret_cast<float4*>(smem);
@@ -357,9 +371,9 @@ __device__ __forceinline__ void dq_body(const StepTable& tab, const DqParams& p,
           mine[(db * 4 + vq) * 64] = make_float4(acc[db][4 * vq], acc[db][4 * vq + 1], acc[db][4 * vq + 2], acc[db][4 * vq + 3]);
     }
     __syncthreads();
-    if (ksp > 0) return;
+    if (ksp > 0 && p.parts == 1) return;
 #pragma unroll 1
-    for (int sp = 1; sp < KS; ++sp) {
+    for (int sp = 1; sp < KS && ksp == 0; ++sp) {
       const float4* theirs = slots + ((sp - 1) * NRB + rb) * C::SLOT_F4 * 64 + end_lane;
 #pragma unroll
       for (int db = 0; db < NDB; ++db)
@@ -370,6 +384,54 @@ __device__ __forceinline__ void dq_body(const StepTable& tab, const DqParams& p,
           acc[db][4 * vq + 2] += x.z; acc[db][4 * vq + 3] += x.w;
         }
     }
+  }
+
+  // ---- several workgroups share the keys of this tile: all park their sums, and the last to arrive adds them up in order
+  // (split_exchange.h)
+  if (p.parts > 1) {
+    int* const role = reinterpret_cast<int*>(smem + C::TILE_BYTES - 16);
+    static_assert(C::COMB_BYTES <= C::TILE_BYTES - 16, "nobody reads there any more");
+    constexpr int WAVE_B = NDB * 16 * 64 * 4;  // bytes per row block and part
+    const int tile_id = bh * p.tiles_total + tt;
+    const __amdgpu_buffer_rsrc_t buf = part_buffer(reinterpret_cast<unsigned char*>(p.ws_part) + (int64_t)tile_id * p.parts * (NRB * WAVE_B));
+    const uint32_t mine = rb * WAVE_B + end_lane * 16;
+    if (ksp == 0) {
+#pragma unroll
+      for (int db = 0; db < NDB; ++db)
+#pragma unroll
+        for (int vq = 0; vq < 4; ++vq)
+          store_part(buf, part * (NRB * WAVE_B) + mine + (db * 4 + vq) * 1024,
+                     floatx4_t{acc[db][4 * vq], acc[db][4 * vq + 1], acc[db][4 * vq + 2], acc[db][4 * vq + 3]});
+    }
+    wait_vmcnt<0>();
+    __syncthreads();
+    if (wave == 0 && end_lane == 0) *role = arrive(p.ws_cnt + tile_id, p.parts);
+    __syncthreads();
+    if (ksp > 0 || *role == kLeaves) return;
+    const float start = *role == kGathers ? 0.f : NAN;
+    floatx16_t sum[NDB];
+#pragma unroll
+    for (int db = 0; db < NDB; ++db)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) sum[db][v] = start;
+    for (int s2 = 0; s2 < p.parts; ++s2) {
+      if (s2 == part) {
+#pragma unroll
+        for (int db = 0; db < NDB; ++db) sum[db] += acc[db];
+      } else {
+#pragma unroll
+        for (int db = 0; db < NDB; ++db)
+#pragma unroll
+          for (int vq = 0; vq < 4; ++vq) {
+            const floatx4_t x = load_part(buf, s2 * (NRB * WAVE_B) + mine + (db * 4 + vq) * 1024);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) sum[db][4 * vq + r] += x[r];
+          }
+      }
+    }
+#pragma unroll
+    for (int db = 0; db < NDB; ++db) acc[db] = sum[db];
+    if (end_ok && !p.overwrite) request_old();
   }
 
   // ---- dQ row += scale * sum: register 4 vq + r of block db is column 32 db + 8 vq + 4 hh + r

@@ -98,7 +98,8 @@ int launch_bwd_bf16(const loong_step_desc& d, const StepGeom* g, int n, const Bw
                     float* const* dk, float* const* dv, void* workspace, int64_t workspace_bytes, void* stream);
 // steps of a run that one launch has room for
 int64_t bwd_steps_that_fit_bf16(const loong_step_desc& d, const StepGeom& g);
-int64_t bwd_workspace_bytes_bf16(const loong_step_desc& d, const StepGeom* g, int n);
+// (`least`: what the launch cannot do without; else what it makes use of)
+int64_t bwd_workspace_bytes_bf16(const loong_step_desc& d, const StepGeom* g, int n, bool least);
 // delta of every row, and with `head` the counters of a workspace cleared; these alone
 int launch_delta(const loong_step_desc& d, const void* o, const void* d_o, float* delta, void* head, void* stream);
 int launch_clear_head(void* head, void* stream);
