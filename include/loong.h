@@ -133,9 +133,8 @@ LOONG_API int loong_attn_step_fwd(const loong_step_desc* desc, const void* q, co
 
 /*
  * A run of forward micro-steps whose visiting chunks are all resident: loong_attn_step_fwd for step 0, with
- * LOONG_FUSE_MERGE for every later one, and, if `o` is not NULL, loong_finalize_out of the result (the same
- * kernels in the same order: bit for bit the same (out, lse, o)); the last step stores the 16-bit `o` beside
- * `out`.  `descs` are equal in all but kv_chunk (LOONG_E_SHAPE otherwise); k, v are host arrays of n_steps device
+ * LOONG_FUSE_MERGE for every later one, and, if `o` is not NULL, loong_finalize_out of the result: bit for bit the same
+ * (out, lse, o), in as few launches as pay off; the last step stores `o` beside `out`.  `descs` are equal in all but kv_chunk (LOONG_E_SHAPE otherwise); k, v are host arrays of n_steps device
  * pointers; `o` [B,Hq,q_len,d] contiguous in desc->dtype, 16-byte aligned (fp32: `out` contiguous too).
  */
 LOONG_API int loong_attn_steps_fwd(const loong_step_desc* descs, int32_t n_steps, const void* q, const void* const* k,
@@ -160,7 +159,7 @@ LOONG_API int loong_lse_merge(int64_t rows, int32_t head_dim, float* out, float*
  * delta is written first; otherwise `o` may be NULL.
  * Outputs: dq [B,Hq,q_len,d] fp32 (o_stride) is ADDED to (zero it before the first
  * step, or let the first step write it: LOONG_OVERWRITE_DQ); every row is updated by one thread group in a fixed order, so dq is
- * bit-reproducible.  dk, dv fp32 contiguous [B,Hkv,kv_len,d] are overwritten, or added to
+ * bit-reproducible (where several workgroups share the keys of a row tile, the last to arrive adds their sums in order).  dk, dv fp32 contiguous [B,Hkv,kv_len,d] are overwritten, or added to
  * with LOONG_ACCUM_DKV (a plain read-modify-write: two calls that add into the same dk, dv
  * must be ordered).  dk, dv are bit-reproducible too: when a step has too few key tiles to
  * fill the chip, several workgroups share a key tile's query loop and the last one to

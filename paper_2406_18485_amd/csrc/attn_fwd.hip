@@ -28,6 +28,9 @@
 // softmax; the partial results are combined through LDS at the end (the log-sum-exp
 // algebra of Update).  Blocks of the (q half, k half) grid that are invisible are never
 // visited; only tiles touching the diagonal or a ragged end apply a mask.
+//
+// Runs.  A launch may serve several micro-steps (N > 1): a workgroup walks over their chunks in visit order, and between two of them
+// forms the running result, (O / l, LSE), as it would store it, in registers.
 #include <hip/hip_runtime.h>
 
 #include "device_utils.h"

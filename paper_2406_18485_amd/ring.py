@@ -2,8 +2,8 @@
 
 The ring is simulated by visiting the K/V chunks, all resident in HBM, in the order in
 which the inner and outer rings of Alg. 2 would deliver them to the simulated rank.  The
-forward is one launch of the step kernel per visit, in that order; the backward, whose visits
-only share sums, takes runs of visits per launch, since every chunk is there.  torch is used
+forward takes runs of visits per launch, one after the other, with the bits of a launch per visit; the
+backward, whose visits only share sums, runs of visits in no order, since every chunk is there.  torch is used
 for device memory and the stream only.
 """
 from __future__ import annotations
