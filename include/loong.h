@@ -73,9 +73,8 @@ extern "C" {
 #define LOONG_WORKSPACE_CLEAN 64  /* bwd: the first LOONG_WORKSPACE_HEAD bytes of `workspace` are zero when the call's kernels start,
                                      so the call need not clear them.  The caller answers for it: it zeroes ALL of them itself,
                                      ordered before its first call on the stream; a call leaves a zero head zero.  (A call
-                                     without the flag clears the head first if it counts there, and leaves it alone if not;
-                                     a run of several steps that forms the delta clears it wherever there is one.)
-                                     Counters that were not zero make dk and dv wrong (NaN for most values they may hold) */
+                                     without the flag clears the head first if it counts there, and leaves it alone if not.)
+                                     Counters that were not zero make dk, dv and dq wrong (NaN for most values they may hold) */
 #define LOONG_WORKSPACE_HEAD 65536
 /* Tuning/testing knob of the 16-bit kernels that own query rows (forward, dQ): bits 8..10 of
  * `flags` hold 1, 2 or 4 to force that many key splits per workgroup (waves that share the

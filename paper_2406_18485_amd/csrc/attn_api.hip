@@ -139,11 +139,8 @@ int loong_attn_steps_bwd(const loong_step_desc* descs, int32_t n_steps, const vo
     if (int rc = workspace_of_run(descs, n_steps, /*least=*/false, &use)) return rc;
     if (need == 0) {
       // none is needed; one that is large enough is used (the keys of a row tile are shared then)
-      const bool clears = workspace && aligned16(workspace) && !(desc->flags & LOONG_WORKSPACE_CLEAN);
-      const bool uses = use > 0 && workspace && aligned16(workspace) && workspace_bytes >= use;
-      // (a run leaves the head of its workspace zero whether it counts or not, where the delta it forms can clear it on the side)
-      if (clears && (uses || (n_steps > 1 && want_delta && workspace_bytes >= kWsHeadBytes))) before.head = workspace;
-      if (!uses) workspace = nullptr;
+      if (use == 0 || !aligned16(workspace) || workspace_bytes < use) workspace = nullptr;
+      if (workspace && !(desc->flags & LOONG_WORKSPACE_CLEAN)) before.head = workspace;
     } else {
       if (!workspace)
         return fail(LOONG_E_NULL, "loong_attn_step_bwd: this step needs a workspace of %lld bytes (loong_workspace_bytes)",

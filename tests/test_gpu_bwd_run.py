@@ -45,7 +45,8 @@ def test_run_equals_its_steps(cp, w, rank, hq, hkv, d, c, batch, ks):
         t.fill_(9.0)
     rep.backward(q, k, v, d_o)
     got = [t.clone() for t in (rep.dq, rep.dk, rep.dv)]
-    assert int(rep.workspace[:P.binding.WORKSPACE_HEAD].max()) == 0   # counters are left clean
+    if P.workspace_bytes_steps(rep._bwd_descs) > 0:   # (else the run does not count, and leaves the memory alone)
+        assert int(rep.workspace[:P.binding.WORKSPACE_HEAD].max()) == 0   # counters are left clean
     rep.backward(q, k, v, d_o)
     assert all(torch.equal(a, b) for a, b in zip(got, (rep.dq, rep.dk, rep.dv)))
     for t, step in enumerate(rep.plan):
@@ -70,6 +71,24 @@ def test_fp32_run_equals_its_steps(cp, rank, hq, hkv, d, c, batch):
         P.attn_step_bwd(_desc(rep.shape, step, 0 if t else P.OVERWRITE_DQ), q, k[src], v[src], rep.o, d_o, rep.lse, rep.delta,
                         rep.dq, rep.dk[src], rep.dv[src])
     for a, b in zip(got, (rep.dq, rep.dk, rep.dv)):
+        _close(a, b)
+
+
+@pytest.mark.parametrize("cp,hq,hkv,d,c,only", [(4, 2, 2, 64, 33, 0), (8, 8, 8, 128, 640, 0), (4, 4, 1, 128, 200, P.BWD_ONLY_DQ)])
+@pytest.mark.parametrize("form_delta", [True, False])
+def test_a_run_that_does_not_count_leaves_its_workspace_alone(cp, hq, hkv, d, c, only, form_delta):
+    rep, q, k, v, d_o = _replay(cp, cp, cp // 2, hq, hkv, d, c, 1)
+    rep.backward(q, k, v, d_o)
+    want = [t.clone() for t in (rep.dq, rep.dk, rep.dv)]
+    flags = only | P.OVERWRITE_DQ | (P.COMPUTE_DELTA if form_delta else 0)
+    descs = (P.StepDesc * cp)(*(_desc(rep.shape, s, flags) for s in rep.plan))
+    assert P.workspace_bytes_steps(descs) == 0
+    ws = torch.full((2 * P.WORKSPACE_HEAD,), 0xA5, dtype=torch.uint8, device=DEV)
+    order = [s["src_rank"] for s in rep.plan]
+    P.attn_steps_bwd(descs, q, [k[s] for s in order], [v[s] for s in order], rep.o, d_o, rep.lse, rep.delta, rep.dq,
+                     [rep.dk[s] for s in order], [rep.dv[s] for s in order], ws)
+    assert bool((ws == 0xA5).all())
+    for a, b in zip((rep.dq, rep.dk, rep.dv), want):
         _close(a, b)
 
 
