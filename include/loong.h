@@ -163,13 +163,14 @@ LOONG_API int loong_lse_merge(int64_t rows, int32_t head_dim, float* out, float*
  * must be ordered).  dk, dv are bit-reproducible too: when a step has too few key tiles to
  * fill the chip, several workgroups share a key tile's query loop and the last one to
  * arrive adds their partial sums in a fixed order.  Those partial sums and their arrival
- * counters live in `workspace`, device memory of the caller's, 16-byte aligned, at least
- * loong_workspace_bytes(desc) bytes (that may be 0: then `workspace` may be NULL; where only the keys of few query rows are
- * shared, partial dQ, a missing or smaller one is not an error: they are not shared then).  It
+ * counters live in `workspace`, device memory of the caller's, 16-byte aligned, of
+ * loong_workspace_bytes(desc) bytes (that may be 0: then `workspace` may be NULL).  With a smaller one, or none, a step does
+ * without what it can: the keys of few query rows are not shared, and the query loops of a head_dim 64 step only until every
+ * compute unit has a workgroup (the sums are those of that division, in its order, then).  It
  * may hold anything on entry (a call that counts clears the counters on `stream` before it does, unless the caller
  * vouches for them: LOONG_WORKSPACE_CLEAN) and holds nothing of value afterwards; calls that share one workspace must be
- * ordered on one stream.  A missing or too small workspace is LOONG_E_NULL / LOONG_E_SHAPE
- * and nothing is enqueued.  The bf16/fp16 kernels only; the fp32 kernels need none.
+ * ordered on one stream.  Where a step cannot do without, a missing or too small workspace is
+ * LOONG_E_NULL / LOONG_E_SHAPE and nothing is enqueued.  The bf16/fp16 kernels only; the fp32 kernels need none.
  * The two halves run as one launch on `stream`; LOONG_BWD_ONLY_DKV / LOONG_BWD_ONLY_DQ
  * run one of them (both flags together: LOONG_E_UNSUPPORTED).
  */
@@ -184,7 +185,7 @@ LOONG_API int loong_attn_step_bwd(const loong_step_desc* desc, const void* q, co
  * summed over all steps in registers before it is added to or written).  `descs` are equal in all but
  * kv_chunk (LOONG_E_SHAPE otherwise); k, v, dk, dv are host arrays of n_steps device pointers; the steps
  * run in no order, so their dk and dv must be distinct memory (equal pointers: LOONG_E_SHAPE).  Flags as for one step;
- * LOONG_COMPUTE_DELTA and LOONG_OVERWRITE_DQ apply once, to the run.  `workspace`: at least
+ * LOONG_COMPUTE_DELTA and LOONG_OVERWRITE_DQ apply once, to the run.  `workspace`:
  * loong_workspace_bytes_steps(descs, n_steps) bytes, same contract.  The results are bit-reproducible.
  */
 LOONG_API int loong_attn_steps_bwd(const loong_step_desc* descs, int32_t n_steps, const void* q, const void* const* k,
@@ -225,7 +226,7 @@ LOONG_API int loong_init_running(int64_t rows, int32_t head_dim, float* out, flo
 LOONG_API int loong_finalize_out(int64_t rows, int32_t head_dim, const float* out, void* o, int32_t dtype,
                        void* stream);
 
-/* Bytes of workspace loong_attn_step_bwd needs for this step (0 when no query loop is shared).
+/* Bytes of workspace loong_attn_step_bwd makes use of for this step (0 when no loop is shared).
  * Host-only; the answer depends on the compute-unit count of the current device (an MI355X's
  * 256 when there is none to ask), so ask on the device that will run the step.  An upper bound
  * over the steps of a replay is the maximum over its descriptors. */

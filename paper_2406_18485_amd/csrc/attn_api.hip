@@ -138,7 +138,7 @@ int loong_attn_steps_bwd(const loong_step_desc* descs, int32_t n_steps, const vo
     if (int rc = workspace_of_run(descs, n_steps, /*least=*/true, &need)) return rc;
     if (int rc = workspace_of_run(descs, n_steps, /*least=*/false, &use)) return rc;
     if (need == 0) {
-      // none is needed; one that is large enough is used (the keys of a row tile are shared then)
+      // none is needed; one that is large enough is used (more workgroups share their loops then)
       if (use == 0 || !aligned16(workspace) || workspace_bytes < use) workspace = nullptr;
       if (workspace && !(desc->flags & LOONG_WORKSPACE_CLEAN)) before.head = workspace;
     } else {

@@ -39,7 +39,8 @@ struct SplitPlan {
   double per_cu, longest_row;  // multiply-adds per head_dim: all / CUs; of a row's keys
 };
 
-SplitPlan plan_split(const StepGeom* g, int n, int G, int Hkv, int B, int q_len, int cus, int per_unit, StepTable* tab) {
+// (`fill`: a single step may split its loops until the chip is full, else only until every unit has a workgroup)
+SplitPlan plan_split(const StepGeom* g, int n, int G, int Hkv, int B, int q_len, int cus, int per_unit, bool fill, StepTable* tab) {
   constexpr int BM = kBwdBM, BN = kBwdBN;
   SplitPlan s{};
   uint32_t entry[kMaxHalves];
@@ -100,8 +101,8 @@ SplitPlan plan_split(const StepGeom* g, int n, int G, int Hkv, int B, int q_len,
     // Where the chip holds more workgroups than units (head_dim 64), loops that stay long are split until it is full; the exchange
     // costs some 12 us.  dK/dV alone, a workgroup per unit / a full chip: 128 tiles in a loop, 8 heads on 2 x 2000 rows x 20000 keys
     // 247 / 219 us; 256 tiles in either of two, 8192 x 8192 310 / 276; 32 and 24 tiles 67 / 69 and 53 / 53; 8 tiles (8 heads on 2 x
-    // 121 x 20787) 23 / 35.
-    if (s.busy > 0 && s.busy * nsplit < (int64_t)per_unit * cus && q_tiles / nsplit >= 48)
+    // 121 x 20787) 23 / 35.  (With a workspace that has no room for it a workgroup per unit will do.)
+    if (fill && s.busy > 0 && s.busy * nsplit < (int64_t)per_unit * cus && q_tiles / nsplit >= 48)
       nsplit = (int)std::min<int64_t>((per_unit * cus + s.busy - 1) / s.busy, 16);
     if (diag && s.busy * nsplit <= 2 * cus) nsplit *= 2;  // (at head_dim 64 at most 1024 parts of 64 KB: the static scratch holds them)
   } else if (s.busy > 0) {
@@ -133,6 +134,16 @@ SplitPlan plan_split(const StepGeom* g, int n, int G, int Hkv, int B, int q_len,
 // bytes of partial sums one launch parks in the workspace
 size_t partial_bytes(const SplitPlan& s, int head_dim) {
   return s.nsplit > 1 ? (size_t)s.busy * s.nsplit * kBwdWaves * (head_dim / 32) * 16 * 64 * sizeof(float) : 0;
+}
+
+SplitPlan plan_step_split(const loong_step_desc& d, const StepGeom* g, int n, bool fill) {
+  return plan_split(g, n, d.n_q_heads / d.n_kv_heads, d.n_kv_heads, d.batch, d.q_len, planning_cus(), wgs_per_unit(d.head_dim), fill, nullptr);
+}
+
+// Does the workspace hold the partial sums of query loops that are split until the chip is full?
+bool has_room(const loong_step_desc& d, const StepGeom* g, int n, const void* workspace, int64_t workspace_bytes) {
+  const size_t bytes = partial_bytes(plan_step_split(d, g, n, /*fill=*/true), d.head_dim);
+  return bytes == 0 || (workspace && workspace_bytes >= kWsHeadBytes + (int64_t)bytes);
 }
 
 // The q segments of a launch, and which of them see keys in any of its steps (which is what the row tiling asks).
@@ -318,7 +329,8 @@ int launch_bwd_bf16(const loong_step_desc& d, const StepGeom* g, int n, const Bw
     c.k = (const uint16_t*)k[t]; c.v = (const uint16_t*)v[t];
     if (s.do_kv) { c.dk = dk[t]; c.dv = dv[t]; }
   }
-  const SplitPlan plan = plan_split(g, n, G, d.n_kv_heads, d.batch, d.q_len, planning_cus(), wgs_per_unit(d.head_dim), &s.tab);
+  const SplitPlan plan = plan_split(g, n, G, d.n_kv_heads, d.batch, d.q_len, planning_cus(), wgs_per_unit(d.head_dim),
+                                    has_room(d, g, n, workspace, workspace_bytes), &s.tab);
   s.rows = seen_rows(g, n);
   if (s.do_kv) {
     DkvParams& p = s.kv;
@@ -372,9 +384,9 @@ int64_t bwd_steps_that_fit_bf16(const loong_step_desc& d, const StepGeom& g) {
 
 int64_t bwd_workspace_bytes_bf16(const loong_step_desc& d, const StepGeom* g, int n, bool least) {
   if (d.kv_len == 0 || d.batch == 0 || (d.flags & LOONG_BWD_ONLY_DQ)) return 0;
-  const SplitPlan plan = plan_split(g, n, d.n_q_heads / d.n_kv_heads, d.n_kv_heads, d.batch, d.q_len, planning_cus(), wgs_per_unit(d.head_dim), nullptr);
-  const int64_t keys = plan.nsplit > 1 ? (int64_t)partial_bytes(plan, d.head_dim) : 0;
-  int64_t rows = 0;
+  const SplitPlan plan = plan_step_split(d, g, n, /*fill=*/true);
+  int64_t keys = (int64_t)partial_bytes(plan, d.head_dim), rows = 0;
+  if (least) keys = std::min(keys, (int64_t)partial_bytes(plan_step_split(d, g, n, /*fill=*/false), d.head_dim));
   if (!least && !(d.flags & LOONG_BWD_ONLY_DKV) && d.q_len > 0)
     rows = (int64_t)row_part_bytes(plan_rows(d, seen_rows(g, n), n, plan, /*do_kv=*/plan.busy > 0, planning_cus()), d.head_dim);
   return keys + rows > 0 ? kWsHeadBytes + keys + rows : 0;

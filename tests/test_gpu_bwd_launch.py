@@ -164,6 +164,36 @@ def test_head_dim_64_gradients_at_the_edges_of_tiles(lq, lk, hq, hkv, ks, dtype)
         assert bool((err <= 8 * eps * (scale + scale.max() / 8) + 1e-6).all()), float((err / (scale + scale.max() / 8) / eps).max())
 
 
+@pytest.mark.parametrize("lq,lk,hq,hkv,parts", [(4096, 4096, 8, 8, 1), (3072, 8192, 8, 4, 1), (8192, 2048, 8, 8, 2)])
+def test_a_step_that_could_fill_the_chip_does_without_the_room_for_it(lq, lk, hq, hkv, parts):
+    """head_dim 64: with a workspace of the reported size the query loops are split until the chip is full, with a smaller one only until
+    every unit has a workgroup (`parts` per key tile), which takes less or none.  The same sums in another order: dk and dv are chains of
+    lq hq / hkv / 16 <= 512 additions, so two orders differ by at most 2 * 512 * 2^-24 = 6.1e-5 of the largest running sum."""
+    g = torch.Generator(device=DEV).manual_seed(lq + lk)
+    mk = lambda h, n: (torch.randn(1, h, n, 64, generator=g, device=DEV) * 0.5).to(torch.bfloat16)
+    t = dict(q=mk(hq, lq), k=mk(hkv, lk), v=mk(hkv, lk), d_o=mk(hq, lq))
+    t["lse"], t["delta"] = torch.full((1, hq, lq), math.log(lk) + 0.1, device=DEV), torch.zeros(1, hq, lq, device=DEV)
+    desc = P.make_desc(batch=1, n_q_heads=hq, n_kv_heads=hkv, head_dim=64, q_len=lq, kv_len=lk, dtype=P.BF16, softmax_scale=0.125,
+                       flags=P.OVERWRITE_DQ)
+    dq = lambda: torch.full(t["q"].shape, 3.0, device=DEV)
+    least = 0 if parts == 1 else P.WORKSPACE_HEAD + -(-lk // 128) * hkv * parts * 65536
+    full = P.workspace_bytes(desc)
+    assert full > least
+    want = _run(t, desc, dq(), torch.full((full,), 0xA5, dtype=torch.uint8, device=DEV))
+    small = torch.full((full - 16,), 0xA5, dtype=torch.uint8, device=DEV)
+    for ws in [small, small[:least]] + ([None] if least == 0 else []):
+        got = _run(t, desc, dq(), ws)
+        for a, b in zip(got, want):
+            assert float((a - b).abs().max()) <= 1e-4 * float(b.abs().max())
+    if least == 0:
+        assert bool((small == 0xA5).all())
+    else:
+        for ws, code in ((small[:least - 16], P.E_SHAPE), (None, P.E_NULL)):
+            with pytest.raises(P.LoongError) as e:
+                _run(t, desc, dq(), ws)
+            assert e.value.code == code
+
+
 @pytest.mark.parametrize("dtype", [P.BF16, P.FP16])
 @pytest.mark.parametrize("d,lq,lk,hq,hkv,ks", [(64, 33, 3500, 2, 1, 0), (128, 121, 6001, 4, 2, 0), (128, 1, 2000, 1, 1, 1), (64, 300, 1700, 3, 3, 2), (128, 64, 1537, 2, 2, 4)])
 def test_keys_of_a_row_tile_shared_by_several_workgroups(d, lq, lk, hq, hkv, ks, dtype):
