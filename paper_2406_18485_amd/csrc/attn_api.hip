@@ -6,7 +6,6 @@
 #include <cstring>
 
 #include "loong_internal.h"
-#include "step_table.h"
 
 using namespace loong;
 
@@ -33,14 +32,7 @@ int check_run(const loong_step_desc* descs, int t, StepGeom* g) {
 // of 820 us below).  Backward passes with 1 / 2 / 4 / all steps per launch, and by the rule: 8 steps of 98 us (4 heads
 // x 4096 rows) 788 / 693 / 546 / 469 us, 469; 8 of 420 us (8 x 8192 rows, one kv head) 3365 / 3336 / 3231 / 3341, 3342; 8 of 800
 // us (4 x 16384) 6424 / 6436 / 6513 / 6779, 6437; 4 of 1010 us (8 x 16000 rows, head_dim 64) 4052 / 4510 / 4777 / 4817, 4058.
-int steps_per_launch(const loong_step_desc* descs, int n_steps) {
-  const loong_step_desc& d = descs[0];
-  double pairs = 0;
-  StepGeom g;
-  for (int t = 0; t < n_steps; ++t) {
-    check_step(&descs[t], &g);
-    for (int a = 0; a < g.nq; ++a) pairs += keys_of_rows(g, a) * g.q[a].len;
-  }
+int steps_per_launch(const loong_step_desc& d, const StepGeom& g, double pairs, int n_steps) {
   const double flops = 14. * d.head_dim * pairs * d.n_q_heads * d.batch;
   const double per_launch = 9.4e9 * d.head_dim;
   const int launches = (int)std::max(std::min(std::ceil(flops / per_launch), (double)n_steps), std::ceil(n_steps / (double)kMaxSteps));
@@ -48,19 +40,36 @@ int steps_per_launch(const loong_step_desc* descs, int n_steps) {
   return d.dtype == LOONG_FP32 ? per : (int)std::min<int64_t>(per, bwd_steps_that_fit_bf16(d, g));  // (every step has as many keys)
 }
 
-// Bytes of workspace the launches of a valid 16-bit run cannot do without (`least`), or all that they make use of.
-int workspace_of_run(const loong_step_desc* descs, int n_steps, bool least, int64_t* bytes) {
-  StepGeom g[kMaxSteps];
-  *bytes = 0;
-  const int per_launch = steps_per_launch(descs, n_steps);
-  for (int t0 = 0; t0 < n_steps; t0 += per_launch) {
-    const int n = std::min(n_steps - t0, per_launch);
-    for (int t = 0; t < n; ++t)
-      if (int rc = check_step(&descs[t0 + t], &g[t])) return rc;
-    *bytes = std::max(*bytes, bwd_workspace_bytes_bf16(descs[0], g, n, least));
+// A backward run, valid as a whole, cut into launches.
+struct BwdRun {
+  const loong_step_desc* descs;
+  int n_steps, per_launch;
+  StepGeom g[kMaxSteps];   // of the launch looked at last
+  loong_step_desc d;       // the same: the first step's, and dq is written by the first launch alone
+
+  int check(const loong_step_desc* descs_, int n_steps_) {
+    descs = descs_; n_steps = n_steps_;
+    double pairs = 0;
+    StepGeom x;
+    for (int t = 0; t < n_steps; ++t) {
+      if (int rc = check_run(descs, t, &x)) return rc;
+      for (int a = 0; a < x.nq; ++a) pairs += keys_of_rows(x, a) * x.q[a].len;
+      if (t < kMaxSteps) g[t] = x;
+    }
+    d = descs[0];
+    per_launch = steps_per_launch(d, x, pairs, n_steps);
+    return LOONG_OK;
   }
-  return LOONG_OK;
-}
+  // The steps of the launch that starts at step t0 (right after check: of the first).
+  int steps(int t0) const { return std::min(n_steps - t0, per_launch); }
+  int look_at(int t0) {
+    for (int t = 0; t < steps(t0); ++t)
+      if (int rc = check_step(&descs[t0 + t], &g[t])) return rc;
+    d = descs[0];
+    if (t0 > 0) d.flags &= ~LOONG_OVERWRITE_DQ;
+    return LOONG_OK;
+  }
+};
 
 }  // namespace
 
@@ -107,10 +116,9 @@ int loong_attn_steps_bwd(const loong_step_desc* descs, int32_t n_steps, const vo
                          void* stream) {
   clear_error();
   if (n_steps < 1) return fail(LOONG_E_SHAPE, "loong_attn_steps_bwd: %d steps", n_steps);
-  StepGeom g[kMaxSteps];
+  BwdRun run;
   // every step is validated before anything is enqueued
-  for (int t = 0; t < n_steps; ++t)
-    if (int rc = check_run(descs, t, &g[0])) return rc;
+  if (int rc = run.check(descs, n_steps)) return rc;
   const loong_step_desc* desc = descs;
   const bool only_dkv = desc->flags & LOONG_BWD_ONLY_DKV, only_dq = desc->flags & LOONG_BWD_ONLY_DQ;
   if (only_dkv && only_dq)
@@ -131,17 +139,29 @@ int loong_attn_steps_bwd(const loong_step_desc* descs, int32_t n_steps, const vo
         return fail(LOONG_E_SHAPE, "loong_attn_steps_bwd: steps %d and %d have the same dk or dv", u, t);
   if (workspace_bytes < 0) return fail(LOONG_E_SHAPE, "loong_attn_step_bwd: negative workspace size");
   if (desc->batch == 0) return LOONG_OK;
-  // (the counters are cleared once for all launches of the run: each leaves them zero)
+  // (the counters are cleared once for all launches of the run that count: each leaves them zero)
   BwdPrologue before{want_delta ? o : nullptr, d_o, delta, nullptr};
-  if (desc->dtype != LOONG_FP32) {  // scratch for shared query loops: checked before anything is enqueued
-    int64_t need = 0, use = 0;
-    if (int rc = workspace_of_run(descs, n_steps, /*least=*/true, &need)) return rc;
-    if (int rc = workspace_of_run(descs, n_steps, /*least=*/false, &use)) return rc;
-    if (need == 0) {
-      // none is needed; one that is large enough is used (more workgroups share their loops then)
-      if (use == 0 || !aligned16(workspace) || workspace_bytes < use) workspace = nullptr;
-      if (workspace && !(desc->flags & LOONG_WORKSPACE_CLEAN)) before.head = workspace;
-    } else {
+  if (desc->dtype == LOONG_FP32) {
+    if (int rc = launch_prologue(*desc, before, stream)) return rc;
+    for (int t0 = 0; t0 < n_steps; t0 += run.per_launch) {
+      if (int rc = t0 ? run.look_at(t0) : LOONG_OK) return rc;
+      if (int rc = launch_bwd_f32(run.d, run.g, run.steps(t0), q, k + t0, v + t0, d_o, lse, delta, dq, only_dq ? nullptr : dk + t0,
+                                  only_dq ? nullptr : dv + t0, stream))
+        return rc;
+    }
+    return LOONG_OK;
+  }
+  // scratch for shared loops: checked before anything is enqueued.  (A run of one launch, as all short ones are, is looked at
+  // and planned once: some 0.5 us for 4 steps, 2.5 for 32, which a call that asked for each size and planned again paid three times.)
+  BwdPlan plan{};
+  bool counts = false;
+  for (int t0 = 0; t0 < n_steps; t0 += run.per_launch) {
+    if (t0) {
+      if (int rc = run.look_at(t0)) return rc;
+      plan = {};
+    }
+    plan_bwd_bf16(run.d, run.g, run.steps(t0), &plan);
+    if (const int64_t need = least_workspace_of(plan)) {
       if (!workspace)
         return fail(LOONG_E_NULL, "loong_attn_step_bwd: this step needs a workspace of %lld bytes (loong_workspace_bytes)",
                     (long long)need);
@@ -149,22 +169,19 @@ int loong_attn_steps_bwd(const loong_step_desc* descs, int32_t n_steps, const vo
       if (workspace_bytes < need)
         return fail(LOONG_E_SHAPE, "loong_attn_step_bwd: workspace of %lld bytes, this step needs %lld (loong_workspace_bytes)",
                     (long long)workspace_bytes, (long long)need);
-      if (!(desc->flags & LOONG_WORKSPACE_CLEAN)) before.head = workspace;
     }
+    counts |= fit_bwd_bf16(&plan, workspace, workspace_bytes);
   }
-  if (desc->dtype == LOONG_FP32)
-    if (int rc = launch_prologue(*desc, before, stream)) return rc;
-  const int per_launch = steps_per_launch(descs, n_steps);
-  for (int t0 = 0; t0 < n_steps; t0 += per_launch) {
-    const int n = std::min(n_steps - t0, per_launch);
-    loong_step_desc d = *desc;
-    for (int t = 0; t < n; ++t)
-      if (int rc = check_step(&descs[t0 + t], &g[t])) return rc;
-    if (t0 > 0) d.flags &= ~LOONG_OVERWRITE_DQ;
-    float *const *dk_t = only_dq ? nullptr : dk + t0, *const *dv_t = only_dq ? nullptr : dv + t0;
-    if (int rc = desc->dtype == LOONG_FP32
-                     ? launch_bwd_f32(d, g, n, q, k + t0, v + t0, d_o, lse, delta, dq, dk_t, dv_t, stream)
-                     : launch_bwd_bf16(d, g, n, t0 ? nullptr : &before, q, k + t0, v + t0, d_o, lse, delta, dq, dk_t, dv_t, workspace, workspace_bytes, stream))
+  if (counts && !(desc->flags & LOONG_WORKSPACE_CLEAN)) before.head = workspace;
+  for (int t0 = 0; t0 < n_steps; t0 += run.per_launch) {
+    if (run.per_launch < n_steps) {
+      if (int rc = run.look_at(t0)) return rc;
+      plan = {};
+      plan_bwd_bf16(run.d, run.g, run.steps(t0), &plan);
+      fit_bwd_bf16(&plan, workspace, workspace_bytes);
+    }
+    if (int rc = launch_bwd_bf16(run.d, plan, run.steps(t0), t0 ? nullptr : &before, q, k + t0, v + t0, d_o, lse, delta, dq,
+                                 only_dq ? nullptr : dk + t0, only_dq ? nullptr : dv + t0, workspace, stream))
       return rc;
   }
   return LOONG_OK;
@@ -177,13 +194,18 @@ int loong_workspace_bytes(const loong_step_desc* desc, int64_t* bytes) {
 int loong_workspace_bytes_steps(const loong_step_desc* descs, int32_t n_steps, int64_t* bytes) {
   clear_error();
   if (n_steps < 1) return fail(LOONG_E_SHAPE, "loong_workspace_bytes_steps: %d steps", n_steps);
-  StepGeom g;
-  for (int t = 0; t < n_steps; ++t)
-    if (int rc = check_run(descs, t, &g)) return rc;
+  BwdRun run;
+  if (int rc = run.check(descs, n_steps)) return rc;
   if (!bytes) return fail(LOONG_E_NULL, "loong_workspace_bytes: NULL result");
   *bytes = 0;
-  if (descs->dtype == LOONG_FP32) return LOONG_OK;
-  return workspace_of_run(descs, n_steps, /*least=*/false, bytes);
+  if (descs->dtype == LOONG_FP32 || descs->batch == 0) return LOONG_OK;
+  for (int t0 = 0; t0 < n_steps; t0 += run.per_launch) {
+    if (int rc = t0 ? run.look_at(t0) : LOONG_OK) return rc;
+    BwdPlan plan{};
+    plan_bwd_bf16(run.d, run.g, run.steps(t0), &plan);
+    *bytes = std::max(*bytes, workspace_of(plan));
+  }
+  return LOONG_OK;
 }
 
 }  // extern "C"

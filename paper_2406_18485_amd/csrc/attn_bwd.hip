@@ -30,19 +30,18 @@ __global__ __launch_bounds__(256) void zero_kernel(int64_t n4, float4* a, float4
   }
 }
 
-// Work list of a launch over `n` micro-steps that differ in the visiting chunk only: the key halves some
+// bytes of partial sums one launch parks in the workspace
+int64_t partial_bytes(int64_t busy, int nsplit, int head_dim) {
+  return nsplit > 1 ? busy * nsplit * kBwdWaves * (head_dim / 32) * 16 * 64 * (int64_t)sizeof(float) : 0;
+}
+
+// Key-owning half, and work list of a launch over `n` micro-steps that differ in the visiting chunk only: the key halves some
 // row sees and those nobody sees (their gradients are cleared), and how many workgroups share the query
 // loop of a key tile.
-struct SplitPlan {
-  int nkt, nsplit;
-  int64_t busy;  // listed key tiles x kv heads x batch
-  double per_cu, longest_row;  // multiply-adds per head_dim: all / CUs; of a row's keys
-};
-
-// (`fill`: a single step may split its loops until the chip is full, else only until every unit has a workgroup)
-SplitPlan plan_split(const StepGeom* g, int n, int G, int Hkv, int B, int q_len, int cus, int per_unit, bool fill, StepTable* tab) {
+void plan_split(const loong_step_desc& d, const StepGeom* g, int n, int cus, BwdPlan& s) {
   constexpr int BM = kBwdBM, BN = kBwdBN;
-  SplitPlan s{};
+  const int G = d.n_q_heads / d.n_kv_heads, Hkv = d.n_kv_heads, B = d.batch, per_unit = wgs_per_unit(d.head_dim);
+  StepTable* const tab = &s.tab;
   uint32_t entry[kMaxHalves];
   int64_t rows[kMaxHalves];
   int n_halves = 0, n_seen = 0, n_list[2] = {0, 0}, n_diag[2] = {0, 0};
@@ -60,7 +59,7 @@ SplitPlan plan_split(const StepGeom* g, int n, int G, int Hkv, int B, int q_len,
         if (cls == LOONG_SKIP || g[t].q[a].len == 0) continue;
         seen += g[t].q[a].len;
         diag |= cls == LOONG_DIAG;
-        if (tab) tab->row[a][n_list[a]] = (uint32_t)t | (uint32_t)kb << 8 | (cls == LOONG_DIAG ? kDiagEntry : 0u);
+        tab->row[a][n_list[a]] = (uint32_t)t | (uint32_t)kb << 8 | (cls == LOONG_DIAG ? kDiagEntry : 0u);
         ++n_list[a];
         n_diag[a] += cls == LOONG_DIAG;
       }
@@ -83,28 +82,37 @@ SplitPlan plan_split(const StepGeom* g, int n, int G, int Hkv, int B, int q_len,
   // (the dK/dV half does 8 head_dim operations per pair, the dQ half 6)
   s.per_cu = 14. * pairs * G * Hkv * B / cus;
   s.longest_row = 6. * most_keys;
-  if (tab) {
-    tab->klen = klen; tab->n_seen = n_seen; tab->n_halves = n_halves;
-    for (int i = 0; i < n_halves; ++i) tab->half[i] = entry[i];
-    for (int a = 0; a < 2; ++a) { tab->n_list[a] = n_list[a]; tab->n_diag[a] = n_diag[a]; }
-    for (int i = 0; i < 2; ++i) {
-      tab->first_half[i] = tab->half[i];
-      for (int a = 0; a < 2; ++a) tab->first_row[a][i] = tab->row[a][i];
-    }
+  tab->klen = klen; tab->n_seen = n_seen; tab->n_halves = n_halves;
+  for (int i = 0; i < n_halves; ++i) tab->half[i] = entry[i];
+  for (int a = 0; a < 2; ++a) { tab->n_list[a] = n_list[a]; tab->n_diag[a] = n_diag[a]; }
+  for (int i = 0; i < 2; ++i) {
+    tab->first_half[i] = tab->half[i];
+    for (int a = 0; a < 2; ++a) tab->first_row[a][i] = tab->row[a][i];
   }
-  int nsplit = 1;
-  const int64_t q_tiles = std::max<int64_t>((int64_t)G * ((q_len + BM - 1) / BM), 1);
+  const int64_t q_tiles = std::max<int64_t>((int64_t)G * ((d.q_len + BM - 1) / BM), 1);
+  // The last workgroup of a key tile adds up all its partial sums alone, at one CU's memory
+  // rate (about 1.1 us per split), while a split shortens the loop by q_tiles x 1.9 us / n:
+  // past n = sqrt(1.76 q_tiles) more splits lengthen the launch.
+  auto at_most = [&](int nsplit) {
+    nsplit = (int)std::min<int64_t>(nsplit, std::max<int64_t>(2, (int64_t)std::sqrt(1.76 * (double)q_tiles)));
+    nsplit = (int)std::min<int64_t>(nsplit, q_tiles);
+    return s.busy > kWsCounters ? 1 : nsplit;  // (cannot happen for one step: loops are only shared when key tiles are few)
+  };
+  s.nsplit = s.nsplit_least = 1;
   if (n == 1) {
     // one step: more than one workgroup when the listed tiles are fewer than the compute units, and
     // twice as many when a diagonal block makes the loop lengths uneven
+    int nsplit = 1;
     if (s.busy > 0 && s.busy < cus) nsplit = (int)std::min<int64_t>((cus + s.busy - 1) / s.busy, 16);
+    auto uneven = [&](int nsplit) { return diag && s.busy * nsplit <= 2 * cus ? 2 * nsplit : nsplit; };  // (at head_dim 64 at most 1024 parts of 64 KB: the static scratch holds them)
+    s.nsplit_least = at_most(uneven(nsplit));
     // Where the chip holds more workgroups than units (head_dim 64), loops that stay long are split until it is full; the exchange
     // costs some 12 us.  dK/dV alone, a workgroup per unit / a full chip: 128 tiles in a loop, 8 heads on 2 x 2000 rows x 20000 keys
     // 247 / 219 us; 256 tiles in either of two, 8192 x 8192 310 / 276; 32 and 24 tiles 67 / 69 and 53 / 53; 8 tiles (8 heads on 2 x
     // 121 x 20787) 23 / 35.  (With a workspace that has no room for it a workgroup per unit will do.)
-    if (fill && s.busy > 0 && s.busy * nsplit < (int64_t)per_unit * cus && q_tiles / nsplit >= 48)
+    if (s.busy > 0 && s.busy * nsplit < (int64_t)per_unit * cus && q_tiles / nsplit >= 48)
       nsplit = (int)std::min<int64_t>((per_unit * cus + s.busy - 1) / s.busy, 16);
-    if (diag && s.busy * nsplit <= 2 * cus) nsplit *= 2;  // (at head_dim 64 at most 1024 parts of 64 KB: the static scratch holds them)
+    s.nsplit = at_most(uneven(nsplit));
   } else if (s.busy > 0) {
     // Several steps: the tiles fill the chip; as many parts as make the longest loop a small part of a unit's time, or fewer
     // where these would end later.  An estimate of that: all work over the places the chip has for workgroups and the longest single
@@ -115,35 +123,14 @@ SplitPlan plan_split(const StepGeom* g, int n, int G, int Hkv, int B, int q_len,
     const int most = (int)std::min(std::max(std::ceil(8. * BN * most_rows * G / (kLoopShare * s.per_cu)), 1.), 16.);
     const double loops = pairs * G * Hkv * B / ((double)BN * BM), longest = ((double)most_rows / BM + 1.) * G;  // tiles of all loops, of the longest (with its ragged ends)
     double best = 0;
+    int nsplit = 1;
     for (int k = 1; k <= most; ++k) {
       const double all = (loops + s.busy * k * (k == 1 ? 3.5 : 8.5 + 0.5 * k)) / (per_unit * cus), one = longest / k + (k == 1 ? 3.5 : 4. + 0.5 * k);
       const double time = std::max(all, one) + 0.25 * std::min(all, one);
       if (k == 1 || time < best) { best = time; nsplit = k; }
     }
+    s.nsplit = s.nsplit_least = at_most(nsplit);
   }
-  // The last workgroup of a key tile adds up all its partial sums alone, at one CU's memory
-  // rate (about 1.1 us per split), while a split shortens the loop by q_tiles x 1.9 us / n:
-  // past n = sqrt(1.76 q_tiles) more splits lengthen the launch.
-  nsplit = (int)std::min<int64_t>(nsplit, std::max<int64_t>(2, (int64_t)std::sqrt(1.76 * (double)q_tiles)));
-  nsplit = (int)std::min<int64_t>(nsplit, q_tiles);
-  if (s.busy > kWsCounters) nsplit = 1;  // (cannot happen for one step: loops are only shared when key tiles are few)
-  s.nsplit = nsplit;
-  return s;
-}
-
-// bytes of partial sums one launch parks in the workspace
-size_t partial_bytes(const SplitPlan& s, int head_dim) {
-  return s.nsplit > 1 ? (size_t)s.busy * s.nsplit * kBwdWaves * (head_dim / 32) * 16 * 64 * sizeof(float) : 0;
-}
-
-SplitPlan plan_step_split(const loong_step_desc& d, const StepGeom* g, int n, bool fill) {
-  return plan_split(g, n, d.n_q_heads / d.n_kv_heads, d.n_kv_heads, d.batch, d.q_len, planning_cus(), wgs_per_unit(d.head_dim), fill, nullptr);
-}
-
-// Does the workspace hold the partial sums of query loops that are split until the chip is full?
-bool has_room(const loong_step_desc& d, const StepGeom* g, int n, const void* workspace, int64_t workspace_bytes) {
-  const size_t bytes = partial_bytes(plan_step_split(d, g, n, /*fill=*/true), d.head_dim);
-  return bytes == 0 || (workspace && workspace_bytes >= kWsHeadBytes + (int64_t)bytes);
 }
 
 // The q segments of a launch, and which of them see keys in any of its steps (which is what the row tiling asks).
@@ -155,41 +142,31 @@ StepGeom seen_rows(const StepGeom* g, int n) {
   return rows;
 }
 
-// How the row-owning half of a launch is divided.  `rows`: the q segments, and which of them see keys in any step.
-struct RowPlan {
-  int ks, parts;          // key splits inside a workgroup; workgroups that share a tile's keys
-  int64_t tiles;          // q tiles x head groups x batch
-};
-
-// bytes of partial dQ it parks, behind the partial sums of the other half
-size_t row_part_bytes(const RowPlan& r, int head_dim) {
-  return r.parts > 1 ? (size_t)r.tiles * r.parts * (kRowWaves / r.ks) * 32 * head_dim * sizeof(float) : 0;
-}
-
 // Few rows and many keys: the loop over the keys of a q tile is the longest thing in the launch and most units have nothing to do,
 // so several workgroups share it.  A part keeps at least 12 tiles: parking and adding up take some 10 us, as long as 8 tiles (24 instead of 12: 115 us for the first run).
 // Whole backward steps, one workgroup -> several per tile: 121 rows x 20787 keys, 8 heads on 2, 232 -> 75 us (head_dim 64: 144 -> 44), 2 x 2
 // heads x 300 x 8000 101 -> 54; runs of 32 steps, 2 heads x 200 rows 115 -> 55, 1 x 600 142 -> 54; 8 x 60 x 3000 26.7 -> 26.9.
 // Only where both halves run: the dQ half alone needs no workspace.
-RowPlan plan_rows(const loong_step_desc& d, const StepGeom& rows, int n, const SplitPlan& plan, bool do_kv, int cus) {
+void plan_rows(const loong_step_desc& d, int n, bool do_kv, int cus, BwdPlan& r) {
   const int G = d.n_q_heads / d.n_kv_heads;
-  RowPlan r{};
   r.ks = forced_key_splits(d.flags);
   if (!r.ks && n > 1 && do_kv) {
     // several steps: the tallest row tiles whose loop still fits beside the other work of a unit
-    for (r.ks = 1; r.ks < 4 && plan.longest_row * (32 * kRowWaves / r.ks) > kRowShare * plan.per_cu;) r.ks *= 2;
+    for (r.ks = 1; r.ks < 4 && r.longest_row * (32 * kRowWaves / r.ks) > kRowShare * r.per_cu;) r.ks *= 2;
   }
-  if (!r.ks) r.ks = pick_key_splits(rows, G, d.n_q_heads, d.batch, 0, cus * wgs_per_unit(d.head_dim));
-  r.tiles = make_row_tiling(rows, G, d.n_q_heads, d.batch, kRowWaves / r.ks, /*list_blind=*/d.flags & LOONG_OVERWRITE_DQ).total_wg;
+  if (!r.ks) r.ks = pick_key_splits(r.rows, G, d.n_q_heads, d.batch, 0, cus * wgs_per_unit(d.head_dim));
+  r.row_tiles = make_row_tiling(r.rows, G, d.n_q_heads, d.batch, kRowWaves / r.ks, /*list_blind=*/d.flags & LOONG_OVERWRITE_DQ).total_wg;
   r.parts = 1;
-  if (do_kv && r.tiles > 0 && 2 * r.tiles <= cus) {
-    const double loop = plan.longest_row / 6. / (r.ks == 1 ? 64 : 32 * r.ks);  // tiles of keys
-    r.parts = (int)std::max<int64_t>(std::min<int64_t>({cus / r.tiles, (int64_t)(loop / 12.), 16}), 1);
+  if (do_kv && r.row_tiles > 0 && 2 * r.row_tiles <= cus) {
+    const double loop = r.longest_row / 6. / (r.ks == 1 ? 64 : 32 * r.ks);  // tiles of keys
+    r.parts = (int)std::max<int64_t>(std::min<int64_t>({cus / r.row_tiles, (int64_t)(loop / 12.), 16}), 1);
+    if (r.parts > 1) r.row_bytes = r.row_tiles * r.parts * (kRowWaves / r.ks) * 32 * d.head_dim * (int64_t)sizeof(float);
     // (a step that fits the static scratch goes on fitting)
-    if (plan.busy + r.tiles > kWsCounters ||
-        kWsHeadBytes + (int64_t)(partial_bytes(plan, d.head_dim) + row_part_bytes(r, d.head_dim)) > LOONG_STATIC_SCRATCH_BYTES) r.parts = 1;
+    if (r.busy + r.row_tiles > kWsCounters || kWsHeadBytes + r.key_bytes + r.row_bytes > LOONG_STATIC_SCRATCH_BYTES) {
+      r.parts = 1;
+      r.row_bytes = 0;
+    }
   }
-  return r;
 }
 
 // ---- kernels: the two halves of a step, alone and in one launch.  In the common launch of one step the
@@ -230,10 +207,8 @@ __global__ __launch_bounds__(kBwdWaves * 64, 2 * wgs_per_unit(D)) void bwd_step_
 
 // What a launch enqueues: either half may be absent (flags, or nothing visible).
 struct StepLaunch {
-  StepTable tab;
   DkvParams kv;
   DqParams q;
-  StepGeom rows;   // the q segments, and which of them see keys in any step
   bool do_kv, do_q;
   bool clear;      // nobody sees any key: dk and dv of all steps are cleared
 };
@@ -242,12 +217,12 @@ struct StepLaunch {
 constexpr int64_t kMaxGrid = kLaunchThreads / (kBwdWaves * 64) - 1;
 
 // Key-owning half: work list and workspace.
-int plan_dkv(StepLaunch& s, const SplitPlan& plan, int flags, int D, void* workspace, int64_t workspace_bytes) {
+int plan_dkv(StepLaunch& s, const BwdPlan& plan, int flags, void* workspace) {
   DkvParams& p = s.kv;
   s.do_kv = false;
   // Only key tiles that some query can see are listed (eight equal ranges of the list, one
   // per XCD, then carry equal work).
-  p.nkt = plan.nkt; p.kt_total = s.tab.n_seen * plan.nkt;
+  p.nkt = plan.nkt; p.kt_total = plan.tab.n_seen * plan.nkt;
   p.nsplit = plan.nsplit;
   p.accumulate = (flags & LOONG_ACCUM_DKV) ? 1 : 0;
   const int64_t total = plan.busy * plan.nsplit;
@@ -258,9 +233,7 @@ int plan_dkv(StepLaunch& s, const SplitPlan& plan, int flags, int D, void* works
   }
   p.map = make_work_map((int64_t)p.Hkv * p.B, (int64_t)p.kt_total * plan.nsplit);
   if (p.map.grid > kMaxGrid) return fail(LOONG_E_UNSUPPORTED, "backward grid too large");
-  if (plan.nsplit > 1) {  // (size and alignment were checked by the entry point, against the same plan)
-    if (!workspace || workspace_bytes < kWsHeadBytes + (int64_t)partial_bytes(plan, D))
-      return fail(LOONG_E_SHAPE, "loong_attn_step_bwd: workspace too small");
+  if (plan.nsplit > 1) {  // (the entry point has fitted the plan to the workspace)
     p.ws_cnt = static_cast<uint32_t*>(workspace);
     p.ws_part = reinterpret_cast<float*>(static_cast<unsigned char*>(workspace) + kWsHeadBytes);
   }
@@ -269,13 +242,13 @@ int plan_dkv(StepLaunch& s, const SplitPlan& plan, int flags, int D, void* works
 }
 
 // Row-owning half: work list and workspace.
-int plan_dq(StepLaunch& s, const RowPlan& plan, int64_t ws_offset, void* workspace) {
+int plan_dq(StepLaunch& s, const BwdPlan& plan, void* workspace) {
   DqParams& p = s.q;
-  const RowTiling rt = make_row_tiling(s.rows, p.G, p.Hq, p.B, kRowWaves / plan.ks, /*list_blind=*/p.overwrite);
+  const RowTiling rt = make_row_tiling(plan.rows, p.G, p.Hq, p.B, kRowWaves / plan.ks, /*list_blind=*/p.overwrite);
   p.parts = plan.parts;
   if (p.parts > 1) {
-    p.ws_cnt = static_cast<uint32_t*>(workspace) + (kWsCounters - plan.tiles);  // (the other half counts from the front)
-    p.ws_part = reinterpret_cast<float*>(static_cast<unsigned char*>(workspace) + ws_offset);
+    p.ws_cnt = static_cast<uint32_t*>(workspace) + (kWsCounters - plan.row_tiles);  // (the other half counts from the front)
+    p.ws_part = reinterpret_cast<float*>(static_cast<unsigned char*>(workspace) + kWsHeadBytes + plan.key_bytes);
   }
   p.GS = rt.GS; p.ntile[0] = rt.ntile[0]; p.ntile[1] = rt.ntile[1];
   p.tiles_total = rt.tiles_total; p.hgroups = rt.hgroups;
@@ -288,35 +261,59 @@ int plan_dq(StepLaunch& s, const RowPlan& plan, int64_t ws_offset, void* workspa
 }
 
 template <class E, int D, int KS>
-int launch_cfg(StepLaunch& s, hipStream_t st) {
+int launch_cfg(StepLaunch& s, const StepTable& tab, hipStream_t st) {
   const dim3 block(kBwdWaves * 64);
   if (s.do_kv && s.do_q && (int64_t)s.kv.map.grid + s.q.map.grid <= kMaxGrid) {
     s.q.first_grid = s.q.rows_first ? s.q.map.grid : s.kv.map.grid;
-    bwd_step_kernel<E, D, KS><<<dim3(s.kv.map.grid + s.q.map.grid), block, 0, st>>>(s.tab, s.kv, s.q);
+    bwd_step_kernel<E, D, KS><<<dim3(s.kv.map.grid + s.q.map.grid), block, 0, st>>>(tab, s.kv, s.q);
   } else {
-    if (s.do_kv) bwd_dkv_kernel<E, D><<<dim3(s.kv.map.grid), block, 0, st>>>(s.tab, s.kv);
-    if (s.do_q) dq_kernel<E, D, KS><<<dim3(s.q.map.grid), block, 0, st>>>(s.tab, s.q);
+    if (s.do_kv) bwd_dkv_kernel<E, D><<<dim3(s.kv.map.grid), block, 0, st>>>(tab, s.kv);
+    if (s.do_q) dq_kernel<E, D, KS><<<dim3(s.q.map.grid), block, 0, st>>>(tab, s.q);
   }
   return check_launch("loong_attn_step_bwd (bf16)");
 }
 
 template <class E>
-int pick_cfg(StepLaunch& s, int head_dim, int ks, hipStream_t st) {
+int pick_cfg(StepLaunch& s, const StepTable& tab, int head_dim, int ks, hipStream_t st) {
   if (head_dim == 128) {
-    if (ks == 1) return launch_cfg<E, 128, 1>(s, st);
-    if (ks == 2) return launch_cfg<E, 128, 2>(s, st);
-    return launch_cfg<E, 128, 4>(s, st);
+    if (ks == 1) return launch_cfg<E, 128, 1>(s, tab, st);
+    if (ks == 2) return launch_cfg<E, 128, 2>(s, tab, st);
+    return launch_cfg<E, 128, 4>(s, tab, st);
   }
-  if (ks == 1) return launch_cfg<E, 64, 1>(s, st);
-  if (ks == 2) return launch_cfg<E, 64, 2>(s, st);
-  return launch_cfg<E, 64, 4>(s, st);
+  if (ks == 1) return launch_cfg<E, 64, 1>(s, tab, st);
+  if (ks == 2) return launch_cfg<E, 64, 2>(s, tab, st);
+  return launch_cfg<E, 64, 4>(s, tab, st);
 }
 
 }  // namespace
 
-int launch_bwd_bf16(const loong_step_desc& d, const StepGeom* g, int n, const BwdPrologue* before, const void* q, const void* const* k,
+void plan_bwd_bf16(const loong_step_desc& d, const StepGeom* g, int n, BwdPlan* plan) {
+  const int cus = planning_cus();
+  plan_split(d, g, n, cus, *plan);
+  const bool do_kv = !(d.flags & LOONG_BWD_ONLY_DQ) && plan->busy > 0;
+  plan->key_bytes = do_kv ? partial_bytes(plan->busy, plan->nsplit, d.head_dim) : 0;
+  plan->least_bytes = do_kv ? partial_bytes(plan->busy, plan->nsplit_least, d.head_dim) : 0;
+  plan->rows = seen_rows(g, n);
+  plan->row_bytes = 0;
+  if (!(d.flags & LOONG_BWD_ONLY_DKV) && d.q_len > 0) plan_rows(d, n, do_kv, cus, *plan);
+}
+
+bool fit_bwd_bf16(BwdPlan* p, const void* workspace, int64_t workspace_bytes) {
+  const int64_t room = workspace && aligned16(workspace) ? workspace_bytes - kWsHeadBytes : 0;
+  if (p->key_bytes > std::max<int64_t>(room, 0)) {
+    p->nsplit = p->nsplit_least;
+    p->key_bytes = p->least_bytes;
+  }
+  if (p->row_bytes > 0 && p->key_bytes + p->row_bytes > room) {
+    p->parts = 1;
+    p->row_bytes = 0;
+  }
+  return p->key_bytes + p->row_bytes > 0;
+}
+
+int launch_bwd_bf16(const loong_step_desc& d, BwdPlan& plan, int n, const BwdPrologue* before, const void* q, const void* const* k,
                     const void* const* v, const void* d_o, const float* lse, const float* delta, float* dq,
-                    float* const* dk, float* const* dv, void* workspace, int64_t workspace_bytes, void* stream) {
+                    float* const* dk, float* const* dv, void* workspace, void* stream) {
   hipStream_t st = static_cast<hipStream_t>(stream);
   DeviceFacts dev;
   if (int rc = device_facts(&dev)) return rc;
@@ -325,13 +322,10 @@ int launch_bwd_bf16(const loong_step_desc& d, const StepGeom* g, int n, const Bw
   s.do_kv = !(d.flags & LOONG_BWD_ONLY_DQ) && d.kv_len > 0;
   s.do_q = !(d.flags & LOONG_BWD_ONLY_DKV) && d.q_len > 0 && (d.kv_len > 0 || (d.flags & LOONG_OVERWRITE_DQ));
   for (int t = 0; t < n; ++t) {
-    StepTable::Chunk& c = s.tab.step[t];
+    StepTable::Chunk& c = plan.tab.step[t];
     c.k = (const uint16_t*)k[t]; c.v = (const uint16_t*)v[t];
     if (s.do_kv) { c.dk = dk[t]; c.dv = dv[t]; }
   }
-  const SplitPlan plan = plan_split(g, n, G, d.n_kv_heads, d.batch, d.q_len, planning_cus(), wgs_per_unit(d.head_dim),
-                                    has_room(d, g, n, workspace, workspace_bytes), &s.tab);
-  s.rows = seen_rows(g, n);
   if (s.do_kv) {
     DkvParams& p = s.kv;
     p.q = (const uint16_t*)q; p.d_o = (const uint16_t*)d_o;
@@ -339,9 +333,9 @@ int launch_bwd_bf16(const loong_step_desc& d, const StepGeom* g, int n, const Bw
     p.B = d.batch; p.Hq = d.n_q_heads; p.Hkv = d.n_kv_heads; p.G = G;
     p.q_len = d.q_len; p.kv_len = d.kv_len;
     for (int i = 0; i < 3; ++i) { p.qs[i] = d.q_stride[i]; p.ks[i] = d.kv_stride[i]; }
-    p.nq = g[0].nq; p.qseg[0] = g[0].q[0]; p.qseg[1] = g[0].q[1];
+    p.nq = plan.rows.nq; p.qseg[0] = plan.rows.q[0]; p.qseg[1] = plan.rows.q[1];
     p.scale = d.softmax_scale; p.c = d.softmax_scale * kLog2e;
-    if (int rc = plan_dkv(s, plan, d.flags, d.head_dim, workspace, workspace_bytes)) return rc;
+    if (int rc = plan_dkv(s, plan, d.flags, workspace)) return rc;
   }
   if (s.do_q) {
     DqParams& p = s.q;
@@ -349,18 +343,13 @@ int launch_bwd_bf16(const loong_step_desc& d, const StepGeom* g, int n, const Bw
     p.lse = lse; p.delta = delta; p.dq = dq;
     p.B = d.batch; p.Hq = d.n_q_heads; p.Hkv = d.n_kv_heads; p.G = G;
     for (int i = 0; i < 3; ++i) { p.qs[i] = d.q_stride[i]; p.ks[i] = d.kv_stride[i]; p.os[i] = d.o_stride[i]; }
-    p.q_len = d.q_len; p.qseg[0] = g[0].q[0]; p.qseg[1] = g[0].q[1];
+    p.q_len = d.q_len; p.qseg[0] = plan.rows.q[0]; p.qseg[1] = plan.rows.q[1];
     p.scale = d.softmax_scale; p.c = d.softmax_scale * kLog2e;
     p.overwrite = (d.flags & LOONG_OVERWRITE_DQ) ? 1 : 0;
     p.rows_first = n > 1;
   }
-  RowPlan row_plan = plan_rows(d, s.rows, n, plan, s.do_kv, dev.cus);
-  const int ks = row_plan.ks;
-  // (a workspace without room for the partial dQ will do: a tile's keys are not shared then)
-  const int64_t row_parts_at = kWsHeadBytes + (int64_t)partial_bytes(plan, d.head_dim);
-  if (row_plan.parts > 1 && (!workspace || workspace_bytes < row_parts_at + (int64_t)row_part_bytes(row_plan, d.head_dim))) row_plan.parts = 1;
   if (s.do_q)
-    if (int rc = plan_dq(s, row_plan, row_parts_at, workspace)) return rc;
+    if (int rc = plan_dq(s, plan, workspace)) return rc;
   const int64_t n4 = (int64_t)d.batch * d.n_kv_heads * d.kv_len * d.head_dim / 4, clear_grid = (n4 + 255) / 256;
   if (s.clear && !launch_fits(clear_grid, 256)) return fail(LOONG_E_UNSUPPORTED, "backward grid too large");
   // ---- the launch fits: from here on work is enqueued
@@ -372,24 +361,14 @@ int launch_bwd_bf16(const loong_step_desc& d, const StepGeom* g, int n, const Bw
     if (int rc = check_launch("loong_attn_step_bwd (clear dk/dv)")) return rc;
   }
   if (!s.do_kv && !s.do_q) return LOONG_OK;
-  if (d.dtype == LOONG_FP16) return pick_cfg<Fp16>(s, d.head_dim, ks, st);
-  return pick_cfg<Bf16>(s, d.head_dim, ks, st);
+  if (d.dtype == LOONG_FP16) return pick_cfg<Fp16>(s, plan.tab, d.head_dim, plan.ks, st);
+  return pick_cfg<Bf16>(s, plan.tab, d.head_dim, plan.ks, st);
 }
 
 // (all its keys counted as seen, and as many workgroups as make_work_map may add)
 int64_t bwd_steps_that_fit_bf16(const loong_step_desc& d, const StepGeom& g) {
   const int64_t per_step = (int64_t)g.nk * ((g.k[0].len + kBwdBN - 1) / kBwdBN) * d.n_kv_heads * d.batch;
   return std::max<int64_t>((kMaxGrid - 8) / std::max<int64_t>(per_step, 1), 1);
-}
-
-int64_t bwd_workspace_bytes_bf16(const loong_step_desc& d, const StepGeom* g, int n, bool least) {
-  if (d.kv_len == 0 || d.batch == 0 || (d.flags & LOONG_BWD_ONLY_DQ)) return 0;
-  const SplitPlan plan = plan_step_split(d, g, n, /*fill=*/true);
-  int64_t keys = (int64_t)partial_bytes(plan, d.head_dim), rows = 0;
-  if (least) keys = std::min(keys, (int64_t)partial_bytes(plan_step_split(d, g, n, /*fill=*/false), d.head_dim));
-  if (!least && !(d.flags & LOONG_BWD_ONLY_DKV) && d.q_len > 0)
-    rows = (int64_t)row_part_bytes(plan_rows(d, seen_rows(g, n), n, plan, /*do_kv=*/plan.busy > 0, planning_cus()), d.head_dim);
-  return keys + rows > 0 ? kWsHeadBytes + keys + rows : 0;
 }
 
 }  // namespace loong

@@ -3,6 +3,7 @@
 #include <stddef.h>
 #include <stdint.h>
 #include "loong.h"
+#include "step_table.h"
 
 namespace loong {
 
@@ -92,14 +93,33 @@ struct BwdPrologue {
   void* head;
 };
 int launch_prologue(const loong_step_desc& d, const BwdPrologue& p, void* stream);
-// (`before`: enqueued first, once the launch is known to fit; or NULL)
-int launch_bwd_bf16(const loong_step_desc& d, const StepGeom* g, int n, const BwdPrologue* before, const void* q, const void* const* k,
+// How a launch over `n` micro-steps that differ in the visiting chunk only is divided (16-bit kernels).
+struct BwdPlan {
+  StepTable tab;             // (the chunks' pointers are the launch's)
+  StepGeom rows;             // the q segments, and which of them see keys in any step
+  int64_t busy;              // listed key tiles x kv heads x batch
+  double per_cu, longest_row;  // multiply-adds per head_dim: all / CUs; of a row's keys
+  int nkt;                   // tiles per key half
+  int nsplit, nsplit_least;  // workgroups that share a key tile's query loop; with as little workspace as the launch can do with
+  int ks, parts;             // row-owning half: key splits inside a workgroup; workgroups that share a tile's keys
+  int64_t row_tiles;         // q tiles x head groups x batch
+  int64_t key_bytes, least_bytes, row_bytes;  // partial sums of the key-owning half, at the least, and behind them of the row-owning half
+};
+inline int64_t workspace_of(const BwdPlan& p) { return p.key_bytes + p.row_bytes > 0 ? kWsHeadBytes + p.key_bytes + p.row_bytes : 0; }
+inline int64_t least_workspace_of(const BwdPlan& p) {
+  const int64_t b = p.key_bytes < p.least_bytes ? p.key_bytes : p.least_bytes;
+  return b > 0 ? kWsHeadBytes + b : 0;
+}
+// (`plan`: zeroed)
+void plan_bwd_bf16(const loong_step_desc& d, const StepGeom* g, int n, BwdPlan* plan);
+// Gives up what a workspace of at least least_workspace_of() has no room for.  Does the launch count in it?
+bool fit_bwd_bf16(BwdPlan* plan, const void* workspace, int64_t workspace_bytes);
+// (a plan fitted to the workspace; `before`: enqueued first, once the launch is known to fit; or NULL)
+int launch_bwd_bf16(const loong_step_desc& d, BwdPlan& plan, int n, const BwdPrologue* before, const void* q, const void* const* k,
                     const void* const* v, const void* d_o, const float* lse, const float* delta, float* dq,
-                    float* const* dk, float* const* dv, void* workspace, int64_t workspace_bytes, void* stream);
+                    float* const* dk, float* const* dv, void* workspace, void* stream);
 // steps of a run that one launch has room for
 int64_t bwd_steps_that_fit_bf16(const loong_step_desc& d, const StepGeom& g);
-// (`least`: what the launch cannot do without; else what it makes use of)
-int64_t bwd_workspace_bytes_bf16(const loong_step_desc& d, const StepGeom* g, int n, bool least);
 // delta of every row, and with `head` the counters of a workspace cleared; these alone
 int launch_delta(const loong_step_desc& d, const void* o, const void* d_o, float* delta, void* head, void* stream);
 int launch_clear_head(void* head, void* stream);

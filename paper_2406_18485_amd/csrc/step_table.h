@@ -9,6 +9,9 @@
 // 321 -> 271 us, with the fragments of bwd_dkv_body.h requested together.
 #pragma once
 #include <stdint.h>
+#ifdef __HIPCC__
+#include <hip/hip_runtime.h>
+#endif
 
 namespace loong {
 
