@@ -409,28 +409,29 @@ __device__ __forceinline__ void dq_body(const StepTable& tab, const DqParams& p,
     __syncthreads();
     if (ksp > 0 || *role == kLeaves) return;
     const float start = *role == kGathers ? 0.f : NAN;
-    floatx16_t sum[NDB];
+    // (32 columns at a time, of NDB parts in flight, the own one among them: the sums of all columns beside the own ones made every
+    // dQ kernel keep 9 registers in scratch memory)
 #pragma unroll
-    for (int db = 0; db < NDB; ++db)
+    for (int db = 0; db < NDB; ++db) {
+      floatx16_t sum;
 #pragma unroll
-      for (int v = 0; v < 16; ++v) sum[db][v] = start;
-    for (int s2 = 0; s2 < p.parts; ++s2) {
-      if (s2 == part) {
+      for (int v = 0; v < 16; ++v) sum[v] = start;
+#pragma unroll 1
+      for (int s2 = 0; s2 < p.parts; s2 += NDB) {
+        floatx4_t x[NDB][4];
 #pragma unroll
-        for (int db = 0; db < NDB; ++db) sum[db] += acc[db];
-      } else {
+        for (int u = 0; u < NDB; ++u)
 #pragma unroll
-        for (int db = 0; db < NDB; ++db)
+          for (int vq = 0; vq < 4; ++vq) x[u][vq] = load_part(buf, min(s2 + u, p.parts - 1) * (NRB * WAVE_B) + mine + (db * 4 + vq) * 1024);
 #pragma unroll
-          for (int vq = 0; vq < 4; ++vq) {
-            const floatx4_t x = load_part(buf, s2 * (NRB * WAVE_B) + mine + (db * 4 + vq) * 1024);
+        for (int u = 0; u < NDB; ++u)
+          if (s2 + u < p.parts) {
 #pragma unroll
-            for (int r = 0; r < 4; ++r) sum[db][4 * vq + r] += x[r];
+            for (int v = 0; v < 16; ++v) sum[v] += x[u][v >> 2][v & 3];
           }
       }
+      acc[db] = sum;
     }
-#pragma unroll
-    for (int db = 0; db < NDB; ++db) acc[db] = sum[db];
     if (end_ok && !p.overwrite) request_old();
   }
 

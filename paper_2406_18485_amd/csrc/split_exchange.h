@@ -1,7 +1,7 @@
 // Exchange of partial results between the workgroups that share one tile's loop (several
 // workgroups walk over parts of it; one adds the parts up).  Every workgroup parks its part in the
 // caller's workspace and then counts itself; the last to arrive adds the others' parts to its own,
-// which it still has in registers, in split order, so the result does not depend on who that is.
+// which it still has in registers (dQ: reads back), in split order, so the result does not depend on who that is.
 // No workgroup waits for another: a launch ends whatever the counters hold.
 //
 // (Letting the last to START gather, chosen by a ticket drawn in the prologue, saves its parking but puts the
