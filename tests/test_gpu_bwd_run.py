@@ -74,6 +74,40 @@ def test_fp32_run_equals_its_steps(cp, rank, hq, hkv, d, c, batch):
         _close(a, b)
 
 
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("cp,rank,hq,hkv,c,batch", [
+    (32, 0, 2, 1, 100, 1), (32, 11, 2, 1, 100, 1), (32, 31, 2, 2, 100, 2), (40, 20, 2, 1, 150, 1), (24, 3, 3, 1, 129, 1), (8, 7, 2, 1, 500, 1)])
+def test_a_run_of_few_rows_shares_its_keys(cp, rank, hq, hkv, c, batch, d):
+    """Row tiles whose keys, those of many chunks, several workgroups share: parts that start inside later key halves, diagonal halves, rows
+    of two segments, of which one sees so little that parts of it are left without a tile, batches, two launches (40 steps)."""
+    rep, q, k, v, d_o = _replay(cp, cp, rank, hq, hkv, d, c, batch)
+    keys_alone = (P.StepDesc * cp)(*(_desc(rep.shape, s, P.OVERWRITE_DQ | P.BWD_ONLY_DKV) for s in rep.plan))
+    assert P.workspace_bytes_steps(rep._bwd_descs) > P.workspace_bytes_steps(keys_alone)   # the partial dQ
+    rep.workspace.fill_(0xA5)
+    for t in (rep.dq, rep.dk, rep.dv):
+        t.fill_(9.0)
+    rep.backward(q, k, v, d_o)
+    got = [t.clone() for t in (rep.dq, rep.dk, rep.dv)]
+    assert int(rep.workspace[:P.WORKSPACE_HEAD].count_nonzero()) == 0
+    order = [s["src_rank"] for s in rep.plan]
+    for flags in (P.OVERWRITE_DQ | P.WORKSPACE_CLEAN, P.WORKSPACE_CLEAN | P.OVERWRITE_DQ, 0):
+        descs = (P.StepDesc * cp)(*(_desc(rep.shape, s, flags) for s in rep.plan))
+        P.attn_steps_bwd(descs, q, [k[s] for s in order], [v[s] for s in order], None, d_o, rep.lse, rep.delta, rep.dq,
+                         [rep.dk[s] for s in order], [rep.dv[s] for s in order], rep.workspace)
+        assert int(rep.workspace[:P.WORKSPACE_HEAD].count_nonzero()) == 0
+        if flags:
+            assert all(torch.equal(a, b) for a, b in zip(got, (rep.dq, rep.dk, rep.dv)))
+    _close(rep.dq, 2 * got[0])   # added to
+    for t, step in enumerate(rep.plan):
+        src = step["src_rank"]
+        P.attn_step_bwd(_desc(rep.shape, step, P.BWD_ONLY_DQ | (0 if t else P.OVERWRITE_DQ)), q, k[src], v[src], None, d_o, rep.lse,
+                        rep.delta, rep.dq, None, None)
+        P.attn_step_bwd(_desc(rep.shape, step, P.BWD_ONLY_DKV), q, k[src], v[src], None, d_o, rep.lse, rep.delta, None, rep.dk[src],
+                        rep.dv[src], rep.workspace)
+    for a, b in zip(got, (rep.dq, rep.dk, rep.dv)):
+        _close(a, b)
+
+
 @pytest.mark.parametrize("cp,hq,hkv,d,c,only", [(4, 2, 2, 64, 33, 0), (8, 8, 8, 128, 640, 0), (4, 4, 1, 128, 200, P.BWD_ONLY_DQ)])
 @pytest.mark.parametrize("form_delta", [True, False])
 def test_a_run_that_does_not_count_leaves_its_workspace_alone(cp, hq, hkv, d, c, only, form_delta):
