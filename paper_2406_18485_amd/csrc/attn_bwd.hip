@@ -115,20 +115,24 @@ void plan_split(const loong_step_desc& d, const StepGeom* g, int n, int cus, Bwd
     s.nsplit = at_most(uneven(nsplit));
   } else if (s.busy > 0) {
     // Several steps: the tiles fill the chip; as many parts as make the longest loop a small part of a unit's time, or fewer
-    // where these would end later.  An estimate of that: all work over the places the chip has for workgroups and the longest single
-    // workgroup, in tiles of a query loop (some 1.9 us); a workgroup's prologue and stores are worth 3.5, parking and
-    // adding up shared sums half a tile more per part, and another 5 when the whole chip does it.  A backward pass, without the estimate -> with it: 8 steps of 2 heads x 2000 rows
-    // 149 -> 102 us, 16 of 4 x 1000 140 -> 112, 3 of 12 x 1400 (head_dim 64) 69 -> 59, 8 of 8 x 1200 137 -> 120, 4 of 32 x 600
-    // 113 -> 95, 4 of 4 x 400 31.9 -> 32.5.  (The estimate alone makes five parts of four on 8 steps of 4 x 16384 rows: 3.6 % longer.)
+    // where these would end clearly earlier.  An estimate of that: all work dealt out over the places the chip has for workgroups, and then the
+    // longest single workgroup, started as the last place falls free; in tiles of a query loop (some 1.9 us).  A workgroup's
+    // prologue and stores are worth 3; parking and adding up shared sums 4 more and half a tile per part when the whole chip
+    // does it, one more for a single workgroup.  A backward pass, without the estimate -> with it: 8 steps of 2 heads x 2000 rows 131 -> 104
+    // us, 16 of 4 x 1000 137 -> 100, 3 of 12 x 1400 (head_dim 64) 61 -> 57, 8 of 8 x 1200 137 -> 120, 4 of 32 x 600 113 -> 88, 32 of 2 x
+    // 638 x batch 2 188 -> 87.  Of 210 runs of 2 to 32 steps of 96 to 11000 rows, each timed with every number of parts, it takes 1.5 %
+    // longer than the best on average (9 % without it), and four of them 2-8 % (0.5-2 us) longer than without it.  (With a quarter of
+    // the longest workgroup instead of all of it 2.5 % and up to 14 % longer than without, as 3 steps of 6 heads on 2 x 4430 rows x batch 2
+    // 643 -> 671.  The estimate alone makes five parts of four on 8 steps of 4 x 16384 rows: 3.6 % longer.)
     const int most = (int)std::min(std::max(std::ceil(8. * BN * most_rows * G / (kLoopShare * s.per_cu)), 1.), 16.);
     const double loops = pairs * G * Hkv * B / ((double)BN * BM), longest = ((double)most_rows / BM + 1.) * G;  // tiles of all loops, of the longest (with its ragged ends)
-    double best = 0;
-    int nsplit = 1;
-    for (int k = 1; k <= most; ++k) {
-      const double all = (loops + s.busy * k * (k == 1 ? 3.5 : 8.5 + 0.5 * k)) / (per_unit * cus), one = longest / k + (k == 1 ? 3.5 : 4. + 0.5 * k);
-      const double time = std::max(all, one) + 0.25 * std::min(all, one);
-      if (k == 1 || time < best) { best = time; nsplit = k; }
-    }
+    auto time = [&](int k) {
+      return (loops + s.busy * k * (k == 1 ? 3. : 7. + 0.5 * k)) / (per_unit * cus) + longest / k + (k == 1 ? 3. : 4.);
+    };
+    int nsplit = most;
+    double best = 0.97 * time(most);
+    for (int k = 1; k < most; ++k)
+      if (time(k) <= best) { best = time(k); nsplit = k; }
     s.nsplit = s.nsplit_least = at_most(nsplit);
   }
 }
@@ -161,8 +165,8 @@ void plan_rows(const loong_step_desc& d, int n, bool do_kv, int cus, BwdPlan& r)
     const double loop = r.longest_row / 6. / (r.ks == 1 ? 64 : 32 * r.ks);  // tiles of keys
     r.parts = (int)std::max<int64_t>(std::min<int64_t>({cus / r.row_tiles, (int64_t)(loop / 12.), 16}), 1);
     if (r.parts > 1) r.row_bytes = r.row_tiles * r.parts * (kRowWaves / r.ks) * 32 * d.head_dim * (int64_t)sizeof(float);
-    // (a step that fits the static scratch goes on fitting)
-    if (r.busy + r.row_tiles > kWsCounters || kWsHeadBytes + r.key_bytes + r.row_bytes > LOONG_STATIC_SCRATCH_BYTES) {
+    // (a step that fits the static scratch goes on fitting; runs do not go there)
+    if (r.busy + r.row_tiles > kWsCounters || (n == 1 && kWsHeadBytes + r.key_bytes + r.row_bytes > LOONG_STATIC_SCRATCH_BYTES)) {
       r.parts = 1;
       r.row_bytes = 0;
     }

@@ -167,6 +167,19 @@ def test_workspace_bytes_follows_the_split_of_the_query_loops():
     assert lib.loong_workspace_bytes(C.byref(small), None) == P.E_NULL
 
 
+@pytest.mark.parametrize("cp,rank,hq,hkv,d,c,batch,halves,parts", [
+    (3, 1, 6, 2, 128, 2215, 2, 5, 3), (2, 1, 8, 8, 128, 1886, 1, 3, 3), (6, 5, 6, 2, 128, 904, 2, 7, 3),   # long loops: what the chip's end waits for
+    (16, 8, 4, 4, 128, 500, 1, 24, 1), (32, 16, 8, 8, 128, 210, 1, 48, 1)])                                # short ones: not worth parking
+def test_runs_split_their_query_loops_where_that_ends_earlier(cp, rank, hq, hkv, d, c, batch, halves, parts):
+    one = dict(batch=batch, n_q_heads=hq, n_kv_heads=hkv, head_dim=d, q_len=2 * c, kv_len=2 * c, dtype=P.BF16, softmax_scale=0.1, causal=True,
+               chunk_len=c, q_chunk=(rank, 2 * cp - 1 - rank), flags=P.BWD_ONLY_DKV)
+    visits = [P.zigzag_mask(cp, cp, rank, t) for t in range(cp)]
+    assert sum(any(v["block_class"][2 * a + b] for a in (0, 1)) for v in visits for b in (0, 1)) == halves
+    descs = (P.StepDesc * cp)(*(P.make_desc(**one, kv_chunk=v["kv_chunk"]) for v in visits))
+    slots = halves * -(-c // 128) * hkv * batch * parts
+    assert P.workspace_bytes_steps(descs) == (16384 * 4 + slots * 8 * (d // 32) * 16 * 64 * 4 if parts > 1 else 0)
+
+
 def test_backward_step_rejects_a_missing_or_small_workspace_before_any_launch():
     """The step that shares query loops needs caller-owned scratch: without it, or with too little or a misaligned
     block, the call returns an argument error and enqueues nothing (fake addresses are never dereferenced)."""
