@@ -16,7 +16,7 @@
 namespace loong {
 namespace {
 
-// workgroups that run on a compute unit together (registers, LDS)
+// workgroups that run on a compute unit together (registers, LDS) where a launch has enough of them
 constexpr int wgs_per_unit(int head_dim) { return head_dim == 64 ? 2 : 1; }
 
 constexpr double kLoopShare = 0.3;  // several steps per launch: a key tile's loop over the time of a unit
@@ -158,7 +158,7 @@ void plan_rows(const loong_step_desc& d, int n, bool do_kv, int cus, BwdPlan& r)
     // several steps: the tallest row tiles whose loop still fits beside the other work of a unit
     for (r.ks = 1; r.ks < 4 && r.longest_row * (32 * kRowWaves / r.ks) > kRowShare * r.per_cu;) r.ks *= 2;
   }
-  if (!r.ks) r.ks = pick_key_splits(r.rows, G, d.n_q_heads, d.batch, 0, cus * wgs_per_unit(d.head_dim));
+  if (!r.ks) r.ks = pick_key_splits(r.rows, G, d.n_q_heads, d.batch, 0, cus * (do_kv ? wgs_per_unit(d.head_dim) : 1));
   r.row_tiles = make_row_tiling(r.rows, G, d.n_q_heads, d.batch, kRowWaves / r.ks, /*list_blind=*/d.flags & LOONG_OVERWRITE_DQ).total_wg;
   r.parts = 1;
   if (do_kv && r.row_tiles > 0 && 2 * r.row_tiles <= cus) {
@@ -186,27 +186,27 @@ void plan_rows(const loong_step_desc& d, int n, bool do_kv, int cus, BwdPlan& r)
 // A backward pass, a launch per step -> the run: 8 steps of 2048 rows x 4096 keys x 8 heads 1003 -> 851 us, 32 steps of
 // 2048 rows x 4 heads, one kv head 1395 -> 529, 4 steps of 400 rows x 4 heads 158 -> 77 (with its forward).
 // (Key-owning workgroups first in a run: 7 % slower at 8 x 2048 rows.)
-template <class E, int D>
-__global__ __launch_bounds__(kBwdWaves * 64, 2 * wgs_per_unit(D)) void bwd_dkv_kernel(const StepTable tab, const DkvParams p) {
-  __shared__ __attribute__((aligned(1024))) unsigned char smem[BwdCfg<D>::SMEM_BYTES];
-  dkv_body<E, D>(tab, p, blockIdx.x, smem);
+template <class E, int D, int W>
+__global__ __launch_bounds__(kBwdWaves * 64, 2 * W) void bwd_dkv_kernel(const StepTable tab, const DkvParams p) {
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[BwdCfg<D, W>::SMEM_BYTES];
+  dkv_body<E, D, W>(tab, p, blockIdx.x, smem);
 }
 
-template <class E, int D, int KS>
-__global__ __launch_bounds__(kRowWaves * 64, 2 * wgs_per_unit(D)) void dq_kernel(const StepTable tab, const DqParams p) {
-  __shared__ __attribute__((aligned(1024))) unsigned char smem[DqCfg<D, KS>::SMEM_BYTES];
-  dq_body<E, D, KS>(tab, p, blockIdx.x, smem);
+template <class E, int D, int KS, int W>
+__global__ __launch_bounds__(kRowWaves * 64, 2 * W) void dq_kernel(const StepTable tab, const DqParams p) {
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[DqCfg<D, KS, W>::SMEM_BYTES];
+  dq_body<E, D, KS, W>(tab, p, blockIdx.x, smem);
 }
 
-template <class E, int D, int KS>
-__global__ __launch_bounds__(kBwdWaves * 64, 2 * wgs_per_unit(D)) void bwd_step_kernel(const StepTable tab, const DkvParams pk, const DqParams pq) {
-  constexpr int BYTES = BwdCfg<D>::SMEM_BYTES > DqCfg<D, KS>::SMEM_BYTES ? BwdCfg<D>::SMEM_BYTES : DqCfg<D, KS>::SMEM_BYTES;
+template <class E, int D, int KS, int W>
+__global__ __launch_bounds__(kBwdWaves * 64, 2 * W) void bwd_step_kernel(const StepTable tab, const DkvParams pk, const DqParams pq) {
+  constexpr int BYTES = BwdCfg<D, W>::SMEM_BYTES > DqCfg<D, KS, W>::SMEM_BYTES ? BwdCfg<D, W>::SMEM_BYTES : DqCfg<D, KS, W>::SMEM_BYTES;
   static_assert(kBwdWaves == kRowWaves, "one workgroup size for both halves");
   __shared__ __attribute__((aligned(1024))) unsigned char smem[BYTES];
   const bool second = blockIdx.x >= pq.first_grid;
   const uint32_t block = blockIdx.x - (second ? pq.first_grid : 0u);
-  if (second == pq.rows_first) dkv_body<E, D>(tab, pk, block, smem);
-  else dq_body<E, D, KS>(tab, pq, block, smem);
+  if (second == pq.rows_first) dkv_body<E, D, W>(tab, pk, block, smem);
+  else dq_body<E, D, KS, W>(tab, pq, block, smem);
 }
 
 // What a launch enqueues: either half may be absent (flags, or nothing visible).
@@ -264,29 +264,44 @@ int plan_dq(StepLaunch& s, const BwdPlan& plan, void* workspace) {
   return LOONG_OK;
 }
 
-template <class E, int D, int KS>
+template <class E, int D, int KS, int W>
 int launch_cfg(StepLaunch& s, const StepTable& tab, hipStream_t st) {
   const dim3 block(kBwdWaves * 64);
   if (s.do_kv && s.do_q && (int64_t)s.kv.map.grid + s.q.map.grid <= kMaxGrid) {
     s.q.first_grid = s.q.rows_first ? s.q.map.grid : s.kv.map.grid;
-    bwd_step_kernel<E, D, KS><<<dim3(s.kv.map.grid + s.q.map.grid), block, 0, st>>>(tab, s.kv, s.q);
+    bwd_step_kernel<E, D, KS, W><<<dim3(s.kv.map.grid + s.q.map.grid), block, 0, st>>>(tab, s.kv, s.q);
   } else {
-    if (s.do_kv) bwd_dkv_kernel<E, D><<<dim3(s.kv.map.grid), block, 0, st>>>(tab, s.kv);
-    if (s.do_q) dq_kernel<E, D, KS><<<dim3(s.q.map.grid), block, 0, st>>>(tab, s.q);
+    if (s.do_kv) bwd_dkv_kernel<E, D, W><<<dim3(s.kv.map.grid), block, 0, st>>>(tab, s.kv);
+    if (s.do_q) dq_kernel<E, D, KS, W><<<dim3(s.q.map.grid), block, 0, st>>>(tab, s.q);
   }
   return check_launch("loong_attn_step_bwd (bf16)");
 }
 
-template <class E>
-int pick_cfg(StepLaunch& s, const StepTable& tab, int head_dim, int ks, hipStream_t st) {
-  if (head_dim == 128) {
-    if (ks == 1) return launch_cfg<E, 128, 1>(s, tab, st);
-    if (ks == 2) return launch_cfg<E, 128, 2>(s, tab, st);
-    return launch_cfg<E, 128, 4>(s, tab, st);
+// head_dim 64 has two forms of either half, with the same results: for two workgroups per unit, and one with the registers, the
+// look-ahead and the LDS of a unit to itself for launches that put hardly more than one on any.  Whole steps, one / two: 190 x 190 x 8
+// heads 12.0 / 12.4 us, 512 x 512 x 8 14.4 / 14.8, 1554 rows of a diagonal step, 4 heads on 1 (280 workgroups) 28.3 / 31.0; 700 x 2000 x
+// 4 (300) 30.9 / 27.7, 1024 x 1024, 16 heads on 4 37.6 / 31.8.  dQ alone: 2048 x 16384, 4 heads on 1 95 / 105, 700 x 900 x 4 x 16
+// heads on 2 (352) 34.3 / 28.5; with a diagonal block, whose loops are uneven, 512 workgroups 209 / 245.
+template <class E, int D, int KS>
+int launch_form(StepLaunch& s, const StepTable& tab, int cus, hipStream_t st) {
+  if constexpr (D == 64) {
+    const int64_t total = (int64_t)(s.do_kv ? s.kv.map.grid : 0) + (s.do_q ? s.q.map.grid : 0);
+    const bool uneven = !s.do_kv && tab.n_diag[0] + tab.n_diag[1] > 0;
+    if (total > cus * 9 / 8 && !uneven) return launch_cfg<E, D, KS, 2>(s, tab, st);
   }
-  if (ks == 1) return launch_cfg<E, 64, 1>(s, tab, st);
-  if (ks == 2) return launch_cfg<E, 64, 2>(s, tab, st);
-  return launch_cfg<E, 64, 4>(s, tab, st);
+  return launch_cfg<E, D, KS, 1>(s, tab, st);
+}
+
+template <class E>
+int pick_cfg(StepLaunch& s, const StepTable& tab, int head_dim, int ks, int cus, hipStream_t st) {
+  if (head_dim == 128) {
+    if (ks == 1) return launch_form<E, 128, 1>(s, tab, cus, st);
+    if (ks == 2) return launch_form<E, 128, 2>(s, tab, cus, st);
+    return launch_form<E, 128, 4>(s, tab, cus, st);
+  }
+  if (ks == 1) return launch_form<E, 64, 1>(s, tab, cus, st);
+  if (ks == 2) return launch_form<E, 64, 2>(s, tab, cus, st);
+  return launch_form<E, 64, 4>(s, tab, cus, st);
 }
 
 }  // namespace
@@ -365,8 +380,8 @@ int launch_bwd_bf16(const loong_step_desc& d, BwdPlan& plan, int n, const BwdPro
     if (int rc = check_launch("loong_attn_step_bwd (clear dk/dv)")) return rc;
   }
   if (!s.do_kv && !s.do_q) return LOONG_OK;
-  if (d.dtype == LOONG_FP16) return pick_cfg<Fp16>(s, plan.tab, d.head_dim, plan.ks, st);
-  return pick_cfg<Bf16>(s, plan.tab, d.head_dim, plan.ks, st);
+  if (d.dtype == LOONG_FP16) return pick_cfg<Fp16>(s, plan.tab, d.head_dim, plan.ks, dev.cus, st);
+  return pick_cfg<Bf16>(s, plan.tab, d.head_dim, plan.ks, dev.cus, st);
 }
 
 // (all its keys counted as seen, and as many workgroups as make_work_map may add)

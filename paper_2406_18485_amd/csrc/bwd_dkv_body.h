@@ -14,7 +14,8 @@
 //            of the matrix cores (the chain starts from C = delta), then E = P o T
 //            (= -dS / scale), dK += E^T Q; dK is multiplied by -scale once, at the end.
 // The E waves run one tile behind the P waves (P of tile t is consumed in the next iteration,
-// from a double-buffered hand-over area; the query tiles stay in LDS for three iterations), so
+// from a double-buffered hand-over area; the query tiles stay in LDS for three iterations, the dO rows of the form for two
+// workgroups per unit for two), so
 // one workgroup barrier per tile suffices and neither role ever waits for the other.  The E
 // waves, which have less element-wise work, also issue the staging loads.  A P wave's own
 // dV += P^T dO of tile t also runs one iteration late, first thing after the barrier, from
@@ -28,7 +29,8 @@
 // work) now hides behind the partner.
 //
 // Per query tile: Q, dO (row-major) and the rows' LSE and delta go from global memory
-// straight into LDS, one tile ahead, with the 16-byte pieces of every row XOR-permuted so
+// straight into LDS, one tile ahead (head_dim 64: the LSE through a register of an E wave; two workgroups per unit: dO and delta an
+// iteration later), with the 16-byte pieces of every row XOR-permuted so
 // that both kinds of LDS read are free of bank conflicts: A operands of S / T are 16-byte
 // reads of Q / dO rows (one key per lane, 16 query rows per 32x32 block in registers);
 // the contractions over rows take P^T / E^T straight from registers as the A operand and
@@ -66,7 +68,8 @@ constexpr int kBwdWaves = 8;            // 4 key groups x {P wave, E wave}
 constexpr int kBwdBN = 128;             // keys per workgroup
 constexpr int kBwdBM = 64;              // query rows per iteration
 
-template <int D>
+// (W: workgroups per unit the form is made for)
+template <int D, int W>
 struct BwdCfg {
   static constexpr int BM = kBwdBM, BN = kBwdBN;
   static constexpr int ROWB = D * 2;               // bytes per row of a Q / dO tile
@@ -74,17 +77,19 @@ struct BwdCfg {
   static constexpr int RPI = 1024 / ROWB;          // rows filled by one wave-level load
   static constexpr int QT_B = BM * ROWB;           // bytes of a Q (or dO) tile
   static constexpr int LI = QT_B / 1024 / 4;       // loads per staging wave (the four E waves) per Q (or dO) tile
-  // head_dim 64 runs two workgroups per unit: one's prologue, epilogue and exchange of partial sums run beside the other's
+  // head_dim 64 can run two workgroups per unit (W = 2): one's prologue, epilogue and exchange of partial sums run beside the other's
   // loop, and four waves per SIMD leave the vector port idle less.  That takes at most 128 registers (operands requested three
   // steps ahead, not four) and half the LDS: the Q rows keep three stages (tile being staged, tile of the P waves, tile of the E
   // waves), but both roles use the dO rows of the E waves' tile only, so these are staged an iteration later, in two (LATE_O).
-  // There the P waves, whose exponentials weigh twice as much beside their matrix work, are the longer path, so the exponent
+  // At head_dim 64 the P waves, whose exponentials weigh twice as much beside their matrix work, are the longer path, so the exponent
   // offsets of a tile's rows are formed once, by the E wave that fetches their LSE (OFFSETS).  dK/dV alone, one workgroup per
   // unit -> two -> with OFFSETS: 1500 rows x 4100 keys x 2 x 8 heads 116 -> 101 -> 87 us, 8192 x 8192 x 8 heads on 2
-  // 298 -> 310 -> 275 (the last with twice the workgroups per query loop), 16384 x 16384 x 8 1165 -> 1040 -> 1023.
+  // 298 -> 310 -> 275 (the last with twice the workgroups per query loop), 16384 x 16384 x 8 1165 -> 1040 -> 1023.  With OFFSETS in
+  // one workgroup per unit ragged and diagonal tiles gain (800 rows, 4 heads on 1, 24.7 -> 22.6), long loops without a mask lose
+  // (16384 x 2048 95 -> 98).
   // At head_dim 128 (registers for one workgroup) both cost: late dO 874 -> 905 us (16384 x 16384 x 4 heads), OFFSETS 516 -> 545
   // (8 steps of 2048 rows x 8 heads): the E waves' path is the longer one there.
-  static constexpr bool LATE_O = D == 64, OFFSETS = D == 64;
+  static constexpr bool LATE_O = W == 2, OFFSETS = D == 64;
   static constexpr int NSTAGE_Q = 3, NSTAGE_O = LATE_O ? 2 : 3;
   static constexpr int Q_STRIDE = (LATE_O ? 1 : 2) * (QT_B + BM * 4), O_STRIDE = Q_STRIDE;
   static constexpr int O_OFF = LATE_O ? NSTAGE_Q * Q_STRIDE : QT_B;            // first dO stage
@@ -97,9 +102,9 @@ struct BwdCfg {
   static_assert(LI >= 1 && LI * 1024 * 4 == QT_B, "tile must split evenly over the staging waves");
 };
 
-template <class E, int D>
+template <class E, int D, int W>
 __device__ __forceinline__ void dkv_body(const StepTable& tab, const DkvParams& p, uint32_t block, unsigned char* smem) {
-  using C = BwdCfg<D>;
+  using C = BwdCfg<D, W>;
   constexpr int BM = C::BM, BN = C::BN, ROWB = C::ROWB, CH = C::CH, LI = C::LI;
   constexpr int NKS = D / 16, NDB = D / 32;
   static_assert(BM == 64, "the pipeline below is written for two 32-row blocks per tile");
@@ -280,7 +285,7 @@ __device__ __forceinline__ void dkv_body(const StepTable& tab, const DkvParams& 
   // P and E = P o T packed, two bf16 per word (elements 2 w, 2 w + 1 of block ib).  A P wave keeps
   // its P across the barrier: dV += P^T dO of tile t runs at the top of iteration t + 1.
   uint32_t w2[2][8];
-  constexpr int PF = D == 64 ? 3 : 4;  // LDS operands are requested PF matrix steps ahead
+  constexpr int PF = W == 2 ? 3 : 4;  // LDS operands are requested PF matrix steps ahead
   // Iteration j: the P waves work on tile j, the E waves on tile j - 1; the Q rows of tile j + 1 and the dO rows of
   // tile j are staged.
   int st_p = 0, st_e = 2, st_n = 1;  // LDS stages of the Q rows of tiles j, j - 1 and j + 1

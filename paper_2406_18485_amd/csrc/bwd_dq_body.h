@@ -53,7 +53,8 @@ struct DqParams {
   bool rows_first;
 };
 
-template <int D, int KS>
+// (W: workgroups per unit the form is made for)
+template <int D, int KS, int W>
 struct DqCfg {
   static constexpr int NRB = kRowWaves / KS;       // 32-row blocks per workgroup
   static constexpr int NJB = KS == 1 ? 2 : 1;      // 32-key blocks per wave and iteration
@@ -63,7 +64,7 @@ struct DqCfg {
   static constexpr int CH = D / 8;                 // 16-byte pieces per row
   static constexpr int TILE_B = TK * ROWB;         // bytes of one K (or V) tile
   static constexpr int BUF_B = 2 * TILE_B;
-  static constexpr int NBUF = BUF_B * 4 <= (D == 64 ? 65536 : 131072) ? 4 : 2;  // (head_dim 64: two workgroups per unit)
+  static constexpr int NBUF = BUF_B * 4 <= 131072 / W ? 4 : 2;
   static constexpr int PD = NBUF - 1;              // tiles in flight ahead of the one being used
   static constexpr int RPI = 1024 / ROWB;          // rows filled by one wave-level load
   static constexpr int KI = TILE_B / 1024 / kRowWaves;  // loads per wave per K (or V) tile
@@ -74,18 +75,18 @@ struct DqCfg {
   static_assert(KI >= 1 && KI * 1024 * kRowWaves == TILE_B, "tile must split evenly over the waves");
 };
 
-template <class E, int D, int KS>
+template <class E, int D, int KS, int W>
 __device__ __forceinline__ void dq_body(const StepTable& tab, const DqParams& p, uint32_t block, unsigned char* smem) {
-  using C = DqCfg<D, KS>;
+  using C = DqCfg<D, KS, W>;
   constexpr int NRB = C::NRB, NJB = C::NJB, BNS = C::BNS, TK = C::TK, NBUF = C::NBUF, PD = C::PD, KI = C::KI;
   constexpr int NDB = D / 32, NKS = D / 16, ROWB = C::ROWB, CH = C::CH;
-  // head_dim 64 runs two workgroups per unit (four waves per SIMD), in at most 128 registers: the chains' starting values are
+  // head_dim 64 can run two workgroups per unit (W = 2, four waves per SIMD), in at most 128 registers: the chains' starting values are
   // made by the matrix cores each time (spread) instead of kept in 32 registers, LDS offsets are two registers
   // (row_read_base), one operand is requested ahead, not four, and what only the end needs is found there.  dQ alone, one
   // workgroup per unit -> two: 16384 x 16384 x 8 heads 730 -> 707 us, 1500 x 4100 x 2 x 8 58.8 -> 52.3, 8192 x 8192 x 8
   // 188 -> 195 (256 workgroups); with the offsets added on the vector port instead 728, 57, 205; two operands ahead
   // spilled: 64 us for the second.
-  constexpr bool LEAN = D == 64;
+  constexpr bool LEAN = W == 2;
 
   // ---- which (batch, head group, q tile): within a head group the tiles with the most
   // visible keys come first

@@ -133,8 +133,9 @@ def test_a_step_too_large_for_a_launch_is_refused_before_anything_runs():
 @pytest.mark.parametrize("dtype", [P.BF16, P.FP16])
 @pytest.mark.parametrize("lq,lk,hq,hkv", [(1, 1, 1, 1), (31, 129, 2, 1), (64, 64, 1, 1), (65, 127, 4, 2), (200, 700, 3, 1), (513, 257, 8, 8)])
 @pytest.mark.parametrize("ks", [1, 2, 4])
-def test_head_dim_64_gradients_at_the_edges_of_tiles(lq, lk, hq, hkv, ks, dtype):
-    """Two workgroups per unit: offsets formed once per query row (rows past the end and rows with LSE = -inf give nothing),
+@pytest.mark.parametrize("per_unit", [1, 2])
+def test_head_dim_64_gradients_at_the_edges_of_tiles(lq, lk, hq, hkv, ks, dtype, per_unit):
+    """One workgroup per unit, and (as many copies of the problem as fill the chip) two: offsets formed once per query row (rows past the end and rows with LSE = -inf give nothing),
     starting values spread by the matrix cores (a row with an LSE and a delta beyond the half's range among them), tiles two and
     four deep.  Against fp64 from the same LSE and delta; the bound is what rounding P, dS, K and Q to 16 bits leaves: about 2^-9
     (2^-12) of the terms' root sum of squares, eight times that for the largest of some 1e5 values."""
@@ -154,14 +155,41 @@ def test_head_dim_64_gradients_at_the_edges_of_tiles(lq, lk, hq, hkv, ks, dtype)
     want = ds @ x(k), group(ds.transpose(-1, -2) @ x(q)), group(p.transpose(-1, -2) @ x(d_o))
     terms = (ds.abs().square() @ x(k).square()).sqrt(), group(ds.square().transpose(-1, -2) @ x(q).square()).sqrt(), group(
         p.square().transpose(-1, -2) @ x(d_o).square()).sqrt()
-    desc = P.make_desc(batch=1, n_q_heads=hq, n_kv_heads=hkv, head_dim=64, q_len=lq, kv_len=lk, dtype=dtype, softmax_scale=0.125,
+    batch = 1 if per_unit == 1 else -(-300 // (hkv * -(-lk // 128)))   # (more than 288 workgroups over keys alone)
+    desc = P.make_desc(batch=batch, n_q_heads=hq, n_kv_heads=hkv, head_dim=64, q_len=lq, kv_len=lk, dtype=dtype, softmax_scale=0.125,
                        flags=P.key_splits(ks))
-    t = dict(q=q.to(DEV), k=k.to(DEV), v=v.to(DEV), d_o=d_o.to(DEV), lse=lse.to(DEV), delta=delta.to(DEV))
-    got = _run(t, desc, torch.zeros(q.shape, device=DEV), workspace_for(desc))
+    t = dict(q=q, k=k, v=v, d_o=d_o, lse=lse, delta=delta)
+    t = {n: x.expand(batch, *x.shape[1:]).contiguous().to(DEV) for n, x in t.items()}
+    got = _run(t, desc, torch.zeros(t["q"].shape, device=DEV), workspace_for(desc))
+    for a in got:   # the copies are one result
+        assert torch.equal(a, a[:1].expand_as(a))
+    got = [a[:1] for a in got]
     eps = 2.0 ** (-9 if dtype == P.BF16 else -12)
     for a, b, scale in zip(got, want, terms):
         err = (a.cpu().double() - b).abs()
         assert bool((err <= 8 * eps * (scale + scale.max() / 8) + 1e-6).all()), float((err / (scale + scale.max() / 8) / eps).max())
+
+
+@pytest.mark.parametrize("dtype", [P.BF16, P.FP16])
+@pytest.mark.parametrize("lq,lk", [(1, 1), (33, 129), (64, 700), (63, 128)])
+@pytest.mark.parametrize("ks", [1, 2, 4])
+def test_either_form_at_head_dim_64_gives_the_same_bits(lq, lk, ks, dtype):
+    """One problem of few workgroups and 300 copies of it, which fill the chip twice: dQ alone, dK/dV alone and both.  (One query tile,
+    so that no loop is shared in either.)"""
+    g = torch.Generator(device=DEV).manual_seed(lq + lk)
+    mk = lambda n: (torch.randn(1, 1, n, 64, generator=g, device=DEV) * 0.5).to(TORCH[dtype])
+    one = dict(q=mk(lq), k=mk(lk), v=mk(lk), d_o=mk(lq), lse=torch.full((1, 1, lq), math.log(lk) + 0.1, device=DEV),
+               delta=torch.randn(1, 1, lq, generator=g, device=DEV) * 0.1)
+    for flags in (0, P.BWD_ONLY_DQ, P.BWD_ONLY_DKV):
+        res = []
+        for batch in (1, 300):
+            desc = P.make_desc(batch=batch, n_q_heads=1, n_kv_heads=1, head_dim=64, q_len=lq, kv_len=lk, dtype=dtype, softmax_scale=0.125,
+                               flags=flags | P.key_splits(ks))
+            assert P.workspace_bytes(desc) == 0
+            t = {n: x.expand(batch, *x.shape[1:]).contiguous() for n, x in one.items()}
+            res.append(_run(t, desc, torch.zeros(t["q"].shape, device=DEV), None))
+        for a, b in zip(*res):
+            assert torch.equal(a.expand_as(b), b)
 
 
 @pytest.mark.parametrize("lq,lk,hq,hkv,parts", [(4096, 4096, 8, 8, 1), (3072, 8192, 8, 4, 1), (8192, 2048, 8, 8, 2)])
