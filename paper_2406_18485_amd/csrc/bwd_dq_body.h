@@ -217,7 +217,10 @@ __device__ __forceinline__ void dq_body(const StepTable& tab, const DqParams& p,
   // byte offsets of this lane's pieces from the first row of a tile (full tiles only; the
   // 32-bit form needs TK rows to span less than 4 GiB, else every tile takes the general path)
   const bool narrow = rowbytes * TK < (int64_t(1) << 32);
-  const uint32_t ld_off = (uint32_t)staged_row(lane) * (uint32_t)rowbytes + staged_piece(lane);
+  // (LEAN: the first one alone, in one register; else one each: the additions to the bases took 1 % of a step)
+  uint32_t ld_off[KI];
+#pragma unroll
+  for (int i = 0; i < KI; ++i) ld_off[i] = (uint32_t)(staged_row(lane) + (LEAN ? 0 : i * 8 * C::RPI)) * (uint32_t)rowbytes + staged_piece(lane);
   auto issue_tile = [&](int t) {  // stages the tile at `ahead` (the t-th of this workgroup) and moves on
     const int64_t tb = (int64_t)ahead.j0 * rowbytes;
     const int last = klen - 1 - ahead.j0;  // last valid row of the tile (>= 0); later rows repeat it
@@ -226,11 +229,12 @@ __device__ __forceinline__ void dq_body(const StepTable& tab, const DqParams& p,
     if (narrow && last >= TK - 1) {  // whole tile: uniform base in scalar registers + per-lane offset
 #pragma unroll
       for (int i = 0; i < KI; ++i) {
-        load_to_lds_16(kbase + tb + i * 8 * C::RPI * rowbytes, ld_off, kl + i * 8192);
-        load_to_lds_16(vbase + tb + i * 8 * C::RPI * rowbytes, ld_off, vl + i * 8192);
+        const int64_t at = tb + (LEAN ? i * 8 * C::RPI * rowbytes : 0);
+        load_to_lds_16(kbase + at, ld_off[LEAN ? 0 : i], kl + i * 8192);
+        load_to_lds_16(vbase + at, ld_off[LEAN ? 0 : i], vl + i * 8192);
       }
     } else {
-      const int ln = lane_again();
+      const int ln = LEAN ? lane_again() : lane;
 #pragma unroll
       for (int i = 0; i < KI; ++i) {
         const int r = min(staged_row(ln) + i * 8 * C::RPI, last);
@@ -253,6 +257,12 @@ __device__ __forceinline__ void dq_body(const StepTable& tab, const DqParams& p,
   for (int db = 0; db < NDB; ++db) {
     tr_lo[db] = tr_rd ^ tr_read_xor(db, 0);
     tr_hi[db] = (tr_rd ^ tr_read_xor(db, 1)) + 8 * ROWB;
+  }
+  if constexpr (!LEAN) {  // (left to itself the compiler forms them anew for every block, on the port that bounds the loop)
+#pragma unroll
+    for (int ks = 0; ks < NKS; ++ks) asm("" : "+v"(row_rds[ks]));
+#pragma unroll
+    for (int db = 0; db < NDB; ++db) asm("" : "+v"(tr_lo[db]), "+v"(tr_hi[db]));
   }
 
   // ---- pipeline: PD tiles in flight.  Everything loaded so far is waited for here, so that
@@ -313,7 +323,7 @@ __device__ __forceinline__ void dq_body(const StepTable& tab, const DqParams& p,
 #pragma unroll
       for (int v = 0; v < 16; ++v) e[v] = fast_exp2(s[v]) * dp[v];
       if (j0 + 32 > klen || (isdiag && j0 + 31 > wrow0)) {  // diagonal or ragged end only
-        const int ln = lane_again(), off = wrow0 + (ln & 31);
+        const int ln = LEAN ? lane_again() : lane, off = wrow0 + (ln & 31);
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
           const int key = j0 + acc_row(v, ln >> 5);
