@@ -60,6 +60,12 @@ struct FwdSteps {
   FwdStep step[N];
 };
 static_assert(kMaxSteps <= 32, "`seen` has a bit per step");
+// (A single step: its classes are those of the parameters' geometry.  All arguments together then take 252 bytes; with 268 every launch of
+// some 10 us took 0.2-0.3 us longer, 512 x 512 x 8 heads 11.1 instead of 10.9, however early they were read.)
+template <>
+struct FwdSteps<1> {
+  const uint16_t *k, *v;
+};
 
 struct FwdParams {
   const uint16_t* q;
@@ -76,6 +82,7 @@ struct FwdParams {
   int hgroups;     // Hq / GS
   WorkMap map;     // units = batch x head groups, items = q tiles
 };
+static_assert(sizeof(FwdSteps<1>) + sizeof(FwdParams) <= 256, "see FwdSteps<1>");
 
 // WGS: workgroups that are to share a unit
 template <int D, int KS, int WGS>
@@ -141,25 +148,37 @@ __global__ __launch_bounds__(kFwdWaves * 64, 2 * WGS) void fwd_kernel(const FwdS
   // the main loop indexes the kernel arguments dynamically)
   const int klen0 = p.g.k[0].len, klen1 = p.g.nk > 1 ? p.g.k[1].len : 0;
   const int kstart0 = p.g.k[0].start, kstart1 = p.g.nk > 1 ? p.g.k[1].start : 0;
-  uint32_t todo = scalar_now(qa ? steps.seen[1] : steps.seen[0]);  // the steps still to do
+  uint32_t todo = 0;  // the steps still to do
+  if constexpr (N > 1) todo = scalar_now(qa ? steps.seen[1] : steps.seen[0]);
   struct Step {
     int cls0, cls1, ntk0, total;   // classes of the key halves; tiles in the first, in both
     const unsigned char *k, *v;    // first row of this head
   };
   auto next_step = [&](uint32_t& todo) {
-    const int t = N == 1 ? 0 : __builtin_ctz(todo);
-    todo &= todo - 1;
-    const uint32_t cls = steps.step[t].cls >> (4 * qa);
+    const uint16_t *k, *v;
     Step s;
-    s.cls0 = cls & 3; s.cls1 = p.g.nk > 1 ? (cls >> 2) & 3 : LOONG_SKIP;
+    if constexpr (N == 1) {
+      k = steps.k; v = steps.v;
+      s.cls0 = qa ? p.g.cls[1][0] : p.g.cls[0][0];
+      s.cls1 = p.g.nk > 1 ? (qa ? p.g.cls[1][1] : p.g.cls[0][1]) : LOONG_SKIP;
+    } else {
+      const int t = __builtin_ctz(todo);
+      todo &= todo - 1;
+      const uint32_t cls = steps.step[t].cls >> (4 * qa);
+      k = steps.step[t].k; v = steps.step[t].v;
+      s.cls0 = cls & 3; s.cls1 = p.g.nk > 1 ? (cls >> 2) & 3 : LOONG_SKIP;
+    }
     const int kend0 = s.cls0 == LOONG_SKIP ? 0 : s.cls0 == LOONG_FULL ? klen0 : min(klen0, last_off_wg + 1);
     const int kend1 = s.cls1 == LOONG_SKIP ? 0 : s.cls1 == LOONG_FULL ? klen1 : min(klen1, last_off_wg + 1);
     s.ntk0 = (kend0 + TK - 1) / TK;
     s.total = s.ntk0 + (kend1 + TK - 1) / TK;
-    s.k = reinterpret_cast<const unsigned char*>(scalar_now(steps.step[t].k + b * p.ks[0] + hk * p.ks[1]));
-    s.v = reinterpret_cast<const unsigned char*>(scalar_now(steps.step[t].v + b * p.ks[0] + hk * p.ks[1]));
+    s.k = reinterpret_cast<const unsigned char*>(scalar_now(k + b * p.ks[0] + hk * p.ks[1]));
+    s.v = reinterpret_cast<const unsigned char*>(scalar_now(v + b * p.ks[0] + hk * p.ks[1]));
     return s;
   };
+  // (a single step is looked up here, with the loads of the other arguments)
+  Step cur;
+  if constexpr (N == 1) cur = next_step(todo);
 
   float* out_row = p.out + b * p.os[0] + h * p.os[1] + (int64_t)my_row * p.os[2];
   float* lse_ptr = p.lse + ((int64_t)b * p.Hq + h) * p.q_len + my_row;
@@ -171,7 +190,7 @@ __global__ __launch_bounds__(kFwdWaves * 64, 2 * WGS) void fwd_kernel(const FwdS
     *reinterpret_cast<uint2*>(dst) = make_uint2(E::pack2(x.x, x.y), E::pack2(x.z, x.w));
   };
 
-  if (todo == 0) {  // nothing visible: neutral partial result, or leave the running one
+  if (N == 1 ? cur.total == 0 : todo == 0) {  // nothing visible: neutral partial result, or leave the running one
     if (p.stored && ksp == 0 && row_ok) {
 #pragma unroll
       for (int db = 0; db < NDB; ++db)
@@ -297,7 +316,7 @@ __global__ __launch_bounds__(kFwdWaves * 64, 2 * WGS) void fwd_kernel(const FwdS
   // their backward 66 -> 64); what it keeps count of costs the other forms 1-3 % of their loops (head_dim 64, or fewer splits).
   constexpr bool STREAM = N > 1 && KS == 4 && D == 128;
   static_assert(!STREAM || PD == 1, "one tile in flight between two steps");
-  Step cur = next_step(todo);
+  if constexpr (N > 1) cur = next_step(todo);
   Step ahead = cur;                       // STREAM: the step of the tile to stage next, that tile, and how many are staged
   uint32_t todo_ahead = todo;
   int t_ahead = 0, staged = 0, nth = 0;   // (nth: tiles used)
@@ -747,7 +766,7 @@ int launch_fwd_bf16(const loong_step_desc* descs, int n, const void* q, const vo
     } while (more);
     p.stored = t == n ? (uint16_t*)stored : nullptr;
     int rc;
-    if (m == 1) rc = launch_steps(FwdSteps<1>{{steps.seen[0], steps.seen[1]}, {steps.step[0]}}, rows, p, d, launch_ks, dev.cus, st);
+    if (m == 1) rc = launch_steps(FwdSteps<1>{steps.step[0].k, steps.step[0].v}, rows, p, d, launch_ks, dev.cus, st);
     else rc = launch_steps(steps, rows, p, d, launch_ks, dev.cus, st);
     if (rc) return rc;
     p.fuse = 1;
