@@ -59,3 +59,12 @@ def _named(kernels, part):
 def test_the_backward_kernels_keep_nothing_in_scratch_memory(kernels):
     for name, k in _named(kernels, "bwd_step_kernel|bwd_dkv_kernel|9dq_kernel").items():
         assert k[".private_segment_fixed_size"] == 0, (name, k[".private_segment_fixed_size"])
+
+
+def test_the_fp32_forward_leaves_room_for_other_workgroups(kernels):
+    """A unit has 160 KB: six workgroups of 16 rows at head_dim 32, four at 64, two at 128.  Only the padded 16-row kernels hold registers
+    in scratch memory."""
+    for name, k in _named(kernels, "fwd_f32_(run_)?kernel").items():
+        np, exact = re.search(r"ILi(\d+)ELb(\d)E", name).groups()
+        assert k[".group_segment_fixed_size"] * {"32": 6, "64": 4, "128": 2}[np] <= 160 * 1024, name
+        assert k[".private_segment_fixed_size"] == 0 or (exact == "0" and k[".private_segment_fixed_size"] <= 132), name
