@@ -245,10 +245,11 @@ __device__ __forceinline__ void dkv_body(const StepTable& tab, const DkvParams& 
     }
   };
   // E wave 0, once the LSE of a staged tile is there: the exponent offsets its rows' score chains start from, -LSE log2 e, and -inf
-  // (P = 0) for rows past the end of the segment and rows that saw no key in the whole attention
+  // (P = 0) for rows past the end of the segment and rows that saw no key in the whole attention (also where the lowest float says so)
   auto store_offsets = [&](int stage) {
+    const float offset = lse_ahead * -kLog2e;
     if (C::OFFSETS && wave == 4)
-      *reinterpret_cast<float*>(smem + stage * C::Q_STRIDE + C::LSE_OFF + lane * 4) = lse_ahead == -INFINITY ? -INFINITY : lse_ahead * -kLog2e;
+      *reinterpret_cast<float*>(smem + stage * C::Q_STRIDE + C::LSE_OFF + lane * 4) = offset == INFINITY ? -INFINITY : offset;
   };
   constexpr std::true_type yes;
   constexpr std::false_type no;

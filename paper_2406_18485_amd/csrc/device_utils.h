@@ -41,13 +41,14 @@ __device__ __forceinline__ floatx16_t mfma32(bf16x8_t a, bf16x8_t b, floatx16_t 
 }
 
 // The start of an accumulator whose column (lane & 31) is all x, from the matrix cores: the lane's fragment holds x in three
-// bf16 pieces, which add up to all of its bits, and is multiplied by ones.
+// bf16 pieces, which add up to all of its bits, and is multiplied by ones.  (The pieces are cut off, not rounded: rounded, the first one
+// of the largest floats would be infinite.)
 typedef short s16x4_t __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ s16x4_t pieces_of(float x, int lane) {
-  const __bf16 a = (__bf16)x;
-  const float r = __builtin_isinf(x) ? 0.f : x - (float)a;
-  const __bf16 b = (__bf16)r, c = (__bf16)(r - (float)b);
-  const s16x4_t f = {__builtin_bit_cast(short, a), __builtin_bit_cast(short, b), __builtin_bit_cast(short, c), 0};
+  auto cut = [](float y) { return __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, y) & 0xffff0000u); };
+  auto piece = [](float y) { return (short)(__builtin_bit_cast(uint32_t, y) >> 16); };
+  const float a = cut(x), r = __builtin_isinf(x) ? 0.f : x - a, b = cut(r), c = r - b;
+  const s16x4_t f = {piece(a), piece(b), piece(c), 0};
   const s16x4_t none = {0, 0, 0, 0};
   return lane < 32 ? f : none;
 }

@@ -170,6 +170,29 @@ def test_head_dim_64_gradients_at_the_edges_of_tiles(lq, lk, hq, hkv, ks, dtype,
         assert bool((err <= 8 * eps * (scale + scale.max() / 8) + 1e-6).all()), float((err / (scale + scale.max() / 8) / eps).max())
 
 
+@pytest.mark.parametrize("batch", [1, 300])   # one and two workgroups per unit
+@pytest.mark.parametrize("ks", [1, 4])
+@pytest.mark.parametrize("most", [3.4e38, 3.4028234663852886e38])
+def test_the_largest_floats_are_no_infinities(batch, ks, most):
+    """head_dim 64: a row whose probabilities are zero (an LSE of 1e6) and whose delta is the largest float takes no part, and an LSE of the
+    lowest float, on the diagonal, means what -inf means."""
+    g = torch.Generator(device=DEV).manual_seed(ks)
+    mk = lambda: (torch.randn(1, 1, 64, 64, generator=g, device=DEV) * 0.5).to(torch.bfloat16).expand(batch, -1, -1, -1).contiguous()
+    t = dict(q=mk(), k=mk(), v=mk(), d_o=mk(), lse=torch.full((batch, 1, 64), 4.0, device=DEV), delta=torch.zeros(batch, 1, 64, device=DEV))
+    t["lse"][:, 0, 5:7] = 1e6
+    t["lse"][:, 0, 40] = -math.inf
+    desc = P.make_desc(batch=batch, n_q_heads=1, n_kv_heads=1, head_dim=64, q_len=64, kv_len=64, dtype=P.BF16, softmax_scale=0.125,
+                       causal=True, chunk_len=32, q_chunk=(0, 1), kv_chunk=(0, 1), flags=P.key_splits(ks))
+    zeros = lambda: torch.zeros(t["q"].shape, device=DEV)
+    want = _run(t, desc, zeros(), workspace_for(desc))
+    t["delta"][:, 0, 5], t["delta"][:, 0, 6] = most, -most
+    got = _run(t, desc, zeros(), workspace_for(desc))
+    assert all(torch.equal(a, b) for a, b in zip(got, want)) and float(got[0][:, 0, 5:7].abs().max()) == 0.0
+    t["lse"][:, 0, 40] = -3.4028234663852886e38
+    got = _run(t, desc, zeros(), workspace_for(desc))
+    assert all(torch.equal(a, b) for a, b in zip(got[1:], want[1:]))
+
+
 @pytest.mark.parametrize("dtype", [P.BF16, P.FP16])
 @pytest.mark.parametrize("lq,lk", [(1, 1), (33, 129), (64, 700), (63, 128)])
 @pytest.mark.parametrize("ks", [1, 2, 4])
