@@ -180,24 +180,32 @@ __global__ __launch_bounds__(kFwdWaves * 64, 2 * WGS) void fwd_kernel(const FwdS
   Step cur;
   if constexpr (N == 1) cur = next_step(todo);
 
-  float* out_row = p.out + b * p.os[0] + h * p.os[1] + (int64_t)my_row * p.os[2];
-  float* lse_ptr = p.lse + ((int64_t)b * p.Hq + h) * p.q_len + my_row;
+  auto out_of = [&](int row) { return p.out + b * p.os[0] + h * p.os[1] + (int64_t)row * p.os[2]; };
+  auto lse_of = [&](int row) { return p.lse + ((int64_t)b * p.Hq + h) * p.q_len + row; };
+  float* const out_row = out_of(my_row);
+  float* const lse_ptr = lse_of(my_row);
 
   // four columns of the stored copy of this lane's row (beside the 16 bytes of `out`: a pass of its own over
   // `out` took 6 us behind 8 steps of 8 heads x 2048 rows)
-  auto store16 = [&](int col, float4 x) {
-    uint16_t* dst = p.stored + (((int64_t)b * p.Hq + h) * p.q_len + my_row) * D + col;
+  auto store16 = [&](int row, int col, float4 x) {
+    uint16_t* dst = p.stored + (((int64_t)b * p.Hq + h) * p.q_len + row) * D + col;
     *reinterpret_cast<uint2*>(dst) = make_uint2(E::pack2(x.x, x.y), E::pack2(x.z, x.w));
   };
 
   if (N == 1 ? cur.total == 0 : todo == 0) {  // nothing visible: neutral partial result, or leave the running one
+    // (Runs: the row is found again, here and at the end.  The compiler puts this branch behind the steps, and what it used was kept in
+    // scratch memory throughout at head_dim 64, two to seven registers; of four splits one is left, loaded once behind the steps.)
+    const int lane = N > 1 ? lane_again() : tid & 63, hh = lane >> 5, off = wrow0 + (lane & 31);
+    const bool row_ok = off < qseg.len;
+    const int my_row = qseg.start + min(off, qseg.len - 1);
+    float* const out_row = out_of(my_row);
     if (p.stored && ksp == 0 && row_ok) {
 #pragma unroll
       for (int db = 0; db < NDB; ++db)
 #pragma unroll
         for (int vq = 0; vq < 4; ++vq) {
           const int col = db * 32 + 8 * vq + 4 * hh;
-          store16(col, p.fuse ? *reinterpret_cast<const float4*>(out_row + col) : make_float4(0.f, 0.f, 0.f, 0.f));
+          store16(my_row, col, p.fuse ? *reinterpret_cast<const float4*>(out_row + col) : make_float4(0.f, 0.f, 0.f, 0.f));
         }
     }
     if (!p.fuse && ksp == 0 && row_ok) {
@@ -206,7 +214,7 @@ __global__ __launch_bounds__(kFwdWaves * 64, 2 * WGS) void fwd_kernel(const FwdS
 #pragma unroll
         for (int vq = 0; vq < 4; ++vq)
           *reinterpret_cast<float4*>(out_row + db * 32 + 8 * vq + 4 * hh) = make_float4(0.f, 0.f, 0.f, 0.f);
-      if (hh == 0) *lse_ptr = -INFINITY;
+      if (hh == 0) *lse_of(my_row) = -INFINITY;
     }
     return;
   }
@@ -575,6 +583,12 @@ __global__ __launch_bounds__(kFwdWaves * 64, 2 * WGS) void fwd_kernel(const FwdS
     if constexpr (!STREAM) stage_first();
   }
 
+  const int end_off = N > 1 ? wrow0 + (lane_again() & 31) : my_off;
+  const int end_row = qseg.start + min(end_off, qseg.len - 1);
+  const bool end_ok = end_off < qseg.len;
+  float* const out_end = out_of(end_row);
+  float* const lse_end = lse_of(end_row);
+
   // ---- combine the key splits through LDS: every split parks (m, l, O^T); split j then
   // folds column block j (32 columns) of all splits, so the four waves share the work
   // (with fewer column blocks than splits the surplus waves leave).
@@ -613,7 +627,7 @@ __global__ __launch_bounds__(kFwdWaves * 64, 2 * WGS) void fwd_kernel(const FwdS
     }
     const float l_tot = sum_with_other_half(l_all);
     const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
-    if (row_ok) {
+    if (end_ok) {
 #pragma unroll
       for (int d2 = 0; d2 < DBW; ++d2) {
         const int db = db0 + d2;
@@ -627,11 +641,11 @@ __global__ __launch_bounds__(kFwdWaves * 64, 2 * WGS) void fwd_kernel(const FwdS
             acc.x += xv.x * w[sp]; acc.y += xv.y * w[sp]; acc.z += xv.z * w[sp]; acc.w += xv.w * w[sp];
           }
           acc = make_float4(acc.x * inv, acc.y * inv, acc.z * inv, acc.w * inv);
-          *reinterpret_cast<float4*>(out_row + db * 32 + 8 * vq + 4 * hh) = acc;
-          if (p.stored) store16(db * 32 + 8 * vq + 4 * hh, acc);
+          *reinterpret_cast<float4*>(out_end + db * 32 + 8 * vq + 4 * hh) = acc;
+          if (p.stored) store16(end_row, db * 32 + 8 * vq + 4 * hh, acc);
         }
       }
-      if (ksp == 0 && hh == 0) *lse_ptr = l_tot > 0.f ? (m_all + fast_log2(l_tot)) * kLn2 : -INFINITY;
+      if (ksp == 0 && hh == 0) *lse_end = l_tot > 0.f ? (m_all + fast_log2(l_tot)) * kLn2 : -INFINITY;
     }
     return;
   }
@@ -639,16 +653,16 @@ __global__ __launch_bounds__(kFwdWaves * 64, 2 * WGS) void fwd_kernel(const FwdS
   // ---- normalise and store
   const float l_tot = sum_with_other_half(l_run);
   const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
-  if (row_ok) {
+  if (end_ok) {
 #pragma unroll
     for (int db = 0; db < NDB; ++db)
 #pragma unroll
       for (int vq = 0; vq < 4; ++vq) {
         const float4 x = make_float4(o[db][4 * vq] * inv, o[db][4 * vq + 1] * inv, o[db][4 * vq + 2] * inv, o[db][4 * vq + 3] * inv);
-        *reinterpret_cast<float4*>(out_row + db * 32 + 8 * vq + 4 * hh) = x;
-        if (p.stored) store16(db * 32 + 8 * vq + 4 * hh, x);
+        *reinterpret_cast<float4*>(out_end + db * 32 + 8 * vq + 4 * hh) = x;
+        if (p.stored) store16(end_row, db * 32 + 8 * vq + 4 * hh, x);
       }
-    if (hh == 0) *lse_ptr = l_tot > 0.f ? (m_run + fast_log2(l_tot)) * kLn2 : -INFINITY;
+    if (hh == 0) *lse_end = l_tot > 0.f ? (m_run + fast_log2(l_tot)) * kLn2 : -INFINITY;
   }
 }
 

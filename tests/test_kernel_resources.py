@@ -56,9 +56,11 @@ def _named(kernels, part):
     return some
 
 
-def test_the_backward_kernels_keep_nothing_in_scratch_memory(kernels):
-    for name, k in _named(kernels, "bwd_step_kernel|bwd_dkv_kernel|9dq_kernel").items():
-        assert k[".private_segment_fixed_size"] == 0, (name, k[".private_segment_fixed_size"])
+def test_the_16_bit_kernels_keep_nothing_in_scratch_memory(kernels):
+    for name, k in _named(kernels, "10fwd_kernel|bwd_step_kernel|bwd_dkv_kernel|9dq_kernel").items():
+        # (head_dim 64, four key splits, two workgroups per unit, a run of steps: one register, loaded once behind the steps)
+        most = 8 if "ELi64ELi4ELi2ELi32E" in name else 0
+        assert k[".private_segment_fixed_size"] <= most, (name, k[".private_segment_fixed_size"])
 
 
 def test_the_fp32_forward_leaves_room_for_other_workgroups(kernels):
