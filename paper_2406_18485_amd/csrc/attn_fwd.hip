@@ -500,7 +500,7 @@ __global__ __launch_bounds__(kFwdWaves * 64, 2 * WGS) void fwd_kernel(const FwdS
     // theirs in the buffer of the tile just used, half of the columns at a time: the next step's first tile is on its way to
     // the other buffer.
     float m_all = m_run, l_all = l_run;
-    if (KS > 1 || !STREAM) __syncthreads();  // all reads of the last tile are done
+    __syncthreads();  // all reads of the last tile are done: its buffer is parked in, or staged into again
     if constexpr (KS > 1) {
       constexpr int HALF = STREAM ? NDB / 2 : NDB, PARKED = (KS - 1) * NRB * HALF * 4096;
       static_assert(!STREAM || PARKED <= C::BUF_B, "half of the columns fit a buffer");
