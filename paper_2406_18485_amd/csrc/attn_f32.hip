@@ -36,27 +36,26 @@
 namespace loong {
 namespace {
 
-// (The 320 bytes are five lines of the scalar cache.  With a few more every launch of some 8 us took 0.3 us longer, and eight bytes off the
-// kernels' arrays behind them cost the backward of 1 row x 2048 keys 4 of 86 us.)
 struct F32Params {
-  const float *q, *k, *v, *d_o, *lse_in, *delta;   // (k, v: forward of a single step)
+  const float *q, *d_o, *lse_in, *delta;
   float *out, *lse, *dq;
+  float* stored;          // forward, or NULL: `out`, contiguous, is also copied here
   int B, Hq, Hkv, G, d, q_len, kv_len;
   int64_t qs[3], ks[3], os[3];
   StepGeom g;
   float scale;
-  float* stored;          // forward, or NULL: `out`, contiguous, is also copied here
-  uint8_t fuse, overwrite, accumulate;
+  int fuse;
+  uint16_t overwrite, accumulate;
   int rtile[2], rtiles;   // row tiles per q segment, in all
   int ktile[2], ktiles;   // key tiles per k segment, in all
   WorkMap rmap, kmap;     // units = batch x q heads (kv heads), items = row (key) tiles
 };
-static_assert(sizeof(F32Params) == 320, "whole lines of the scalar cache");
 
 // The micro-steps of a backward launch (a pass of 4 steps, 2 heads x 256 rows, d = 64, with its forward: 81 us
 // with a launch per step, 61 with one): they share the geometry but for the block classes (two bits each:
 // q segment 0 x key segments 0, 1, then q segment 1).
-struct F32Run {
+// (On a line of the scalar cache: eight bytes off, the backward of 1 row x 2048 keys, d = 128, takes 90 us, not 86.)
+struct alignas(64) F32Run {
   const float *k[kMaxSteps], *v[kMaxSteps];
   float *dk[kMaxSteps], *dv[kMaxSteps];
   uint32_t cls[kMaxSteps];
@@ -65,11 +64,17 @@ struct F32Run {
 uint32_t classes(const StepGeom& g) { return g.cls[0][0] | g.cls[0][1] << 2 | g.cls[1][0] << 4 | g.cls[1][1] << 6; }
 // The micro-steps of a forward launch: a step is some 8 us of latencies, of which the launch, the first loads and the way of
 // the running rows through memory are the larger part (4 steps of 2 heads x 256 rows, d = 64: 38 -> 22 us).  A single step
-// has a kernel without the search for the next one (256 rows, 2 heads on 1, d = 64: 8.9 -> 8.2 us, 2048 x 512 x 6 27.0 -> 24.9).
+// has a kernel without the search for the next one (256 rows, 2 heads on 1, d = 64: 8.9 -> 8.2 us, 2048 x 512 x 6 27.0 -> 24.9),
+// whose arguments take no more lines of the scalar cache than it needs (one more is 0.3 us).
+template <int N>
 struct F32Steps {
-  const float *k[kMaxSteps], *v[kMaxSteps];
-  uint32_t cls[kMaxSteps];
+  const float *k[N], *v[N];
+  uint32_t cls[N];
   int n;
+};
+template <>
+struct F32Steps<1> {
+  const float *k, *v;
 };
 __device__ __forceinline__ StepGeom with_classes(const StepGeom& g, uint32_t c) {
   StepGeom x = g;
@@ -260,14 +265,18 @@ __device__ __forceinline__ void add_waves(typename F::Acc& a, floatx4_t* slots, 
 
 // ---- forward: RB x 16 query rows per workgroup (RB = 2 where rows are many: half the reads of K and V), over the
 // launch's steps.  Between two steps the running result goes through LDS as it would go through memory: the same bits.
-// (`steps` is NULL for a single step, which the parameters describe.)
-template <int NP, bool EXACT, int RB>
-__device__ __forceinline__ void fwd_f32_body(const F32Params& p, const F32Steps* steps) {
+template <int NP, bool EXACT, int RB, int N>
+__global__ __launch_bounds__(kMaxWaves * 64 / RB) void fwd_f32_kernel(const F32Params p, const F32Steps<N> steps) {
   using F = Frag<NP, EXACT>;
   constexpr int NM = F::NM;
   __shared__ floatx4_t slots[kMaxWaves * (NM + 1) * 64];
-  // (between two steps the running result goes where the first wave's part was, which the thread that forms it alone reads)
-  auto state_of = [&](int rb) { return slots + rb * (NM + 1) * 64 + (threadIdx.x & 63); };
+  // The running result between two steps goes where the first wave's part was, which the thread that forms it alone reads.  (Padded
+  // 16-row form, which runs out of registers: apart; they are given out better then, head_dim 100, 100 rows x 4000 keys x 2 heads 118 us
+  // against 131.)
+  constexpr bool APART = !EXACT && RB == 1;
+  __shared__ floatx4_t apart[APART ? NM * 64 : 1];
+  floatx4_t* const state = APART ? apart : slots;
+  constexpr int STATE_RB = APART ? NM : NM + 1;
   int bh, rank;
   if (!decode_work(p.rmap, blockIdx.x, bh, rank)) return;
   const int tt = p.rtiles - 1 - rank;  // late rows see more keys: first
@@ -283,18 +292,18 @@ __device__ __forceinline__ void fwd_f32_body(const F32Params& p, const F32Steps*
   const float *kbase = nullptr, *vbase = nullptr;
   int step = -1;
   auto next_step = [&] {
-    if (!steps) {
+    if constexpr (N == 1) {
       if (++step) return false;
       keys = keys_of_rows(p.g, qa, min(row0 + kT * RB, qs.len) - 1);
-      kbase = p.k + b * p.ks[0] + hk * p.ks[1];
-      vbase = p.v + b * p.ks[0] + hk * p.ks[1];
+      kbase = steps.k + b * p.ks[0] + hk * p.ks[1];
+      vbase = steps.v + b * p.ks[0] + hk * p.ks[1];
       return keys.total > 0;
     } else {
-      for (++step; step < steps->n; ++step) {
-        keys = keys_of_rows(with_classes(p.g, steps->cls[step]), qa, min(row0 + kT * RB, qs.len) - 1);
+      for (++step; step < steps.n; ++step) {
+        keys = keys_of_rows(with_classes(p.g, steps.cls[step]), qa, min(row0 + kT * RB, qs.len) - 1);
         if (keys.total == 0) continue;
-        kbase = steps->k[step] + b * p.ks[0] + hk * p.ks[1];
-        vbase = steps->v[step] + b * p.ks[0] + hk * p.ks[1];
+        kbase = steps.k[step] + b * p.ks[0] + hk * p.ks[1];
+        vbase = steps.v[step] + b * p.ks[0] + hk * p.ks[1];
         return true;
       }
       return false;
@@ -418,7 +427,7 @@ __device__ __forceinline__ void fwd_f32_body(const F32Params& p, const F32Steps*
       for (int w = 0; w < waves; ++w) acc += part[w * step_w + pc * 64] * fast_exp2(part[w * step_w + NM * 64][0] - m_ref);
       acc = acc * inv;
       if (more) {
-        state_of(rb)[pc * 64] = acc;
+        state[(rb * STATE_RB + pc) * 64 + lane] = acc;
       } else if (row_ok && (EXACT || F::piece_col(pc, g) < p.d)) {
         *reinterpret_cast<floatx4_t*>(p.out + orow[rb] + F::piece_col(pc, g)) = acc;
         if (p.stored) *reinterpret_cast<floatx4_t*>(p.stored + orow[rb] + F::piece_col(pc, g)) = acc;
@@ -437,19 +446,10 @@ __device__ __forceinline__ void fwd_f32_body(const F32Params& p, const F32Steps*
     o[rb] = F::zero();
     if (wave == 0 && m[rb] != -INFINITY) {
 #pragma unroll
-      for (int pc = 0; pc < NM; ++pc) F::set_piece(o[rb], pc, state_of(rb)[pc * 64]);
+      for (int pc = 0; pc < NM; ++pc) F::set_piece(o[rb], pc, state[(rb * STATE_RB + pc) * 64 + lane]);
     }
   }
   }
-}
-
-template <int NP, bool EXACT, int RB>
-__global__ __launch_bounds__(kMaxWaves * 64 / RB) void fwd_f32_kernel(const F32Params p) {
-  fwd_f32_body<NP, EXACT, RB>(p, nullptr);
-}
-template <int NP, bool EXACT, int RB>
-__global__ __launch_bounds__(kMaxWaves * 64 / RB) void fwd_f32_run_kernel(const F32Params p, const F32Steps steps) {
-  fwd_f32_body<NP, EXACT, RB>(p, &steps);
 }
 
 // ---- backward, row-owning half: the share of dQ of 16 query rows that the launch's steps have
@@ -637,22 +637,21 @@ int pick_waves(int64_t workgroups, int most) {
 }
 
 template <int NP, bool EXACT, int RB>
-int launch_fwd_form(const F32Params& p, const F32Steps& steps, int waves, hipStream_t st) {
+int launch_fwd_form(const F32Params& p, const F32Steps<kMaxSteps>& steps, int waves, hipStream_t st) {
   if (!launch_fits(p.rmap.grid, waves * 64)) return fail(LOONG_E_UNSUPPORTED, "fp32 path: forward grid too large");
-  // (The padded 16-row form, which runs out of registers, is faster as compiled for a run: head_dim 100, 100 rows x 4000 keys x 2 heads 131 us
-  // against 142.)
+  // (the padded 16-row form as compiled for a run is the faster one: 118 us against 142)
   if constexpr (EXACT || RB == 2) {
     if (steps.n == 1) {
-      fwd_f32_kernel<NP, EXACT, RB><<<dim3(p.rmap.grid), dim3(waves * 64), 0, st>>>(p);
+      fwd_f32_kernel<NP, EXACT, RB, 1><<<dim3(p.rmap.grid), dim3(waves * 64), 0, st>>>(p, F32Steps<1>{steps.k[0], steps.v[0]});
       return check_launch("loong_attn_step_fwd (fp32)");
     }
   }
-  fwd_f32_run_kernel<NP, EXACT, RB><<<dim3(p.rmap.grid), dim3(waves * 64), 0, st>>>(p, steps);
+  fwd_f32_kernel<NP, EXACT, RB, kMaxSteps><<<dim3(p.rmap.grid), dim3(waves * 64), 0, st>>>(p, steps);
   return check_launch("loong_attn_step_fwd (fp32)");
 }
 
 template <int NP, bool EXACT>
-int launch_fwd(F32Params& p, const F32Steps& steps, int cus, hipStream_t st) {
+int launch_fwd(F32Params& p, const F32Steps<kMaxSteps>& steps, int cus, hipStream_t st) {
   // 32-row workgroups where they still put two on every unit (16384 rows, d = 128, a pass of two steps: 131 us
   // against 156 with two waves per tile).  16-row ones share a tile among eight waves while that is at most two
   // waves per SIMD, else among four (4 heads x 600 rows, d = 128: 35 us with four, 41 with eight, 51 with two).
@@ -707,14 +706,13 @@ int launch_fwd_f32(const loong_step_desc* descs, int n, const void* q, const voi
   F32Params p = make_params(d, g);
   p.q = (const float*)q; p.out = out; p.lse = lse;
   for (int t = 0; t < n;) {
-    F32Steps steps;
+    F32Steps<kMaxSteps> steps;
     steps.n = 0;
     for (; t < n && steps.n < kMaxSteps; ++t, ++steps.n) {
       if (int rc = check_step(&descs[t], &p.g)) return rc;
       steps.k[steps.n] = (const float*)k[t]; steps.v[steps.n] = (const float*)v[t];
       steps.cls[steps.n] = classes(p.g);
     }
-    p.k = steps.k[0]; p.v = steps.v[0];
     p.stored = t == n ? (float*)stored : nullptr;
     if (int rc = d.head_dim == 32    ? launch_fwd<32, true>(p, steps, dev.cus, st)
                  : d.head_dim == 64  ? launch_fwd<64, true>(p, steps, dev.cus, st)

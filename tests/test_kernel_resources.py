@@ -66,7 +66,7 @@ def test_the_16_bit_kernels_keep_nothing_in_scratch_memory(kernels):
 def test_the_fp32_forward_leaves_room_for_other_workgroups(kernels):
     """A unit has 160 KB: six workgroups of 16 rows at head_dim 32, four at 64, two at 128.  Only the padded 16-row kernels hold registers
     in scratch memory."""
-    for name, k in _named(kernels, "fwd_f32_(run_)?kernel").items():
+    for name, k in _named(kernels, "14fwd_f32_kernel").items():
         np, exact = re.search(r"ILi(\d+)ELb(\d)E", name).groups()
         assert k[".group_segment_fixed_size"] * {"32": 6, "64": 4, "128": 2}[np] <= 160 * 1024, name
         assert k[".private_segment_fixed_size"] == 0 or (exact == "0" and k[".private_segment_fixed_size"] <= 132), name
