@@ -281,13 +281,13 @@ int launch_cfg(StepLaunch& s, const StepTable& tab, hipStream_t st) {
 // look-ahead and the LDS of a unit to itself for launches that put hardly more than one on any.  Whole steps, one / two: 190 x 190 x 8
 // heads 12.0 / 12.4 us, 512 x 512 x 8 14.4 / 14.8, 1554 rows of a diagonal step, 4 heads on 1 (280 workgroups) 28.3 / 31.0; 700 x 2000 x
 // 4 (300) 30.9 / 27.7, 1024 x 1024, 16 heads on 4 37.6 / 31.8.  dQ alone: 2048 x 16384, 4 heads on 1 95 / 105, 700 x 900 x 4 x 16
-// heads on 2 (352) 34.3 / 28.5; with a diagonal block, whose loops are uneven, 512 workgroups 209 / 245.
+// heads on 2 (352) 34.3 / 28.5; with a diagonal block, whose loops are uneven, 512 workgroups 209 / 245.  dK/dV alone: 1500 x 1500, 6 heads on 2 (264) 37.5 / 35.5.
 template <class E, int D, int KS>
 int launch_form(StepLaunch& s, const StepTable& tab, int cus, hipStream_t st) {
   if constexpr (D == 64) {
     const int64_t total = (int64_t)(s.do_kv ? s.kv.map.grid : 0) + (s.do_q ? s.q.map.grid : 0);
     const bool uneven = !s.do_kv && tab.n_diag[0] + tab.n_diag[1] > 0;
-    if (total > cus * 9 / 8 && !uneven) return launch_cfg<E, D, KS, 2>(s, tab, st);
+    if (total > (s.do_kv && s.do_q ? cus * 9 / 8 : cus) && !uneven) return launch_cfg<E, D, KS, 2>(s, tab, st);
   }
   return launch_cfg<E, D, KS, 1>(s, tab, st);
 }
