@@ -198,7 +198,7 @@ LOONG_API int loong_workspace_bytes_steps(const loong_step_desc* descs, int32_t 
  * loong_attn_step_bwd for callers that cannot allocate device memory or bring a workspace: code
  * under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same
  * arguments, semantics, results (bit for bit) and errors as loong_attn_step_bwd, except that
- * the scratch of the dK/dV kernel is an array of LOONG_STATIC_SCRATCH_BYTES inside the library's
+ * the scratch (partial dK/dV and dQ, counters) is an array of LOONG_STATIC_SCRATCH_BYTES inside the library's
  * device code (each GPU the library is used on holds its own copy until the process ends).
  * The call allocates and frees nothing and does not synchronise.  A step that needs more
  * scratch than the array holds (loong_workspace_bytes(desc) > LOONG_STATIC_SCRATCH_BYTES) is

@@ -687,7 +687,8 @@ int launch_cfg(const FwdSteps<N>& steps, const StepGeom& rows, FwdParams& p, int
     // with: 8 steps of 8 heads x 2048 rows x 4096 keys 394 -> 356 us, of 8 x 1200 x 2400 227 -> 209, 4 x 3500 x 7000 596 -> 534,
     // 6 x 2000 x 4000 355 -> 318; but 16 x 1000 x 2000 220 -> 224, 8 x 512 x 1024 97 -> 100, 5 x 1300 x 2600 (105 workgroups)
     // 182 -> 187, two heads 279 -> 286; two q heads per kv head 341 -> 341, four 329 -> 338; head_dim 64 225 -> 239.  On
-    // inputs that are in cache 2 % longer throughout.
+    // inputs that are in cache 2 % longer throughout.  Single steps, cold and cached: 2048 x 4096 x 8 heads 51.5 -> 47.5 and 44.2 -> 45.5 us,
+    // 3600 x 16384 x 4 189 -> 153 and 143 -> 148.  (Chunks that have just come from another device are in no cache of this one.)
     if constexpr (KS == 4) {
       if (p.G == 1 && p.B * p.Hkv >= 4 && p.g.nk * p.g.k[0].len >= 2304 && total >= cus * 7 / 8) {
         fwd_kernel<E, D, KS, 1, N, true><<<grid, block, 0, st>>>(steps, p);

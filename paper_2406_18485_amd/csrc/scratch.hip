@@ -1,6 +1,6 @@
 // loong_attn_step_bwd_static: the backward micro-step for callers that cannot allocate device
 // memory (code under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc).
-// The scratch of the dK/dV kernel (arrival counters and the partial sums of shared query loops)
+// The scratch of the step (arrival counters and the partial sums of shared loops)
 // lives in a device array that is part of the library's code object instead of a buffer the
 // caller brings: every GPU the library runs on holds its own copy from the first use of the
 // library on it until the process ends.
@@ -12,8 +12,9 @@
 
 namespace {
 
-// counters + 64 MiB of partial sums: enough for every step of the 32K..1M-token benchmark shapes
-// (at most 512 (key tile, split) slots of 128 KiB)
+// counters + 64 MiB of partial sums: enough for every step of the 32K..1M-token benchmark shapes (at most 512 (key tile,
+// split) slots of 128 KiB), for every step at head_dim 64 (at most 1024 slots of 64 KiB), and for the partial dQ where the step
+// plans any (it plans none that does not fit behind the slots)
 constexpr int64_t kScratchBytes = LOONG_STATIC_SCRATCH_BYTES;
 static_assert(loong::kWsHeadBytes == LOONG_WORKSPACE_HEAD, "header and layout disagree");
 static_assert(kScratchBytes == loong::kWsHeadBytes + ((int64_t)64 << 20), "header and layout disagree");
