@@ -165,8 +165,9 @@ LOONG_API int loong_lse_merge(int64_t rows, int32_t head_dim, float* out, float*
  * arrive adds their partial sums in a fixed order.  Those partial sums and their arrival
  * counters live in `workspace`, device memory of the caller's, 16-byte aligned, of
  * loong_workspace_bytes(desc) bytes (that may be 0: then `workspace` may be NULL).  With a smaller one, or none, a step does
- * without what it can: the keys of few query rows are not shared, and the query loops of a head_dim 64 step only until every
- * compute unit has a workgroup (the sums are those of that division, in its order, then).  It
+ * without what it can: the keys of few query rows are not shared, the query loops of a run by as many workgroups as there is
+ * room for, if need be none, and those of a single head_dim 64 step likewise as long as every compute unit has a workgroup (the
+ * sums are those of that division, in its order, then).  It
  * may hold anything on entry (a call that counts clears the counters on `stream` before it does, unless the caller
  * vouches for them: LOONG_WORKSPACE_CLEAN) and holds nothing of value afterwards; calls that share one workspace must be
  * ordered on one stream.  Where a step cannot do without, a missing or too small workspace is

@@ -133,7 +133,8 @@ void plan_split(const loong_step_desc& d, const StepGeom* g, int n, int cus, Bwd
     double best = 0.97 * time(most);
     for (int k = 1; k < most; ++k)
       if (time(k) <= best) { best = time(k); nsplit = k; }
-    s.nsplit = s.nsplit_least = at_most(nsplit);
+    s.nsplit = at_most(nsplit);
+    s.nsplit_least = 1;  // (the estimate is about speed: with less room than it asks for, fewer parts will do)
   }
 }
 
@@ -319,9 +320,10 @@ void plan_bwd_bf16(const loong_step_desc& d, const StepGeom* g, int n, BwdPlan* 
 
 bool fit_bwd_bf16(BwdPlan* p, const void* workspace, int64_t workspace_bytes) {
   const int64_t room = workspace && aligned16(workspace) ? workspace_bytes - kWsHeadBytes : 0;
-  if (p->key_bytes > std::max<int64_t>(room, 0)) {
-    p->nsplit = p->nsplit_least;
-    p->key_bytes = p->least_bytes;
+  if (p->key_bytes > std::max<int64_t>(room, 0)) {  // as many parts as there is room for
+    const int64_t part = p->key_bytes / p->nsplit;
+    p->nsplit = std::max(p->nsplit_least, (int)(std::max<int64_t>(room, 0) / part));
+    p->key_bytes = p->nsplit > 1 ? part * p->nsplit : 0;
   }
   if (p->row_bytes > 0 && p->key_bytes + p->row_bytes > room) {
     p->parts = 1;

@@ -126,6 +126,35 @@ def test_a_run_that_does_not_count_leaves_its_workspace_alone(cp, hq, hkv, d, c,
         _close(a, b)
 
 
+@pytest.mark.parametrize("cp,rank,hq,hkv,d,c,batch", [(4, 0, 4, 4, 128, 1025, 1), (4, 0, 2, 2, 128, 1046, 2), (3, 2, 4, 2, 64, 892, 1), (40, 20, 2, 1, 64, 150, 1)])
+def test_a_run_does_with_the_room_there_is(cp, rank, hq, hkv, d, c, batch):
+    """Loops shared by as many workgroups as the workspace has room for, down to one and no workspace: the same sums in other orders
+    (chains of some 8200 keys / 16 additions at most), counters left zero, nothing written past the room, the same bits every time."""
+    rep, q, k, v, d_o = _replay(cp, cp, rank, hq, hkv, d, c, batch)
+    rep.backward(q, k, v, d_o)
+    want = [t.clone() for t in (rep.dq, rep.dk, rep.dv)]
+    full = P.workspace_bytes_steps(rep._bwd_descs)
+    assert full > 0
+    order = [s["src_rank"] for s in rep.plan]
+    descs = (P.StepDesc * cp)(*(_desc(rep.shape, s, P.OVERWRITE_DQ | P.COMPUTE_DELTA) for s in rep.plan))
+    ws = torch.empty(full, dtype=torch.uint8, device=DEV)
+    for room in (full - 16, full // 2 // 16 * 16, P.WORKSPACE_HEAD, 0):
+        ws.fill_(0xA5)
+        got = []
+        for _ in range(2):
+            for t in (rep.dq, rep.dk, rep.dv):
+                t.fill_(9.0)
+            P.attn_steps_bwd(descs, q, [k[s] for s in order], [v[s] for s in order], rep.o, d_o, rep.lse, rep.delta, rep.dq,
+                             [rep.dk[s] for s in order], [rep.dv[s] for s in order], ws[:room])
+            assert bool((ws[room:] == 0xA5).all())
+            got.append([t.clone() for t in (rep.dq, rep.dk, rep.dv)])
+        head = ws[:min(room, P.WORKSPACE_HEAD)]
+        assert not bool(head.any()) or bool((head == 0xA5).all())   # (left alone where the run does not count)
+        assert all(torch.equal(a, b) for a, b in zip(*got))
+        for a, b in zip(got[0], want):
+            _close(a, b)
+
+
 def test_run_adds_to_what_is_there_and_halves_run_alone():
     rep, q, k, v, d_o = _replay(4, 2, 1, 4, 2, 64, 161, 1)
     rep.backward(q, k, v, d_o)
