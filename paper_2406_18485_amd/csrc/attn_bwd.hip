@@ -120,8 +120,10 @@ void plan_split(const loong_step_desc& d, const StepGeom* g, int n, int cus, Bwd
     // prologue and stores are worth 3; parking and adding up shared sums 4 more and half a tile per part when the whole chip
     // does it, one more for a single workgroup.  A backward pass, without the estimate -> with it: 8 steps of 2 heads x 2000 rows 131 -> 104
     // us, 16 of 4 x 1000 137 -> 100, 3 of 12 x 1400 (head_dim 64) 61 -> 57, 8 of 8 x 1200 137 -> 120, 4 of 32 x 600 113 -> 88, 32 of 2 x
-    // 638 x batch 2 188 -> 87.  Of 210 runs of 2 to 32 steps of 96 to 11000 rows, each timed with every number of parts, it takes 1.5 %
-    // longer than the best on average (9 % without it), and four of them 2-8 % (0.5-2 us) longer than without it.  (With a quarter of
+    // 638 x batch 2 188 -> 87.  Of 670 runs of 2 to 32 steps of 96 to 11000 rows, each timed with every number of parts, it takes 1.5 to
+    // 2 % longer than the best on average (6 to 9 % without it), and sixteen of them 2-9 % longer than without it: how the parts and the
+    // workgroups of the dQ half, which come first, fill the last places is not in it (6 steps of 3 heads on 1 x 1268 rows: four parts 56 us, the
+    // six it takes 69).  (With a quarter of
     // the longest workgroup instead of all of it 2.5 % and up to 14 % longer than without, as 3 steps of 6 heads on 2 x 4430 rows x batch 2
     // 643 -> 671.  The estimate alone makes five parts of four on 8 steps of 4 x 16384 rows: 3.6 % longer.)
     const int most = (int)std::min(std::max(std::ceil(8. * BN * most_rows * G / (kLoopShare * s.per_cu)), 1.), 16.);
